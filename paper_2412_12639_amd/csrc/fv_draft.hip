@@ -4,6 +4,7 @@
 // pass lives in fv_draft_step.hpp (compiled with the fv_step.hip units).
 #include "fv_host.hpp"
 #include "fv_draft_kernels.hpp"
+#include "fv_lstm_chain.hpp"
 
 #include <algorithm>
 #include <cstring>
@@ -60,6 +61,8 @@ void make_draft_layout(const fv_cfg& t, int n_wg, DraftLayout& L) {
     for (int i = 0; i < GM_COUNT; ++i) ngmax = std::max(ngmax, core.gm[i].n_strips_pad);
     L.ticket_bytes = (size_t)ngmax * 4;
     L.off_tickets = take(L.ticket_bytes);
+    L.chain_bytes = 256 + 2 * 2 * h * 2;   // two arrival counters 128 bytes apart, then [layer][2][h] bf16
+    L.off_chain = take(L.chain_bytes);
     L.total = o;
 }
 
@@ -87,7 +90,73 @@ int upload_tables(fv_drafter* d) {
     return FV_OK;
 }
 
+// Fragments per wavefront of the built chain kernel that takes hidden size h, 0 if none does.
+int lstm_chain_size(int h) {
+    if (h % 128 || h > 4096) return 0;
+    for (int nkf : {2, 4, 8, 16, 32})
+        if (h / 128 <= nkf) return nkf;
+    return 0;
+}
+
+template <int NKF>
+int launch_chain_t(const LstmChainArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(k_lstm_chain<NKF>, dim3(a.h / 16), dim3(256), lstm_chain_smem(NKF), st, a);
+    return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
+}
+template <int NKF>
+int set_chain_attr() {
+    HIPCHK(hipFuncSetAttribute((const void*)k_lstm_chain<NKF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lstm_chain_smem(NKF)));
+    return FV_OK;
+}
+
+// Whether the chain kernel takes this drafter: bf16, a hidden size whose recurrent matrix fits into the registers and LDS of
+// h / 16 compute units (h up to 4096), and a device with that many.  At hidden 4096 a row then costs 3.4 us per layer instead
+// of 33; wider drafters and fp32 ones stream the matrix once per row as before.
+int lstm_chain_fits(const fv_cfg& c, bool& fits) {
+    fits = false;
+    if (c.dtype != FV_BF16 || !lstm_chain_size(c.hidden)) return FV_OK;
+    int dev = 0, cus = 0;
+    HIPCHK(hipGetDevice(&dev));
+    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    if (c.hidden / 16 > cus) return FV_OK;
+    int rc = FV_E_BAD_ARG;
+    switch (lstm_chain_size(c.hidden)) {
+        case 2: rc = set_chain_attr<2>(); break;
+        case 4: rc = set_chain_attr<4>(); break;
+        case 8: rc = set_chain_attr<8>(); break;
+        case 16: rc = set_chain_attr<16>(); break;
+        case 32: rc = set_chain_attr<32>(); break;
+    }
+    fits = rc == FV_OK;
+    return rc;
+}
+
 }  // namespace
+
+int launch_lstm_chain(fv_drafter* d, const DraftPass& ps, int layer, int Tp) {
+    fv_ctx* c = d->core;
+    const DraftLayout& dl = d->lay;
+    const int h = c->cfg.hidden;
+    LstmChainArgs a;
+    a.Wt = (const uint4*)(d->arena + dl.off_w[2 * layer + 1]); a.zeros = c->at<uint4>(c->lay.off_zeros);
+    a.g_in = d->at<float>(dl.off_gin); a.bias = d->at<float>(dl.off_bias) + (size_t)layer * 4 * h; a.state = d->state(layer);
+    a.xnext = layer == 0 ? d->at<void>(dl.off_xh) : nullptr;
+    a.sync = d->at<uint32_t>(dl.off_chain) + 32 * layer;
+    a.xchg = d->at<uint16_t>(dl.off_chain + 256) + (size_t)layer * 2 * h;
+    a.fault = d->at<uint32_t>(dl.off_bad) + 1; a.aborted = d->at<uint32_t>(dl.off_bad) + 2;
+    a.t0 = 0; a.r0 = ps.r0; a.n = ps.n; a.lpred = FV_DRAFT_STATE_COMMITTED; a.Tp = Tp; a.h = h;
+    a.expect = (unsigned)(h / 16) + (d->chain_test ? 1u : 0u);
+    a.arrive_looks = d->chain_test ? 2u : 4000u;   // some milliseconds
+    a.spin_limit = FV_EXCHANGE_SPINS;
+    switch (lstm_chain_size(h)) {
+        case 2: return launch_chain_t<2>(a, c->stream);
+        case 4: return launch_chain_t<4>(a, c->stream);
+        case 8: return launch_chain_t<8>(a, c->stream);
+        case 16: return launch_chain_t<16>(a, c->stream);
+        case 32: return launch_chain_t<32>(a, c->stream);
+    }
+    return FV_E_BAD_ARG;
+}
 
 extern "C" {
 
@@ -145,6 +214,9 @@ int fv_drafter_create(fv_ctx* target, int32_t k, void* dev_arena, size_t arena_b
         d->kind_ih0 = (base == GEMM_PAIRED && !d->lay.ih0.paired_ok) ? GEMM_DIRECT : base;
         d->kind_hh = (base == GEMM_PAIRED && !d->lay.hh.paired_ok) ? GEMM_DIRECT : base;
     }
+    rc = lstm_chain_fits(target->cfg, d->chain_ok);
+    if (rc) return fail(rc);
+    { const char* e = getenv("FV_EXCHANGE_TEST"); d->chain_test = e && !strcmp(e, "chain"); }
     if (hipHostMalloc((void**)&d->h_tab, (size_t)FV_DRAFT_TABLES * FV_MAX_TREE * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
     if (hipHostMalloc((void**)&d->h_out, (FV_MAX_TREE + 64) * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
     memset(d->h_tab, 0, (size_t)FV_DRAFT_TABLES * FV_MAX_TREE * 4);
@@ -228,15 +300,24 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
         HIPCHK(hipEventRecord(d->core->ev0, st));
         DraftPass ps;
         ps.r0 = 0; ps.n = m; ps.l0 = 0; ps.lvl_n.assign(m, 1); ps.ext = dev_features;
-        rc = pass_any(d, ps);
-        if (rc) return rc;
-        StateKeepArgs ka;
-        ka.state0 = d->state(0); ka.state1 = d->state(1); ka.row = m - 1; ka.h = cf.hidden;
-        hipLaunchKernelGGL(k_state_keep, dim3((2 * cf.hidden + 255) / 256), dim3(256), 0, st, ka);
-        HIPCHK(hipGetLastError());
-        HIPCHK(hipEventRecord(d->core->ev1, st));
-        HIPCHK(hipMemcpyAsync(d->h_out + FV_MAX_TREE, d->at<int32_t>(d->lay.off_bad), 8, hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
+        // One row costs a chain launch as much as the separate launches (the matrix is read once either way).  A chain launch
+        // whose workgroups did not get on the chip together has done nothing; the pass is then run again without.
+        ps.chain = d->chain_ok && m >= 2;
+        for (;;) {
+            rc = pass_any(d, ps);
+            if (rc) return rc;
+            StateKeepArgs ka;
+            ka.state0 = d->state(0); ka.state1 = d->state(1); ka.aborted = d->at<uint32_t>(d->lay.off_bad) + 2; ka.row = m - 1; ka.h = cf.hidden;
+            hipLaunchKernelGGL(k_state_keep, dim3((2 * cf.hidden + 255) / 256), dim3(256), 0, st, ka);
+            HIPCHK(hipGetLastError());
+            HIPCHK(hipEventRecord(d->core->ev1, st));
+            HIPCHK(hipMemcpyAsync(d->h_out + FV_MAX_TREE, d->at<int32_t>(d->lay.off_bad), 12, hipMemcpyDeviceToHost, st));
+            HIPCHK(hipStreamSynchronize(st));
+            if (!ps.chain || !d->h_out[FV_MAX_TREE + 2] || d->h_out[FV_MAX_TREE + 1]) break;
+            hipLaunchKernelGGL(k_draft_fill, dim3(1), dim3(256), 0, st, d->at<uint32_t>(d->lay.off_bad), 0u, (size_t)3);
+            HIPCHK(hipGetLastError());
+            ps.chain = false;
+        }
         if (d->h_out[FV_MAX_TREE + 1]) { d->part_dirty = true; return FV_E_EXCHANGE_TIMEOUT; }
         float ms = 0.f;
         HIPCHK(hipEventElapsedTime(&ms, d->core->ev0, d->core->ev1));

@@ -78,12 +78,14 @@ struct DraftInArgs {
     const int32_t* node_tok;  // [256]
     const void* table;        // embedding [V][h]
     void* xz;                 // [2h/E][Tp][E]
+    uint32_t* chain; int chain_words;   // exchange area of the chain launches to clear (0 words: none)
     int r0, n, Tp, h, vocab;
 };
 
 template <typename EL>
 static __global__ __launch_bounds__(256) void k_draft_in(DraftInArgs a) {
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx < (size_t)a.chain_words) a.chain[idx] = 0u;   // (fewer words than threads: 64 + 2h against 2h / 4 * Tp)
     const int t = (int)(idx % a.Tp);
     const int f0 = (int)(idx / a.Tp) * 4;
     if (f0 >= 2 * a.h) return;
@@ -199,11 +201,12 @@ static __global__ __launch_bounds__(256) void k_lstm_cell(LstmCellArgs a) {
     }
 }
 
-// state after the last committed pair <- state of phase row `row` (both layers are laid out back to back)
-struct StateKeepArgs { float* state0; float* state1; int row, h; };
+// state after the last committed pair <- state of phase row `row` (both layers are laid out back to back); not if *aborted
+// (a chain launch gave up: the rows' states are not there)
+struct StateKeepArgs { float* state0; float* state1; const uint32_t* aborted; int row, h; };
 static __global__ __launch_bounds__(256) void k_state_keep(StateKeepArgs a) {
     const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= 2 * a.h) return;
+    if (idx >= 2 * a.h || *a.aborted) return;
     a.state0[(size_t)FV_MAX_TREE * 2 * a.h + idx] = a.state0[(size_t)a.row * 2 * a.h + idx];
     a.state1[(size_t)FV_MAX_TREE * 2 * a.h + idx] = a.state1[(size_t)a.row * 2 * a.h + idx];
 }

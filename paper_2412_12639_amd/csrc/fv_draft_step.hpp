@@ -3,6 +3,7 @@
 // block with the relaxed causal mask -> LM head -> top lists.
 #pragma once
 #include "fv_draft_kernels.hpp"
+#include "fv_lstm_chain.hpp"
 
 static DraftTables draft_tables(const fv_drafter* d) {
     DraftTables t;
@@ -70,6 +71,7 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         DraftInArgs da;
         da.tab = tab; da.fout = d->at<float>(dl.off_fout); da.ext = ps.ext; da.node_tok = d->at<int32_t>(dl.off_node_tok);
         da.table = d->target->arena + d->target->lay.off_embed; da.xz = d->at<void>(dl.off_xz);
+        da.chain = d->at<uint32_t>(dl.off_chain); da.chain_words = ps.chain ? (int)(dl.chain_bytes / 4) : 0;
         da.r0 = ps.r0; da.n = n; da.Tp = Tp; da.h = h; da.vocab = cf.vocab;
         const size_t items = (size_t)(2 * h / 4) * Tp;
         hipLaunchKernelGGL((k_draft_in<EL>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, da);
@@ -87,6 +89,19 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
             ga.logits = d->at<float>(dl.off_gin); ga.Vpad = 4 * h;
             int rc = launch_gemm<EL, D, EPI_LOGITS>(c, Tp, ga, kind, &d->scr);
             if (rc) return rc;
+        }
+        if (ps.chain) {   // all rows in one launch
+            int rc = launch_lstm_chain(d, ps, layer, Tp);
+            if (rc) return rc;
+            if (layer == 1) {
+                LstmOutArgs oa;
+                oa.state = d->state(1); oa.x = c->at<float>(ly.off_x); oa.xb = c->at<void>(ly.off_xb); oa.gain = c->gain(0); oa.ssq = c->at<float>(ly.off_ssq);
+                oa.r0 = ps.r0; oa.t0 = 0; oa.n = n; oa.Tp = Tp; oa.h = h;
+                const size_t items = (size_t)(h / 4) * n;
+                hipLaunchKernelGGL((k_lstm_out<EL>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, oa);
+                HIPCHK(hipGetLastError());
+            }
+            continue;
         }
         int l0 = ps.l0;
         for (size_t lv = 0; lv < ps.lvl_n.size(); ++lv) {

@@ -141,6 +141,7 @@ struct DraftLayout {
     size_t off_state = 0, state_layer_bytes = 0;
     size_t off_fout = 0, off_top_tok = 0, off_top_val = 0, off_logits = 0, off_node_tok = 0, off_tables = 0, off_bad = 0;
     size_t off_part = 0, part_bytes = 0, off_tickets = 0, ticket_bytes = 0;
+    size_t off_chain = 0, chain_bytes = 0;   // exchange area of the chain kernel: arrival counters, hidden states of both layers
     size_t total = 0;
 };
 
@@ -151,6 +152,7 @@ struct DraftPass {
     std::vector<int> lvl_n;          // rows per LSTM level
     int e0 = 0, n_exp = 0;           // tree nodes this pass generates: exp_list[e0 .. e0+n_exp)
     const float* ext = nullptr;      // external features (device), rows addressed by feat_src = -1 - e
+    bool chain = false;              // rows follow each other one by one and both LSTM layers run as chain launches (fv_lstm_chain.hpp)
 };
 
 struct fv_drafter {
@@ -171,6 +173,8 @@ struct fv_drafter {
     int32_t* h_out = nullptr;     // pinned [256] node tokens + [1] error flag
     float last_ms = 0.f;
     int kind_ih0 = 0, kind_hh = 0;   // GemmKind up to 64 rows
+    bool chain_ok = false;           // the recurrent matrix fits on the chip (lstm_chain_fits)
+    bool chain_test = false;         // FV_EXCHANGE_TEST=chain: chain launches wait for a workgroup that does not exist, and give up
 
     template <typename T> T* at(size_t off) const { return (T*)(arena + off); }
     float* state(int layer) const { return (float*)(arena + lay.off_state + (size_t)layer * lay.state_layer_bytes); }
@@ -204,6 +208,8 @@ template <typename EL, int D> int read_kv_t(fv_ctx* c, int layer, int slot0, int
 // upload one weight tensor (up to three host pieces) and re-tile it on the device (independent of D)
 // one pass of the drafter (defined in fv_draft_step.hpp, part of the fv_step.hip units)
 template <typename EL, int D> int run_draft_pass(fv_drafter* d, const DraftPass& ps);
+// ---- defined in fv_draft.hip: one layer's recurrence over the rows of a chain pass (bf16 only)
+int launch_lstm_chain(fv_drafter* d, const DraftPass& ps, int layer, int Tp);
 template <typename EL>
 int tile_upload(fv_ctx* c, int kind, const GemmPlan& p, char* out, const void* h0, size_t n0, const void* h1, size_t n1,
                 const void* h2, size_t n2, int N);

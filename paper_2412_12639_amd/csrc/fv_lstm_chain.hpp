@@ -1,0 +1,264 @@
+// The recurrent half of one LSTM layer over a chain of rows, as one launch: the recurrent matrix stays on the chip
+// (registers and LDS of all compute units) while the rows follow each other.
+//
+// What bounds it.  A chain is serial: row t needs the hidden state of row t - 1.  As separate launches (gather, weight
+// multiplication, cell) every row streams the whole 4h x h matrix again: 134 MB and 33 us per row and layer at hidden
+// 4096, of which 23 us are the stream.  That matrix is 512 KiB per compute unit, and a compute unit has 512 KiB of
+// vector registers and 160 KiB of LDS: each wavefront keeps 96 of its 128 fragments in registers and 32 in LDS, the
+// matrix is read once per launch, and a row costs what the exchange of the hidden state and 128 matrix instructions per
+// wavefront cost.
+// Measured at hidden 4096: 64 rows 243 us per layer (29 us to read the matrix, 3.4 us a row) against 2100; 4 rows 42 against 130.
+//
+// Split: workgroup w owns hidden units 16w .. 16w+15 with their four gates (four 16-row blocks); its four wavefronts
+// take a quarter of the K range each, so a wavefront needs only a quarter of the previous hidden state.  The sums of the
+// four wavefronts meet in LDS (the one barrier of a step), wavefront 0 applies the cell and publishes 16 new values.
+//
+// Exchange: the hidden state is published as bf16 (what the weight multiplication takes) in two buffers used in turn, by
+// write-through stores, and read past the caches.  No flag or barrier across workgroups: |h| <= 1, so bit 14 of its bf16
+// pattern (the top exponent bit) is always zero, and carries the phase of the buffer's use instead; every 4-byte word
+// says itself whether it has arrived.  (A NaN, the only other value a cell can give, would use that bit: with it cleared a
+// NaN's pattern lies strictly above that of 1.0, where no finite state lies, so the reader restores it.)  A buffer is overwritten
+// for step s + 2 only by a workgroup that has all of step s + 1, hence after every workgroup has read step s.
+//
+// All workgroups must be on the chip at the same time.  They say so first: each adds one to a counter, loads its
+// weights, and starts only when the counter shows that everybody has arrived.  If that takes too long (other streams
+// hold compute units), one of them turns the counter's top bit on, which all of them read as "leave": the launch ends
+// without having written anything but *aborted, and the host runs the pass again as separate launches.  After a start
+// nothing but the workgroups' own progress is waited for.
+#pragma once
+#include "fv_device.hpp"
+#include "fv_draft_kernels.hpp"
+
+struct LstmChainArgs {
+    const uint4* Wt;       // tiled recurrent matrix [4h][h]
+    const uint4* zeros;    // at least 1 KiB of zeros
+    const float* g_in;     // [Tp][4h] input multiplication of the pass's rows
+    const float* bias;     // [4h]
+    float* state;          // this layer's state rows [257][2][h]
+    void* xnext;           // [h/8][Tp][8] next layer's input, or null
+    uint16_t* xchg;        // [2][h], zero when the launch starts
+    uint32_t* sync;        // arrival counter, zero when the launch starts
+    uint32_t* aborted;     // set to 1 when the workgroups did not get on the chip together
+    uint32_t* fault;       // set to 1 when a published value did not arrive
+    int t0, r0, n;         // the chain: pass rows t0 .. t0+n-1, state rows r0 + t0 ..
+    int lpred;             // state row the first one continues
+    int Tp, h;
+    unsigned expect;       // arrivals to wait for (the grid; one more in the test of the give-up path)
+    unsigned arrive_looks; // looks at the counter before giving up
+    unsigned spin_limit;   // looks at a published value that has not arrived
+};
+
+// K fragments (32 columns) per wavefront, rounded up to a built size, and how many of them stay in registers: all, or three of
+// every four (hidden 4096: 96 of 128 registers quads; 128 KiB of LDS for the rest)
+constexpr int lstm_chain_reg_frags(int nkf) { return nkf > 16 ? nkf / 4 * 3 : nkf; }
+constexpr size_t lstm_chain_smem(int nkf) {
+    return ((size_t)4 * (nkf - lstm_chain_reg_frags(nkf)) * 4 * 64 + (size_t)4 * nkf * 4) * 16 + 2 * 4 * 4 * 16 * 4 + 16;
+}
+
+template <int NKF>
+static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+    constexpr int RKF = lstm_chain_reg_frags(NKF), LKF = NKF - RKF;
+    constexpr int GF = NKF < 4 ? NKF : 4;
+    static_assert(NKF % GF == 0 && (LKF == 0 || LKF == NKF / 4), "whole groups");
+    constexpr int NV = (4 * NKF + 63) / 64;        // 16-byte pieces of the hidden state per lane
+    constexpr int SC1 = 16;
+    constexpr unsigned LEAVE = 0x80000000u, TAG = 0x40004000u;
+    extern __shared__ uint4 lds_chain[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int u = lane & 15, q = lane >> 4;
+    const int wg = blockIdx.x, h = a.h;
+    const int kf_real = h >> 7, quarter = h >> 2;
+    uint4* const wl = lds_chain + (size_t)wave * LKF * 4 * 64 + lane;                       // [LKF][4 gates][64 lanes] of this wavefront
+    uint4* const hs = lds_chain + (size_t)4 * LKF * 4 * 64 + (size_t)wave * NKF * 4;        // its quarter of the hidden state
+    float* const part = (float*)(lds_chain + (size_t)4 * LKF * 4 * 64 + (size_t)4 * NKF * 4);   // [2][4 wavefronts][4 gates][16]
+    unsigned* const go = (unsigned*)(part + 2 * 4 * 4 * 16);
+
+    if (tid == 0) __hip_atomic_fetch_add(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+    // weights: row block g = gate g, rows g*h + 16*wg ..; the matrix is tiled for 32-row strips and 16-column fragments, of
+    // which a 16x16x32 operand takes half the rows of two neighbours.  Columns past h (sizes between the built ones) are zero.
+    const int n_half = h >> 6;   // half K batches
+    auto w_addr = [&](int g, int kf) {
+        const int strip = g * (h >> 5) + (wg >> 1);
+        const int F = wave * (h >> 6) + 2 * kf + (q >> 1);
+        const uint4* p = a.Wt + ((((size_t)(strip >> 1) * n_half + (F >> 2)) * 2 + (strip & 1)) * 4 + (F & 3)) * 64 + (wg & 1) * 16 + u + 32 * (q & 1);
+        return kf < kf_real ? p : a.zeros + lane;
+    };
+    u32x4_t w[RKF][4];   // fragments in K order; with some of them in LDS every fourth is there
+#pragma unroll
+    for (int i = 0; i < RKF; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) w[i][g] = *(const u32x4_t*)w_addr(g, LKF > 0 ? i / 3 * 4 + i % 3 : i);
+    // The matrix instructions take their operand from the accumulation registers as well, but the compiler, left alone, parks
+    // values there and copies them back before each use; said once that a value lives there, it uses it in place.
+#pragma unroll
+    for (int i = 0; i < RKF; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            if (i * 4 + g < RKF * 4 - 36) asm volatile("" : "+a"(w[i][g]));
+    for (int i = 0; i < LKF; ++i) {
+        uint4 v[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) v[g] = *w_addr(g, 4 * i + 3);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) wl[(i * 4 + g) * 64] = v[g];
+    }
+
+    // the state the chain continues
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int vec = lane + 64 * j;
+        if (vec < 4 * NKF) {
+            float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (vec < 4 * kf_real) {
+                const float4* sp = (const float4*)(a.state + (size_t)a.lpred * 2 * h + wave * quarter + vec * 8);
+                const float4 x0 = sp[0], x1 = sp[1];
+                f[0] = x0.x; f[1] = x0.y; f[2] = x0.z; f[3] = x0.w; f[4] = x1.x; f[5] = x1.y; f[6] = x1.z; f[7] = x1.w;
+            }
+            hs[vec] = Tr<BF16>::pack(f);
+        }
+    }
+    // wavefront 0: lane (q, u) owns gate q of unit u; every lane of a unit keeps the same cell state
+    const size_t unit = (size_t)16 * wg + u;
+    const float bias = a.bias[(size_t)q * h + unit];
+    float c = a.state[((size_t)a.lpred * 2 + 1) * h + unit];
+
+    if (tid == 0) {
+        unsigned seen = 0;
+        for (unsigned looks = 0;; ++looks) {
+            seen = __hip_atomic_load(a.sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((seen & LEAVE) || seen == a.expect) break;
+            if (looks >= a.arrive_looks) {   // "everybody is here" and "leave" exclude each other: one word decides
+                unsigned old = seen;
+                if (__hip_atomic_compare_exchange_strong(a.sync, &old, seen | LEAVE, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                    seen |= LEAVE;
+                    break;
+                }
+                continue;
+            }
+            __builtin_amdgcn_s_sleep(8);
+        }
+        if (seen & LEAVE) __hip_atomic_store(a.aborted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *go = (seen & LEAVE) ? 0u : 1u;
+    }
+    __syncthreads();
+    if (*go == 0u) return;
+
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.xchg, 0, 4 * h, 0x00020000);
+    const float* gin_p = a.g_in + (size_t)a.t0 * 4 * h + (size_t)q * h + unit;
+    float gin = *gin_p;
+    unsigned limit = a.spin_limit;
+    for (int s = 0; s < a.n; ++s) {
+        const float gin_now = gin;
+        if (s + 1 < a.n) gin = gin_p[(size_t)(s + 1) * 4 * h];
+        if (s > 0) {   // this wavefront's quarter of the state of step s - 1
+            const unsigned ph = (((s - 1) >> 1) & 1) ? 0u : TAG;
+            u32x4_t v[NV];
+            for (unsigned looks = 0;; ++looks) {
+                asm volatile("" ::: "memory");   // a look is a look: the loads stay in the loop
+                unsigned off = 0u;
+#pragma unroll
+                for (int j = 0; j < NV; ++j) {
+                    const int vec = (lane + 64 * j < 4 * kf_real) ? lane + 64 * j : 4 * kf_real - 1;
+                    v[j] = __builtin_amdgcn_raw_buffer_load_b128(xrs, (unsigned)((((s - 1) & 1) * h + wave * quarter + vec * 8) * 2), 0, SC1);
+                }
+#pragma unroll
+                for (int j = 0; j < NV; ++j) off |= (v[j].x ^ ph) | (v[j].y ^ ph) | (v[j].z ^ ph) | (v[j].w ^ ph);
+                if (__all((off & TAG) == 0u)) break;
+                if (looks >= limit) {
+                    limit = 0;   // the results are lost: the rest is not waited for either
+                    if (lane == 0) __hip_atomic_store(a.fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+            }
+            auto plain = [&](unsigned x) {
+                x ^= ph;
+                const unsigned over = ((x & 0x7fff7fffu) + 0x407f407fu) & 0x80008000u;   // halves above 1.0: a NaN without its top exponent bit
+                return x | (over >> 1);
+            };
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+                if (lane + 64 * j < 4 * kf_real) hs[lane + 64 * j] = make_uint4(plain(v[j].x), plain(v[j].y), plain(v[j].z), plain(v[j].w));
+        }
+        __builtin_amdgcn_wave_barrier();   // hs belongs to this wavefront: LDS accesses of one wavefront stay in order
+        floatx4 acc[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+        // groups of GF fragments; the LDS reads of a group are out while the group before it multiplies
+        u32x4_t b[2][GF], wb[2][4];
+        auto fetch = [&](int gr, u32x4_t (&bd)[GF], u32x4_t (&wd)[4]) {
+#pragma unroll
+            for (int j = 0; j < GF; ++j) bd[j] = *(const u32x4_t*)&hs[(gr * GF + j) * 4 + q];   // the same column in all sixteen
+            if constexpr (LKF > 0) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) wd[g] = *(const u32x4_t*)&wl[(gr * 4 + g) * 64];
+            }
+        };
+        fetch(0, b[0], wb[0]);
+#pragma unroll
+        for (int gr = 0; gr < NKF / GF; ++gr) {
+            if (gr + 1 < NKF / GF) fetch(gr + 1, b[(gr + 1) & 1], wb[(gr + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < GF; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const u32x4_t wv = (LKF > 0 && j == 3) ? wb[gr & 1][g] : w[LKF > 0 ? (gr * 3 + j) % RKF : gr * GF + j][g];
+                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv), __builtin_bit_cast(bf16x8_t, b[gr & 1][j]), acc[g], 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_wave_barrier();
+        // lane (q, any column): rows 4q .. 4q+3 of every gate block
+        float* const ps = part + (s & 1) * (4 * 4 * 16);
+        if (u == 0) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) *(floatx4*)(ps + (wave * 4 + g) * 16 + 4 * q) = acc[g];
+        }
+        __syncthreads();   // part[s & 1] is next written after the barrier of step s + 1, which wavefront 0 reaches when it has read it
+        if (wave == 0) {
+            float g_rec = ps[(0 * 4 + q) * 16 + u];
+#pragma unroll
+            for (int w_ = 1; w_ < 4; ++w_) g_rec += ps[(w_ * 4 + q) * 16 + u];
+            const float pre = gin_now + g_rec + bias;
+            const float act = (q == 2) ? tanhf(pre) : fv_sigmoid(pre);
+            const float gi = __shfl(act, u), gf = __shfl(act, 16 + u), gg = __shfl(act, 32 + u), go_ = __shfl(act, 48 + u);
+            c = gf * c + gi * gg;
+            const float hn = go_ * tanhf(c);
+            const __bf16 hb = (__bf16)hn;
+            const unsigned mine = __builtin_bit_cast(uint16_t, hb), other = (unsigned)__shfl_xor((int)mine, 1);
+            const unsigned pair = mine | (other << 16);   // even lanes: units u, u + 1
+            const bool packs = q == 0 && (u & 1) == 0;
+            if (packs && s + 1 < a.n)
+                __builtin_amdgcn_raw_buffer_store_b32((pair & ~TAG) | (((s >> 1) & 1) ? 0u : TAG), xrs, (unsigned)(((s & 1) * h + (int)unit) * 2), 0, SC1);
+            const int t = a.t0 + s;
+            if (q < 2) a.state[((size_t)(a.r0 + t) * 2 + q) * h + unit] = q == 0 ? hn : c;
+            if (a.xnext && packs) *(unsigned*)((char*)a.xnext + ((unit >> 3) * a.Tp + t) * 16 + (unit & 7) * 2) = pair;
+        }
+    }
+}
+
+// What LAYER 1 leaves for the decoder block, for rows whose states are there: the residual stream x, x * gain and the
+// per-strip sums of squares (the second half of k_lstm_cell).
+struct LstmOutArgs { const float* state; float* x; void* xb; const float* gain; float* ssq; int r0, t0, n, Tp, h; };
+template <typename EL>
+static __global__ __launch_bounds__(256) void k_lstm_out(LstmOutArgs a) {
+    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const int qn = a.h / 4;
+    const int i = (int)(idx / qn);
+    const int f0 = (int)(idx % qn) * 4;
+    if (i >= a.n) return;                  // whole strips leave together: h is a multiple of 64
+    const int t = a.t0 + i;
+    const float4 v = *(const float4*)(a.state + (size_t)(a.r0 + t) * 2 * a.h + f0);
+    ((float4*)a.x)[(size_t)(f0 >> 2) * a.Tp + t] = v;
+    const float4 gn = *(const float4*)(a.gain + f0);
+    store4_act<EL>(a.xb, a.Tp, f0, t, v.x * gn.x, v.y * gn.y, v.z * gn.z, v.w * gn.w);
+    float ssq = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    ssq += __shfl_xor(ssq, 1);
+    ssq += __shfl_xor(ssq, 2);
+    ssq += __shfl_xor(ssq, 4);
+    if ((f0 & 31) == 0) a.ssq[(size_t)(f0 >> 5) * a.Tp + t] = ssq;
+}

@@ -277,3 +277,43 @@ def test_drafted_tree_goes_through_verification():
         assert dr.state()[0] == tgt.state()[0]
     dr.close()
     tgt.close()
+
+
+@pytest.mark.parametrize("hidden", [256, 384, 512, 1024])
+@pytest.mark.parametrize("give_up", [False, True])
+def test_chain_launches(hidden, give_up, monkeypatch):
+    """Commits whose rows go through the LSTM in one launch per layer: two rows (the shortest), an odd count, a whole piece and
+    one row more (the second piece is a single row), at hidden sizes that fill a built kernel and one that does not (384).
+    give_up: the launches' workgroups wait for one that does not exist and leave; the separate launches must take over and the
+    call must not show it."""
+    import torch
+    from dataclasses import replace
+    from paper_2412_12639_amd.binding import FalconDrafter, FalconVerifier
+    if give_up:
+        monkeypatch.setenv("FV_EXCHANGE_TEST", "chain")
+    s = replace(shape_by_name("tiny-bf16"), name=f"tiny-bf16-h{hidden}", hidden=hidden)
+    lw, dw = gen_weights(s, seed=61, gain_jitter=0.1), gen_drafter_weights(s, seed=62, gain_jitter=0.1)
+    tgt = FalconVerifier(s, 200, 64)
+    tgt.init_weights(lw)
+    dr = FalconDrafter(tgt, 2)
+    dr.init_weights(dw)
+    orc = do.DrafterOracle(s, lw, dw, 2, 200)
+    for n in (2, 7, 65, 64, 1):
+        feats = gen_features(400 + n, n, s.hidden)
+        toks = np.random.default_rng(n).integers(0, s.vocab, n)
+        dr.commit(toks, torch.from_numpy(feats).cuda())
+        f_ref, l_ref = orc.commit(feats, toks)
+        rows = dr.state()[2]
+        assert rows == (n - 1) % 64 + 1
+        ef, el = _rel(dr.rows("features", 0, rows), f_ref[-rows:]), _rel(dr.rows("logits", 0, rows), l_ref[-rows:])
+        kd, vd = dr.read_kv(orc.L - n, n)
+        ek, ev = _rel(kd, orc.K[orc.L - n:orc.L]), _rel(vd, orc.V[orc.L - n:orc.L])
+        say(f"  hidden {hidden}, {n} pairs: features {ef:.2e}, logits {el:.2e}, k {ek:.2e}, v {ev:.2e}")
+        assert max(ef, el, ek, ev) <= 2e-2       # the bar of every bf16 commit above: the same formats, other sums
+    feats = np.full((3, s.hidden), 1.0, dtype=np.float32)
+    feats[1, 5] = np.nan                         # a state that is no number goes through the exchange as one
+    with pytest.raises(Exception) as e:
+        dr.commit([1, 2, 3], torch.from_numpy(feats).cuda())
+    assert e.value.status == -10
+    dr.close()
+    tgt.close()
