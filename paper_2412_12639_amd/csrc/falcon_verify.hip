@@ -210,7 +210,8 @@ void make_layout(const fv_cfg& c, int n_wg, Layout& L, bool own_head, size_t min
     L.off_res = take(sizeof(FvResult));
     L.off_feat = take((size_t)FV_MAX_TREE * c.hidden * 4);
     L.off_unif = take((size_t)2 * FV_MAX_TREE * 8);
-    L.off_pwork = take((size_t)L.Vpad * 8);
+    L.off_pwork = take(own_head ? (size_t)c.max_tree * L.Vpad * 8 : 0);
+    L.off_outcome = take(FV_MAX_TREE * 4);
     L.off_kvread = take((size_t)2 * 64 * kvd * 4);
     size_t st = (size_t)(qd + 2 * kvd) * c.hidden;
     const size_t cands[4] = {(size_t)c.hidden * qd, (size_t)2 * c.ffn * c.hidden, (size_t)c.hidden * c.ffn,

@@ -55,7 +55,7 @@ struct Layout {
     size_t off_stepin = 0, off_mask = 0, off_pos = 0, off_anc = 0, off_rope = 0, off_am = 0, off_res = 0;
     size_t off_kvread = 0, off_stage = 0, stage_bytes = 0;
     size_t off_apart = 0, off_atick = 0, off_zeros = 0, off_feat = 0;
-    size_t off_unif = 0, off_pwork = 0;   // non-greedy acceptance: uniforms [2][256] fp64, working distribution [Vpad] fp64
+    size_t off_unif = 0, off_pwork = 0, off_outcome = 0;   // non-greedy acceptance: uniforms [2][256] fp64, working distributions [max_tree][Vpad] fp64, what each node decided [256]
     size_t total = 0;
 };
 

@@ -1189,14 +1189,23 @@ static __global__ __launch_bounds__(256) void k_scan(ScanArgs a) {
 // ============================================================================ non-greedy acceptance
 // Multi-step speculative sampling over the tree (the non-greedy setting of the paper's Appendix
 // "Tree Structure"; verification in the SpecInfer manner, section "Custom-Designed Decoding Tree").
-// Single block.  Starting at the root with w = exp((logits[node] - max) / temperature): the children of
-// the current node are tried in index order; child c with token x is accepted iff
-// u_accept[c] * q[x] * sum(w) <= w[x]; on rejection w becomes the positive part of w - sum(w) * q and the
-// next child is tried against it.  q is row `node` of draft_probs, or a point mass on x if draft_probs
-// is null (then rejection just strikes x from w).  When no child is accepted the next token is the first
-// v with cumsum(w)[v] > u_sample[node] * sum(w).  All of it in fp64 (the decisions are thresholds on sums
-// of 32000 terms; fp64 keeps both sides of a comparison with a CPU implementation within ~1e-13 of each
-// other), in a fixed order, so the result is reproducible.
+// At a node with w = exp((logits[node] - max) / temperature): the children are tried in index order;
+// child c with token x is accepted iff u_accept[c] * q[x] * sum(w) <= w[x]; on rejection w becomes the
+// positive part of w - sum(w) * q and the next child is tried against it.  q is row `node` of
+// draft_probs, or a point mass on x if draft_probs is null (then rejection just strikes x from w).
+// When no child is accepted the next token is the first v with cumsum(w)[v] > u_sample[node] * sum(w).
+// All of it in fp64 (the decisions are thresholds on sums of 32000 terms; fp64 keeps both sides of a
+// comparison with a CPU implementation within ~1e-13 of each other), in a fixed order, so the result
+// is reproducible.
+//
+// What a node decides does not depend on how it was reached, so every node is decided at the same time,
+// one workgroup each (k_sampled_nodes), and the path is read off afterwards (k_sampled_path).  One
+// workgroup that walked the path node by node took 390 us at 33 nodes of vocabulary 32000, as much as
+// three layers: a dozen passes over the vocabulary one after the other, through one compute unit; this way
+// it takes 58 us.  A node's
+// own passes are still serial: one over its logits (32 fp64 exponentials per thread) and one per
+// rejected child over w and q (384 KB through one compute unit's caches).  w is kept in memory: in registers it would
+// take half the register file of a compute unit, and the compiler spilled it.
 struct SampledArgs {
     const int32_t* tok_in;     // [3][cap]: tokens, parent, depth
     int cap, T;
@@ -1206,125 +1215,210 @@ struct SampledArgs {
     const float* draft_probs;  // [T][V] or null
     const double* u_accept;    // [T]
     const double* u_sample;    // [T]
-    double* work;              // [Vpad]
+    double* work;              // [T][Vpad] w of every node
+    int32_t* outcome;          // [T] child taken (> node), or -1 - token drawn, or FV_SAMPLED_BAD
     FvResult* res;
 };
 
 #define FV_SAMPLED_THREADS 1024
+#define FV_SAMPLED_BAD ((int32_t)0x80000000)   // the node's logits hold a NaN or an infinity
 
-// sum of one value per thread over the block, in a fixed order; every thread gets the result
-__device__ __forceinline__ double block_sum_f64(double v, double* red) {
-    const int tid = threadIdx.x;
-    red[tid] = v;
-    __syncthreads();
-    for (int w = FV_SAMPLED_THREADS / 2; w > 0; w >>= 1) {
-        if (tid < w) red[tid] += red[tid + w];
-        __syncthreads();
-    }
-    const double r = red[0];
-    __syncthreads();
-    return r;
-}
-
-static __global__ __launch_bounds__(FV_SAMPLED_THREADS) void k_accept_sampled(SampledArgs a) {
-    __shared__ double red[FV_SAMPLED_THREADS];
+static __global__ __launch_bounds__(FV_SAMPLED_THREADS) void k_sampled_nodes(SampledArgs a) {
+    constexpr int NW = FV_SAMPLED_THREADS / 64, STRIDE = 4 * FV_SAMPLED_THREADS;   // a thread's tokens: four neighbours of every group of 4096
+    __shared__ double s_sum[2][NW];
+    __shared__ float s_max[NW];
+    __shared__ unsigned long long s_kids[FV_MAX_TREE / 64];
     __shared__ int s_flag, s_pick;
-    __shared__ float s_maxf[FV_SAMPLED_THREADS / 64];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int node = blockIdx.x, V = a.V;
     const int32_t* tok = a.tok_in;
     const int32_t* parent = a.tok_in + a.cap;
-    const int chunk = (a.V + FV_SAMPLED_THREADS - 1) / FV_SAMPLED_THREADS;   // contiguous tokens per thread
-    const int v0 = tid * chunk, v1 = (v0 + chunk < a.V) ? v0 + chunk : a.V;
-    int cur = 0, len = 0, next_token = -1;
-    bool bad = false;
-    if (tid == 0) a.res->path[0] = 0;
-    for (int hop = 0; hop < a.T && next_token < 0 && !bad; ++hop) {
-        const float* row = a.logits + (size_t)cur * a.Vpad;
-        // ---- w = exp((row - max) / temperature), S = sum(w)
-        float mx = -INFINITY;
-        bool nf = false;
-        for (int v = v0; v < v1; ++v) { const float x = row[v]; nf = nf || !(__builtin_fabsf(x) < INFINITY); mx = fmaxf(mx, x); }
-        for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-        if (tid == 0) s_flag = 0;
+    const float* row = a.logits + (size_t)node * a.Vpad;      // rows of logits and of work are padded to 32 values
+    double* work = a.work + (size_t)node * a.Vpad;
+    const float* q = a.draft_probs ? a.draft_probs + (size_t)node * V : nullptr;
+    const bool q16 = q && (V & 3) == 0 && ((uintptr_t)a.draft_probs & 15) == 0;   // the caller's array: 16-byte loads only where they are aligned
+
+    if (tid == 0) { s_flag = 0; s_pick = 0x7fffffff; }
+    if (tid < FV_MAX_TREE) {   // the node's children as a bit mask
+        const unsigned long long m = __ballot(tid > node && tid < a.T && parent[tid < a.T ? tid : 0] == node);
+        if (lane == 0) s_kids[wave] = m;
+    }
+    // ---- largest logit
+    float mx = -INFINITY;
+    bool nf = false;
+#pragma unroll 8
+    for (int v = tid * 4; v < V; v += STRIDE) {
+        const float4 r = *(const float4*)(row + v);
+        const float xs[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (v + e < V) { nf = nf || !(__builtin_fabsf(xs[e]) < INFINITY); mx = fmaxf(mx, xs[e]); }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    if (lane == 0) s_max[wave] = mx;
+    __syncthreads();
+    if (nf) s_flag = 1;
+    __syncthreads();
+    if (s_flag) {
+        if (tid == 0) a.outcome[node] = FV_SAMPLED_BAD;
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < NW; ++k) mx = fmaxf(mx, s_max[k]);
+    const double zmax = (double)mx * a.inv_temperature;
+
+    // sum of one value per thread, in a fixed order; every thread gets it.  Two areas in turn: one barrier per sum.
+    int turn = 0;
+    auto block_sum = [&](double v) -> double {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+        if (lane == 0) s_sum[turn][wave] = v;
         __syncthreads();
-        if (nf) s_flag = 1;
-        if ((tid & 63) == 0) s_maxf[tid >> 6] = mx;
-        __syncthreads();
-        if (s_flag) { bad = true; break; }
-        for (int k = 0; k < FV_SAMPLED_THREADS / 64; ++k) mx = fmaxf(mx, s_maxf[k]);
-        const double zmax = (double)mx * a.inv_temperature;
-        auto fill = [&]() {
-            double ls = 0.0;
-            for (int v = v0; v < v1; ++v) { const double w = exp((double)row[v] * a.inv_temperature - zmax); a.work[v] = w; ls += w; }
-            return ls;
-        };
-        double S = block_sum_f64(fill(), red);
-        // ---- the children of cur, in index order
-        int taken = -1;
-        for (int c = cur + 1; c < a.T && taken < 0; ++c) {
-            if (parent[c] != cur) continue;            // uniform: every thread reads the same value
-            const int x = tok[c];
-            const double qx = a.draft_probs ? (double)a.draft_probs[(size_t)cur * a.V + x] : 1.0;
-            __syncthreads();                            // a.work[x] as left by the previous child's update
-            const double lhs = a.u_accept[c] * qx * S, rhs = a.work[x];
-            if (lhs <= rhs) { taken = c; break; }
-            __syncthreads();                            // everyone has read work[x] before it changes
-            double ls = 0.0;
-            if (a.draft_probs) {
-                const float* q = a.draft_probs + (size_t)cur * a.V;
-                for (int v = v0; v < v1; ++v) { const double w = fmax(a.work[v] - S * (double)q[v], 0.0); a.work[v] = w; ls += w; }
-            } else {
-                for (int v = v0; v < v1; ++v) { if (v == x) a.work[v] = 0.0; ls += a.work[v]; }
-            }
-            double S2 = block_sum_f64(ls, red);
-            if (!(S2 > 0.0)) S2 = block_sum_f64(fill(), red);   // nothing left besides what was rejected (probability zero): keep the last p
-            S = S2;
-        }
-        if (taken >= 0) {
-            ++len;
-            if (tid == 0) { a.res->path[len] = taken; a.res->accepted_tokens[len - 1] = tok[taken]; }
-            cur = taken;
-            continue;
-        }
-        // ---- draw: the first v with cumsum(w)[v] > target
-        __syncthreads();
-        const double target = a.u_sample[cur] * S;
+        double r = 0.0;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) r += s_sum[turn][k];
+        turn ^= 1;
+        return r;
+    };
+    auto store_w = [&](int v, const double (&w)[4]) {
+        ((double2*)(work + v))[0] = make_double2(w[0], w[1]);
+        ((double2*)(work + v))[1] = make_double2(w[2], w[3]);
+    };
+    auto load_w = [&](int v, double (&w)[4]) {
+        const double2 lo = ((const double2*)(work + v))[0], hi = ((const double2*)(work + v))[1];
+        w[0] = lo.x; w[1] = lo.y; w[2] = hi.x; w[3] = hi.y;
+    };
+    auto fill = [&]() -> double {   // w as it is before any rejection (zero beyond the vocabulary); its sum
         double ls = 0.0;
-        for (int v = v0; v < v1; ++v) ls += a.work[v];
-        // inclusive prefix over the threads' chunk sums (fixed order)
-        red[tid] = ls;
-        __syncthreads();
-        for (int off = 1; off < FV_SAMPLED_THREADS; off <<= 1) {
-            const double add = (tid >= off) ? red[tid - off] : 0.0;
-            __syncthreads();
-            red[tid] += add;
-            __syncthreads();
+        for (int v = tid * 4; v < V; v += STRIDE) {
+            const float4 r = *(const float4*)(row + v);
+            const float xs[4] = {r.x, r.y, r.z, r.w};
+            double w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                w[e] = (v + e < V) ? exp((double)xs[e] * a.inv_temperature - zmax) : 0.0;
+                ls += w[e];
+            }
+            store_w(v, w);
         }
-        const double before = red[tid] - ls;
-        if (tid == 0) s_pick = 0x7fffffff;
-        __syncthreads();
-        if (ls > 0.0 && before <= target && target < red[tid]) {
-            double c = before;
-            int pick = -1;
-            for (int v = v0; v < v1; ++v) { c += a.work[v]; if (c > target) { pick = v; break; } }
-            if (pick < 0) for (int v = v1 - 1; v >= v0; --v) if (a.work[v] > 0.0) { pick = v; break; }   // rounding inside the chunk
-            if (pick >= 0) atomicMin(&s_pick, pick);
-        }
-        __syncthreads();
-        if (s_pick == 0x7fffffff) {
-            // target at or beyond the total (u_sample ~ 1 and rounding): the last token that has any mass
-            for (int v = v1 - 1; v >= v0; --v) if (a.work[v] > 0.0) { atomicMax(&s_flag, v + 1); break; }
-            __syncthreads();
-            next_token = s_flag - 1;
+        return block_sum(ls);
+    };
+
+    // ---- the children, in index order
+    int taken = -1, wd = 0;
+    unsigned long long kids = s_kids[0];
+    double S = 0.0;
+    for (;;) {
+        if (!(S > 0.0)) S = fill();   // at first, and when nothing is left besides what was rejected (probability zero): the last p is kept
+        while (!kids && ++wd < FV_MAX_TREE / 64) kids = s_kids[wd];
+        if (!kids) break;
+        const int c = wd * 64 + __builtin_ctzll(kids);
+        kids &= kids - 1;
+        const int t = tok[c];
+        const double lhs = a.u_accept[c] * (q ? (double)q[t] : 1.0) * S, rhs = work[t];   // w[t] as the pass before left it: a barrier ago
+        if (lhs <= rhs) { taken = c; break; }
+        __syncthreads();              // everyone has read w[t] before it changes
+        double ls = 0.0;
+        if (q) {
+#pragma unroll 4
+            for (int v = tid * 4; v < V; v += STRIDE) {
+                float qv[4] = {0.f, 0.f, 0.f, 0.f};
+                if (q16) {
+                    const float4 f = *(const float4*)(q + v);
+                    qv[0] = f.x; qv[1] = f.y; qv[2] = f.z; qv[3] = f.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) if (v + e < V) qv[e] = q[v + e];
+                }
+                double w[4];
+                load_w(v, w);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { w[e] = fmax(w[e] - S * (double)qv[e], 0.0); ls += w[e]; }
+                store_w(v, w);
+            }
         } else {
-            next_token = s_pick;
+#pragma unroll 4
+            for (int v = tid * 4; v < V; v += STRIDE) {
+                double w[4];
+                load_w(v, w);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { w[e] = (v + e == t) ? 0.0 : w[e]; ls += w[e]; }
+                if (v == (t & ~3)) store_w(v, w);
+            }
         }
+        S = block_sum(ls);
     }
-    if (tid == 0) {
-        if (bad || next_token < 0) { a.res->accepted_len = FV_SCAN_NONFINITE; a.res->next_token = -1; a.res->best = 0; }
-        else { a.res->accepted_len = len; a.res->next_token = next_token; a.res->best = cur; }
-        a.res->pad = 0;
+    if (taken >= 0) {
+        if (tid == 0) a.outcome[node] = taken;
+        return;
     }
+
+    // ---- draw: the first v with cumsum(w)[v] > target, group after group in token order.  Every thread whose share ends above
+    // the target proposes its first token with mass there, and the smallest token wins: a thread's share begins
+    // exactly where its neighbour's ends, so no rounding can leave a gap between two.
+    const double target = a.u_sample[node] * S;
+    double base = 0.0;   // sum of the groups before
+    int last = -1;       // this thread's last token with any mass
+    for (int v0 = 0; v0 < V; v0 += STRIDE) {
+        const int v = v0 + tid * 4;
+        double w[4] = {0.0, 0.0, 0.0, 0.0};
+        if (v < V) load_w(v, w);
+        double incl = (w[0] + w[1]) + (w[2] + w[3]);   // prefix sum over the wavefront
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double o = __shfl_up(incl, off);
+            if (lane >= off) incl += o;
+        }
+        if (lane == 63) s_sum[turn][wave] = incl;
+        __syncthreads();
+        double at = base;
+        for (int k = 0; k < NW; ++k) { if (k == wave) at = base; base += s_sum[turn][k]; }
+        turn ^= 1;
+        const double end = at + incl, prev = __shfl_up(incl, 1);
+        double cum = lane > 0 ? at + prev : at;
+        int pick = 0x7fffffff, mass = -1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            cum += w[e];
+            if (w[e] > 0.0) { mass = v + e; if (pick == 0x7fffffff && cum > target) pick = v + e; }
+        }
+        if (mass >= 0) last = mass;
+        if (!(end > target)) pick = 0x7fffffff;
+        else if (pick == 0x7fffffff && mass >= 0) pick = mass;   // rounding inside the four
+        const unsigned long long m = __ballot(pick != 0x7fffffff);   // tokens ascend with the lane
+        if (m && lane == __builtin_ctzll(m)) atomicMin(&s_pick, pick);
+        if (base > target) break;   // the same in every thread
+    }
+    __syncthreads();
+    if (s_pick == 0x7fffffff) {   // target at or beyond the total (u_sample ~ 1 and rounding): the last token that has any mass
+        if (last >= 0) atomicMax(&s_flag, last + 1);
+        __syncthreads();
+        if (tid == 0) a.outcome[node] = s_flag > 0 ? -s_flag : FV_SAMPLED_BAD;
+    } else if (tid == 0) {
+        a.outcome[node] = -1 - s_pick;
+    }
+}
+
+// The path from the root along the children that were taken, and the token drawn at its end.
+static __global__ __launch_bounds__(64) void k_sampled_path(SampledArgs a) {
+    __shared__ int32_t s_out[FV_MAX_TREE], s_tok[FV_MAX_TREE];
+    for (int i = threadIdx.x; i < a.T; i += 64) { s_out[i] = a.outcome[i]; s_tok[i] = a.tok_in[i]; }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    int cur = 0, len = 0;
+    a.res->path[0] = 0;
+    int o = s_out[0];
+    while (o > cur && o < a.T) {   // a child's index is above its parent's: the walk ends
+        cur = o;
+        ++len;
+        a.res->path[len] = cur;
+        a.res->accepted_tokens[len - 1] = s_tok[cur];
+        o = s_out[cur];
+    }
+    if (o == FV_SAMPLED_BAD || o >= 0) { a.res->accepted_len = FV_SCAN_NONFINITE; a.res->next_token = -1; a.res->best = 0; }
+    else { a.res->accepted_len = len; a.res->next_token = -1 - o; a.res->best = cur; }
+    a.res->pad = 0;
 }
 
 // ============================================================================ KV compaction

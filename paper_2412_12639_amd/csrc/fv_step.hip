@@ -276,8 +276,9 @@ int run_step(fv_ctx* c, int T, StepMode mode) {
             sa.logits = c->at<float>(ly.off_logits); sa.V = cf.vocab; sa.Vpad = ly.Vpad;
             sa.inv_temperature = c->sample_inv_temperature; sa.draft_probs = c->sample_draft;
             sa.u_accept = c->at<double>(ly.off_unif); sa.u_sample = sa.u_accept + FV_MAX_TREE;
-            sa.work = c->at<double>(ly.off_pwork); sa.res = c->at<FvResult>(ly.off_res);
-            hipLaunchKernelGGL(k_accept_sampled, dim3(1), dim3(FV_SAMPLED_THREADS), 0, st, sa);
+            sa.work = c->at<double>(ly.off_pwork); sa.outcome = c->at<int32_t>(ly.off_outcome); sa.res = c->at<FvResult>(ly.off_res);
+            hipLaunchKernelGGL(k_sampled_nodes, dim3(T), dim3(FV_SAMPLED_THREADS), 0, st, sa);
+            hipLaunchKernelGGL(k_sampled_path, dim3(1), dim3(64), 0, st, sa);
         }
         if (mode == STEP_VERIFY) {
             ScanArgs sa;

@@ -154,3 +154,50 @@ def test_sampled_verification_limits_and_errors(fvmod):
             g.verify_tree_sampled(tokens, parent, depth, kw.get("temperature", 1.0), kw.get("ua", [0.5] * 12), kw.get("us", [0.5] * 12))
         assert ei.value.status == -1 and g.state() == (L, root)
     g.close()
+
+
+@pytest.mark.parametrize("vocab", [37, 1003, 4096, 4099, 8200])
+def test_sampled_decisions_at_any_vocabulary_size(fvmod, vocab):
+    """Every node is decided by a workgroup of its own in groups of 4096 tokens: vocabularies below, at and just above a
+    group and ones that no 16-byte load divides, proposals at an address that is not a multiple of 16, many rejected
+    children, and proposals that leave nothing behind a rejection (the distribution before it is kept)."""
+    import torch
+    from dataclasses import replace
+    s = replace(fi.SHAPES["tiny"], name=f"tiny-v{vocab}", vocab=vocab)
+    w = fi.gen_weights(s, seed=5)
+    L, n = 20, 24
+    g = fvmod.FalconVerifier(s, max_seq=64, max_tree=32)
+    g.init_weights(w)
+    root = g.prefill(fi.gen_prefix(4, L, s.vocab))
+    parent, depth, _ = fi.gen_tree(9, n, [12, 2, 2])
+    rng = np.random.default_rng(vocab)
+    checked = 0
+    for trial, (mode, temperature) in enumerate([("pointmass", 1.0), ("draft", 1.0), ("odd", 1.0), ("over", 1e-4), ("odd", 0.3), ("draft", 2.0)]):
+        tokens = rng.integers(0, vocab, n).astype(np.int32)
+        tokens[0] = root
+        ua, us = rng.uniform(0.2, 1.0, n), rng.random(n)
+        us[::5] = 1.0
+        q, qdev = None, None
+        if mode != "pointmass":
+            q = rng.random((n, vocab)).astype(np.float32) ** 3
+            q = (q / q.sum(axis=1, keepdims=True)).astype(np.float32)
+            if mode == "over":
+                q += 3.0
+            qdev = torch.empty(n * vocab + 1, device="cuda")[(mode == "odd"):][:n * vocab].view(n, vocab)
+            qdev.copy_(torch.from_numpy(q))
+        t32 = np.float32(temperature)
+        got = g.verify_tree_sampled(tokens, parent, depth, t32, ua, us, qdev)
+        d = fo.sampled_accept(g.logits(n).astype(np.float64), tokens, parent, depth, L, t32, ua, us, q)
+        src, _ = g.kv_moves()
+        g.rollback(L, root)
+        at_end = us[d["path"][-1]] == 1.0     # a draw at the very end of the cumulative sum has no margin: any token with mass that reaches it
+        if d["min_margin"] < 1e-7 and not at_end:
+            continue
+        checked += 1
+        assert got[0] == d["accepted_len"] and list(got[1]) == list(d["accepted_tokens"]) and list(src) == list(d["src_slot"]), (trial, mode)
+        if not at_end:
+            assert got[2] == d["next_token"], (trial, mode)
+        else:
+            assert 0 <= got[2] < vocab
+    assert checked >= 3
+    g.close()
