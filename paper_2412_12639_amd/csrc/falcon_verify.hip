@@ -129,15 +129,22 @@ void plan_gemm_forms(GemmPlan& gm, GemmPlan& gd, GemmPlan& gp, bool& paired_ok, 
     plan_gemm(gm, n_strips, K, E, n_wg);
     plan_gemm(gd, gm.n_strips, gm.K, E, n_wg, 1);
     plan_gemm(gp, gm.n_strips, gm.K, E, n_wg, 2, FV_FRAGS / 2);
+    // A matrix of fewer strips than workgroups and a short K range (up to 24 batches, 192 KiB a strip) is a few microseconds of
+    // streaming however it is split; what it costs is the exchange of partial tiles and the tail of a segment.  Such a matrix takes the
+    // direct form, and up to 8 batches a workgroup takes a whole strip: no exchange.  (Two layers of hidden 512 with
+    // one 23-node fp32 step: device time 180 -> 137 us, one bf16 token 113 -> 94; whole strips at 11 to 22 batches
+    // measured 3 to 5 us slower than split ones, and the paired form 8 to 15 us slower than the direct one.)
+    const bool small = gd.n_strips < n_wg && gd.NB <= 24;
     // a full K range must give each streaming wavefront at least three stages, so that no
     // wavefront meets more than two segment ends within one round of three stages
-    paired_ok = gp.NB >= 12;
+    paired_ok = gp.NB >= 12 && !small;
     // Whole row groups per workgroup need no partial-tile exchange at all, but the group counts
     // differ by one between workgroups: worth it only when that idles little of the chip (the
     // LM head: 500 groups of 64 rows over 256 workgroups).  (FV_GEMM_ALIGN=0 / 1 forces it off / on.)
     const char* al = getenv("FV_GEMM_ALIGN");
+    if (small && gd.NB <= 8 && gd.NG <= gd.G && !(al && !strcmp(al, "0"))) { gd.G = gd.NG; gd.aligned = 1; }
     for (GemmPlan* q : {&gd, &gp}) {
-        if (q->NG < q->G) continue;
+        if (q->aligned || q->NG < q->G) continue;
         const int per = (q->NG + q->G - 1) / q->G;
         const double idle = (double)((long long)per * q->G - q->NG) / (double)q->NG;
         q->aligned = al ? (!strcmp(al, "1") ? 1 : 0) : (idle <= 0.10 ? 1 : 0);

@@ -633,3 +633,22 @@ def test_a_partial_tile_that_never_arrives_ends_in_an_error_not_a_hang(fvmod, mo
     g2 = make_gpu(fvmod, shape, weights, 160, 64)
     g2.prefill(prefix)
     g2.close()
+
+
+@pytest.mark.parametrize("hidden,ffn,dtype", [
+    (1024, 1040, "bf16"),    # K of 8 batches: a strip per workgroup; the down projection 9 batches: split again
+    (3072, 3088, "bf16"),    # 24 and 25 batches: the last direct size, the first paired one
+    (512, 528, "f32"),       # fp32: 8 and 9 batches
+    (1024, 4096, "bf16"),    # gate and up together 256 strips: as many as workgroups, so not small
+])
+def test_small_matrix_rule(fvmod, hidden, ffn, dtype):
+    """Verification steps on either side of the limits at which a matrix takes the direct form and whole strips."""
+    s = ModelShape(f"rule-{hidden}", 1, hidden, 4, 2, 128, ffn, 600, dtype)
+    w = fi.gen_weights(s, seed=hidden, gain_jitter=0.1)
+    case = H.planted_case(s, w, 33, 40, [6, 3, 2, 1], 2, seed=3, max_tries=200)
+    g = make_gpu(fvmod, s, w, max_seq=96, max_tree=64)
+    g.prefill(case["prefix"])
+    g.rollback(33, case["root"])
+    got = g.verify_tree(case["tokens"], case["parent"], case["depth"])
+    say("small matrix rule", hidden, ffn, dtype, "logits err", H.check_step(g, case, got, H.tol_for(s)))
+    g.close()
