@@ -127,6 +127,14 @@ int build_split_tables(const GemmPlan& p, std::vector<int>& tab) {
 // (one strip per wavefront) and its paired form (two strips per wavefront, half-batch stages).
 void plan_gemm_forms(GemmPlan& gm, GemmPlan& gd, GemmPlan& gp, bool& paired_ok, int n_strips, int K, int E, int n_wg) {
     plan_gemm(gm, n_strips, K, E, n_wg);
+    // Above 64 rows a partial tile is 64 or 128 KiB, so row groups are cut into equal parts, one a workgroup, where that
+    // occupies at least three quarters of the chip: 192 partial tiles instead of 352 for QKV at the 7B shape, none
+    // instead of 500 for its head.  (256 rows, 7B: QKV 43.0 us either way and 10 -> 6 us to reduce, head 86 + 17 -> 86; a gate/up
+    // launch on 172 workgroups takes 73 us against 63 + 12 on 256, at 128 rows 58 against 48 + 7: equal ranges stay there.)
+    if (const int k = std::min(n_wg / gm.NG, gm.NB); k >= 1 && 4 * gm.NG * k >= 3 * n_wg) {
+        gm.G = gm.NG * k;
+        gm.segmax = 2;
+    }
     plan_gemm(gd, gm.n_strips, gm.K, E, n_wg, 1);
     plan_gemm(gp, gm.n_strips, gm.K, E, n_wg, 2, FV_FRAGS / 2);
     // A matrix of fewer strips than workgroups and a short K range (up to 24 batches, 192 KiB a strip) is a few microseconds of
@@ -230,6 +238,20 @@ void make_layout(const fv_cfg& c, int n_wg, Layout& L, bool own_head, size_t min
     // attention key-split partials: at most 8 parts per (head, node block) item, items for 256 rows
     L.off_apart = take((size_t)c.n_q_heads * 8 * 8 * (d / 32 * 1024 + 64) * 4);
     L.off_atick = take((size_t)c.n_q_heads * 8 * 4);
+    if (own_head && c.dtype == FV_BF16 && c.max_seq > 256) {
+        const size_t P = L.Pm = (int)std::min(rup(c.max_seq, 256), (size_t)FV_PROMPT_ROWS);
+        L.off_px = take((size_t)c.hidden * P * 4);
+        L.off_pxb = take((size_t)L.gm[GM_QKV].Kpad * P * L.ESZ);
+        L.off_pq = take((size_t)qd * P * L.ESZ);
+        L.off_pqlo = take((size_t)qd * P * L.ESZ);
+        L.off_pattn = take((size_t)L.gm[GM_O].Kpad * P * L.ESZ);
+        L.off_pact = take((size_t)L.gm[GM_DN].Kpad * P * L.ESZ);
+        L.off_pssq = take((size_t)(c.hidden / 32) * P * 4);
+        L.off_prinv = take(P * 4);
+        L.off_prope = take(P * (d / 2) * 8);
+        L.off_pmask = take(256 * 4 * 8);
+        L.off_ptok = take(P * 4);
+    }
     L.total = o;
 }
 
@@ -407,6 +429,7 @@ int fv_create_ex(const fv_cfg* cfg, void* dev_arena, size_t arena_bytes, void* h
     { const char* e = getenv("FV_EXCHANGE_TEST"); c->exchange_test = e && !strcmp(e, "timeout"); }
     auto fail = [&](int code) { fv_destroy(c); return code; };
     if (hipHostMalloc((void**)&c->h_in, 3 * FV_MAX_TREE * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
+    if (c->lay.Pm > 0 && hipHostMalloc((void**)&c->h_prompt, (size_t)cfg->max_seq * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
     if (hipHostMalloc((void**)&c->h_res, sizeof(FvResult), hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
     if (hipHostMalloc((void**)&c->h_unif, 2 * FV_MAX_TREE * 8, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
     if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) return fail(FV_E_HIP);
@@ -472,6 +495,7 @@ extern "C" {
 void fv_destroy(fv_ctx* c) {
     if (!c) return;
     if (c->h_in) (void)hipHostFree(c->h_in);
+    if (c->h_prompt) (void)hipHostFree(c->h_prompt);
     if (c->h_res) (void)hipHostFree(c->h_res);
     if (c->h_unif) (void)hipHostFree(c->h_unif);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
@@ -500,8 +524,22 @@ int fv_prefill(fv_ctx* c, const int32_t* tokens, int32_t n, int32_t* next_token)
     c->prefilled = false;
     c->cur_len = 0;
     int done = 0;
+    const int tail = (n - 1) % c->cfg.max_tree + 1;   // rows of the last chunk, whose logits and activations can be read back
+    if (c->lay.Pm > 0) {
+        // Rows before the last chunk go through the layers up to Pm at a time.  Worth it above 256 rows and two chunks: a layer of
+        // the 7B shape takes 226 us for a chunk of 256 rows, 111 for one of 64, and 430 for 512 rows at once, 830 for 1792.
+        memcpy(c->h_prompt, tokens, (size_t)n * 4);
+        while (n - tail - done > 256 && n - tail - done >= 2 * c->cfg.max_tree) {
+            const int m = std::min(n - tail - done, c->lay.Pm);
+            const int rc = c->cfg.head_dim == 128 ? run_prompt<BF16, 128>(c, c->h_prompt + done, m) : run_prompt<BF16, 64>(c, c->h_prompt + done, m);
+            if (rc) return rc;
+            done += m;
+            c->cur_len = done;
+        }
+    }
     while (done < n) {
-        const int m = (n - done < c->cfg.max_tree) ? n - done : c->cfg.max_tree;
+        const int left = (done < n - tail) ? n - tail - done : n - done;
+        const int m = (left < c->cfg.max_tree) ? left : c->cfg.max_tree;
         for (int i = 0; i < m; ++i) {   // a chain: every token follows the previous one
             c->h_in[i] = tokens[done + i];
             c->h_in[FV_MAX_TREE + i] = i - 1;

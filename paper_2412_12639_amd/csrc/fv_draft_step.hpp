@@ -143,12 +143,12 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         AttnArgs aa;
         aa.q = c->at<uint4>(ly.off_q); aa.q_lo = c->at<uint4>(ly.off_qlo); aa.kc = (const uint4*)c->kc(0); aa.vc = (const uint4*)c->vc(0);
         aa.out = c->at<void>(ly.off_attn); aa.mask = c->at<uint64_t>(ly.off_mask);
-        aa.Tp = Tp; aa.T = n; aa.TK = ps.r0 + n; aa.L = d->L0; aa.Hq = cf.n_q_heads; aa.Hkv = cf.n_kv_heads; aa.S_pad = ly.S_pad;
+        aa.Tp = Tp; aa.ld = Tp; aa.pieces = 1; aa.T = n; aa.TK = ps.r0 + n; aa.L = d->L0; aa.Hq = cf.n_q_heads; aa.Hkv = cf.n_kv_heads; aa.S_pad = ly.S_pad;
         aa.scale = 1.f / std::sqrt((float)D);
         aa.ks = attn_key_split(cf.n_q_heads * (Tp / 32), d->L0 + ps.r0 + n, 256);
         aa.part = c->scr->apart; aa.tickets = c->scr->atick;
-        hipLaunchKernelGGL((k_attn<EL, D>), dim3(cf.n_q_heads * (Tp / 32) * aa.ks), dim3(256), 0, st, aa);
-        HIPCHK(hipGetLastError());
+        int rc = launch_attn<EL, D>(aa, cf.n_q_heads * (Tp / 32), 1, d->L0 + ps.r0 + n, st);
+        if (rc) return rc;
     }
     {
         GemmArgs ga = core_args(GM_O, core_kind(GM_O), c->layer_w(0, 1), ly.off_attn, false);

@@ -1,0 +1,238 @@
+// GEMM for more than 64 rows, bf16: both operands go through a ring of LDS stages that the memory system fills by
+// itself (global loads with an LDS destination), and the wavefronts do nothing but read fragments and multiply.
+//
+// What bounds it.  At 128 / 256 rows a matrix is read once and multiplied by 128 / 256 columns: about as long in HBM as
+// on the matrix cores, so both have to run at once.  The shared-activation kernel (k_gemm) keeps each strip in one
+// wavefront, so four wavefronts read the whole activation chunk from LDS (a fragment of 32 rows x 16 columns for every
+// 1 KiB of it: as many LDS cycles as matrix cycles), and stages it through registers two stages ahead.
+// Here a wavefront takes RS strips x half of the columns (RS + TB/2 KiB of LDS reads per RS * TB/2 matrix
+// instructions), nothing passes through registers, and the two rings run as far ahead as their memories need.
+//
+// Tile: 2 * RS strips x TB * 32 columns, four wavefronts as 2 x 2.  A stage is 32 columns of K: two weight fragments of every
+// strip (1 KiB each, as tiled in memory) and four 16-byte vectors of every column.  One barrier per stage, in its
+// middle: the second half of a stage multiplies while the first fragments of the next one are read, and the slot that
+// everybody has left by then is filled again.
+//
+// WIDE = false: up to 256 rows, one block of columns; the (row group, K batch) space is cut into G equal ranges exactly as for
+// k_gemm, partial tiles are stored and k_gemm_fix, launched behind, reduces them.
+// WIDE = true: more rows (a prompt): one workgroup per tile over the whole K range, column tiles of 256.
+#pragma once
+// (included from fv_kernels.hpp after k_gemm_fix)
+
+constexpr int ring_slots(int TB) { return TB == 4 ? 9 : 6; }
+constexpr int ring_stage_bytes(int TB) { return FV_R * 2048 + TB * 32 * 64; }
+constexpr size_t ring_smem(int TB) { return (size_t)ring_slots(TB) * ring_stage_bytes(TB) + (size_t)TB * 32 * 4 + 4096; }
+
+template <int N> __device__ __forceinline__ void wait_vm() {   // all but the N youngest vector memory operations of this wavefront
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+template <int TB, int D, int EPI, bool WIDE>
+__global__ __launch_bounds__(256, 1) void k_gemm_ring(GemmArgs a) {
+    constexpr int NS = ring_slots(TB), SB = ring_stage_bytes(TB), AB = FV_R * 2048;
+    constexpr int RS = 2, CB = TB / 2, TT = TB * 32;    // strips and column blocks of a wavefront, columns of the tile
+    constexpr int LX = TT / 64, LPS = 2 + LX;           // loads per wavefront and stage: one strip's weights, one of four vectors of every column
+    static_assert(LPS * (NS - 2) <= 63, "the outstanding-load counter");
+    extern __shared__ __attribute__((aligned(16))) char ring[];
+    float* const rinv_lds = (float*)(ring + NS * SB);
+    float* const red_lds = rinv_lds + TT;               // [1024]
+    const int tid = threadIdx.x, lane = tid & 63, tl = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1, wc = wave & 1;
+    const int NST = 4 * a.NB;                           // stages of a row group
+    const int ld = WIDE ? a.ld : TT;                    // rows of the activation buffers
+    int g0, k0, n, t0 = 0;                              // first group, its first stage, stages, first column
+    if constexpr (WIDE) {
+        // Workgroups go to the XCDs round-robin: the column tiles of a row group get block indices of one residue mod 8,
+        // close together, so a group's weights come from HBM once and then from that XCD's L2.
+        const int tiles = ld / TT, x = blockIdx.x & 7, j = blockIdx.x >> 3;
+        g0 = (j / tiles) * 8 + x;
+        if (g0 >= a.NG) return;
+        t0 = (j % tiles) * TT;
+        k0 = 0; n = NST;
+    } else {
+        const long long U = (long long)a.NG * a.NB;     // computed, not looked up, as in k_gemm
+        const int u0 = (int)(U * blockIdx.x / a.G), u1 = (int)(U * (blockIdx.x + 1) / a.G);
+        g0 = u0 / a.NB; k0 = 4 * (u0 - g0 * a.NB); n = 4 * (u1 - u0);
+    }
+
+    // ---- fill: wavefront w brings strip w's weights and vector w of the activations, through buffer descriptors (bounds-checked;
+    // the place in the matrix is a scalar, the lane's share a constant)
+    const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.Wt, 0, (int)((unsigned)a.NG * FV_R * a.NB * 8192u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, (int)((unsigned)a.NB * 256u * (unsigned)ld), 0x00020000);
+    int fg = g0, fk = k0, fn = 0, fslot = 0;            // group, stage inside it, stages issued, slot
+    unsigned wo = 0, xo = 0;
+    auto place = [&]() {                                // of the stage to fill next
+        const int strip = fg * FV_R + wave;             // tiled [strip pair][half K batch][2 strips][4 frags]: a stage of a strip is 2 KiB
+        wo = ((((unsigned)(strip >> 1) * (2 * a.NB) + (fk >> 1)) * 2 + (strip & 1)) * 4 + (fk & 1) * 2) * 1024u;
+        xo = ((unsigned)(fk * 4 + wave) * (unsigned)ld + (unsigned)t0) * 16u;
+    };
+    auto load = [&](int i) {                            // load i of the stage (a constant after unrolling)
+        typedef __attribute__((address_space(3))) void* lptr;
+        char* const w = ring + fslot * SB + wave * 2048;
+        char* const x = ring + fslot * SB + AB + wave * (TT * 16);
+        switch (i) {
+            case 0: __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 0, 0); break;
+            case 1: __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 1024, 0); break;
+            case 2: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 0, 0); break;
+            case 3: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 1024, 0); break;
+            case 4: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 2048, 0); break;
+            case 5: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 3072, 0); break;
+        }
+    };
+    auto filled = [&]() {
+        ++fn;
+        if (++fk == NST) { fk = 0; ++fg; }
+        if (++fslot == NS) fslot = 0;
+    };
+    auto fill_first = [&]() {
+        for (int i = 0; i < NS - 1 && fn < n; ++i) {
+            place();
+#pragma unroll
+            for (int j = 0; j < LPS; ++j) load(j);
+            filled();
+        }
+    };
+    // stage s has landed, as far as this wavefront fills it (behind the last stage to fill, everything is waited for)
+    auto landed = [&](int s) { if (s + NS - 3 < n) wait_vm<LPS * (NS - 3)>(); else wait_vm<0>(); };
+
+    // ---- RMSNorm factors of the tile's columns
+    if constexpr (EPI != EPI_RESID) {
+        if constexpr (WIDE) {
+            const float rv = a.rinv_out[t0 + tid];
+            fill_first();
+            rinv_lds[tid] = rv;
+        } else {
+            constexpr int C4 = TT / 4, SL = 256 / C4, NP = 128 / SL;   // the first 128 strips' sums are out before the rings' first loads
+            const int col = tid % C4, sl = tid / C4;
+            const float4* sp = (const float4*)a.ssq_in + col;
+            float4 s4 = make_float4(0.f, 0.f, 0.f, 0.f);
+            float4 v[NP];
+#pragma unroll
+            for (int k = 0; k < NP; ++k) v[k] = (sl + k * SL < a.n_ssq) ? sp[(size_t)(sl + k * SL) * C4] : make_float4(0.f, 0.f, 0.f, 0.f);
+            __builtin_amdgcn_sched_barrier(0);
+            fill_first();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < NP; ++k) { s4.x += v[k].x; s4.y += v[k].y; s4.z += v[k].z; s4.w += v[k].w; }
+            for (int i = sl + NP * SL; i < a.n_ssq; i += SL) {
+                const float4 u = sp[(size_t)i * C4];
+                s4.x += u.x; s4.y += u.y; s4.z += u.z; s4.w += u.w;
+            }
+            ((float4*)red_lds)[sl * C4 + col] = s4;
+            __syncthreads();
+            if (tid < TT) {
+                float tot = 0.f;
+#pragma unroll
+                for (int p = 0; p < SL; ++p) tot += red_lds[p * TT + tid];
+                const float rv = rsqrtf(tot * a.inv_h + a.eps);
+                rinv_lds[tid] = rv;
+                if (blockIdx.x == 0) a.rinv_out[tid] = rv;   // for k_gemm_fix
+            }
+        }
+    } else {
+        fill_first();
+    }
+
+    struct Frags { u32x4 w[RS], x[CB]; };
+    auto read = [&](Frags& d, int slot, int f, int i) {   // fragment i (a constant) of half f, in the order they are used: strip 0, the column blocks, strip 1
+        const char* s = ring + slot * SB;
+        if (i == 0 || i > CB) d.w[i == 0 ? 0 : 1] = *(const u32x4*)(s + ((wr * RS + (i == 0 ? 0 : 1)) * 2 + f) * 1024 + lane * 16);
+        else d.x[i - 1] = *(const u32x4*)(s + AB + ((2 * f + g) * TT + (wc * CB + i - 1) * 32 + tl) * 16);
+    };
+    floatx16 acc[RS][CB];
+    auto clear = [&]() {
+#pragma unroll
+        for (int r = 0; r < RS; ++r)
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[r][c][i] = 0.f;
+    };
+    // Multiplies a half stage; between(i) runs behind matrix instruction i.  Reads and loads are issued there, one at a time: a
+    // wavefront issues in order, and a burst of them ahead of the matrix instructions leaves the matrix cores idle meanwhile.
+    auto mul = [&](const Frags& d, auto&& between) {
+#pragma unroll
+        for (int r = 0; r < RS; ++r)
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, d.w[r]), __builtin_bit_cast(bf16x8_t, d.x[c]), acc[r][c], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                between(r * CB + c);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    constexpr int NM = RS * CB, NR = RS + CB;   // matrix instructions and fragment reads of a half stage
+    static_assert(NR <= NM && LPS <= NM, "one of each behind a matrix instruction");
+
+    // ---- what happens to the sums of a segment: the epilogue if it covered the whole K range, else partial tiles for k_gemm_fix
+    auto flush = [&](int gi, bool whole, int seg) {
+        if (whole) {
+#pragma unroll
+            for (int r = 0; r < RS; ++r) {
+                const int strip = gi * FV_R + wr * RS + r;
+                if (strip >= a.n_strips) continue;
+#pragma unroll
+                for (int c = 0; c < CB; ++c) {
+                    __builtin_amdgcn_sched_barrier(0);   // one tile after the other: what the next ones read would be spilled
+                    const int tb = t0 / 32 + wc * CB + c;
+                    EpiPre pre;
+                    bool have = false;
+                    if constexpr (EPI == EPI_RESID) { resid_preload(a, ld, strip, tb, lane, pre); have = true; }
+                    float v[16];
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) v[i] = acc[r][c][i];
+                    gemm_epilogue<BF16, D, EPI>(a, ld, strip, tb, lane, v, rinv_lds - t0, pre, have);
+                }
+            }
+        } else {
+            const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc((void*)a.part, 0, (int)a.part_bytes, 0x00020000);
+#pragma unroll
+            for (int r = 0; r < RS; ++r)
+#pragma unroll
+                for (int c = 0; c < CB; ++c) {
+                    const unsigned o = ((unsigned)((((int)blockIdx.x * a.segmax + seg) * FV_R + wr * RS + r) * TB + wc * CB + c) * 1024u + (unsigned)lane * 4u) * 4u;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        u32x4 v;
+                        v.x = __float_as_uint(acc[r][c][4 * q]); v.y = __float_as_uint(acc[r][c][4 * q + 1]);
+                        v.z = __float_as_uint(acc[r][c][4 * q + 2]); v.w = __float_as_uint(acc[r][c][4 * q + 3]);
+                        __builtin_amdgcn_raw_buffer_store_b128(v, prs, o + q * 1024u, 0, 0);
+                    }
+                }
+        }
+    };
+
+    clear();
+    landed(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // and the LDS stores above
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    Frags p, q;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) read(p, 0, 0, i);
+    int gi = g0, k = k0, seg = 0, seg_k0 = k0, slot = 0;
+    for (int s = 0; s < n; ++s) {
+        mul(p, [&](int i) { if (i < NR) read(q, slot, 1, i); });
+        if (++slot == NS) slot = 0;
+        if (s + 1 < n) {
+            landed(s + 1);
+            __builtin_amdgcn_s_barrier();   // everybody's part of stage s + 1 is there, and everybody has left stage s - 1
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const bool fills = fn < n;
+        if (fills) place();
+        // the reads behind the last stage are of no use; without a branch around them their wait count is known
+        mul(q, [&](int i) {
+            if (i < NR) read(p, slot, 0, i);
+            if (fills && i >= NM - LPS) load(i - (NM - LPS));
+        });
+        if (fills) filled();
+        if (++k == NST || s + 1 == n) {
+            flush(gi, WIDE || (seg_k0 == 0 && k == NST), seg);
+            ++seg; ++gi; k = 0; seg_k0 = 0;
+            clear();
+            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): nothing but fragment reads is pending where the loop closes, so that their waits can count
+        }
+    }
+}

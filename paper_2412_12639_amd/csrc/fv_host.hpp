@@ -56,6 +56,9 @@ struct Layout {
     size_t off_kvread = 0, off_stage = 0, stage_bytes = 0;
     size_t off_apart = 0, off_atick = 0, off_zeros = 0, off_feat = 0;
     size_t off_unif = 0, off_pwork = 0, off_outcome = 0;   // non-greedy acceptance: uniforms [2][256] fp64, working distributions [max_tree][Vpad] fp64, what each node decided [256]
+    // a long prompt's rows before the last piece (bf16): up to Pm rows at once, in buffers of their own
+    int Pm = 0;
+    size_t off_px = 0, off_pxb = 0, off_pq = 0, off_pqlo = 0, off_pattn = 0, off_pact = 0, off_pssq = 0, off_prinv = 0, off_prope = 0, off_pmask = 0, off_ptok = 0;
     size_t total = 0;
 };
 
@@ -97,6 +100,7 @@ struct fv_ctx {
     int last_T = 0, last_Tp = 0, last_L = 0;
     bool last_was_verify = false;
     int32_t* h_in = nullptr;      // pinned [3][256]
+    int32_t* h_prompt = nullptr;  // pinned [max_seq]: the prompt while its pieces are on their way (lay.Pm > 0 only)
     FvResult* h_res = nullptr;    // pinned
     double* h_unif = nullptr;     // pinned [2][256]: u_accept, u_sample of a non-greedy step
     double sample_inv_temperature = 1.0;      // of the non-greedy step being run
@@ -202,6 +206,8 @@ int upload_tiled(fv_ctx* c, const GemmPlan& p, char* out, const void* host, size
 // ---- defined in fv_step.hip, instantiated once per (EL, D) pair
 // One pass of the decoder over T new rows whose tokens/parent/depth are in c->h_in.
 template <typename EL, int D> int run_step(fv_ctx* c, int T, StepMode mode);
+// m prompt rows (h_tok: pinned, untouched until the stream is waited for) behind slot cur_len: K and V into the cache, nothing else
+template <typename EL, int D> int run_prompt(fv_ctx* c, const int32_t* h_tok, int m);
 // dynamic shared memory limits of the GEMM kernels of this pair
 template <typename EL, int D> int set_gemm_attrs_d();
 template <typename EL, int D> int read_kv_t(fv_ctx* c, int layer, int slot0, int n, float* k_out, float* v_out);

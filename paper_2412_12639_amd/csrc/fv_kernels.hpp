@@ -65,6 +65,39 @@ static __global__ __launch_bounds__(256) void k_ingest(IngestArgs a) {
     }
 }
 
+// Prompt rows: a chain.  Positions and rotary rows of Tp rows from slot L on; the masks of one piece of 256 rows, which are
+// those of every piece.  (k_ingest would walk up to 255 parents per row.)
+struct PromptIngestArgs { int T, Tp, L, half_d; double log2_base; uint64_t* mask; float2* rope_cs; };
+static __global__ __launch_bounds__(256) void k_ingest_prompt(PromptIngestArgs a) {
+    const int t0 = blockIdx.x * 4, tid = threadIdx.x;
+    if (t0 < 256 && tid < 16) {
+        const int i = t0 + (tid >> 2), w = tid & 3, n = i + 1 - 64 * w;   // row i sees rows 0..i
+        a.mask[i * 4 + w] = n <= 0 ? 0ull : n >= 64 ? ~0ull : (1ull << n) - 1ull;
+    }
+    for (int e = t0 * a.half_d + tid; e < (t0 + 4) * a.half_d; e += 256) {
+        const int t = e / a.half_d, i = e % a.half_d;
+        if (t >= a.Tp) break;
+        const int p = (t < a.T) ? a.L + t : 0;
+        const double inv_freq = exp2(-(double)i / (double)a.half_d * a.log2_base);
+        double s, c;
+        sincos((double)p * inv_freq, &s, &c);
+        a.rope_cs[e] = make_float2((float)c, (float)s);
+    }
+}
+
+// RMSNorm factor of every row from the per-strip sums of squares, 64 rows per workgroup
+struct RinvArgs { const float* ssq; float* rinv; int n_ssq, ld; float inv_h, eps; };
+static __global__ __launch_bounds__(256) void k_rinv(RinvArgs a) {
+    __shared__ float red[256];
+    const int tid = threadIdx.x, t = blockIdx.x * 64 + (tid & 63), sl = tid >> 6;
+    float s = 0.f;
+#pragma unroll 8
+    for (int i = sl; i < a.n_ssq; i += 4) s += a.ssq[(size_t)i * a.ld + t];
+    red[tid] = s;
+    __syncthreads();
+    if (tid < 64) a.rinv[t] = rsqrtf((red[tid] + red[tid + 64] + red[tid + 128] + red[tid + 192]) * a.inv_h + a.eps);
+}
+
 // ============================================================================ embed
 // x[:, t] = E[tok[t]];  also emits the first GEMM's input  xb = x * gain  (un-normalised;
 // the RMSNorm scale 1/sqrt(mean(x^2)+eps) is applied to the GEMM result instead, it is a
@@ -81,7 +114,7 @@ struct EmbedArgs {
 
 template <typename EL>
 __global__ void k_embed(EmbedArgs a) {
-    const int s = blockIdx.x, t = threadIdx.x;
+    const int s = blockIdx.x, t = blockIdx.y * blockDim.x + threadIdx.x;
     if (t >= a.Tp) return;
     float ssq = 0.f;
     for (int q = 0; q < 8; ++q) {
@@ -170,6 +203,7 @@ struct GemmArgs {
     // EPI_LOGITS
     float* logits;       // [Tp][Vpad]
     int Vpad;
+    int ld;              // ring kernel over a prompt: rows of the activation buffers (a multiple of 256)
 };
 
 // Epilogue of one 32-row strip x 32-token block, in accumulator layout: lane (tl, g), acc[i] is
@@ -736,6 +770,7 @@ __global__ __launch_bounds__(256) void k_gemm_fix(GemmArgs a) {
 }
 
 #include "fv_gemm_direct.hpp"
+#include "fv_gemm_ring.hpp"
 
 // ============================================================================ tree attention
 // For node t and query head qh: softmax over {cache slots 0..L-1} U {tree slots L+j : j in
@@ -752,6 +787,8 @@ struct AttnArgs {
     void* out;               // vector-major [Hq*D/E][Tp]
     const uint64_t* mask;    // [Tp][4]
     int Tp, T, L, Hq, Hkv, S_pad;
+    int ld;                  // rows of the q and out buffers (Tp, or more when a prompt's pieces are rows of one buffer)
+    int pieces;              // > 1: grid.y prompt pieces of 256 rows each, row 0 of piece j at slot L + 256 j; T counts all rows
     int TK;                  // step rows whose keys exist, slots L .. L+TK-1 (= T in a verification step; a drafting pass also sees
                              // the rows of the phase's earlier passes); the masks have no bits at or above TK
     float scale;
@@ -783,10 +820,10 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
     constexpr bool SPLIT = (E == 8);   // bf16: q and the probabilities enter the matrix cores as hi + lo pairs
     uint4 qf[NF], qfl[SPLIT ? NF : 1];
 #pragma unroll
-    for (int fr = 0; fr < NF; ++fr) qf[fr] = a.q[((size_t)(qh * (D / E) + 2 * fr + g)) * a.Tp + t];
+    for (int fr = 0; fr < NF; ++fr) qf[fr] = a.q[((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t];
     if constexpr (SPLIT) {
 #pragma unroll
-        for (int fr = 0; fr < NF; ++fr) qfl[fr] = a.q_lo[((size_t)(qh * (D / E) + 2 * fr + g)) * a.Tp + t];
+        for (int fr = 0; fr < NF; ++fr) qfl[fr] = a.q_lo[((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t];
     }
     uint64_t mk[4];
 #pragma unroll
@@ -954,7 +991,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int blk = 0; blk < 4; ++blk)
-                    store4_act<EL>(a.out, a.Tp, qh * D + db * 32 + 8 * blk + 4 * g, t, r[db][4 * blk] * inv,
+                    store4_act<EL>(a.out, a.ld, qh * D + db * 32 + 8 * blk + 4 * g, t, r[db][4 * blk] * inv,
                                         r[db][4 * blk + 1] * inv, r[db][4 * blk + 2] * inv, r[db][4 * blk + 3] * inv);
         }
         return;
@@ -1009,7 +1046,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         const float inv = (ltot > 0.f) ? 1.f / ltot : 0.f;
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk)
-            store4_act<EL>(a.out, a.Tp, qh * D + db * 32 + 8 * blk + 4 * g, t, accv[4 * blk] * inv, accv[4 * blk + 1] * inv,
+            store4_act<EL>(a.out, a.ld, qh * D + db * 32 + 8 * blk + 4 * g, t, accv[4 * blk] * inv, accv[4 * blk + 1] * inv,
                                 accv[4 * blk + 2] * inv, accv[4 * blk + 3] * inv);
     }
 }
@@ -1023,6 +1060,15 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
     // KV head -- are given to workgroups of one XCD: a head's K/V then comes from HBM once and is
     // re-read from that L2, instead of once per XCD that touches it.  (Only locality depends on the
     // dispatch order; any other order computes the same thing.)
+    if (a.pieces > 1) {   // this piece's rows, and the keys of the pieces before it
+        const int r0 = 256 * (int)blockIdx.y;
+        a.L += r0;
+        a.T = (a.T - r0 < 256) ? a.T - r0 : 256;
+        a.TK = a.T;
+        a.q += r0;
+        a.q_lo += r0;
+        a.out = (char*)a.out + (size_t)r0 * 16;
+    }
     int item = blockIdx.x / a.ks, part = blockIdx.x % a.ks;
     if ((a.Hq & 7) == 0) {
         const int x = blockIdx.x & 7, j = blockIdx.x >> 3;

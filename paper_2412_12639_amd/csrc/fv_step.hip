@@ -57,6 +57,20 @@ int launch_gemm_paired_t(fv_ctx* c, const GemmArgs& ga) {
 // The direct and paired kernels need the partial area all zeros when they start and leave it so; the
 // shared-activation kernel (and a step that ran into the time-out) leaves partial sums behind.  `scr` is the
 // scratch `ga.part` belongs to: its host flag says which of the two states the area is in.
+// More than 64 rows, bf16.  Row groups with several contributors are always reduced by k_gemm_fix: the whole chip adds what
+// one last arriver would pull through its compute unit.
+template <int TB, int D, int EPI>
+int launch_gemm_ring_t(fv_ctx* c, const GemmArgs& ga) {
+    hipLaunchKernelGGL((k_gemm_ring<TB, D, EPI, false>), dim3(ga.G), dim3(256), ring_smem(TB), c->stream, ga);
+    if (hipGetLastError() != hipSuccess) return FV_E_HIP;
+    if (ga.n_fix > 0) {
+        const int tiles = ga.n_fix * FV_R * TB;
+        hipLaunchKernelGGL((k_gemm_fix<BF16, TB, D, EPI>), dim3((tiles + 3) / 4), dim3(256), 0, c->stream, ga);
+        if (hipGetLastError() != hipSuccess) return FV_E_HIP;
+    }
+    return FV_OK;
+}
+
 template <typename EL, int D, int EPI>
 int launch_gemm(fv_ctx* c, int Tp, const GemmArgs& ga, int kind, const StepScratch* scr) {
     const bool marked = (kind == GEMM_DIRECT || kind == GEMM_PAIRED) && Tp <= 64;
@@ -71,11 +85,14 @@ int launch_gemm(fv_ctx* c, int Tp, const GemmArgs& ga, int kind, const StepScrat
     }
     if (kind == GEMM_DIRECT) return Tp == 32 ? launch_gemm_direct_t<EL, 1, D, EPI>(c, ga) : launch_gemm_direct_t<EL, 2, D, EPI>(c, ga);
     if (kind == GEMM_PAIRED) return Tp == 32 ? launch_gemm_paired_t<EL, 1, D, EPI>(c, ga) : launch_gemm_paired_t<EL, 2, D, EPI>(c, ga);
-    switch (Tp) {
-        case 32: return launch_gemm_t<EL, 1, D, EPI>(c, ga);
-        case 64: return launch_gemm_t<EL, 2, D, EPI>(c, ga);
-        case 128: return launch_gemm_t<EL, 4, D, EPI>(c, ga);
-        case 256: return launch_gemm_t<EL, 8, D, EPI>(c, ga);
+    if (Tp == 32) return launch_gemm_t<EL, 1, D, EPI>(c, ga);
+    if (Tp == 64) return launch_gemm_t<EL, 2, D, EPI>(c, ga);
+    if constexpr (Tr<EL>::E == 8) {
+        if (Tp == 128) return launch_gemm_ring_t<4, D, EPI>(c, ga);
+        if (Tp == 256) return launch_gemm_ring_t<8, D, EPI>(c, ga);
+    } else {
+        if (Tp == 128) return launch_gemm_t<EL, 4, D, EPI>(c, ga);
+        if (Tp == 256) return launch_gemm_t<EL, 8, D, EPI>(c, ga);
     }
     return FV_E_BAD_ARG;
 }
@@ -83,8 +100,15 @@ int launch_gemm(fv_ctx* c, int Tp, const GemmArgs& ga, int kind, const StepScrat
 template <typename EL, int D, int EPI>
 int set_gemm_attrs_e() {
     // the 256-token instantiation double-buffers 2 x 64 KiB of activations in LDS
-    HIPCHK(hipFuncSetAttribute((const void*)k_gemm<EL, 8, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 256 * 256));
-    HIPCHK(hipFuncSetAttribute((const void*)k_gemm<EL, 4, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 256));
+    if constexpr (Tr<EL>::E == 8) {
+        HIPCHK(hipFuncSetAttribute((const void*)k_gemm_ring<8, D, EPI, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem(8)));
+        HIPCHK(hipFuncSetAttribute((const void*)k_gemm_ring<4, D, EPI, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem(4)));
+        if constexpr (EPI != EPI_LOGITS)
+            HIPCHK(hipFuncSetAttribute((const void*)k_gemm_ring<8, D, EPI, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem(8)));
+    } else {
+        HIPCHK(hipFuncSetAttribute((const void*)k_gemm<EL, 8, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 256 * 256));
+        HIPCHK(hipFuncSetAttribute((const void*)k_gemm<EL, 4, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 256));
+    }
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_direct<EL, 1, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_DIRECT_SMEM_FLOATS(1) * 4));
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_direct<EL, 2, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_DIRECT_SMEM_FLOATS(2) * 4));
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_paired<EL, 1, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_PAIRED_SMEM_FLOATS(1) * 4));
@@ -110,6 +134,12 @@ static int attn_key_split(int items, int n_keys, int n_wg) {
     if (ks > 8) ks = 8;
     if (ks < 1) ks = 1;
     return ks;
+}
+
+template <typename EL, int D>
+int launch_attn(const AttnArgs& aa, int items, int pieces, int, hipStream_t st) {
+    hipLaunchKernelGGL((k_attn<EL, D>), dim3(items * aa.ks, pieces), dim3(256), 0, st, aa);
+    return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
 }
 
 // Step-independent attention (fv_attn_canon.hpp): taken by verification steps (one-token steps are
@@ -225,12 +255,12 @@ int run_step(fv_ctx* c, int T, StepMode mode) {
             AttnArgs aa;
             aa.q = c->at<uint4>(ly.off_q); aa.q_lo = c->at<uint4>(ly.off_qlo); aa.kc = (const uint4*)c->kc(l); aa.vc = (const uint4*)c->vc(l);
             aa.out = c->at<void>(ly.off_attn); aa.mask = c->at<uint64_t>(ly.off_mask);
-            aa.Tp = Tp; aa.T = T; aa.TK = T; aa.L = L; aa.Hq = cf.n_q_heads; aa.Hkv = cf.n_kv_heads; aa.S_pad = ly.S_pad;
+            aa.Tp = Tp; aa.ld = Tp; aa.pieces = 1; aa.T = T; aa.TK = T; aa.L = L; aa.Hq = cf.n_q_heads; aa.Hkv = cf.n_kv_heads; aa.S_pad = ly.S_pad;
             aa.scale = 1.f / std::sqrt((float)D);
             aa.ks = attn_key_split(cf.n_q_heads * (Tp / 32), L + T, 256);
             aa.part = c->scr->apart; aa.tickets = c->scr->atick;
-            hipLaunchKernelGGL((k_attn<EL, D>), dim3(cf.n_q_heads * (Tp / 32) * aa.ks), dim3(256), 0, st, aa);
-            HIPCHK(hipGetLastError());
+            int rc_a = launch_attn<EL, D>(aa, cf.n_q_heads * (Tp / 32), 1, L + T, st);
+            if (rc_a) return rc_a;
         }
         {   // output projection, residual add, statistics + input of the FFN norm
             PhaseTimer pt(c, FV_PH_GEMM);
@@ -373,8 +403,10 @@ int read_kv_t(fv_ctx* c, int layer, int slot0, int n, float* k_out, float* v_out
 
 
 #include "fv_draft_step.hpp"
+#include "fv_prompt.hpp"
 
 template int run_step<FV_INST_EL, FV_INST_D>(fv_ctx*, int, StepMode);
+template int run_prompt<FV_INST_EL, FV_INST_D>(fv_ctx*, const int32_t*, int);
 template int run_draft_pass<FV_INST_EL, FV_INST_D>(fv_drafter*, const DraftPass&);
 template int set_gemm_attrs_d<FV_INST_EL, FV_INST_D>();
 template int read_kv_t<FV_INST_EL, FV_INST_D>(fv_ctx*, int, int, int, float*, float*);

@@ -8,6 +8,8 @@
 #define FV_R 4            // strips (wavefronts) per GEMM workgroup
 #define FV_FRAGS 8        // weight frags per K batch
 
+#define FV_PROMPT_ROWS 2048   // prompt rows that go through the layers at once
+
 #define FV_DRAFT_KMAX 8   // largest k of the semi-autoregressive drafter
 #define FV_DRAFT_MMAX 32  // longest top list per drafter row
 

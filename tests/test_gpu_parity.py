@@ -652,3 +652,31 @@ def test_small_matrix_rule(fvmod, hidden, ffn, dtype):
     got = g.verify_tree(case["tokens"], case["parent"], case["depth"])
     say("small matrix rule", hidden, ffn, dtype, "logits err", H.check_step(g, case, got, H.tol_for(s)))
     g.close()
+
+
+@pytest.mark.parametrize("n,max_tree", [
+    (320, 32),       # 288 rows at once (two pieces, the second of 32), then the last chunk of 32
+    (289, 32),       # 288 and a chunk of one row
+    (777, 256),      # 768 - three whole pieces - and a chunk of 9
+    (513, 256),      # two chunks' worth, and one row
+    (2400, 64),      # 2048, then 288 more at once, then the last chunk
+])
+def test_long_prompt_rows_at_once(fvmod, n, max_tree):
+    """Rows of a long bf16 prompt before its last chunk go through the layers together: cache, logits of the last chunk and the
+    next token against the oracle."""
+    s, w = SHAPES["small-gqa"], weights_of("small-gqa")
+    tol = H.tol_for(s)
+    prefix = fi.gen_prefix(n, n, s.vocab)
+    wo = {k: (fi.f32_from_bf16_bits(v) if v.dtype == np.uint16 else v) for k, v in w.items()}
+    o = fo.Oracle(s, wo, max_seq=n + 8, dtype=np.float32)
+    o.prefill(prefix)
+    g = make_gpu(fvmod, s, w, max_seq=n + 40, max_tree=max_tree)
+    nxt = g.prefill(prefix)
+    rows = (n - 1) % max_tree + 1
+    err = H.row_rel_err(g.logits(rows).astype(np.float64), o.last_logits[-rows:]).max()
+    e = H.check_cache(g, o, s, n, tol)
+    say("long prompt", n, max_tree, "logits err", err, "cache err", e)
+    assert err <= tol and g.state() == (n, nxt)
+    if fo.top2_margin(o.last_logits[-1]) > tol * np.max(np.abs(o.last_logits[-1])):
+        assert nxt == o.pending
+    g.close()
