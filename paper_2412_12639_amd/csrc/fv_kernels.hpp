@@ -803,8 +803,11 @@ struct AttnArgs {
 #define FV_ATTN_SMEM_FLOATS(D) (3 * ((D) / 32) * 64 * 16 + 8 * 32 + 4)
 #define FV_ATTN_PART_FLOATS(D) (((D) / 32) * 1024 + 64)
 
-// One (query head, block of 32 nodes) item, key part `part` of a.ks.
-template <typename EL, int D>
+// One (query head, block of 32 nodes) item, key part `part` of a.ks.  AHEAD: the next block's tiles are requested before the
+// current ones are used, in two register sets (with one wavefront per SIMD nothing else hides a block's trip to memory):
+// 250 nodes behind 2048 keys 1039 -> 1013 us a step of four layers.  The loop's body is in the code twice then, and ranges of
+// a few blocks per wavefront lose to that what they gain (1 % of a step at 1 to 4 blocks); see attn_ahead.
+template <typename EL, int D, bool AHEAD>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part, float* smem) {
     constexpr int E = Tr<EL>::E;
     constexpr int NF = D / (2 * E);      // K frags per key block
@@ -939,11 +942,29 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
                 if constexpr (SPLIT) o[db] = Tr<EL>::mma(vt[db * NQ + q], pbl[q], o[db]);
             }
     };
-    for (int kb = kb_lo + wave; kb < kb_hi; kb += 4) {
-        uint4 kt[NF], vt[DB * NQ];
-        load_block(kt, vt, kb);
-        __builtin_amdgcn_sched_barrier(0);   // the 16 requests stay together, ahead of everything that uses them
-        use_block(kt, vt, kb);
+    int kb = kb_lo + wave;
+    if constexpr (!AHEAD) {
+        for (; kb < kb_hi; kb += 4) {
+            uint4 kt[NF], vt[DB * NQ];
+            load_block(kt, vt, kb);
+            __builtin_amdgcn_sched_barrier(0);   // the 16 requests stay together, ahead of everything that uses them
+            use_block(kt, vt, kb);
+        }
+    } else if (kb < kb_hi) {
+        uint4 kt0[NF], vt0[DB * NQ], kt1[NF], vt1[DB * NQ];
+        load_block(kt0, vt0, kb);
+        for (;;) {
+            __builtin_amdgcn_sched_barrier(0);   // the 16 requests stay together, ahead of everything that uses them
+            if (kb + 4 < kb_hi) load_block(kt1, vt1, kb + 4);
+            __builtin_amdgcn_sched_barrier(0);
+            use_block(kt0, vt0, kb);
+            if ((kb += 4) >= kb_hi) break;
+            __builtin_amdgcn_sched_barrier(0);
+            if (kb + 4 < kb_hi) load_block(kt0, vt0, kb + 4);
+            __builtin_amdgcn_sched_barrier(0);
+            use_block(kt1, vt1, kb);
+            if ((kb += 4) >= kb_hi) break;
+        }
     }
     l_run += __shfl_xor(l_run, 32);
 
@@ -1052,7 +1073,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
 }
 
 // grid = items * ks
-template <typename EL, int D>
+template <typename EL, int D, bool AHEAD>
 __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) float smem[FV_ATTN_SMEM_FLOATS(D)];
     // Workgroups go to the 8 XCDs round-robin (workgroup b runs on XCD b % 8) and every XCD has its
@@ -1077,7 +1098,7 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
         item = head * TB + w / a.ks;
         part = w % a.ks;
     }
-    attn_body<EL, D>(a, item, part, smem);
+    attn_body<EL, D, AHEAD>(a, item, part, smem);
 }
 
 #include "fv_attn_canon.hpp"
