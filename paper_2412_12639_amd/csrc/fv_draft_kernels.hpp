@@ -34,6 +34,7 @@ struct DraftTables {
 struct DraftIngestArgs {
     DraftTables tab;
     int r0, n, Tp, half_d;
+    int chain;               // the rows follow each other from row 0 on: no walk
     double log2_base;
     uint64_t* mask;          // [Tp][4]
     float2* rope_cs;         // [Tp][half_d]
@@ -44,7 +45,9 @@ static __global__ __launch_bounds__(256) void k_draft_ingest(DraftIngestArgs a) 
     const int t0 = blockIdx.x * 4, t1 = (t0 + 4 < a.Tp) ? t0 + 4 : a.Tp;
     for (int t = t0 + tid; t < t1; t += 256) {
         uint64_t m[4] = {0, 0, 0, 0};
-        if (t < a.n) {
+        if (t < a.n && a.chain) {
+            for (int w = 0; w < 4; ++w) { const int k = t + 1 - 64 * w; m[w] = k <= 0 ? 0ull : k >= 64 ? ~0ull : (1ull << k) - 1ull; }
+        } else if (t < a.n) {
             const int r = a.r0 + t;
             int j = r, guard = 0;
             while (j >= 0 && j < FV_MAX_TREE && guard++ < FV_MAX_TREE) {   // the host made pred[j] < j; the guard bounds the walk anyway

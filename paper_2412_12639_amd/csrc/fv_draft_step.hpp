@@ -65,7 +65,7 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
     }
     {
         DraftIngestArgs ia;
-        ia.tab = tab; ia.r0 = ps.r0; ia.n = n; ia.Tp = Tp; ia.half_d = D / 2; ia.log2_base = std::log2((double)cf.rope_base);
+        ia.tab = tab; ia.chain = ps.commit ? 1 : 0; ia.r0 = ps.r0; ia.n = n; ia.Tp = Tp; ia.half_d = D / 2; ia.log2_base = std::log2((double)cf.rope_base);
         ia.mask = c->at<uint64_t>(ly.off_mask); ia.rope_cs = c->at<float2>(ly.off_rope);
         hipLaunchKernelGGL(k_draft_ingest, dim3((Tp + 3) / 4), dim3(256), 0, st, ia);
         DraftInArgs da;
