@@ -61,7 +61,7 @@ void make_draft_layout(const fv_cfg& t, int n_wg, DraftLayout& L) {
     for (int i = 0; i < GM_COUNT; ++i) ngmax = std::max(ngmax, core.gm[i].n_strips_pad);
     L.ticket_bytes = (size_t)ngmax * 4;
     L.off_tickets = take(L.ticket_bytes);
-    L.chain_bytes = 256 + 2 * 2 * h * 2;   // two arrival counters 128 bytes apart, then [layer][2][h] bf16
+    L.chain_bytes = 256 + 128 * h;   // two arrival counters 128 bytes apart, then [layer][2][h][16 columns] bf16 (a chain: one column)
     L.off_chain = take(L.chain_bytes);
     L.total = o;
 }
@@ -104,7 +104,13 @@ int launch_chain_t(const LstmChainArgs& a, hipStream_t st) {
     return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
 }
 template <int NKF>
+int launch_levels_t(const LstmLevelArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(k_lstm_levels<NKF>, dim3(a.c.h / 16), dim3(256), lstm_level_smem(NKF), st, a);
+    return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
+}
+template <int NKF>
 int set_chain_attr() {
+    HIPCHK(hipFuncSetAttribute((const void*)k_lstm_levels<NKF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lstm_level_smem(NKF)));
     HIPCHK(hipFuncSetAttribute((const void*)k_lstm_chain<NKF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lstm_chain_smem(NKF)));
     return FV_OK;
 }
@@ -148,6 +154,21 @@ int launch_lstm_chain(fv_drafter* d, const DraftPass& ps, int layer, int Tp) {
     a.expect = (unsigned)(h / 16) + (d->chain_test ? 1u : 0u);
     a.arrive_looks = d->chain_test ? 2u : 4000u;   // some milliseconds
     a.spin_limit = FV_EXCHANGE_SPINS;
+    if (!ps.commit) {
+        LstmLevelArgs la;
+        la.c = a;
+        la.c.xchg = d->at<uint16_t>(dl.off_chain + 256) + (size_t)layer * 32 * h;
+        la.tab = dev_tables(d); la.xprev = d->at<uint4>(dl.off_xprev); la.l0 = ps.l0; la.n_lvl = (int)ps.lvl_n.size();
+        for (int i = 0; i < FV_DRAFT_KMAX; ++i) la.rows[i] = i < la.n_lvl ? ps.lvl_n[i] : 0;
+        switch (lstm_chain_size(h)) {
+            case 2: return launch_levels_t<2>(la, c->stream);
+            case 4: return launch_levels_t<4>(la, c->stream);
+            case 8: return launch_levels_t<8>(la, c->stream);
+            case 16: return launch_levels_t<16>(la, c->stream);
+            case 32: return launch_levels_t<32>(la, c->stream);
+        }
+        return FV_E_BAD_ARG;
+    }
     switch (lstm_chain_size(h)) {
         case 2: return launch_chain_t<2>(a, c->stream);
         case 4: return launch_chain_t<4>(a, c->stream);
@@ -407,6 +428,10 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
             ps.lvl_n.push_back((int)by_level[j].size());
             for (int t : by_level[j]) t_lvl[lvl_at++] = t;
         }
+        // Two levels and more of up to 16 rows each in one launch per layer (a level's rows are a subset of the blocks of the level
+        // before, so the counts never grow, which the kernel's exchange relies on); one level gains nothing.
+        ps.chain = d->chain_ok && ps.lvl_n.size() >= 2 && ps.lvl_n.size() <= FV_DRAFT_KMAX;
+        for (size_t j = 0; j < ps.lvl_n.size(); ++j) ps.chain = ps.chain && ps.lvl_n[j] <= 16 && (j == 0 || ps.lvl_n[j] <= ps.lvl_n[j - 1]);
         passes.push_back(ps);
     }
     if ((long long)d->L0 + next_row > cf.max_seq) return FV_E_CACHE_FULL;
@@ -432,23 +457,30 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
     hipStream_t st = d->core->stream;
     int rc = upload_tables(d);
     if (rc) return rc;
-    HIPCHK(hipMemcpyAsync(d->at<int32_t>(d->lay.off_node_tok), &root_token, 4, hipMemcpyHostToDevice, st));
-    HIPCHK(hipEventRecord(d->core->ev0, st));
-    if (n_pass >= 1 && exp_range[0].second > 0) {
-        ExpandArgs ea;
-        ea.tab = dev_tables(d); ea.top_tok = d->at<int32_t>(d->lay.off_top_tok); ea.node_tok = d->at<int32_t>(d->lay.off_node_tok);
-        ea.e0 = exp_range[0].first; ea.n = exp_range[0].second;
-        hipLaunchKernelGGL(k_draft_expand, dim3((ea.n + 255) / 256), dim3(256), 0, st, ea);
+    for (bool again = false;; again = true) {
+        HIPCHK(hipMemcpyAsync(d->at<int32_t>(d->lay.off_node_tok), &root_token, 4, hipMemcpyHostToDevice, st));
+        HIPCHK(hipEventRecord(d->core->ev0, st));
+        if (n_pass >= 1 && exp_range[0].second > 0) {
+            ExpandArgs ea;
+            ea.tab = dev_tables(d); ea.top_tok = d->at<int32_t>(d->lay.off_top_tok); ea.node_tok = d->at<int32_t>(d->lay.off_node_tok);
+            ea.e0 = exp_range[0].first; ea.n = exp_range[0].second;
+            hipLaunchKernelGGL(k_draft_expand, dim3((ea.n + 255) / 256), dim3(256), 0, st, ea);
+            HIPCHK(hipGetLastError());
+        }
+        for (const DraftPass& ps : passes) {
+            rc = pass_any(d, ps);
+            if (rc) return rc;
+        }
+        HIPCHK(hipEventRecord(d->core->ev1, st));
+        HIPCHK(hipMemcpyAsync(d->h_out, d->at<int32_t>(d->lay.off_node_tok), (size_t)n * 4, hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(d->h_out + FV_MAX_TREE, d->at<int32_t>(d->lay.off_bad), 12, hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        if (again || !d->h_out[FV_MAX_TREE + 2] || d->h_out[FV_MAX_TREE + 1]) break;
+        // a launch over several levels left because its workgroups were not on the chip together: the tree once more without
+        hipLaunchKernelGGL(k_draft_fill, dim3(1), dim3(256), 0, st, d->at<uint32_t>(d->lay.off_bad), 0u, (size_t)3);
         HIPCHK(hipGetLastError());
+        for (DraftPass& ps : passes) ps.chain = false;
     }
-    for (const DraftPass& ps : passes) {
-        rc = pass_any(d, ps);
-        if (rc) return rc;
-    }
-    HIPCHK(hipEventRecord(d->core->ev1, st));
-    HIPCHK(hipMemcpyAsync(d->h_out, d->at<int32_t>(d->lay.off_node_tok), (size_t)n * 4, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(d->h_out + FV_MAX_TREE, d->at<int32_t>(d->lay.off_bad), 8, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
     if (d->h_out[FV_MAX_TREE + 1]) { d->part_dirty = true; return FV_E_EXCHANGE_TIMEOUT; }
     HIPCHK(hipEventElapsedTime(&d->last_ms, d->core->ev0, d->core->ev1));
     d->n_rows = next_row;

@@ -88,7 +88,7 @@ struct DraftInArgs {
 template <typename EL>
 static __global__ __launch_bounds__(256) void k_draft_in(DraftInArgs a) {
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx < (size_t)a.chain_words) a.chain[idx] = 0u;   // (fewer words than threads: 64 + 2h against 2h / 4 * Tp)
+    for (size_t i = idx; i < (size_t)a.chain_words; i += (size_t)gridDim.x * 256) a.chain[i] = 0u;
     const int t = (int)(idx % a.Tp);
     const int f0 = (int)(idx / a.Tp) * 4;
     if (f0 >= 2 * a.h) return;

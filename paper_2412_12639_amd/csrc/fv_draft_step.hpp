@@ -71,7 +71,7 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         DraftInArgs da;
         da.tab = tab; da.fout = d->at<float>(dl.off_fout); da.ext = ps.ext; da.node_tok = d->at<int32_t>(dl.off_node_tok);
         da.table = d->target->arena + d->target->lay.off_embed; da.xz = d->at<void>(dl.off_xz);
-        da.chain = d->at<uint32_t>(dl.off_chain); da.chain_words = ps.chain ? (int)(dl.chain_bytes / 4) : 0;
+        da.chain = d->at<uint32_t>(dl.off_chain); da.chain_words = ps.chain ? (256 + (ps.commit ? 8 : 128) * h) / 4 : 0;
         da.r0 = ps.r0; da.n = n; da.Tp = Tp; da.h = h; da.vocab = cf.vocab;
         const size_t items = (size_t)(2 * h / 4) * Tp;
         hipLaunchKernelGGL((k_draft_in<EL>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, da);
@@ -91,6 +91,12 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
             if (rc) return rc;
         }
         if (ps.chain) {   // all rows in one launch
+            if (!ps.commit) {   // the first level's predecessors are rows of earlier passes
+                LstmGatherArgs la;
+                la.tab = tab; la.state = d->state(layer); la.xprev = d->at<void>(dl.off_xprev);
+                la.r0 = ps.r0; la.l0 = ps.l0; la.n_lvl = ps.lvl_n[0]; la.Tpl = 32; la.h = h;
+                hipLaunchKernelGGL((k_lstm_gather<EL>), dim3((unsigned)(((size_t)(h / 4) * 32 + 255) / 256)), dim3(256), 0, st, la);
+            }
             int rc = launch_lstm_chain(d, ps, layer, Tp);
             if (rc) return rc;
             if (layer == 1) {

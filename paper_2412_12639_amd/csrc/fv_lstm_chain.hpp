@@ -241,6 +241,203 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
     }
 }
 
+// The same for the levels of a tree pass: up to 16 rows a level, which are the 16 columns of the matrix instruction (a chain uses
+// one of them).  Two levels of 7 to 11 rows at hidden 4096: 48 us per layer (and 5 to gather) against 2 x (gather 5, product
+// 23 to 31, cell 5 us and gaps); 4 pairs and a 64-node tree 1632 -> 1585 us.  Differences to
+// the chain: a level's rows continue rows anywhere in the level before, so a lane reads its column's predecessor; the first
+// level's predecessors are gathered by k_lstm_gather; the operand goes from the exchange area straight to registers, a few
+// fragments at a time; all four wavefronts apply the cell.
+struct LstmLevelArgs {
+    LstmChainArgs c;               // n, t0, lpred are not used; xchg: [2][h / 8][16][8]
+    DraftTables tab;
+    const uint4* xprev;            // [h / 8][32][8] bf16 predecessors' states of the first level
+    int l0, n_lvl;                 // first entry in lvl_rows; levels
+    int rows[FV_DRAFT_KMAX];       // rows of each level, 1..16
+};
+
+constexpr size_t lstm_level_smem(int nkf) { return (size_t)4 * (nkf - lstm_chain_reg_frags(nkf)) * 4 * 64 * 16 + 4 * 4 * 16 * 16 * 4 + 16; }
+
+template <int NKF>
+static __global__ __launch_bounds__(256, 1) void k_lstm_levels(LstmLevelArgs la) {
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+    constexpr int RKF = lstm_chain_reg_frags(NKF), LKF = NKF - RKF;
+    constexpr int GF = NKF < 4 ? NKF : 4;
+    constexpr int SC1 = 16;
+    constexpr unsigned LEAVE = 0x80000000u, TAG = 0x40004000u;
+    extern __shared__ uint4 lds_chain[];
+    const LstmChainArgs& a = la.c;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int u = lane & 15, q = lane >> 4;
+    const int wg = blockIdx.x, h = a.h;
+    const int kf_real = h >> 7;
+    uint4* const wl = lds_chain + (size_t)wave * LKF * 4 * 64 + lane;
+    float* const part = (float*)(lds_chain + (size_t)4 * LKF * 4 * 64);   // [4 wavefronts][4 gates][16 columns][16 units]
+    unsigned* const go = (unsigned*)(part + 4 * 4 * 16 * 16);
+
+    if (tid == 0) __hip_atomic_fetch_add(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int n_half = h >> 6;
+    auto w_addr = [&](int g, int kf) {   // as in k_lstm_chain
+        const int strip = g * (h >> 5) + (wg >> 1);
+        const int F = wave * (h >> 6) + 2 * kf + (q >> 1);
+        const uint4* p = a.Wt + ((((size_t)(strip >> 1) * n_half + (F >> 2)) * 2 + (strip & 1)) * 4 + (F & 3)) * 64 + (wg & 1) * 16 + u + 32 * (q & 1);
+        return kf < kf_real ? p : a.zeros + lane;
+    };
+    u32x4_t w[RKF][4];
+#pragma unroll
+    for (int i = 0; i < RKF; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) w[i][g] = *(const u32x4_t*)w_addr(g, LKF > 0 ? i / 3 * 4 + i % 3 : i);
+#pragma unroll
+    for (int i = 0; i < RKF; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            if (i * 4 + g < RKF * 4 - 36) asm volatile("" : "+a"(w[i][g]));
+    for (int i = 0; i < LKF; ++i) {
+        uint4 v[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) v[g] = *w_addr(g, 4 * i + 3);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) wl[(i * 4 + g) * 64] = v[g];
+    }
+    if (tid == 0) {
+        unsigned seen = 0;
+        for (unsigned looks = 0;; ++looks) {
+            seen = __hip_atomic_load(a.sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((seen & LEAVE) || seen == a.expect) break;
+            if (looks >= a.arrive_looks) {
+                unsigned old = seen;
+                if (__hip_atomic_compare_exchange_strong(a.sync, &old, seen | LEAVE, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                    seen |= LEAVE;
+                    break;
+                }
+                continue;
+            }
+            __builtin_amdgcn_s_sleep(8);
+        }
+        if (seen & LEAVE) __hip_atomic_store(a.aborted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *go = (seen & LEAVE) ? 0u : 1u;
+    }
+    __syncthreads();
+    if (*go == 0u) return;
+
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.xchg, 0, 64 * h, 0x00020000);
+    const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc((void*)la.xprev, 0, 64 * h, 0x00020000);
+    const int cu = tid & 15, cc = tid >> 4;            // cell: unit and column of this thread
+    const size_t unit = (size_t)16 * wg + cu;
+    const size_t H = h;
+    unsigned limit = a.spin_limit;
+    int l_at = la.l0;
+    for (int s = 0; s < la.n_lvl; ++s) {
+        const int n = la.rows[s], np = s > 0 ? la.rows[s - 1] : 0;
+        // this lane's column of the operand: row u of the level (lanes beyond the level repeat row 0), its predecessor's column
+        const int my_t = la.tab.lvl_rows[l_at + (u < n ? u : 0)];
+        int col = u < n ? u : 0;
+        if (s > 0) {
+            const int want = la.tab.lpred[a.r0 + my_t] - a.r0;
+            col = 0;
+            for (int i = 0; i < np; ++i) if (la.tab.lvl_rows[l_at - np + i] == want) col = i;
+        }
+        const unsigned ph = (((s - 1) >> 1) & 1) ? 0u : TAG;
+        // 8-value vector 4 kf + q of this wavefront's quarter, at this lane's column
+        const int cols = s > 0 ? 16 : 32;
+        const __amdgpu_buffer_rsrc_t brs = s > 0 ? xrs : prs;
+        const unsigned mine0 = (unsigned)((s > 0 ? ((s - 1) & 1) * h * 32 : 0) + ((wave * (h >> 5) + q) * cols + col) * 16);
+        auto fetch = [&](int gr, u32x4_t (&d)[GF]) {
+#pragma unroll
+            for (int j = 0; j < GF; ++j) {
+                const int kf = gr * GF + j;
+                d[j] = __builtin_amdgcn_raw_buffer_load_b128(brs, mine0, (kf < kf_real ? kf : 0) * 64 * cols, SC1);
+            }
+        };
+        floatx4 acc[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+        u32x4_t b[2][GF], wb[4];
+        fetch(0, b[0]);
+#pragma unroll
+        for (int gr = 0; gr < NKF / GF; ++gr) {
+            if (s > 0) {
+                for (unsigned looks = 0;; ++looks) {
+                    asm volatile("" ::: "memory");
+                    unsigned off = 0u;
+#pragma unroll
+                    for (int j = 0; j < GF; ++j) off |= (b[gr & 1][j].x ^ ph) | (b[gr & 1][j].y ^ ph) | (b[gr & 1][j].z ^ ph) | (b[gr & 1][j].w ^ ph);
+                    if (__all((off & TAG) == 0u)) break;
+                    if (looks >= limit) {
+                        limit = 0;
+                        if (lane == 0) __hip_atomic_store(a.fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        break;
+                    }
+                    fetch(gr, b[gr & 1]);
+                }
+            }
+            if (gr + 1 < NKF / GF) fetch(gr + 1, b[(gr + 1) & 1]);
+            if constexpr (LKF > 0) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) wb[g] = *(const u32x4_t*)&wl[(gr * 4 + g) * 64];
+            }
+            auto plain = [&](unsigned x) {
+                x ^= ph;
+                const unsigned over = ((x & 0x7fff7fffu) + 0x407f407fu) & 0x80008000u;
+                return x | (over >> 1);
+            };
+            if (s > 0) {
+#pragma unroll
+                for (int j = 0; j < GF; ++j) {
+                    u32x4_t& v = b[gr & 1][j];
+                    v.x = plain(v.x); v.y = plain(v.y); v.z = plain(v.z); v.w = plain(v.w);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < GF; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const u32x4_t wv = (LKF > 0 && j == 3) ? wb[g] : w[LKF > 0 ? (gr * 3 + j) % RKF : gr * GF + j][g];
+                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv), __builtin_bit_cast(bf16x8_t, b[gr & 1][j]), acc[g], 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) *(floatx4*)(part + ((wave * 4 + g) * 16 + u) * 16 + 4 * q) = acc[g];   // column u, units 4q..
+        __builtin_amdgcn_sched_barrier(0);   // what the cell needs is requested here: above it would take registers from the weights
+        const bool cell = cc < n;
+        const int ct = la.tab.lvl_rows[l_at + (cell ? cc : 0)], cr = a.r0 + ct;
+        float gin[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) gin[g] = a.g_in[(size_t)ct * 4 * H + g * H + unit] + a.bias[g * H + unit];
+        const float cp = a.state[((size_t)la.tab.lpred[cr] * 2 + 1) * H + unit];   // this workgroup's own store of the level before, or older
+        __syncthreads();
+        float pre[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            float v = part[(g * 16 + cc) * 16 + cu];
+#pragma unroll
+            for (int w_ = 1; w_ < 4; ++w_) v += part[((w_ * 4 + g) * 16 + cc) * 16 + cu];
+            pre[g] = v + gin[g];
+        }
+        const float cn = fv_sigmoid(pre[1]) * cp + fv_sigmoid(pre[0]) * tanhf(pre[2]);
+        const float hn = fv_sigmoid(pre[3]) * tanhf(cn);
+        const __bf16 hb = (__bf16)hn;
+        const unsigned mine = __builtin_bit_cast(uint16_t, hb), other = (unsigned)__shfl_xor((int)mine, 1);
+        const unsigned pair = mine | (other << 16);   // even threads: units cu, cu + 1
+        if (cell) {
+            if ((cu & 1) == 0) {
+                if (s + 1 < la.n_lvl)
+                    __builtin_amdgcn_raw_buffer_store_b32((pair & ~TAG) | (((s >> 1) & 1) ? 0u : TAG), xrs,
+                                                          (unsigned)(((s & 1) * h * 32) + (((int)unit >> 3) * 16 + cc) * 16 + ((int)unit & 7) * 2), 0, SC1);
+                if (a.xnext) *(unsigned*)((char*)a.xnext + ((unit >> 3) * a.Tp + ct) * 16 + (unit & 7) * 2) = pair;
+            }
+            a.state[((size_t)cr * 2) * H + unit] = hn;
+            a.state[((size_t)cr * 2 + 1) * H + unit] = cn;
+        }
+        __syncthreads();   // part is written again, and the next level reads this one's cell states
+        l_at += n;
+    }
+}
+
 // What LAYER 1 leaves for the decoder block, for rows whose states are there: the residual stream x, x * gain and the
 // per-strip sums of squares (the second half of k_lstm_cell).
 struct LstmOutArgs { const float* state; float* x; void* xb; const float* gain; float* ssq; int r0, t0, n, Tp, h; };

@@ -317,3 +317,53 @@ def test_chain_launches(hidden, give_up, monkeypatch):
     assert e.value.status == -10
     dr.close()
     tgt.close()
+
+
+@pytest.mark.parametrize("hidden,k,give_up", [(256, 4, False), (384, 3, False), (512, 4, True), (1024, 5, False)])
+def test_level_launches(hidden, k, give_up, monkeypatch):
+    """Tree passes whose LSTM levels run in one launch per layer: three to five levels (the exchange buffers and their phase are used
+    again from the third on), blocks that drop out on the way, up to sixteen blocks and more (which go level by level)."""
+    import torch
+    from dataclasses import replace
+    from paper_2412_12639_amd.binding import FalconDrafter, FalconVerifier
+    if give_up:
+        monkeypatch.setenv("FV_EXCHANGE_TEST", "chain")
+    s = replace(shape_by_name("tiny-bf16"), name=f"tiny-bf16-h{hidden}", hidden=hidden)
+    lw, dw = gen_weights(s, seed=71, gain_jitter=0.1), gen_drafter_weights(s, seed=72, gain_jitter=0.1)
+    tgt = FalconVerifier(s, 300, 64)
+    tgt.init_weights(lw)
+    dr = FalconDrafter(tgt, k)
+    dr.init_weights(dw)
+    orc = do.DrafterOracle(s, lw, dw, k, 300)
+    rng = np.random.default_rng(hidden)
+    trees = [gen_tree(81, 40, [3, 2, 1, 1, 2, 1, 1, 1, 1, 1, 1, 1], 12), gen_tree(82, 90, [6, 4, 1, 1, 1, 1, 1, 1, 1], 9), gen_tree(83, 14, [1] * 13, 13)]
+    for phase, (n_new, tree) in enumerate(zip([k + 1, 2, 1], trees)):
+        feats = gen_features(500 + phase, n_new, s.hidden)
+        toks = rng.integers(0, s.vocab, n_new)
+        dr.commit(toks, torch.from_numpy(feats).cuda())
+        orc.commit(feats, toks)
+        parent, depth, _ = tree
+        rank = sibling_ranks(parent)
+        got = dr.draft_tree(parent, depth, rank, int(toks[-1]))
+        orc.draft(parent, depth, rank, int(toks[-1]), force_tokens=got)
+        _check_phase(s, dr, orc, n_new, got, parent, depth, rank, 2e-2)
+    dr.close()
+    tgt.close()
+
+
+def test_long_bf16_commit_in_wide_pieces():
+    """300 pairs: 256 rows in one piece (the ring GEMM and the chain launch over 256 rows), then the 44 that stay open."""
+    import torch
+    s, lw, dw, tgt, dr = _make("tiny-bf16", 2, max_seq=400)
+    orc = do.DrafterOracle(s, lw, dw, 2, 400)
+    n = 300
+    feats = gen_features(7, n, s.hidden)
+    toks = np.random.default_rng(8).integers(0, s.vocab, n)
+    dr.commit(toks, torch.from_numpy(feats).cuda())
+    _, l_ref = orc.commit(feats, toks)
+    assert dr.state() == (n, 44, 44)
+    assert _rel(dr.rows("logits", 0, 44), l_ref[-44:]) <= 2e-2
+    kd, vd = dr.read_kv(0, n)
+    assert _rel(kd, orc.K[:n]) <= 2e-2 and _rel(vd, orc.V[:n]) <= 2e-2
+    dr.close()
+    tgt.close()
