@@ -30,25 +30,26 @@ struct IngestArgs {
 #define FV_PH_END
 #endif
 
-static __global__ __launch_bounds__(256) void k_ingest(IngestArgs a) {
-    // one workgroup per four rows: their ancestor masks (a short chain of dependent loads each) and
-    // their rows of the rotary table (double-precision sincos, one or two entries per thread)
+// one workgroup (`blk`) per four rows: their ancestor masks (a chain of dependent reads each, from LDS: out of memory 256 rows of a
+// prompt took 25 us) and their rows of the rotary table (double-precision sincos, one or two entries per thread)
+__device__ __forceinline__ void ingest_rows(const IngestArgs& a, int blk, int32_t* s_parent, int32_t* s_depth) {
     const int tid = threadIdx.x;
-    const int32_t* parent = a.tok_in + a.cap;
-    const int32_t* depth = a.tok_in + 2 * a.cap;
-    const int t0 = blockIdx.x * 4, t1 = (t0 + 4 < a.Tp) ? t0 + 4 : a.Tp;
+    if (tid < a.T) { s_parent[tid] = a.tok_in[a.cap + tid]; s_depth[tid] = a.tok_in[2 * a.cap + tid]; }
+    __syncthreads();
+    const int t0 = blk * 4, t1 = (t0 + 4 < a.Tp) ? t0 + 4 : a.Tp;
     for (int i = t0 + tid; i < t1; i += 256) {
         uint64_t m[4] = {0, 0, 0, 0};
         int p = 0;
         if (i < a.T) {
             int j = i, guard = 0;
-            const bool by_depth = a.anc && depth[i] <= FV_CANON_DEPTH;
+            const bool by_depth = a.anc && s_depth[i] <= FV_CANON_DEPTH;
             while (j >= 0 && guard++ < FV_MAX_TREE) {   // host validated parent[j] < j; guard bounds the walk anyway
-                m[j >> 6] |= 1ull << (j & 63);
-                if (by_depth && depth[j] >= 0 && depth[j] <= FV_CANON_DEPTH) a.anc[i * (FV_CANON_DEPTH + 1) + depth[j]] = (uint8_t)j;
-                j = parent[j];
+#pragma unroll
+                for (int w = 0; w < 4; ++w) m[w] |= (j >> 6) == w ? 1ull << (j & 63) : 0ull;
+                if (by_depth && s_depth[j] >= 0 && s_depth[j] <= FV_CANON_DEPTH) a.anc[i * (FV_CANON_DEPTH + 1) + s_depth[j]] = (uint8_t)j;
+                j = s_parent[j];
             }
-            p = a.L + depth[i];
+            p = a.L + s_depth[i];
         }
         for (int w = 0; w < 4; ++w) a.mask[i * 4 + w] = m[w];
         a.pos[i] = p;
@@ -56,7 +57,7 @@ static __global__ __launch_bounds__(256) void k_ingest(IngestArgs a) {
     const int n = t1 * a.half_d;
     for (int e = t0 * a.half_d + tid; e < n; e += 256) {
         const int t = e / a.half_d, i = e % a.half_d;
-        const int p = (t < a.T) ? a.L + depth[t] : 0;
+        const int p = (t < a.T) ? a.L + s_depth[t] : 0;
         // angle = pos * base^(-2i/d), d = 2*half_d
         const double inv_freq = exp2(-(double)i / (double)a.half_d * a.log2_base);
         double s, c;
@@ -66,7 +67,7 @@ static __global__ __launch_bounds__(256) void k_ingest(IngestArgs a) {
 }
 
 // Prompt rows: a chain.  Positions and rotary rows of Tp rows from slot L on; the masks of one piece of 256 rows, which are
-// those of every piece.  (k_ingest would walk up to 255 parents per row.)
+// those of every piece.  (ingest_rows would walk up to 255 parents per row.)
 struct PromptIngestArgs { int T, Tp, L, half_d; double log2_base; uint64_t* mask; float2* rope_cs; };
 static __global__ __launch_bounds__(256) void k_ingest_prompt(PromptIngestArgs a) {
     const int t0 = blockIdx.x * 4, tid = threadIdx.x;
@@ -112,11 +113,11 @@ struct EmbedArgs {
     int h, T, Tp;
 };
 
+// 32 features (strip s) of row t
 template <typename EL>
-__global__ void k_embed(EmbedArgs a) {
-    const int s = blockIdx.x, t = blockIdx.y * blockDim.x + threadIdx.x;
-    if (t >= a.Tp) return;
+__device__ __forceinline__ void embed_strip(const EmbedArgs& a, int s, int t) {
     float ssq = 0.f;
+#pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int f0 = s * 32 + q * 4;
         float v[4] = {0.f, 0.f, 0.f, 0.f};
@@ -130,6 +131,23 @@ __global__ void k_embed(EmbedArgs a) {
         ssq += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
     }
     a.ssq_part[(size_t)s * a.Tp + t] = ssq;
+}
+
+// prompt rows: grid (h / 32, Tp / 256)
+template <typename EL>
+__global__ __launch_bounds__(256) void k_embed(EmbedArgs a) { embed_strip<EL>(a, blockIdx.x, blockIdx.y * 256 + threadIdx.x); }
+
+// The start of a step, ingest and embedding side by side in one launch (they do not depend on each other): the first n_embed
+// workgroups take 256 / Tp strips each, the others four rows.  Tp is 32, 64, 128 or 256.
+template <typename EL>
+__global__ __launch_bounds__(256) void k_begin(IngestArgs ia, EmbedArgs ea, int n_embed) {
+    __shared__ int32_t s_parent[FV_MAX_TREE], s_depth[FV_MAX_TREE];
+    if ((int)blockIdx.x < n_embed) {
+        const int s = blockIdx.x * (256 / ea.Tp) + threadIdx.x / ea.Tp;
+        if (s < ea.h / 32) embed_strip<EL>(ea, s, threadIdx.x % ea.Tp);
+    } else {
+        ingest_rows(ia, blockIdx.x - n_embed, s_parent, s_depth);
+    }
 }
 
 // ============================================================================ skinny GEMM
@@ -1164,95 +1182,6 @@ static __global__ __launch_bounds__(256) void k_argmax(ArgmaxArgs a) {
     }
 }
 
-// ============================================================================ longest accepted path
-// Single block.  match[i] = (i is the root) or tok[i] == argmax[parent[i]]; node i is
-// accepted iff every node of its ancestor set matches; best = deepest accepted node, lowest
-// index among equals; path = members of best's ancestor set in increasing index (= depth) order.
-// Features of the accepted path for the next drafting round: row j = the LM head's input (final
-// RMSNorm of the last layer's output) of path node j, j = 0..accepted_len, fp32 [max_tree][h].
-// One block per possible path position; blocks beyond the path leave at once.
-struct FeatureArgs {
-    const FvResult* res;
-    const float* x;          // residual stream after the last layer, fp32 [h/4][Tp][4]
-    const float* ssq;        // its per-strip sums of squares [h/32][Tp]
-    const float* gain;       // final norm gain [h]
-    float* out;              // [max_tree][h]
-    int h, Tp;
-    float inv_h, eps;
-};
-
-static __global__ __launch_bounds__(256) void k_features(FeatureArgs a) {
-    __shared__ float red[256];
-    const int j = blockIdx.x, tid = threadIdx.x;
-    if (j > a.res->accepted_len) return;
-    const int t = a.res->path[j];
-    float s = 0.f;
-    for (int i = tid; i < a.h / 32; i += 256) s += a.ssq[(size_t)i * a.Tp + t];
-    red[tid] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (tid < w) red[tid] += red[tid + w];
-        __syncthreads();
-    }
-    const float rinv = rsqrtf(red[0] * a.inv_h + a.eps);
-    for (int f = tid; f < a.h; f += 256)
-        a.out[(size_t)j * a.h + f] = a.x[((size_t)(f >> 2) * a.Tp + t) * 4 + (f & 3)] * rinv * a.gain[f];
-}
-
-struct ScanArgs {
-    const int32_t* tok_in;   // [3][cap]
-    int cap, T;
-    const uint64_t* mask;
-    const int32_t* am;
-    FvResult* res;
-};
-
-static __global__ __launch_bounds__(256) void k_scan(ScanArgs a) {
-    __shared__ unsigned long long mbits[4];
-    __shared__ int best_key;
-    __shared__ int any_bad;
-    const int i = threadIdx.x;
-    const int32_t* tok = a.tok_in;
-    const int32_t* parent = a.tok_in + a.cap;
-    const int32_t* depth = a.tok_in + 2 * a.cap;
-    if (i < 4) mbits[i] = 0ull;
-    if (i == 0) { best_key = -1; any_bad = 0; }
-    __syncthreads();
-    if (i < a.T && a.am[i] < 0) any_bad = 1;   // a row without a greedy choice (non-finite logits)
-    if (i < a.T) {
-        const bool match = (i == 0) || (tok[i] == a.am[parent[i]]);
-        if (match) atomicOr(&mbits[i >> 6], 1ull << (i & 63));
-    }
-    __syncthreads();
-    if (i < a.T) {
-        bool ok = true;
-        for (int w = 0; w < 4; ++w) ok = ok && ((a.mask[i * 4 + w] & ~mbits[w]) == 0ull);
-        if (ok) atomicMax(&best_key, depth[i] * 512 + (511 - i));
-    }
-    __syncthreads();
-    if (any_bad) {   // no decision: accepted_len = FV_SCAN_NONFINITE tells the host, nothing is compacted
-        if (i == 0) { a.res->accepted_len = FV_SCAN_NONFINITE; a.res->next_token = -1; a.res->best = 0; a.res->pad = 0; }
-        return;
-    }
-    const int best = 511 - (best_key & 511);
-    if (i == 0) {
-        a.res->accepted_len = depth[best];
-        a.res->next_token = a.am[best];
-        a.res->best = best;
-        a.res->pad = 0;
-    }
-    if (i < a.T) {
-        const uint64_t* mb = a.mask + best * 4;
-        if ((mb[i >> 6] >> (i & 63)) & 1ull) {
-            int rank = 0;
-            for (int w = 0; w < (i >> 6); ++w) rank += __popcll(mb[w]);
-            rank += __popcll(mb[i >> 6] & ((1ull << (i & 63)) - 1ull));
-            a.res->path[rank] = i;
-            if (rank >= 1) a.res->accepted_tokens[rank - 1] = tok[i];
-        }
-    }
-}
-
 // ============================================================================ non-greedy acceptance
 // Multi-step speculative sampling over the tree (the non-greedy setting of the paper's Appendix
 // "Tree Structure"; verification in the SpecInfer manner, section "Custom-Designed Decoding Tree").
@@ -1266,7 +1195,7 @@ static __global__ __launch_bounds__(256) void k_scan(ScanArgs a) {
 // is reproducible.
 //
 // What a node decides does not depend on how it was reached, so every node is decided at the same time,
-// one workgroup each (k_sampled_nodes), and the path is read off afterwards (k_sampled_path).  One
+// one workgroup each (k_sampled_nodes), and the path is read off afterwards (k_finish).  One
 // workgroup that walked the path node by node took 390 us at 33 nodes of vocabulary 32000, as much as
 // three layers: a dozen passes over the vocabulary one after the other, through one compute unit; this way
 // it takes 58 us.  A node's
@@ -1467,47 +1396,132 @@ static __global__ __launch_bounds__(FV_SAMPLED_THREADS) void k_sampled_nodes(Sam
     }
 }
 
-// The path from the root along the children that were taken, and the token drawn at its end.
-static __global__ __launch_bounds__(64) void k_sampled_path(SampledArgs a) {
-    __shared__ int32_t s_out[FV_MAX_TREE], s_tok[FV_MAX_TREE];
-    for (int i = threadIdx.x; i < a.T; i += 64) { s_out[i] = a.outcome[i]; s_tok[i] = a.tok_in[i]; }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    int cur = 0, len = 0;
-    a.res->path[0] = 0;
-    int o = s_out[0];
-    while (o > cur && o < a.T) {   // a child's index is above its parent's: the walk ends
-        cur = o;
-        ++len;
-        a.res->path[len] = cur;
-        a.res->accepted_tokens[len - 1] = s_tok[cur];
-        o = s_out[cur];
-    }
-    if (o == FV_SAMPLED_BAD || o >= 0) { a.res->accepted_len = FV_SCAN_NONFINITE; a.res->next_token = -1; a.res->best = 0; }
-    else { a.res->accepted_len = len; a.res->next_token = -1 - o; a.res->best = cur; }
-    a.res->pad = 0;
-}
-
-// ============================================================================ KV compaction
-// For every layer and KV head: cache slot L + j <- cache slot L + path[j], j = 0..a.
-// Tree K/V were written at slots L + node index; path[j] >= j, and thread e moves element e
-// for j = 0, 1, ... in order, so a slot is always read before it can be overwritten.
-struct CompactArgs {
-    void* kcache;      // [NL][Hkv][S_pad*D]
+// ============================================================================ end of a step
+// The accepted path, and what is kept of it: one launch.  Every workgroup finds the path by itself (a few KB of node data and
+// a microsecond; handing it on would be a launch, 5 us with its gap, and a step of two small layers is 100 us) and then does its
+// share:
+//   workgroup 0 writes the result record;
+//   T workgroups, one per possible path position, write a feature row: the LM head's input (final RMSNorm of the last layer's
+//     output) of path node j, j = 0..accepted_len, fp32 [max_tree][h];
+//   the others compact the cache, 256 / D slabs (layer, KV head) each: slot L + j <- slot L + path[j], j = 0..accepted_len.
+//     Tree K/V were written at slots L + node index; path[j] >= j, and a thread moves its feature for j = 0, 1, ... in
+//     order, so a slot is always read before it can be overwritten.
+// Greedy: match[i] = (i is the root) or tok[i] == argmax[parent[i]]; node i is accepted iff every node of its ancestor set
+// matches; best = deepest accepted node, lowest index among equals; path = members of best's ancestor set in increasing index
+// (= depth) order.  SAMPLED: from the root along the children the nodes took, to the token drawn at the end.
+struct FinishArgs {
+    const int32_t* tok_in;     // [3][cap]
+    int cap, T;
+    const uint64_t* mask;      // greedy
+    const int32_t* am;         // greedy: [Tp]
+    const int32_t* outcome;    // SAMPLED: [T], see SampledArgs
+    FvResult* res;
+    // features
+    const float* x;            // residual stream after the last layer, fp32 [h/4][Tp][4]
+    const float* ssq;          // its per-strip sums of squares [h/32][Tp]
+    const float* gain;         // final norm gain [h]
+    float* feat;               // [max_tree][h]
+    int h, Tp;
+    float inv_h, eps;
+    // compaction
+    void* kcache;              // [slabs][S_pad*D]
     void* vcache;
-    const FvResult* res;
-    int L, S_pad;
+    int slabs, L, S_pad;
 };
 
-template <typename EL, int D>
-__global__ void k_compact(CompactArgs a) {
-    const int e = threadIdx.x;   // feature, blockDim.x == D
-    char* ks = (char*)a.kcache + (size_t)blockIdx.x * a.S_pad * D * Tr<EL>::ESZ;
-    char* vs = (char*)a.vcache + (size_t)blockIdx.x * a.S_pad * D * Tr<EL>::ESZ;
+template <typename EL, int D, bool SAMPLED>
+__global__ __launch_bounds__(256) void k_finish(FinishArgs a) {
+    __shared__ unsigned long long mbits[4];
+    __shared__ int best_key, any_bad, s_len, s_next, s_best;
+    __shared__ int32_t s_path[FV_MAX_TREE], s_tok[FV_MAX_TREE], s_out[SAMPLED ? FV_MAX_TREE : 1];
+    __shared__ float red[256];
+    const int i = threadIdx.x;
+    const int32_t* tok = a.tok_in;
+    const int32_t* parent = a.tok_in + a.cap;
+    const int32_t* depth = a.tok_in + 2 * a.cap;
+    if (i < a.T) s_tok[i] = tok[i];
+    if constexpr (!SAMPLED) {
+        if (i < 4) mbits[i] = 0ull;
+        if (i == 0) { best_key = -1; any_bad = 0; }
+        __syncthreads();
+        uint64_t mk[4] = {0, 0, 0, 0};
+        if (i < a.T) {
+            if (a.am[i] < 0) any_bad = 1;   // a row without a greedy choice (non-finite logits)
+            for (int w = 0; w < 4; ++w) mk[w] = a.mask[i * 4 + w];
+            const bool match = (i == 0) || (s_tok[i] == a.am[parent[i]]);
+            if (match) atomicOr(&mbits[i >> 6], 1ull << (i & 63));
+        }
+        __syncthreads();
+        if (i < a.T) {
+            bool ok = true;
+            for (int w = 0; w < 4; ++w) ok = ok && ((mk[w] & ~mbits[w]) == 0ull);
+            if (ok) atomicMax(&best_key, depth[i] * 512 + (511 - i));
+        }
+        __syncthreads();
+        const int best = 511 - (best_key & 511);
+        const uint64_t* mb = a.mask + best * 4;
+        if (i < a.T && ((mb[i >> 6] >> (i & 63)) & 1ull)) {
+            int rank = 0;
+            for (int w = 0; w < (i >> 6); ++w) rank += __popcll(mb[w]);
+            rank += __popcll(mb[i >> 6] & ((1ull << (i & 63)) - 1ull));
+            s_path[rank] = i;
+        }
+        if (i == 0) {   // no decision: FV_SCAN_NONFINITE tells the host, nothing is kept
+            s_best = any_bad ? 0 : best;
+            s_len = any_bad ? FV_SCAN_NONFINITE : depth[best];
+            s_next = any_bad ? -1 : a.am[best];
+        }
+    } else {
+        if (i < a.T) s_out[i] = a.outcome[i];
+        __syncthreads();
+        if (i == 0) {
+            int cur = 0, len = 0, o = s_out[0];
+            s_path[0] = 0;
+            while (o > cur && o < a.T) {   // a child's index is above its parent's: the walk ends
+                cur = o;
+                s_path[++len] = cur;
+                o = s_out[cur];
+            }
+            const bool bad = o == FV_SAMPLED_BAD || o >= 0;
+            s_best = bad ? 0 : cur;
+            s_len = bad ? FV_SCAN_NONFINITE : len;
+            s_next = bad ? -1 : -1 - o;
+        }
+    }
+    __syncthreads();
+    const int len = s_len;
+    int b = blockIdx.x;
+    if (b == 0) {
+        if (i == 0) { a.res->accepted_len = len; a.res->next_token = s_next; a.res->best = s_best; a.res->pad = 0; }
+        if (i <= len) {
+            a.res->path[i] = s_path[i];
+            if (i >= 1) a.res->accepted_tokens[i - 1] = s_tok[s_path[i]];
+        }
+        return;
+    }
+    if (--b < a.T) {
+        if (b > len) return;
+        const int t = s_path[b];
+        float s = 0.f;
+        for (int k = i; k < a.h / 32; k += 256) s += a.ssq[(size_t)k * a.Tp + t];
+        red[i] = s;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if (i < w) red[i] += red[i + w];
+            __syncthreads();
+        }
+        const float rinv = rsqrtf(red[0] * a.inv_h + a.eps);
+        for (int f = i; f < a.h; f += 256)
+            a.feat[(size_t)b * a.h + f] = a.x[((size_t)(f >> 2) * a.Tp + t) * 4 + (f & 3)] * rinv * a.gain[f];
+        return;
+    }
+    const int slab = (b - a.T) * (256 / D) + i / D, e = i % D;
+    if (slab >= a.slabs) return;
+    char* ks = (char*)a.kcache + (size_t)slab * a.S_pad * D * Tr<EL>::ESZ;
+    char* vs = (char*)a.vcache + (size_t)slab * a.S_pad * D * Tr<EL>::ESZ;
     typedef typename Tr<EL>::elem_t el_t;
-    const int n = a.res->accepted_len;
-    for (int j = 0; j <= n && j < FV_MAX_TREE; ++j) {
-        const int src = a.res->path[j];
+    for (int j = 0; j <= len; ++j) {
+        const int src = s_path[j];
         if (src == j) continue;
         ((el_t*)ks)[kcache_index<EL, D>(a.L + j, e)] = ((el_t*)ks)[kcache_index<EL, D>(a.L + src, e)];
         ((el_t*)vs)[vcache_index<EL, D>(a.L + j, e)] = ((el_t*)vs)[vcache_index<EL, D>(a.L + src, e)];

@@ -205,14 +205,14 @@ int run_step(fv_ctx* c, int T, StepMode mode) {
         ia.log2_base = std::log2((double)cf.rope_base);
         ia.mask = c->at<uint64_t>(ly.off_mask); ia.pos = c->at<int32_t>(ly.off_pos); ia.rope_cs = c->at<float2>(ly.off_rope);
         ia.anc = c->at<uint8_t>(ly.off_anc);
-        hipLaunchKernelGGL(k_ingest, dim3((Tp + 3) / 4), dim3(256), 0, st, ia);
         EmbedArgs ea;
         ea.table = c->at<void>(ly.off_embed); ea.tok = c->at<int32_t>(ly.off_stepin); ea.gain = c->gain(0);
         ea.x = c->at<float>(ly.off_x);
         ea.xb = c->at<void>(ly.off_xb);
         ea.ssq_part = c->at<float>(ly.off_ssq);
         ea.h = h; ea.T = T; ea.Tp = Tp;
-        hipLaunchKernelGGL((k_embed<EL>), dim3(h / 32), dim3(Tp < 64 ? 64 : Tp), 0, st, ea);
+        const int per = 256 / Tp, n_embed = (h / 32 + per - 1) / per;
+        hipLaunchKernelGGL((k_begin<EL>), dim3(n_embed + Tp / 4), dim3(256), 0, st, ia, ea, n_embed);
     }
     HIPCHK(hipGetLastError());
 
@@ -314,27 +314,19 @@ int run_step(fv_ctx* c, int T, StepMode mode) {
             sa.u_accept = c->at<double>(ly.off_unif); sa.u_sample = sa.u_accept + FV_MAX_TREE;
             sa.work = c->at<double>(ly.off_pwork); sa.outcome = c->at<int32_t>(ly.off_outcome); sa.res = c->at<FvResult>(ly.off_res);
             hipLaunchKernelGGL(k_sampled_nodes, dim3(T), dim3(FV_SAMPLED_THREADS), 0, st, sa);
-            hipLaunchKernelGGL(k_sampled_path, dim3(1), dim3(64), 0, st, sa);
-        }
-        if (mode == STEP_VERIFY) {
-            ScanArgs sa;
-            sa.tok_in = c->at<int32_t>(ly.off_stepin); sa.cap = FV_MAX_TREE; sa.T = T;
-            sa.mask = c->at<uint64_t>(ly.off_mask); sa.am = c->at<int32_t>(ly.off_am); sa.res = c->at<FvResult>(ly.off_res);
-            hipLaunchKernelGGL(k_scan, dim3(1), dim3(256), 0, st, sa);
         }
         if (mode == STEP_VERIFY || mode == STEP_VERIFY_SAMPLED) {
-            CompactArgs ca;
-            ca.kcache = c->at<void>(ly.off_k); ca.vcache = c->at<void>(ly.off_v); ca.res = c->at<FvResult>(ly.off_res);
-            ca.L = L; ca.S_pad = ly.S_pad;
-            hipLaunchKernelGGL((k_compact<EL, D>), dim3(cf.n_layers * cf.n_kv_heads), dim3(D), 0, st, ca);
-            // features of the accepted path (what the drafter is given next to the tokens)
-            FeatureArgs fa;
+            // accepted path, its features (what the drafter is given next to the tokens), cache compaction
+            FinishArgs fa;
+            fa.tok_in = c->at<int32_t>(ly.off_stepin); fa.cap = FV_MAX_TREE; fa.T = T;
+            fa.mask = c->at<uint64_t>(ly.off_mask); fa.am = c->at<int32_t>(ly.off_am); fa.outcome = c->at<int32_t>(ly.off_outcome);
             fa.res = c->at<FvResult>(ly.off_res);
-            fa.x = c->at<float>(ly.off_x);
-            fa.ssq = c->at<float>(ly.off_ssq);
-            fa.gain = c->gain(2 * cf.n_layers); fa.out = c->at<float>(ly.off_feat);
+            fa.x = c->at<float>(ly.off_x); fa.ssq = c->at<float>(ly.off_ssq); fa.gain = c->gain(2 * cf.n_layers); fa.feat = c->at<float>(ly.off_feat);
             fa.h = h; fa.Tp = Tp; fa.inv_h = 1.f / (float)h; fa.eps = cf.rms_eps;
-            hipLaunchKernelGGL(k_features, dim3(T), dim3(256), 0, st, fa);
+            fa.kcache = c->at<void>(ly.off_k); fa.vcache = c->at<void>(ly.off_v); fa.slabs = cf.n_layers * cf.n_kv_heads; fa.L = L; fa.S_pad = ly.S_pad;
+            const dim3 grid(1 + T + (fa.slabs * D + 255) / 256);
+            if (mode == STEP_VERIFY) hipLaunchKernelGGL((k_finish<EL, D, false>), grid, dim3(256), 0, st, fa);
+            else hipLaunchKernelGGL((k_finish<EL, D, true>), grid, dim3(256), 0, st, fa);
         }
         HIPCHK(hipGetLastError());
     }
