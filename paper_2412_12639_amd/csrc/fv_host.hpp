@@ -52,7 +52,7 @@ struct Layout {
     size_t off_k = 0, off_v = 0, kv_layer_bytes = 0;
     size_t off_x = 0, off_xb = 0, off_q = 0, off_qlo = 0, off_attn = 0, off_act = 0, off_logits = 0;
     size_t off_ssq = 0, off_rinv = 0, off_part = 0, part_bytes = 0, off_tickets = 0;
-    size_t off_stepin = 0, off_mask = 0, off_pos = 0, off_anc = 0, off_rope = 0, off_am = 0, off_res = 0;
+    size_t off_stepin = 0, off_mask = 0, off_pos = 0, off_anc = 0, off_rope = 0, off_res = 0;
     size_t off_kvread = 0, off_stage = 0, stage_bytes = 0;
     size_t off_apart = 0, off_atick = 0, off_zeros = 0, off_feat = 0;
     size_t off_unif = 0, off_pwork = 0, off_outcome = 0;   // non-greedy acceptance: uniforms [2][256] fp64, working distributions [max_tree][Vpad] fp64, what each node decided [256]

@@ -1135,10 +1135,12 @@ __device__ __forceinline__ void argmax_combine(float& v, int& i, float ov, int o
     if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
 }
 
-static __global__ __launch_bounds__(256) void k_argmax(ArgmaxArgs a) {
-    __shared__ float sv[4];
-    __shared__ int si[4];
-    __shared__ int sbad[4];
+// NT threads: a row of 32000 values took 256 threads four rounds of requests (13 us for a single row), 1024 take one.
+template <int NT>
+static __global__ __launch_bounds__(NT) void k_argmax(ArgmaxArgs a) {
+    __shared__ float sv[NT / 64];
+    __shared__ int si[NT / 64];
+    __shared__ int sbad[NT / 64];
     const int t = blockIdx.x, tid = threadIdx.x;
     const float* row = a.logits + (size_t)t * a.Vpad;
     float bv = -INFINITY;
@@ -1147,16 +1149,16 @@ static __global__ __launch_bounds__(256) void k_argmax(ArgmaxArgs a) {
     // eight 16-byte loads in flight per thread (the row is a latency chain otherwise: one load per
     // trip of a loop the compiler does not pipeline); indices past Vpad are not touched, values
     // between V and Vpad are skipped
-    for (int v0 = tid * 4; v0 < a.V; v0 += 8 * 256 * 4) {
+    for (int v0 = tid * 4; v0 < a.V; v0 += 8 * NT * 4) {
         float4 x[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int v = v0 + k * 256 * 4;
+            const int v = v0 + k * NT * 4;
             x[k] = (v < a.V) ? *(const float4*)(row + v) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int v = v0 + k * 256 * 4;
+            const int v = v0 + k * NT * 4;
             const float xs[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
 #pragma unroll
             for (int c = 0; c < 4; ++c)
@@ -1177,8 +1179,9 @@ static __global__ __launch_bounds__(256) void k_argmax(ArgmaxArgs a) {
     if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; sbad[tid >> 6] = wbad ? 1 : 0; }
     __syncthreads();
     if (tid == 0) {
-        for (int w = 1; w < 4; ++w) argmax_combine(bv, bi, sv[w], si[w]);
-        a.am[t] = (sbad[0] | sbad[1] | sbad[2] | sbad[3]) ? -1 : bi;
+        int any = sbad[0];
+        for (int w = 1; w < NT / 64; ++w) { argmax_combine(bv, bi, sv[w], si[w]); any |= sbad[w]; }
+        a.am[t] = any ? -1 : bi;
     }
 }
 

@@ -304,8 +304,10 @@ int run_step(fv_ctx* c, int T, StepMode mode) {
         }
         PhaseTimer pt(c, FV_PH_OTHER);
         ArgmaxArgs am;
-        am.logits = c->at<float>(ly.off_logits); am.am = c->at<int32_t>(ly.off_am); am.V = cf.vocab; am.Vpad = ly.Vpad;
-        hipLaunchKernelGGL(k_argmax, dim3(T), dim3(256), 0, st, am);
+        am.logits = c->at<float>(ly.off_logits); am.am = c->at<FvResult>(ly.off_res)->argmax; am.V = cf.vocab; am.Vpad = ly.Vpad;
+        // one round of requests per row where it has more than a round's worth for 256 threads (8192 values)
+        if (cf.vocab > 8192) hipLaunchKernelGGL(k_argmax<1024>, dim3(T), dim3(1024), 0, st, am);
+        else hipLaunchKernelGGL(k_argmax<256>, dim3(T), dim3(256), 0, st, am);
         if (mode == STEP_VERIFY_SAMPLED) {
             SampledArgs sa;
             sa.tok_in = c->at<int32_t>(ly.off_stepin); sa.cap = FV_MAX_TREE; sa.T = T;
@@ -319,7 +321,7 @@ int run_step(fv_ctx* c, int T, StepMode mode) {
             // accepted path, its features (what the drafter is given next to the tokens), cache compaction
             FinishArgs fa;
             fa.tok_in = c->at<int32_t>(ly.off_stepin); fa.cap = FV_MAX_TREE; fa.T = T;
-            fa.mask = c->at<uint64_t>(ly.off_mask); fa.am = c->at<int32_t>(ly.off_am); fa.outcome = c->at<int32_t>(ly.off_outcome);
+            fa.mask = c->at<uint64_t>(ly.off_mask); fa.am = c->at<FvResult>(ly.off_res)->argmax; fa.outcome = c->at<int32_t>(ly.off_outcome);
             fa.res = c->at<FvResult>(ly.off_res);
             fa.x = c->at<float>(ly.off_x); fa.ssq = c->at<float>(ly.off_ssq); fa.gain = c->gain(2 * cf.n_layers); fa.feat = c->at<float>(ly.off_feat);
             fa.h = h; fa.Tp = Tp; fa.inv_h = 1.f / (float)h; fa.eps = cf.rms_eps;
@@ -331,14 +333,12 @@ int run_step(fv_ctx* c, int T, StepMode mode) {
         HIPCHK(hipGetLastError());
     }
     HIPCHK(hipEventRecord(c->ev1, st));
-    if (mode == STEP_VERIFY || mode == STEP_VERIFY_SAMPLED)
-        HIPCHK(hipMemcpyAsync(c->h_res, c->at<FvResult>(ly.off_res), sizeof(FvResult), hipMemcpyDeviceToHost, st));
-    else {
-        if (mode == STEP_PREFILL_LAST)
-            HIPCHK(hipMemcpyAsync(&c->h_res->next_token, c->at<int32_t>(ly.off_am) + (T - 1), 4, hipMemcpyDeviceToHost, st));
-        HIPCHK(hipMemcpyAsync(&c->h_res->fault, &c->at<FvResult>(ly.off_res)->fault, 4, hipMemcpyDeviceToHost, st));
-    }
+    // the result record comes back whole (3 KB), the rows' greedy choices with it: asking for those separately would be a second
+    // synchronous copy, 10 us of a step that takes 150
+    if (mode != STEP_PREFILL_MID) HIPCHK(hipMemcpyAsync(c->h_res, c->at<FvResult>(ly.off_res), sizeof(FvResult), hipMemcpyDeviceToHost, st));
+    else HIPCHK(hipMemcpyAsync(&c->h_res->fault, &c->at<FvResult>(ly.off_res)->fault, 4, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
+    if (mode == STEP_PREFILL_LAST) c->h_res->next_token = c->h_res->argmax[T - 1];
     if (c->h_res->fault) {
         if (c->scr->dirty) *c->scr->dirty = true;   // unconsumed partial tiles may be left behind
         return FV_E_EXCHANGE_TIMEOUT;

@@ -21,6 +21,7 @@ struct FvResult {
     uint32_t fault, pad2[3];   // fault: set by a GEMM whose partial-tile wait ran out (never cleared: the context is unusable then)
     int32_t path[FV_MAX_TREE];
     int32_t accepted_tokens[FV_MAX_TREE];
+    int32_t argmax[FV_MAX_TREE];   // greedy choice at every row of the step (-1: none), read back with the rest
 };
 
 enum { TILE_NAT = 0, TILE_QKV = 1, TILE_GU = 2 };   // weight re-tiling: natural row order, q|k|v with rotary pairing, gate/up interleaved
