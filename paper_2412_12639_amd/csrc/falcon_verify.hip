@@ -237,7 +237,9 @@ void make_layout(const fv_cfg& c, int n_wg, Layout& L, bool own_head, size_t min
     // attention key-split partials: at most 8 parts per (head, node block) item, items for 256 rows
     L.off_apart = take((size_t)c.n_q_heads * 8 * 8 * (d / 32 * 1024 + 64) * 4);
     L.off_atick = take((size_t)c.n_q_heads * 8 * 4);
-    if (own_head && c.dtype == FV_BF16 && c.max_seq > 256) {
+    bool ring = own_head && c.dtype == FV_BF16;
+    for (int i = 0; i < GM_COUNT; ++i) ring = ring && gemm_ring_takes(L.gm[i].NG, L.gm[i].NB);
+    if (ring && c.max_seq > 256) {
         const size_t P = L.Pm = (int)std::min(rup(c.max_seq, 256), (size_t)FV_PROMPT_ROWS);
         L.off_px = take((size_t)c.hidden * P * 4);
         L.off_pxb = take((size_t)L.gm[GM_QKV].Kpad * P * L.ESZ);
@@ -274,11 +276,11 @@ int validate_tree(const fv_cfg& c, const int32_t* tok, const int32_t* parent, co
 }
 
 template <typename EL>
-int run_step_d(fv_ctx* c, int T, StepMode mode) {
-    return c->cfg.head_dim == 128 ? run_step<EL, 128>(c, T, mode) : run_step<EL, 64>(c, T, mode);
+int run_step_d(fv_ctx* c, int T, StepMode mode, int from_prompt) {
+    return c->cfg.head_dim == 128 ? run_step<EL, 128>(c, T, mode, from_prompt) : run_step<EL, 64>(c, T, mode, from_prompt);
 }
-int run_step_any(fv_ctx* c, int T, StepMode mode) {
-    const int rc = c->cfg.dtype == FV_BF16 ? run_step_d<BF16>(c, T, mode) : run_step_d<F32>(c, T, mode);
+int run_step_any(fv_ctx* c, int T, StepMode mode, int from_prompt = -1) {
+    const int rc = c->cfg.dtype == FV_BF16 ? run_step_d<BF16>(c, T, mode, from_prompt) : run_step_d<F32>(c, T, mode, from_prompt);
     // a step that did not run to its end may leave partial tiles nobody consumed: have the area cleared before its next use
     if (rc != FV_OK && c->scr && c->scr->dirty) *c->scr->dirty = true;
     return rc;
@@ -523,16 +525,20 @@ int fv_prefill(fv_ctx* c, const int32_t* tokens, int32_t n, int32_t* next_token)
     c->prefilled = false;
     c->cur_len = 0;
     int done = 0;
+    int from_prompt = -1;                             // the last chunk's first row in the prompt buffers, if it came along
     const int tail = (n - 1) % c->cfg.max_tree + 1;   // rows of the last chunk, whose logits and activations can be read back
     if (c->lay.Pm > 0) {
         // Rows before the last chunk go through the layers up to Pm at a time.  Worth it above 256 rows and two chunks: a layer of
         // the 7B shape takes 226 us for a chunk of 256 rows, 111 for one of 64, and 430 for 512 rows at once, 830 for 1792.
         memcpy(c->h_prompt, tokens, (size_t)n * 4);
         while (n - tail - done > 256 && n - tail - done >= 2 * c->cfg.max_tree) {
-            const int m = std::min(n - tail - done, c->lay.Pm);
+            int m = std::min(n - tail - done, c->lay.Pm);
+            // The last chunk's rows come along through all layers but the last where they fit: into the padding of the 256-row tiles, or
+            // as a tile more where they are many (above 64 rows a chunk of its own costs 150 to 230 us a layer, a tile 110).
+            if (done + m == n - tail && m + tail <= c->lay.Pm && c->cfg.n_layers > 1 && (tail > 64 || rup(m, 256) == rup(m + tail, 256))) { from_prompt = m; m += tail; }
             const int rc = c->cfg.head_dim == 128 ? run_prompt<BF16, 128>(c, c->h_prompt + done, m) : run_prompt<BF16, 64>(c, c->h_prompt + done, m);
             if (rc) return rc;
-            done += m;
+            done += from_prompt >= 0 ? m - tail : m;
             c->cur_len = done;
         }
     }
@@ -545,7 +551,7 @@ int fv_prefill(fv_ctx* c, const int32_t* tokens, int32_t n, int32_t* next_token)
             c->h_in[2 * FV_MAX_TREE + i] = i;
         }
         const bool last = done + m == n;
-        int rc = run_step_any(c, m, last ? STEP_PREFILL_LAST : STEP_PREFILL_MID);
+        int rc = run_step_any(c, m, last ? STEP_PREFILL_LAST : STEP_PREFILL_MID, last ? from_prompt : -1);
         if (rc) return rc;
         done += m;
         c->cur_len = done;   // every row of a prompt chunk is kept, already in place

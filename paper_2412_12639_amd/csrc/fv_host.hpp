@@ -62,6 +62,9 @@ struct Layout {
     size_t total = 0;
 };
 
+// Whether the ring kernel (bf16, more than 64 rows) can address a matrix of NG groups of FV_R strips and NB K batches.
+inline bool gemm_ring_takes(int NG, int NB) { return (unsigned long long)NG * FV_R * NB * 8192 < (1ull << 32); }
+
 inline int pad_tokens(int n) {   // token count padded to 32, 64, 128 or 256
     int tp = 32;
     while (tp < n) tp *= 2;
@@ -206,7 +209,7 @@ int upload_tiled(fv_ctx* c, const GemmPlan& p, char* out, const void* host, size
 
 // ---- defined in fv_step.hip, instantiated once per (EL, D) pair
 // One pass of the decoder over T new rows whose tokens/parent/depth are in c->h_in.
-template <typename EL, int D> int run_step(fv_ctx* c, int T, StepMode mode);
+template <typename EL, int D> int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt);
 // m prompt rows (h_tok: pinned, untouched until the stream is waited for) behind slot cur_len: K and V into the cache, nothing else
 template <typename EL, int D> int run_prompt(fv_ctx* c, const int32_t* h_tok, int m);
 // dynamic shared memory limits of the GEMM kernels of this pair

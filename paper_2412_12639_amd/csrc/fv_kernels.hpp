@@ -86,6 +86,24 @@ static __global__ __launch_bounds__(256) void k_ingest_prompt(PromptIngestArgs a
     }
 }
 
+// The last rows of a prompt that went through the layers with the others: residual stream, GEMM input and statistics of rows
+// r0 .. r0+T-1 from the prompt's buffers (ld rows) into a step's (Tp rows; rows beyond T zero).  One workgroup per strip.
+struct SliceArgs { const float4* x; const char* xb; const float* ssq; float4* x_out; char* xb_out; float* ssq_out; int r0, T, Tp, ld; };
+template <typename EL>
+static __global__ __launch_bounds__(256) void k_prompt_slice(SliceArgs a) {
+    const int s = blockIdx.x, t = threadIdx.x;
+    if (t >= a.Tp) return;
+    const bool real = t < a.T;
+    const int r = a.r0 + (real ? t : 0);
+    const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) a.x_out[(size_t)(s * 8 + q) * a.Tp + t] = real ? a.x[(size_t)(s * 8 + q) * a.ld + r] : z4;
+    constexpr int NV = 32 / Tr<EL>::E;   // 16-byte vectors of the GEMM input per strip
+#pragma unroll
+    for (int q = 0; q < NV; ++q) ((float4*)a.xb_out)[(size_t)(s * NV + q) * a.Tp + t] = real ? ((const float4*)a.xb)[(size_t)(s * NV + q) * a.ld + r] : z4;
+    a.ssq_out[(size_t)s * a.Tp + t] = real ? a.ssq[(size_t)s * a.ld + r] : 0.f;
+}
+
 // RMSNorm factor of every row from the per-strip sums of squares, 64 rows per workgroup
 struct RinvArgs { const float* ssq; float* rinv; int n_ssq, ld; float inv_h, eps; };
 static __global__ __launch_bounds__(256) void k_rinv(RinvArgs a) {

@@ -87,13 +87,12 @@ int launch_gemm(fv_ctx* c, int Tp, const GemmArgs& ga, int kind, const StepScrat
     if (kind == GEMM_PAIRED) return Tp == 32 ? launch_gemm_paired_t<EL, 1, D, EPI>(c, ga) : launch_gemm_paired_t<EL, 2, D, EPI>(c, ga);
     if (Tp == 32) return launch_gemm_t<EL, 1, D, EPI>(c, ga);
     if (Tp == 64) return launch_gemm_t<EL, 2, D, EPI>(c, ga);
-    if constexpr (Tr<EL>::E == 8) {
-        if (Tp == 128) return launch_gemm_ring_t<4, D, EPI>(c, ga);
-        if (Tp == 256) return launch_gemm_ring_t<8, D, EPI>(c, ga);
-    } else {
-        if (Tp == 128) return launch_gemm_t<EL, 4, D, EPI>(c, ga);
-        if (Tp == 256) return launch_gemm_t<EL, 8, D, EPI>(c, ga);
+    if constexpr (Tr<EL>::E == 8) {   // the ring kernel addresses a matrix with 32-bit offsets
+        if (gemm_ring_takes(ga.NG, ga.NB) && Tp == 128) return launch_gemm_ring_t<4, D, EPI>(c, ga);
+        if (gemm_ring_takes(ga.NG, ga.NB) && Tp == 256) return launch_gemm_ring_t<8, D, EPI>(c, ga);
     }
+    if (Tp == 128) return launch_gemm_t<EL, 4, D, EPI>(c, ga);
+    if (Tp == 256) return launch_gemm_t<EL, 8, D, EPI>(c, ga);
     return FV_E_BAD_ARG;
 }
 
@@ -105,10 +104,9 @@ int set_gemm_attrs_e() {
         HIPCHK(hipFuncSetAttribute((const void*)k_gemm_ring<4, D, EPI, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem(4)));
         if constexpr (EPI != EPI_LOGITS)
             HIPCHK(hipFuncSetAttribute((const void*)k_gemm_ring<8, D, EPI, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem(8)));
-    } else {
-        HIPCHK(hipFuncSetAttribute((const void*)k_gemm<EL, 8, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 256 * 256));
-        HIPCHK(hipFuncSetAttribute((const void*)k_gemm<EL, 4, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 256));
     }
+    HIPCHK(hipFuncSetAttribute((const void*)k_gemm<EL, 8, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 256 * 256));
+    HIPCHK(hipFuncSetAttribute((const void*)k_gemm<EL, 4, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 256));
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_direct<EL, 1, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_DIRECT_SMEM_FLOATS(1) * 4));
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_direct<EL, 2, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_DIRECT_SMEM_FLOATS(2) * 4));
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_paired<EL, 1, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_PAIRED_SMEM_FLOATS(1) * 4));
@@ -183,9 +181,10 @@ static bool plan_canon_attention(const fv_ctx* c, int T, int Tp, StepMode mode, 
     return true;
 }
 
-// One pass of the decoder over T new rows whose tokens/parent/depth are in c->h_in.
+// One pass of the decoder over T new rows whose tokens/parent/depth are in c->h_in.  from_prompt >= 0: the rows are the last ones of
+// a prompt whose layers but the last have been computed with the others (run_prompt), from row from_prompt of its buffers on.
 template <typename EL, int D>
-int run_step(fv_ctx* c, int T, StepMode mode) {
+int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
     const fv_cfg& cf = c->cfg;
     const Layout& ly = c->lay;
     const int Tp = pad_tokens(T);
@@ -211,8 +210,15 @@ int run_step(fv_ctx* c, int T, StepMode mode) {
         ea.xb = c->at<void>(ly.off_xb);
         ea.ssq_part = c->at<float>(ly.off_ssq);
         ea.h = h; ea.T = T; ea.Tp = Tp;
-        const int per = 256 / Tp, n_embed = (h / 32 + per - 1) / per;
+        const int per = 256 / Tp, n_embed = from_prompt >= 0 ? 0 : (h / 32 + per - 1) / per;
         hipLaunchKernelGGL((k_begin<EL>), dim3(n_embed + Tp / 4), dim3(256), 0, st, ia, ea, n_embed);
+        if (from_prompt >= 0) {
+            SliceArgs sl;
+            sl.x = c->at<float4>(ly.off_px); sl.xb = c->at<char>(ly.off_pxb); sl.ssq = c->at<float>(ly.off_pssq);
+            sl.x_out = c->at<float4>(ly.off_x); sl.xb_out = c->at<char>(ly.off_xb); sl.ssq_out = c->at<float>(ly.off_ssq);
+            sl.r0 = from_prompt; sl.T = T; sl.Tp = Tp; sl.ld = (int)rup(from_prompt + T, 256);
+            hipLaunchKernelGGL((k_prompt_slice<EL>), dim3(h / 32), dim3(256), 0, st, sl);
+        }
     }
     HIPCHK(hipGetLastError());
 
@@ -239,7 +245,7 @@ int run_step(fv_ctx* c, int T, StepMode mode) {
     CanonArgs ca;
     const bool canon = plan_canon_attention<EL, D>(c, T, Tp, mode, ca);
 
-    for (int l = 0; l < cf.n_layers; ++l) {
+    for (int l = from_prompt >= 0 ? cf.n_layers - 1 : 0; l < cf.n_layers; ++l) {
         int rc;
         {   // q, k, v projections of the normalised input, rotary at pos = L + depth, K/V to cache slots L + i
             PhaseTimer pt(c, FV_PH_GEMM);
@@ -403,7 +409,7 @@ int read_kv_t(fv_ctx* c, int layer, int slot0, int n, float* k_out, float* v_out
 #include "fv_draft_step.hpp"
 #include "fv_prompt.hpp"
 
-template int run_step<FV_INST_EL, FV_INST_D>(fv_ctx*, int, StepMode);
+template int run_step<FV_INST_EL, FV_INST_D>(fv_ctx*, int, StepMode, int);
 template int run_prompt<FV_INST_EL, FV_INST_D>(fv_ctx*, const int32_t*, int);
 template int run_draft_pass<FV_INST_EL, FV_INST_D>(fv_drafter*, const DraftPass&);
 template int set_gemm_attrs_d<FV_INST_EL, FV_INST_D>();

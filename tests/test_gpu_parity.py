@@ -655,11 +655,12 @@ def test_small_matrix_rule(fvmod, hidden, ffn, dtype):
 
 
 @pytest.mark.parametrize("n,max_tree", [
-    (320, 32),       # 288 rows at once (two pieces, the second of 32), then the last chunk of 32
+    (320, 32),       # 288 rows at once (two pieces, the second of 32), the last chunk of 32 in their padding
     (289, 32),       # 288 and a chunk of one row
     (777, 256),      # 768 - three whole pieces - and a chunk of 9
     (513, 256),      # two chunks' worth, and one row
-    (2400, 64),      # 2048, then 288 more at once, then the last chunk
+    (700, 256),      # 512 rows and the 188 of the last chunk with them as a tile more
+    (2400, 64),      # 2048, then 288 more at once with the last chunk in their padding
 ])
 def test_long_prompt_rows_at_once(fvmod, n, max_tree):
     """Rows of a long bf16 prompt before its last chunk go through the layers together: cache, logits of the last chunk and the
