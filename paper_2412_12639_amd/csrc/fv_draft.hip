@@ -435,23 +435,16 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
         passes.push_back(ps);
     }
     if ((long long)d->L0 + next_row > cf.max_seq) return FV_E_CACHE_FULL;
-    // which nodes each pass generates (pass 0: the root block, whose outputs exist since the commit)
-    std::vector<std::vector<int>> gen_nodes(n_pass);
+    // the list row and rank every node's token is read from (the root block's lists exist since the commit)
     for (int i = 1; i < n; ++i) {
         const int dd = depth[i], p = (dd - 1) / k, j = (dd - 1) % k;
         const int a = ancestor_at(i, p * k);
         if (j >= (int)rows_of[a].size()) return FV_E_BAD_ARG;
         t_gen[i] = rows_of[a][j];
         t_rank[i] = rank[i];
-        gen_nodes[p].push_back(i);
+        t_exp[exp_at++] = i;
     }
     t_gen[0] = 0; t_rank[0] = 0;
-    std::vector<std::pair<int, int>> exp_range(n_pass);
-    for (int p = 0; p < n_pass; ++p) {
-        exp_range[p] = {exp_at, (int)gen_nodes[p].size()};
-        for (int i : gen_nodes[p]) t_exp[exp_at++] = i;
-    }
-    for (int p = 1; p < n_pass; ++p) { passes[p - 1].e0 = exp_range[p].first; passes[p - 1].n_exp = exp_range[p].second; }
 
     // ---- run: tokens stay on the device between passes
     hipStream_t st = d->core->stream;
@@ -460,16 +453,16 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
     for (bool again = false;; again = true) {
         HIPCHK(hipMemcpyAsync(d->at<int32_t>(d->lay.off_node_tok), &root_token, 4, hipMemcpyHostToDevice, st));
         HIPCHK(hipEventRecord(d->core->ev0, st));
-        if (n_pass >= 1 && exp_range[0].second > 0) {
-            ExpandArgs ea;
-            ea.tab = dev_tables(d); ea.top_tok = d->at<int32_t>(d->lay.off_top_tok); ea.node_tok = d->at<int32_t>(d->lay.off_node_tok);
-            ea.e0 = exp_range[0].first; ea.n = exp_range[0].second;
-            hipLaunchKernelGGL(k_draft_expand, dim3((ea.n + 255) / 256), dim3(256), 0, st, ea);
-            HIPCHK(hipGetLastError());
-        }
         for (const DraftPass& ps : passes) {
             rc = pass_any(d, ps);
             if (rc) return rc;
+        }
+        if (exp_at > 0) {   // every node's token (the passes read theirs from the top lists)
+            ExpandArgs ea;
+            ea.tab = dev_tables(d); ea.top_tok = d->at<int32_t>(d->lay.off_top_tok); ea.node_tok = d->at<int32_t>(d->lay.off_node_tok);
+            ea.e0 = 0; ea.n = exp_at;
+            hipLaunchKernelGGL(k_draft_expand, dim3((ea.n + 255) / 256), dim3(256), 0, st, ea);
+            HIPCHK(hipGetLastError());
         }
         HIPCHK(hipEventRecord(d->core->ev1, st));
         HIPCHK(hipMemcpyAsync(d->h_out, d->at<int32_t>(d->lay.off_node_tok), (size_t)n * 4, hipMemcpyDeviceToHost, st));

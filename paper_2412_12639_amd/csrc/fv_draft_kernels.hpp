@@ -25,7 +25,7 @@ struct DraftTables {
     const int32_t* lvl_rows;   // [256] rows of each pass grouped by LSTM level (pass-local indices)
     const int32_t* node_gen;   // [256] tree node -> output row id whose top list holds its token
     const int32_t* node_rank;  // [256] tree node -> rank in that list
-    const int32_t* exp_list;   // [256] tree nodes grouped by the pass that generates them
+    const int32_t* exp_list;   // [256] tree nodes whose token comes from a list (all but the root)
 };
 
 // ============================================================================ mask, positions, rotary table
@@ -40,9 +40,9 @@ struct DraftIngestArgs {
     float2* rope_cs;         // [Tp][half_d]
 };
 
-static __global__ __launch_bounds__(256) void k_draft_ingest(DraftIngestArgs a) {
+__device__ __forceinline__ void draft_ingest_rows(const DraftIngestArgs& a, int blk) {   // four rows
     const int tid = threadIdx.x;
-    const int t0 = blockIdx.x * 4, t1 = (t0 + 4 < a.Tp) ? t0 + 4 : a.Tp;
+    const int t0 = blk * 4, t1 = (t0 + 4 < a.Tp) ? t0 + 4 : a.Tp;
     for (int t = t0 + tid; t < t1; t += 256) {
         uint64_t m[4] = {0, 0, 0, 0};
         if (t < a.n && a.chain) {
@@ -78,17 +78,20 @@ struct DraftInArgs {
     DraftTables tab;
     const float* fout;        // [256 + KMAX][h] predicted features by output row id
     const float* ext;         // external features [..][h] (true features of committed pairs), may be null
-    const int32_t* node_tok;  // [256]
+    const int32_t* top_tok;   // [256 + KMAX][FV_DRAFT_MMAX] top lists by output row id: a node's token is entry node_rank of row node_gen's
     const void* table;        // embedding [V][h]
     void* xz;                 // [2h/E][Tp][E]
     uint32_t* chain; int chain_words;   // exchange area of the chain launches to clear (0 words: none)
     int r0, n, Tp, h, vocab;
 };
 
+// The start of a pass, input rows and ingest side by side in one launch (they do not depend on each other; a small launch is 5 us
+// with its gap): the first n_in workgroups take 256 four-feature groups each, the others four rows' masks and rotary entries.
 template <typename EL>
-static __global__ __launch_bounds__(256) void k_draft_in(DraftInArgs a) {
+static __global__ __launch_bounds__(256) void k_draft_begin(DraftInArgs a, DraftIngestArgs ia, int n_in) {
+    if ((int)blockIdx.x >= n_in) { draft_ingest_rows(ia, blockIdx.x - n_in); return; }
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    for (size_t i = idx; i < (size_t)a.chain_words; i += (size_t)gridDim.x * 256) a.chain[i] = 0u;
+    for (size_t i = idx; i < (size_t)a.chain_words; i += (size_t)n_in * 256) a.chain[i] = 0u;
     const int t = (int)(idx % a.Tp);
     const int f0 = (int)(idx / a.Tp) * 4;
     if (f0 >= 2 * a.h) return;
@@ -102,7 +105,7 @@ static __global__ __launch_bounds__(256) void k_draft_in(DraftInArgs a) {
             v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
         } else {
             const int nd = a.tab.tok_node[r];
-            int tok = (nd >= 0) ? a.node_tok[nd] : a.tab.tok_val[r];
+            int tok = (nd >= 0) ? a.top_tok[(size_t)a.tab.node_gen[nd] * FV_DRAFT_MMAX + a.tab.node_rank[nd]] : a.tab.tok_val[r];
             if (tok < 0 || tok >= a.vocab) tok = 0;   // only after a non-finite row, which fails the phase anyway
             const size_t base = (size_t)tok * a.h + (f0 - a.h);
 #pragma unroll
@@ -217,10 +220,8 @@ static __global__ __launch_bounds__(256) void k_state_keep(StateKeepArgs a) {
 // ============================================================================ outputs of a pass
 // predicted feature rows: the block's residual stream after its MLP, fp32 [256 + KMAX][h] by output row id
 struct DraftOutArgs { const float* x; float* fout; int r0, n, Tp, h; };
-static __global__ __launch_bounds__(256) void k_draft_out(DraftOutArgs a) {
-    const int t = blockIdx.x;
-    if (t >= a.n) return;
-    for (int f = threadIdx.x; f < a.h; f += 256)
+__device__ __forceinline__ void draft_out_row(const DraftOutArgs& a, int t) {
+    for (int f = threadIdx.x; f < a.h; f += blockDim.x)
         a.fout[(size_t)(a.r0 + t) * a.h + f] = a.x[((size_t)(f >> 2) * a.Tp + t) * 4 + (f & 3)];
 }
 
@@ -263,13 +264,14 @@ __device__ __forceinline__ unsigned long long topm_wave_max(unsigned long long k
     return k;
 }
 
-static __global__ __launch_bounds__(FV_TOPM_THREADS) void k_topm(TopmArgs a) {
+// (workgroups n .. 2n-1 write the predicted feature rows, which wait for nothing the top lists do)
+static __global__ __launch_bounds__(FV_TOPM_THREADS) void k_topm(TopmArgs a, DraftOutArgs oa) {
+    if ((int)blockIdx.x >= a.n) { draft_out_row(oa, blockIdx.x - a.n); return; }
     __shared__ unsigned long long wave_key[16];
     __shared__ unsigned long long cand[FV_TOPM_FAST];
     __shared__ int rank_of[FV_TOPM_FAST];
     __shared__ int n_cand, any_bad;
     const int t = blockIdx.x, tid = threadIdx.x, wave = tid >> 6;
-    if (t >= a.n) return;
     const float* row = a.logits + (size_t)t * a.Vpad;
     if (tid == 0) { n_cand = 0; any_bad = 0; }
     if (tid < FV_TOPM_FAST) rank_of[tid] = 0;

@@ -67,14 +67,14 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         DraftIngestArgs ia;
         ia.tab = tab; ia.chain = ps.commit ? 1 : 0; ia.r0 = ps.r0; ia.n = n; ia.Tp = Tp; ia.half_d = D / 2; ia.log2_base = std::log2((double)cf.rope_base);
         ia.mask = c->at<uint64_t>(ly.off_mask); ia.rope_cs = c->at<float2>(ly.off_rope);
-        hipLaunchKernelGGL(k_draft_ingest, dim3((Tp + 3) / 4), dim3(256), 0, st, ia);
         DraftInArgs da;
-        da.tab = tab; da.fout = d->at<float>(dl.off_fout); da.ext = ps.ext; da.node_tok = d->at<int32_t>(dl.off_node_tok);
+        da.tab = tab; da.fout = d->at<float>(dl.off_fout); da.ext = ps.ext; da.top_tok = d->at<int32_t>(dl.off_top_tok);
         da.table = d->target->arena + d->target->lay.off_embed; da.xz = d->at<void>(dl.off_xz);
         da.chain = d->at<uint32_t>(dl.off_chain); da.chain_words = ps.chain ? (256 + (ps.commit ? 8 : 128) * h) / 4 : 0;
         da.r0 = ps.r0; da.n = n; da.Tp = Tp; da.h = h; da.vocab = cf.vocab;
         const size_t items = (size_t)(2 * h / 4) * Tp;
-        hipLaunchKernelGGL((k_draft_in<EL>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, da);
+        const int n_in = (int)((items + 255) / 256);
+        hipLaunchKernelGGL((k_draft_begin<EL>), dim3(n_in + (Tp + 3) / 4), dim3(256), 0, st, da, ia, n_in);
         HIPCHK(hipGetLastError());
     }
 
@@ -176,11 +176,6 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         int rc = launch_gemm<EL, D, EPI_RESID>(c, Tp, ga, core_kind(GM_DN), &d->scr);
         if (rc) return rc;
     }
-    {
-        DraftOutArgs oa;
-        oa.x = c->at<float>(ly.off_x); oa.fout = d->at<float>(dl.off_fout); oa.r0 = ps.r0; oa.n = n; oa.Tp = Tp; oa.h = h;
-        hipLaunchKernelGGL(k_draft_out, dim3(n), dim3(256), 0, st, oa);
-    }
     {   // the target's LM head on the predicted features; the logits of every phase row are kept (row r at r * Vpad)
         GemmArgs ga = core_args(GM_LM, core_kind(GM_LM), d->target->arena + d->target->lay.off_lm, ly.off_xb, false);
         ga.logits = d->at<float>(dl.off_logits) + (size_t)ps.r0 * ly.Vpad; ga.Vpad = ly.Vpad;
@@ -192,12 +187,9 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         ta.logits = d->at<float>(dl.off_logits) + (size_t)ps.r0 * ly.Vpad; ta.top_tok = d->at<int32_t>(dl.off_top_tok);
         ta.top_val = d->at<float>(dl.off_top_val); ta.bad = d->at<int32_t>(dl.off_bad);
         ta.r0 = ps.r0; ta.n = n; ta.V = cf.vocab; ta.Vpad = ly.Vpad; ta.m = FV_DRAFT_MMAX;
-        hipLaunchKernelGGL(k_topm, dim3(n), dim3(FV_TOPM_THREADS), 0, st, ta);   // vocab <= 32768, checked at creation
-    }
-    if (ps.n_exp > 0) {
-        ExpandArgs ea;
-        ea.tab = tab; ea.top_tok = d->at<int32_t>(dl.off_top_tok); ea.node_tok = d->at<int32_t>(dl.off_node_tok); ea.e0 = ps.e0; ea.n = ps.n_exp;
-        hipLaunchKernelGGL(k_draft_expand, dim3((ps.n_exp + 255) / 256), dim3(256), 0, st, ea);
+        DraftOutArgs oa;
+        oa.x = c->at<float>(ly.off_x); oa.fout = d->at<float>(dl.off_fout); oa.r0 = ps.r0; oa.n = n; oa.Tp = Tp; oa.h = h;
+        hipLaunchKernelGGL(k_topm, dim3(2 * n), dim3(FV_TOPM_THREADS), 0, st, ta, oa);   // vocab <= 32768, checked at creation
     }
     HIPCHK(hipGetLastError());
     return FV_OK;

@@ -157,7 +157,6 @@ struct DraftPass {
     int r0 = 0, n = 0;
     int l0 = 0;                      // first entry of this pass in lvl_rows
     std::vector<int> lvl_n;          // rows per LSTM level
-    int e0 = 0, n_exp = 0;           // tree nodes this pass generates: exp_list[e0 .. e0+n_exp)
     const float* ext = nullptr;      // external features (device), rows addressed by feat_src = -1 - e
     bool commit = false;             // committed pairs: phase rows 0, 1, 2, ... in causal order
     bool chain = false;              // rows follow each other one by one and both LSTM layers run as chain launches (fv_lstm_chain.hpp)
