@@ -5,16 +5,22 @@
 // on the matrix cores, so both have to run at once.  The shared-activation kernel (k_gemm) keeps each strip in one
 // wavefront, so four wavefronts read the whole activation chunk from LDS (a fragment of 32 rows x 16 columns for every
 // 1 KiB of it: as many LDS cycles as matrix cycles), and stages it through registers two stages ahead.
-// Here a wavefront takes RS strips x half of the columns (RS + TB/2 KiB of LDS reads per RS * TB/2 matrix
-// instructions), nothing passes through registers, and the two rings run as far ahead as their memories need.
+// Here a wavefront takes two strips x half of the columns (2 + TB/2 KiB of LDS reads per TB matrix instructions),
+// nothing passes through registers, and the ring is filled five (256 rows) or eight (128 rows) stages ahead.  The four together still
+// take longer than the longest: 7B QKV at 256 rows, 34 us where matrix instructions alone take 18.5 (the chip's power limit: 1.39
+// PFLOP/s), the weights 17.4, activations 12, fragment reads 8.5.
 //
-// Tile: 2 * RS strips x TB * 32 columns, four wavefronts as 2 x 2.  A stage is 32 columns of K: two weight fragments of every
+// Measured (7B width, 256 rows, kernel and reduction together, k_gemm -> this): QKV 62 -> 55 us, head 104 -> 93, O and down
+// 38.5 -> 37 each, gate/up 79 -> 80 (whose reduction k_gemm had in its launch);
+// prompt products of 1792 rows 868 to 928 TFLOP/s (library 900 to 1220); as 256-row launches they ran at 350 to 500.
+//
+// Tile: four strips x TB * 32 columns, four wavefronts as 2 x 2.  A stage is 32 columns of K: two weight fragments of every
 // strip (1 KiB each, as tiled in memory) and four 16-byte vectors of every column.  One barrier per stage, in its
 // middle: the second half of a stage multiplies while the first fragments of the next one are read, and the slot that
 // everybody has left by then is filled again.
 //
-// WIDE = false: up to 256 rows, one block of columns; the (row group, K batch) space is cut into G equal ranges exactly as for
-// k_gemm, partial tiles are stored and k_gemm_fix, launched behind, reduces them.
+// WIDE = false: up to 256 rows, one block of columns; the (row group, K batch) space is cut into G ranges as for k_gemm,
+// partial tiles are stored and k_gemm_fix, launched behind, reduces them.
 // WIDE = true: more rows (a prompt): one workgroup per tile over the whole K range, column tiles of 256.
 #pragma once
 // (included from fv_kernels.hpp after k_gemm_fix)
