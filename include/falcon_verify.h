@@ -132,7 +132,8 @@ int fv_init_weights(fv_ctx* ctx, const fv_host_weights* host_weights);
 /* Run a prompt of n >= 1 host tokens, fill cache slots 0..n-1, and return the target's
  * greedy next token in *next_token (host).  Resets the context state: L = n, pending
  * root = *next_token.  The prompt goes through the same kernels as verification, in
- * chain-shaped chunks of at most max_tree tokens. */
+ * chain-shaped chunks of at most max_tree tokens; bf16: the rows of a long prompt before its last chunk
+ * go through the layers together.  The read-back calls below see the last chunk either way. */
 int fv_prefill(fv_ctx* ctx, const int32_t* host_tokens, int32_t n, int32_t* next_token);
 
 /* One tree-verification step (the operation described at the top).  Inputs are host
