@@ -47,7 +47,7 @@ int run_prompt(fv_ctx* c, const int32_t* h_tok, int m) {
             HIPCHK(hipGetLastError());
             return FV_OK;
         };
-        auto grid = [&](const GemmArgs& ga) { return dim3((unsigned)((ga.NG + 7) / 8 * 8 * (ld / 256))); };
+        auto grid = [&](const GemmArgs& ga) { return dim3(8u * (unsigned)std::min((ga.NG + 7) / 8 * (ld / 256), 32)); };   // one workgroup per compute unit at most
         for (int l = 0; l < cf.n_layers; ++l) {
             int rc = rinv();
             if (rc) return rc;
@@ -56,7 +56,7 @@ int run_prompt(fv_ctx* c, const int32_t* h_tok, int m) {
                 GemmArgs ga = args(GM_QKV, c->layer_w(l, 0), ly.off_pxb);
                 ga.q_out = c->at<void>(ly.off_pq); ga.q_lo_out = c->at<void>(ly.off_pqlo); ga.kcache = c->kc(l); ga.vcache = c->vc(l);
                 ga.rope_cs = c->at<float2>(ly.off_prope); ga.Hq = cf.n_q_heads; ga.Hkv = cf.n_kv_heads; ga.L = L; ga.S_pad = ly.S_pad;
-                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_QKV, true>), grid(ga), dim3(256), ring_smem(8), st, ga);
+                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_QKV, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
                 HIPCHK(hipGetLastError());
             }
             if (l + 1 == cf.n_layers) break;   // nothing reads the last layer's rows: their K and V are what is wanted
@@ -75,7 +75,7 @@ int run_prompt(fv_ctx* c, const int32_t* h_tok, int m) {
                 PhaseTimer pt(c, FV_PH_GEMM);
                 GemmArgs ga = args(GM_O, c->layer_w(l, 1), ly.off_pattn);
                 ga.x_in = ga.x = c->at<float>(ly.off_px); ga.xb = c->at<void>(ly.off_pxb); ga.gain_next = c->gain(2 * l + 1); ga.ssq_out = c->at<float>(ly.off_pssq);
-                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_RESID, true>), grid(ga), dim3(256), ring_smem(8), st, ga);
+                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_RESID, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
                 HIPCHK(hipGetLastError());
             }
             rc = rinv();
@@ -84,14 +84,14 @@ int run_prompt(fv_ctx* c, const int32_t* h_tok, int m) {
                 PhaseTimer pt(c, FV_PH_GEMM);
                 GemmArgs ga = args(GM_GU, c->layer_w(l, 2), ly.off_pxb);
                 ga.act = c->at<void>(ly.off_pact);
-                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_SWIGLU, true>), grid(ga), dim3(256), ring_smem(8), st, ga);
+                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_SWIGLU, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
                 HIPCHK(hipGetLastError());
             }
             {
                 PhaseTimer pt(c, FV_PH_GEMM);
                 GemmArgs ga = args(GM_DN, c->layer_w(l, 3), ly.off_pact);
                 ga.x_in = ga.x = c->at<float>(ly.off_px); ga.xb = c->at<void>(ly.off_pxb); ga.gain_next = c->gain(2 * (l + 1)); ga.ssq_out = c->at<float>(ly.off_pssq);
-                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_RESID, true>), grid(ga), dim3(256), ring_smem(8), st, ga);
+                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_RESID, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
                 HIPCHK(hipGetLastError());
             }
         }

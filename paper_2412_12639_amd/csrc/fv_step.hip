@@ -56,7 +56,7 @@ int launch_gemm_paired_t(fv_ctx* c, const GemmArgs& ga) {
 // one last arriver would pull through its compute unit.
 template <int TB, int D, int EPI>
 int launch_gemm_ring_t(fv_ctx* c, const GemmArgs& ga) {
-    hipLaunchKernelGGL((k_gemm_ring<TB, D, EPI, false>), dim3(ga.G), dim3(256), ring_smem(TB), c->stream, ga);
+    hipLaunchKernelGGL((k_gemm_ring<TB, D, EPI, false>), dim3(ga.G), dim3(FV_RING_THREADS), ring_smem(TB), c->stream, ga);
     if (hipGetLastError() != hipSuccess) return FV_E_HIP;
     if (ga.n_fix > 0) {
         const int tiles = ga.n_fix * FV_R * TB;

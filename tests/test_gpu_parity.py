@@ -693,6 +693,17 @@ def test_long_prompt_of_one_layer(fvmod, n, max_tree):
     test_long_prompt_rows_at_once(fvmod, n, max_tree, "tiny-bf16")
 
 
+@pytest.mark.parametrize("hidden,n", [
+    (128, 1500),     # a K range of four stages (fewer than the ring holds), six column tiles, up to four tiles a workgroup
+    (256, 700),      # three column tiles: a workgroup's tiles lie in different columns
+])
+def test_long_prompt_of_several_tiles_a_workgroup(fvmod, hidden, n):
+    """Products with more tiles than compute units: gate and up of a wide FFN (513 strips, a ragged last row group)."""
+    s = ModelShape(f"wide-{hidden}", 2, hidden, hidden // 64, hidden // 64, 64, 8208, 600, "bf16")
+    SHAPES[s.name], _W[s.name] = s, fi.gen_weights(s, seed=hidden, gain_jitter=0.1)
+    test_long_prompt_rows_at_once(fvmod, n, 64, s.name)
+
+
 @pytest.mark.parametrize("n,max_tree", [
     (704, 64),       # the last chunk along with the others
     (544, 256),      # 512 rows at once, then a chunk of 32 rows, where the long prompt's last chunk had 232
