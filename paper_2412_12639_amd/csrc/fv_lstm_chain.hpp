@@ -4,10 +4,11 @@
 // What bounds it.  A chain is serial: row t needs the hidden state of row t - 1.  As separate launches (gather, weight
 // multiplication, cell) every row streams the whole 4h x h matrix again: 134 MB and 33 us per row and layer at hidden
 // 4096, of which 23 us are the stream.  That matrix is 512 KiB per compute unit, and a compute unit has 512 KiB of
-// vector registers and 160 KiB of LDS: each wavefront keeps 96 of its 128 fragments in registers and 32 in LDS, the
-// matrix is read once per launch, and a row costs what the exchange of the hidden state and 128 matrix instructions per
-// wavefront cost.
-// Measured at hidden 4096: 64 rows 243 us per layer (29 us to read the matrix, 3.4 us a row) against 2100; 4 rows 42 against 130.
+// vector registers and 160 KiB of LDS: each wavefront keeps three quarters of its share in registers and one in LDS, the
+// matrix is read once per launch, and a row costs what the exchange of the hidden state (0.7 us), 64 matrix instructions per
+// wavefront (0.7), the sum over the wavefronts (0.1) and the cell (0.4) cost.
+// Measured at hidden 4096: 256 rows 510 us per layer (29 us to read the matrix, 1.9 us a row; before the sparse form of the matrix
+// instruction, the barrier in front of the looks and the short cell 880, 3.34 a row) against 8400; 4 rows 33 against 130.
 //
 // Split: workgroup w owns hidden units 16w .. 16w+15 with their four gates (four 16-row blocks); its four wavefronts
 // take a quarter of the K range each, so a wavefront needs only a quarter of the previous hidden state.  The sums of the
@@ -56,13 +57,57 @@ constexpr size_t lstm_chain_smem(int nkf) {
     return ((size_t)4 * (nkf - lstm_chain_reg_frags(nkf)) * 4 * 64 + (size_t)4 * nkf * 4) * 16 + 2 * 4 * 4 * 16 * 4 + 16;
 }
 
+// Sigmoid, or tanh, of a gate: both from e^-|a| (a = x or 2x) and one quotient, without a branch between the lanes of different gates
+// (the library's functions, of which every lane ran both, took two thirds of the cell's 0.63 us).  Small tanh by its series, where 1 - e
+// cancels.  Largest error against 64 bits over 1e-6 .. 100: sigmoid 0.50e-7 (the library's 0.89e-7), tanh 0.85e-7 (0.78e-7).
+__device__ __forceinline__ float lstm_gate(float x, bool th) {
+    const float ax = fabsf(x), a = th ? 2.f * ax : ax;
+    const float L = -1.44269504f, hi = a * L, lo = fmaf(a, L, -hi) + a * -1.92596299e-8f;   // -a log2(e) in two parts
+    const float e0 = __builtin_amdgcn_exp2f(hi), e = a < 100.f ? fmaf(e0, lo * 0.693147181f, e0) : 0.f;
+    const float d = 1.f + e, d_lo = e - (d - 1.f);
+    const float num = th ? 2.f * e : (x >= 0.f ? 1.f : e);
+    const float r0 = __builtin_amdgcn_rcpf(d);
+    float r = num * r0;
+    r = fmaf(r0, fmaf(-d_lo, r, fmaf(-d, r, num)), r);
+    if (th) {
+        r = 1.f - r;
+        const float x2 = x * x;
+        float t = fmaf(x2, -929569.f / 638512875.f, 21844.f / 6081075.f);
+        t = fmaf(x2, t, -1382.f / 155925.f);
+        t = fmaf(x2, t, 62.f / 2835.f);
+        t = fmaf(x2, t, -17.f / 315.f);
+        t = fmaf(x2, t, 2.f / 15.f);
+        t = fmaf(x2, t, -1.f / 3.f);
+        r = ax < 0.5f ? fmaf(x, x2 * t, x) : copysignf(r, x);
+    }
+    return x == x ? r : x;
+}
+
+// acc += a (two of every four columns) * w, the weights in accumulation registers or in vector registers.  Written out, because the compiler's
+// form copies weights that live in accumulation registers to others before each use (eight moves an instruction, as long as two of
+// them).  It does not see that this is a matrix instruction: chain_mma_done() goes between the last of a row of them and the first use of acc.
+typedef float chain_f4 __attribute__((ext_vector_type(4)));
+typedef unsigned int chain_u4 __attribute__((ext_vector_type(4)));
+typedef unsigned int chain_u8 __attribute__((ext_vector_type(8)));
+template <bool ACC_REGS>
+__device__ __forceinline__ void chain_mma(chain_f4& acc, const chain_u4& a, const chain_u8& w, int pick) {
+    if constexpr (ACC_REGS) asm volatile("v_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "a"(w), "v"(pick));
+    else asm volatile("v_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "v"(w), "v"(pick));
+}
+__device__ __forceinline__ void chain_mma_done(chain_f4 (&acc)[4]) {
+    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
+}
+
 template <int NKF>
 static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
     typedef float floatx4 __attribute__((ext_vector_type(4)));
     typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-    constexpr int RKF = lstm_chain_reg_frags(NKF), LKF = NKF - RKF;
-    constexpr int GF = NKF < 4 ? NKF : 4;
-    static_assert(NKF % GF == 0 && (LKF == 0 || LKF == NKF / 4), "whole groups");
+    typedef unsigned int u32x8_t __attribute__((ext_vector_type(8)));
+    typedef __bf16 bf16x16_t __attribute__((ext_vector_type(16)));
+    constexpr int NM = NKF / 2, RM = lstm_chain_reg_frags(NKF) / 2, LM = NM - RM;   // 64-column instructions per gate; with their weights in registers, in LDS
+    constexpr int GM = NM < 4 ? NM : 4;
+    constexpr int PIN = RM * 4 < 30 ? 0 : 30;   // weights in accumulation registers
+    static_assert(NM % GM == 0 && (LM == 0 || LM == NM / 4), "whole groups");
     constexpr int NV = (4 * NKF + 63) / 64;        // 16-byte pieces of the hidden state per lane
     constexpr int SC1 = 16;
     constexpr unsigned LEAVE = 0x80000000u, TAG = 0x40004000u;
@@ -72,9 +117,9 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
     const int u = lane & 15, q = lane >> 4;
     const int wg = blockIdx.x, h = a.h;
     const int kf_real = h >> 7, quarter = h >> 2;
-    uint4* const wl = lds_chain + (size_t)wave * LKF * 4 * 64 + lane;                       // [LKF][4 gates][64 lanes] of this wavefront
-    uint4* const hs = lds_chain + (size_t)4 * LKF * 4 * 64 + (size_t)wave * NKF * 4;        // its quarter of the hidden state
-    float* const part = (float*)(lds_chain + (size_t)4 * LKF * 4 * 64 + (size_t)4 * NKF * 4);   // [2][4 wavefronts][4 gates][16]
+    uint4* const wl = lds_chain + (size_t)wave * LM * 8 * 64 + lane;                       // [LM][4 gates][2 halves][64 lanes] of this wavefront
+    uint4* const hs = lds_chain + (size_t)4 * LM * 8 * 64 + (size_t)wave * NKF * 4;        // its quarter of the hidden state
+    float* const part = (float*)(lds_chain + (size_t)4 * LM * 8 * 64 + (size_t)4 * NKF * 4);   // [2][4 wavefronts][4 gates][16]
     unsigned* const go = (unsigned*)(part + 2 * 4 * 4 * 16);
 
     if (tid == 0) __hip_atomic_fetch_add(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -88,26 +133,44 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
         const uint4* p = a.Wt + ((((size_t)(strip >> 1) * n_half + (F >> 2)) * 2 + (strip & 1)) * 4 + (F & 3)) * 64 + (wg & 1) * 16 + u + 32 * (q & 1);
         return kf < kf_real ? p : a.zeros + lane;
     };
-    u32x4_t w[RKF][4];   // fragments in K order; with some of them in LDS every fourth is there
+    u32x8_t w[RM][4];   // in K order; with some of them in LDS every fourth is there
 #pragma unroll
-    for (int i = 0; i < RKF; ++i)
+    for (int i = 0; i < RM; ++i)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) w[i][g] = *(const u32x4_t*)w_addr(g, LKF > 0 ? i / 3 * 4 + i % 3 : i);
+        for (int g = 0; g < 4; ++g) {
+            const int m = LM > 0 ? i / 3 * 4 + i % 3 : i;
+            const uint4 lo = *w_addr(g, 2 * m), hi = *w_addr(g, 2 * m + 1);
+            w[i][g] = u32x8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        }
     // The matrix instructions take their operand from the accumulation registers as well, but the compiler, left alone, parks
     // values there and copies them back before each use; said once that a value lives there, it uses it in place.
 #pragma unroll
-    for (int i = 0; i < RKF; ++i)
+    for (int i = 0; i < RM; ++i)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            if (i * 4 + g < RKF * 4 - 36) asm volatile("" : "+a"(w[i][g]));
-    for (int i = 0; i < LKF; ++i) {
-        uint4 v[4];
+            if (i * 4 + g < PIN) asm volatile("" : "+a"(w[i][g]));
+    for (int i = 0; i < LM; ++i) {
+        uint4 v[4][2];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) v[g] = *w_addr(g, 4 * i + 3);
+        for (int g = 0; g < 4; ++g)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) wl[(i * 4 + g) * 64] = v[g];
+            for (int e = 0; e < 2; ++e) v[g][e] = *w_addr(g, 2 * (4 * i + 3) + e);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) wl[((i * 4 + g) * 2 + e) * 64] = v[g][e];
     }
 
+    // The hidden state as the sparse operand.  A matrix instruction has sixteen columns for it and a chain one row, but the instruction for
+    // matrices with two values in every four takes twice the K range in the same time; so even rows of the operand hold values 0 and 1 of
+    // every four, odd rows values 2 and 3, and the result is the sum of an even and an odd row.  16 columns of K: 16 bytes for the even
+    // rows, 16 for the odd ones.
+    auto put_state = [&](int vec, uint4 v) {   // 8 values
+        uint2* const p = (uint2*)hs + (vec >> 1) * 4 + (vec & 1);
+        p[0] = make_uint2(v.x, v.z);
+        p[2] = make_uint2(v.y, v.w);
+    };
+    const int pick = (u & 1) ? (int)0xEEEEEEEE : 0x44444444;   // which two of every four this lane's row has
     // the state the chain continues
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
@@ -119,7 +182,7 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
                 const float4 x0 = sp[0], x1 = sp[1];
                 f[0] = x0.x; f[1] = x0.y; f[2] = x0.z; f[3] = x0.w; f[4] = x1.x; f[5] = x1.y; f[6] = x1.z; f[7] = x1.w;
             }
-            hs[vec] = Tr<BF16>::pack(f);
+            put_state(vec, Tr<BF16>::pack(f));
         }
     }
     // wavefront 0: lane (q, u) owns gate q of unit u; every lane of a unit keeps the same cell state
@@ -158,7 +221,22 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
     for (int s = 0; s < a.n; ++s) {
         const float gin_now = gin;
         if (s + 1 < a.n) gin = gin_p[(size_t)(s + 1) * 4 * h];
+        u32x8_t wb[4];
+        auto fetch_w = [&](int gr) {
+            if constexpr (LM > 0) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const uint4 lo = wl[((gr * 4 + g) * 2) * 64], hi = wl[((gr * 4 + g) * 2 + 1) * 64];
+                    wb[g] = u32x8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                }
+            }
+        };
+        fetch_w(0);    // the first group's, while the state is waited for
+        __builtin_amdgcn_sched_barrier(0);
         if (s > 0) {   // this wavefront's quarter of the state of step s - 1
+            // Nobody looks for the others' values before this workgroup's own are out: the looks of three wavefronts that have nothing
+            // else to do (8 KiB a workgroup and look, past the caches) held up everybody's stores (a row 2.57 -> 1.90 us).
+            __builtin_amdgcn_s_barrier();
             const unsigned ph = (((s - 1) >> 1) & 1) ? 0u : TAG;
             u32x4_t v[NV];
             for (unsigned looks = 0;; ++looks) {
@@ -185,42 +263,44 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
             };
 #pragma unroll
             for (int j = 0; j < NV; ++j)
-                if (lane + 64 * j < 4 * kf_real) hs[lane + 64 * j] = make_uint4(plain(v[j].x), plain(v[j].y), plain(v[j].z), plain(v[j].w));
+                if (lane + 64 * j < 4 * kf_real) put_state(lane + 64 * j, make_uint4(plain(v[j].x), plain(v[j].y), plain(v[j].z), plain(v[j].w)));
         }
         __builtin_amdgcn_wave_barrier();   // hs belongs to this wavefront: LDS accesses of one wavefront stay in order
         floatx4 acc[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-        // groups of GF fragments; the LDS reads of a group are out while the group before it multiplies
-        u32x4_t b[2][GF], wb[2][4];
-        auto fetch = [&](int gr, u32x4_t (&bd)[GF], u32x4_t (&wd)[4]) {
+        asm volatile("s_nop 1" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
+        // groups of GM instructions a gate; the state of a group is read from LDS while the group before it multiplies, the weights of its
+        // last instructions while its first ones do
+        u32x4_t b[2][GM];
+        auto fetch = [&](int gr, u32x4_t (&bd)[GM]) {
 #pragma unroll
-            for (int j = 0; j < GF; ++j) bd[j] = *(const u32x4_t*)&hs[(gr * GF + j) * 4 + q];   // the same column in all sixteen
-            if constexpr (LKF > 0) {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) wd[g] = *(const u32x4_t*)&wl[(gr * 4 + g) * 64];
-            }
+            for (int j = 0; j < GM; ++j) bd[j] = *(const u32x4_t*)&hs[((gr * GM + j) * 4 + q) * 2 + (u & 1)];
         };
-        fetch(0, b[0], wb[0]);
+        fetch(0, b[0]);
 #pragma unroll
-        for (int gr = 0; gr < NKF / GF; ++gr) {
-            if (gr + 1 < NKF / GF) fetch(gr + 1, b[(gr + 1) & 1], wb[(gr + 1) & 1]);
+        for (int gr = 0; gr < NM / GM; ++gr) {
+            if (gr > 0) fetch_w(gr);
+            if (gr + 1 < NM / GM) fetch(gr + 1, b[(gr + 1) & 1]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < GF; ++j)
+            for (int j = 0; j < GM; ++j)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const u32x4_t wv = (LKF > 0 && j == 3) ? wb[gr & 1][g] : w[LKF > 0 ? (gr * 3 + j) % RKF : gr * GF + j][g];
-                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv), __builtin_bit_cast(bf16x8_t, b[gr & 1][j]), acc[g], 0, 0, 0);
+                    if (LM > 0 && j == 3) { chain_mma<false>(acc[g], b[gr & 1][j], wb[g], pick); continue; }
+                    const int i = LM > 0 ? (gr * 3 + j) % RM : gr * GM + j;
+                    if (i * 4 + g < PIN) chain_mma<true>(acc[g], b[gr & 1][j], w[i][g], pick);
+                    else chain_mma<false>(acc[g], b[gr & 1][j], w[i][g], pick);
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_wave_barrier();
-        // lane (q, any column): rows 4q .. 4q+3 of every gate block
+        chain_mma_done(acc);
+        // every lane has an even and an odd row of each gate, for unit u: lane (q, u) hands on gate q
         float* const ps = part + (s & 1) * (4 * 4 * 16);
-        if (u == 0) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) *(floatx4*)(ps + (wave * 4 + g) * 16 + 4 * q) = acc[g];
+        {
+            const float s0 = acc[0][0] + acc[0][1], s1 = acc[1][0] + acc[1][1], s2 = acc[2][0] + acc[2][1], s3 = acc[3][0] + acc[3][1];
+            ps[wave * 64 + lane] = q == 0 ? s0 : q == 1 ? s1 : q == 2 ? s2 : s3;
         }
         __syncthreads();   // part[s & 1] is next written after the barrier of step s + 1, which wavefront 0 reaches when it has read it
         if (wave == 0) {
@@ -228,12 +308,12 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
 #pragma unroll
             for (int w_ = 1; w_ < 4; ++w_) g_rec += ps[(w_ * 4 + q) * 16 + u];
             const float pre = gin_now + g_rec + bias;
-            const float act = (q == 2) ? tanhf(pre) : fv_sigmoid(pre);
+            const float act = lstm_gate(pre, q == 2);
             const float gi = __shfl(act, u), gf = __shfl(act, 16 + u), gg = __shfl(act, 32 + u), go_ = __shfl(act, 48 + u);
             c = gf * c + gi * gg;
-            const float hn = go_ * tanhf(c);
+            const float hn = go_ * lstm_gate(c, true);
             const __bf16 hb = (__bf16)hn;
-            const unsigned mine = __builtin_bit_cast(uint16_t, hb), other = (unsigned)__shfl_xor((int)mine, 1);
+            const unsigned mine = __builtin_bit_cast(uint16_t, hb), other = (unsigned)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xF, 0xF, false);   // the neighbour's
             const unsigned pair = mine | (other << 16);   // even lanes: units u, u + 1
             const bool packs = q == 0 && (u & 1) == 0;
             if (packs && s + 1 < a.n)
@@ -424,8 +504,8 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_levels(LstmLevelArgs la)
             for (int w_ = 1; w_ < 4; ++w_) v += part[((w_ * 4 + g) * 16 + cc) * 16 + cu];
             pre[g] = v + gin[g];
         }
-        const float cn = fv_sigmoid(pre[1]) * cp + fv_sigmoid(pre[0]) * tanhf(pre[2]);
-        const float hn = fv_sigmoid(pre[3]) * tanhf(cn);
+        const float cn = lstm_gate(pre[1], false) * cp + lstm_gate(pre[0], false) * lstm_gate(pre[2], true);
+        const float hn = lstm_gate(pre[3], false) * lstm_gate(cn, true);
         const __bf16 hb = (__bf16)hn;
         const unsigned mine = __builtin_bit_cast(uint16_t, hb), other = (unsigned)__shfl_xor((int)mine, 1);
         const unsigned pair = mine | (other << 16);   // even threads: units cu, cu + 1
