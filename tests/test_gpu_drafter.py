@@ -417,6 +417,36 @@ def test_long_bf16_commit_in_wide_pieces():
     tgt.close()
 
 
+@pytest.mark.parametrize("n,k", [
+    (68, 4),     # four rows stay open: the piece before them leaves only states, K and V
+    (67, 4),     # three: the first level of the tree comes from the last row of that piece, which is computed in full
+    (325, 5),    # three pieces, the open one just long enough
+])
+def test_tree_behind_a_commit_in_pieces(n, k):
+    """The tree drafted behind a long commit, at the number of open rows where the piece before stops being read."""
+    import torch
+    s, lw, dw, tgt, dr = _make("tiny-bf16", k, max_seq=400)
+    orc = do.DrafterOracle(s, lw, dw, k, 400)
+    feats = gen_features(n, n, s.hidden)
+    toks = np.random.default_rng(n).integers(0, s.vocab, n)
+    dr.commit(toks, torch.from_numpy(feats).cuda())
+    orc.commit(feats, toks)
+    tail = (n - 1) % 64 + 1
+    assert dr.state() == (n, tail, tail)
+    f_ref, l_ref = np.array(orc.phase["f"]), np.array(orc.phase["logits"])
+    assert _rel(dr.rows("features", 0, tail), f_ref[-tail:]) <= 2e-2 and _rel(dr.rows("logits", 0, tail), l_ref[-tail:]) <= 2e-2
+    kd, vd = dr.read_kv(0, n)
+    assert _rel(kd, orc.K[:n]) <= 2e-2 and _rel(vd, orc.V[:n]) <= 2e-2
+    parent, depth, _ = gen_tree(31, 40, [4, 3, 2, 2, 1, 1], 6)
+    rank = sibling_ranks(parent)
+    got = dr.draft_tree(parent, depth, rank, int(toks[-1]))
+    ref = orc.draft(parent, depth, rank, int(toks[-1]), force_tokens=got)
+    first = [i for i in range(len(parent)) if depth[i] <= k]     # what the committed rows' lists give
+    assert sum(got[i] != ref[i] for i in first) <= 1             # a near-tie at most
+    dr.close()
+    tgt.close()
+
+
 def test_reset_after_a_commit_that_was_no_numbers():
     """200 pairs with a NaN among them leave NaNs in the cache and, 256 rows wide, in the block's activations, where the padding of its
     FFN's K range (688 to 768) lies for 64 and 32 rows.  After a reset the drafter is bitwise a new one: a commit, a tree behind it."""
