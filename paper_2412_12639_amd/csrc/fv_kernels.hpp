@@ -843,11 +843,12 @@ struct AttnArgs {
 #define FV_ATTN_SMEM_FLOATS(D) (3 * ((D) / 32) * 64 * 16 + 8 * 32 + 4)
 #define FV_ATTN_PART_FLOATS(D) (((D) / 32) * 1024 + 64)
 
-// One (query head, block of 32 nodes) item, key part `part` of a.ks.  AHEAD: the next block's tiles are requested before the
-// current ones are used, in two register sets (with one wavefront per SIMD nothing else hides a block's trip to memory).  The loop's
-// body is in the code twice then, and ranges of a few blocks per wavefront lose to that what they gain (1 % of a step at 1 to 4 blocks);
+// One (query head, block of 32 nodes) item, key part `part` of a.ks.  SHARE: two workgroups of this form fit a compute unit, so that
+// one wavefront of a SIMD is at its softmax or waits for K and V while the other multiplies.  For that q, the same in all four
+// wavefronts, lies in LDS (64 registers less), scores are kept in units of log2 (one multiply-add and the exponential a score), and a
+// block every node sees goes without the tests.  Over ranges of a few blocks a wavefront it loses what the way through LDS costs;
 // launch_attn has the rule and the figures.
-template <typename EL, int D, bool AHEAD>
+template <typename EL, int D, bool SHARE>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part, float* smem) {
     constexpr int E = Tr<EL>::E;
     constexpr int NF = D / (2 * E);      // K frags per key block
@@ -861,13 +862,26 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
     const int t = tb * 32 + tl;
 
     constexpr bool SPLIT = (E == 8);   // bf16: q and the probabilities enter the matrix cores as hi + lo pairs
-    uint4 qf[NF], qfl[SPLIT ? NF : 1];
+    constexpr int NQF = SHARE ? 1 : NF;
+    uint4 qf[NQF], qfl[SPLIT ? NQF : 1];
+    uint4* const q_lds = (uint4*)(smem + FV_ATTN_SMEM_FLOATS(D)) + lane;   // SHARE: [fragment][hi, lo][64 lanes]
+    auto q_at = [&](const uint4* q, int fr) { return q[((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t]; };
+    if constexpr (SHARE) {
+        for (int fr = wave; fr < NF; fr += 4) {
+            q_lds[(2 * fr) * 64] = q_at(a.q, fr);
+            if constexpr (SPLIT) q_lds[(2 * fr + 1) * 64] = q_at(a.q_lo, fr);
+        }
+        __syncthreads();
+    } else {
 #pragma unroll
-    for (int fr = 0; fr < NF; ++fr) qf[fr] = a.q[((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t];
-    if constexpr (SPLIT) {
+        for (int fr = 0; fr < NQF; ++fr) qf[fr] = q_at(a.q, fr);
+        if constexpr (SPLIT) {
 #pragma unroll
-        for (int fr = 0; fr < NF; ++fr) qfl[fr] = a.q_lo[((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t];
+            for (int fr = 0; fr < NQF; ++fr) qfl[fr] = q_at(a.q_lo, fr);
+        }
     }
+    const float scale2 = a.scale * 1.44269504f;   // SHARE
+    auto ex = [](float x) { return SHARE ? __builtin_amdgcn_exp2f(x) : __expf(x); };   // of differences of maxima
     uint64_t mk[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) mk[w] = (t < a.T) ? a.mask[t * 4 + w] : 0ull;
@@ -903,13 +917,36 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         floatx16 s, s1;
 #pragma unroll
         for (int i = 0; i < 16; ++i) { s[i] = 0.f; s1[i] = 0.f; }
+        if constexpr (SHARE) {
+            uint4 qb[2][4];   // a pair of fragments, hi and lo, read while the pair before multiplies
+            auto read_q = [&](int fr, uint4 (&d)[4]) {
 #pragma unroll
-        for (int fr = 0; fr < NF; fr += 2) {
-            s = Tr<EL>::mma(kt[fr], qf[fr], s);
-            s1 = Tr<EL>::mma(kt[fr + 1], qf[fr + 1], s1);
-            if constexpr (SPLIT) {
-                s = Tr<EL>::mma(kt[fr], qfl[fr], s);
-                s1 = Tr<EL>::mma(kt[fr + 1], qfl[fr + 1], s1);
+                for (int k = 0; k < 4; ++k) if (SPLIT || !(k & 1)) d[k] = q_lds[(2 * fr + k) * 64];
+            };
+            read_q(0, qb[0]);
+#pragma unroll
+            for (int fr = 0; fr < NF; fr += 2) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (fr + 2 < NF) read_q(fr + 2, qb[(fr / 2 + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                const uint4 (&d)[4] = qb[(fr / 2) & 1];
+                s = Tr<EL>::mma(kt[fr], d[0], s);
+                s1 = Tr<EL>::mma(kt[fr + 1], d[2], s1);
+                if constexpr (SPLIT) {
+                    s = Tr<EL>::mma(kt[fr], d[1], s);
+                    s1 = Tr<EL>::mma(kt[fr + 1], d[3], s1);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+#pragma unroll
+            for (int fr = 0; fr < NF; fr += 2) {
+                s = Tr<EL>::mma(kt[fr], qf[fr % NQF], s);
+                s1 = Tr<EL>::mma(kt[fr + 1], qf[(fr + 1) % NQF], s1);
+                if constexpr (SPLIT) {
+                    s = Tr<EL>::mma(kt[fr], qfl[fr % NQF], s);
+                    s1 = Tr<EL>::mma(kt[fr + 1], qfl[(fr + 1) % NQF], s1);
+                }
             }
         }
 #pragma unroll
@@ -936,12 +973,18 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         }
         float p[16];
         float mx = -1e30f;
+        auto seen = [&](int i) { return ((vbits >> (8 * (i >> 2) + (i & 3))) & 1u) != 0u; };   // key 8*(i/4) + 4*g + i%4 of the block
+        if (SHARE && n0 <= -32) {   // keys every node sees
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const bool vis = (vbits >> (8 * (i >> 2) + (i & 3))) & 1u;   // key 8*(i/4) + 4*g + i%4 of the block
-            p[i] = vis ? s[i] * a.scale : -1e30f;
-            mx = fmaxf(mx, p[i]);
+            for (int i = 0; i < 16; ++i) { p[i] = s[i]; mx = fmaxf(mx, p[i]); }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                p[i] = seen(i) ? (SHARE ? s[i] : s[i] * a.scale) : -1e30f;
+                mx = fmaxf(mx, p[i]);
+            }
         }
+        if constexpr (SHARE) mx *= scale2;
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         // Lazy rescale: the running reference m_run only has to be near the running maximum, not equal
         // to it -- exp(score - m_run) stays below e^8 as long as no row's maximum has grown by more than
@@ -949,8 +992,8 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         // accumulators (64 registers, a read-multiply-write each) are rescaled only when some row of the
         // wavefront crosses that bound; after the first blocks of a long key range that is rare.
         const float m_cand = fmaxf(m_run, mx);
-        if (__any(m_cand - m_run > 8.f)) {
-            const float alpha = __expf(m_run - m_cand);
+        if (__any(m_cand - m_run > (SHARE ? 11.5f : 8.f))) {
+            const float alpha = ex(m_run - m_cand);
             l_run *= alpha;
             m_run = m_cand;
 #pragma unroll
@@ -959,10 +1002,15 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
                 for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
         }
         float psum = 0.f;
+        if (SHARE && n0 <= -32) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            p[i] = (p[i] > -1e29f) ? __expf(p[i] - m_run) : 0.f;
-            psum += p[i];
+            for (int i = 0; i < 16; ++i) { p[i] = fmaxf(__builtin_amdgcn_exp2f(fmaf(p[i], scale2, -m_run)), 0.f); psum += p[i]; }   // a score that is no number counts for nothing, as below
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                p[i] = (p[i] > -1e29f) ? (SHARE ? __builtin_amdgcn_exp2f(fmaf(p[i], scale2, -m_run)) : __expf(p[i] - m_run)) : 0.f;
+                psum += p[i];
+            }
         }
         l_run += psum;
         uint4 pb[NQ], pbl[SPLIT ? NQ : 1];
@@ -982,29 +1030,11 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
                 if constexpr (SPLIT) o[db] = Tr<EL>::mma(vt[db * NQ + q], pbl[q], o[db]);
             }
     };
-    int kb = kb_lo + wave;
-    if constexpr (!AHEAD) {
-        for (; kb < kb_hi; kb += 4) {
-            uint4 kt[NF], vt[DB * NQ];
-            load_block(kt, vt, kb);
-            __builtin_amdgcn_sched_barrier(0);   // the 16 requests stay together, ahead of everything that uses them
-            use_block(kt, vt, kb);
-        }
-    } else if (kb < kb_hi) {
-        uint4 kt0[NF], vt0[DB * NQ], kt1[NF], vt1[DB * NQ];
-        load_block(kt0, vt0, kb);
-        for (;;) {
-            __builtin_amdgcn_sched_barrier(0);   // the 16 requests stay together, ahead of everything that uses them
-            if (kb + 4 < kb_hi) load_block(kt1, vt1, kb + 4);
-            __builtin_amdgcn_sched_barrier(0);
-            use_block(kt0, vt0, kb);
-            if ((kb += 4) >= kb_hi) break;
-            __builtin_amdgcn_sched_barrier(0);
-            if (kb + 4 < kb_hi) load_block(kt0, vt0, kb + 4);
-            __builtin_amdgcn_sched_barrier(0);
-            use_block(kt1, vt1, kb);
-            if ((kb += 4) >= kb_hi) break;
-        }
+    for (int kb = kb_lo + wave; kb < kb_hi; kb += 4) {
+        uint4 kt[NF], vt[DB * NQ];
+        load_block(kt, vt, kb);
+        __builtin_amdgcn_sched_barrier(0);   // the 16 requests stay together, ahead of everything that uses them
+        use_block(kt, vt, kb);
     }
     l_run += __shfl_xor(l_run, 32);
 
@@ -1030,7 +1060,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         for (int w = 0; w < 4; ++w) M = fmaxf(M, sm[w * 32 + tl]);
         float wgt[4];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) { wgt[w] = __expf(sm[w * 32 + tl] - M); lsum += wgt[w] * sl[w * 32 + tl]; }
+        for (int w = 0; w < 4; ++w) { wgt[w] = ex(sm[w * 32 + tl] - M); lsum += wgt[w] * sl[w * 32 + tl]; }
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
 #pragma unroll
@@ -1099,7 +1129,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         for (int i = 0; i < 16; ++i) accv[i] = 0.f;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {   // part order
-            const float wc = (c < a.ks) ? __expf(mc[c] - Mx) : 0.f;
+            const float wc = (c < a.ks) ? ex(mc[c] - Mx) : 0.f;
             ltot += wc * lc[c];
 #pragma unroll
             for (int i = 0; i < 16; ++i) accv[i] += wc * v[c][i];
@@ -1113,9 +1143,9 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
 }
 
 // grid = items * ks
-template <typename EL, int D, bool AHEAD>
-__global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
-    __shared__ __attribute__((aligned(16))) float smem[FV_ATTN_SMEM_FLOATS(D)];
+template <typename EL, int D, bool SHARE>
+__global__ __launch_bounds__(256, SHARE ? 2 : 1) void k_attn(AttnArgs a) {
+    __shared__ __attribute__((aligned(16))) float smem[FV_ATTN_SMEM_FLOATS(D) + (SHARE ? D * 32 : 0)];
     // Workgroups go to the 8 XCDs round-robin (workgroup b runs on XCD b % 8) and every XCD has its
     // own L2, so all node blocks and key parts of a query head -- and the query heads that share a
     // KV head -- are given to workgroups of one XCD: a head's K/V then comes from HBM once and is
@@ -1138,7 +1168,7 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
         item = head * TB + w / a.ks;
         part = w % a.ks;
     }
-    attn_body<EL, D, AHEAD>(a, item, part, smem);
+    attn_body<EL, D, SHARE>(a, item, part, smem);
 }
 
 #include "fv_attn_canon.hpp"

@@ -68,7 +68,7 @@ int run_prompt(fv_ctx* c, const int32_t* h_tok, int m) {
                 aa.Tp = 256; aa.ld = ld; aa.pieces = ld / 256; aa.T = m; aa.TK = m; aa.L = L; aa.Hq = cf.n_q_heads; aa.Hkv = cf.n_kv_heads; aa.S_pad = ly.S_pad;
                 aa.scale = 1.f / std::sqrt((float)D);
                 aa.ks = 1; aa.part = nullptr; aa.tickets = nullptr;   // more pieces than one: no key split, hence no partial triples
-                rc = launch_attn<EL, D>(aa, cf.n_q_heads * 8, ld / 256, L + m, st);
+                rc = launch_attn<EL, D>(aa, cf.n_q_heads * 8, ld / 256, st);
                 if (rc) return rc;
             }
             {

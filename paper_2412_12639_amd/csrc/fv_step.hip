@@ -122,33 +122,41 @@ int set_gemm_attrs_d() {
     if (!rc) rc = set_gemm_attrs_e<EL, D, EPI_LOGITS>();
     return rc;
 }
+// Which form of the attention: SHARE (two workgroups a compute unit) where there are at least half as many items as compute units.  us a
+// layer against the other form at the same split: 128 items 0 to 1 less at 11 to 50 blocks of keys, 2.3 less at 125; 256 items 0.3 to 4 less;
+// 320 items of 13B at 18 blocks 27.4 -> 19.6, at 130 blocks 113 -> 73.6; head size 64, 512 items, 14.9 -> 13.7 and 68 -> 57; a prompt of
+// 2000 rows 122 -> 84.  Fewer items: equal to 0.7 more.  bf16 only (fp32 tiles do not fit half a register file).
+template <typename EL>
+static bool attn_shares(int items) { return Tr<EL>::E == 8 && items >= 128; }
+
 // Key split of the attention: enough workgroups per (head, node block) item to cover the CUs,
 // but at least two 32-key blocks each.
-static int attn_key_split(int n_heads, int n_blocks, int n_keys, int n_wg) {
+static int attn_key_split(int n_heads, int n_blocks, int n_keys, int n_wg, bool share) {
     const int items = n_heads * n_blocks;
     int ks = n_wg / (items > 0 ? items : 1);
     const int nkb = (n_keys + 31) / 32;
     if (ks > nkb / 2) ks = nkb / 2;
     if (ks > 8) ks = 8;
     if (ks < 1) ks = 1;
-    // Up to two thirds of the chip and a long key range: three parts each are two rounds of a third, if the parts of a head run on
-    // one XCD (heads a multiple of eight, see k_attn).  160 items, us a layer against one part, merge included: 132 blocks 4.4 to 5.9
-    // less, 100 blocks 0.1 to 1.1 less, 84 blocks 1.0 less to 0.6 more, 69 blocks 0.6 to 1.6 more, 31 blocks 5 to 6 more; 36 heads (144
-    // items) 2 to 7 more at 9 to 132 blocks.
-    if (ks == 1 && n_heads % 8 == 0 && items > n_wg / 2 && 3 * items <= 2 * n_wg && nkb >= 96) ks = 3;
+    if (n_heads % 8) return ks;   // more parts lose where the parts of a head do not run on one XCD (144 items of 36 heads, see k_attn)
+    if (share) {
+        // Two workgroups for every compute unit, from 12 blocks a part on.  us a layer, merge included, 2 -> 4 parts of 128 items: 21.0 -> 20.3 at
+        // 50 blocks, 34.7 -> 31.7 at 125, but 16.8 -> 17.2 at 29; 1 -> 3 of 160: 26.0 -> 22.3 and 51 -> 36 (13 blocks 13.8 -> 14.8); 1 -> 2 of
+        // 256: 30.2 -> 27.6 and 58 -> 49 (32 blocks 21.6 -> 21.9, 16 blocks 15.1 -> 18.1).
+        const int two = 2 * n_wg / items < 8 ? 2 * n_wg / items : 8;
+        if (two > ks && nkb >= 12 * two) ks = two;
+    } else if (ks == 1 && items > n_wg / 2 && 3 * items <= 2 * n_wg && nkb >= 96) {
+        // Up to two thirds of the chip and a long key range: three parts each are two rounds of a third (160 items, us a layer: 132 blocks 4.4 to
+        // 5.9 less, 100 blocks 0.1 to 1.1 less, 84 blocks 1.0 less to 0.6 more).
+        ks = 3;
+    }
     return ks;
 }
 
-// The form that requests a block ahead: where each item has a compute unit to itself and is not split to fill the chip (129 to 256
-// items, in one part or three) and a wavefront's share of the keys is eight blocks and more.  us a layer against the plain form: 256
-// items of head size 64 0.8 less at 43 blocks, 2.0 less at 68, 4.1 less at 133, of head size 128 even at 40 to 72 and 0.9 to 2.0 less at 133 to 136;
-// three parts of 160 items 0.7 less.  Elsewhere it loses: parts that fill the chip (64 nodes behind 4200 keys, one behind 8300) 0.5 to 1.3
-// more; 512 items of head size 64, whose workgroups no longer share a compute unit, 12 more at 72 blocks, 23 more at 139, and a prompt of
-// 2040 rows 42 more.  bf16 only: two sets of fp32 tiles do not fit the registers (52 of them spilled).
 template <typename EL, int D>
-int launch_attn(const AttnArgs& aa, int items, int pieces, int n_keys, hipStream_t st) {
+int launch_attn(const AttnArgs& aa, int items, int pieces, hipStream_t st) {
     constexpr bool CAN = Tr<EL>::E == 8;
-    if (CAN && items > 128 && items * pieces <= 256 && (n_keys + 31) / 32 >= 32 * aa.ks) hipLaunchKernelGGL((k_attn<EL, D, CAN>), dim3(items * aa.ks, pieces), dim3(256), 0, st, aa);
+    if (attn_shares<EL>(items)) hipLaunchKernelGGL((k_attn<EL, D, CAN>), dim3(items * aa.ks, pieces), dim3(256), 0, st, aa);
     else hipLaunchKernelGGL((k_attn<EL, D, false>), dim3(items * aa.ks, pieces), dim3(256), 0, st, aa);
     return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
 }
@@ -289,9 +297,9 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
             aa.out = c->at<void>(ly.off_attn); aa.mask = c->at<uint64_t>(ly.off_mask);
             aa.Tp = Tp; aa.ld = Tp; aa.pieces = 1; aa.T = T; aa.TK = T; aa.L = L; aa.Hq = cf.n_q_heads; aa.Hkv = cf.n_kv_heads; aa.S_pad = ly.S_pad;
             aa.scale = 1.f / std::sqrt((float)D);
-            aa.ks = attn_key_split(cf.n_q_heads, Tp / 32, L + T, 256);
+            aa.ks = attn_key_split(cf.n_q_heads, Tp / 32, L + T, 256, attn_shares<EL>(cf.n_q_heads * (Tp / 32)));
             aa.part = c->scr->apart; aa.tickets = c->scr->atick;
-            int rc_a = launch_attn<EL, D>(aa, cf.n_q_heads * (Tp / 32), 1, L + T, st);
+            int rc_a = launch_attn<EL, D>(aa, cf.n_q_heads * (Tp / 32), 1, st);
             if (rc_a) return rc_a;
         }
         {   // output projection, residual add, statistics + input of the FFN norm

@@ -755,8 +755,8 @@ def test_long_prompts_are_measured_whole(fvmod, n, max_tree, gemms, attns):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("L", [1030, 2600, 3050])
 def test_attention_over_long_ranges(fvmod, dtype, L):
-    """96 nodes of 40 query heads are 160 (head, node block) items: 36 and 85 key blocks in one part, 99 in three parts (bf16: with a
-    block requested ahead).  fp32 takes the plain form everywhere."""
+    """96 nodes of 40 query heads are 160 (head, node block) items: fp32 36 and 85 key blocks in one part, 99 in three;
+    bf16 three parts, two workgroups a compute unit."""
     s = ModelShape(f"heads40-{dtype}", 1, 256, 40, 8, 64, 272, 600, dtype)
     w = fi.gen_weights(s, seed=40, gain_jitter=0.1)
     tol = H.tol_for(s)
@@ -773,4 +773,31 @@ def test_attention_over_long_ranges(fvmod, dtype, L):
     got = g.verify_tree(tokens, parent, depth)
     case = dict(res=res, parent=parent, depth=depth, tokens=tokens, hidden=o.last_hidden.copy())
     say("long range", dtype, L, "logits err", H.check_step(g, case, got, tol, L=L, oracle_decisions=False))
+    g.close()
+
+
+@pytest.mark.parametrize("heads,kv,d,nodes,L", [
+    (64, 64, 64, 33, 5),       # 128 items, the fewest that share compute units: two blocks, all keys tested
+    (64, 8, 64, 64, 32),       # the prefix a whole block: seen by every node, tested by none
+    (64, 16, 64, 40, 1497),    # 49 blocks: four parts of 128 items, ragged
+    (32, 8, 128, 250, 517),    # 256 items of head size 128, 24 blocks: two parts
+    (36, 4, 64, 190, 900),     # 216 items of heads that are no multiple of eight: one part
+])
+def test_attention_with_two_workgroups_a_compute_unit(fvmod, heads, kv, d, nodes, L):
+    """The form of the attention from 128 (head, node block) items on, at the edges of its key ranges and splits."""
+    s = ModelShape(f"share{heads}-{d}", 1, 256, heads, kv, d, 272, 600, "bf16")
+    w = fi.gen_weights(s, seed=heads, gain_jitter=0.1)
+    tol = H.tol_for(s)
+    prefix = fi.gen_prefix(L, L, s.vocab)
+    o = fo.Oracle(s, _oracle_weights(w), max_seq=L + 260, dtype=np.float32)
+    root = o.prefill(prefix)
+    parent, depth, _ = fi.gen_tree(L, nodes, [8, 4, 2, 2, 1, 1])
+    tokens = fi.trees.fill_tokens(L, parent, s.vocab, root)
+    res = o.verify_tree(tokens, parent, depth)
+    g = make_gpu(fvmod, s, w, max_seq=L + 260, max_tree=256)
+    g.prefill(prefix)
+    g.rollback(L, root)
+    got = g.verify_tree(tokens, parent, depth)
+    case = dict(res=res, parent=parent, depth=depth, tokens=tokens, hidden=o.last_hidden.copy())
+    say("shared compute units", heads, d, nodes, L, "logits err", H.check_step(g, case, got, tol, L=L, oracle_decisions=False))
     g.close()
