@@ -704,6 +704,18 @@ def test_long_prompt_of_several_tiles_a_workgroup(fvmod, hidden, n):
     test_long_prompt_rows_at_once(fvmod, n, 64, s.name)
 
 
+@pytest.mark.parametrize("hidden,ffn,n,max_tree", [
+    (128, 4112, 700, 256),    # down's 132 stages in four parts of 33, one row group
+    (128, 6640, 700, 64),     # two parts, then a step whose kernels need the partial area clear again
+    (1152, 2064, 520, 64),    # two parts of 34, nine row groups: one XCD has two; the last column tile has 8 rows
+])
+def test_long_prompt_in_parts_of_the_k_range(fvmod, hidden, ffn, n, max_tree):
+    """Products with fewer tiles than half the compute units and a long K range are cut along it."""
+    s = ModelShape(f"parts-{hidden}-{ffn}", 2, hidden, hidden // 64, hidden // 64, 64, ffn, 600, "bf16")
+    SHAPES[s.name], _W[s.name] = s, fi.gen_weights(s, seed=hidden, gain_jitter=0.1)
+    test_long_prompt_rows_at_once(fvmod, n, max_tree, s.name)
+
+
 @pytest.mark.parametrize("n,max_tree", [
     (704, 64),       # the last chunk along with the others
     (544, 256),      # 512 rows at once, then a chunk of 32 rows, where the long prompt's last chunk had 232
