@@ -704,6 +704,18 @@ def test_long_prompt_of_several_tiles_a_workgroup(fvmod, hidden, n):
     test_long_prompt_rows_at_once(fvmod, n, 64, s.name)
 
 
+@pytest.mark.parametrize("n,max_tree", [
+    (129, 64),       # 128 rows at once, the fewest, and the last chunk's one row in their padding
+    (161, 32),       # one piece, ragged
+    (192, 64),       # 128 rows and a last chunk of 64
+    (300, 256),      # a piece of 256 and a chunk of its own
+    (400, 256),      # 256 and the 144 of the last chunk with them
+])
+def test_short_prompt_rows_at_once(fvmod, n, max_tree):
+    """The same for prompts of few rows, one piece of 256 among them."""
+    test_long_prompt_rows_at_once(fvmod, n, max_tree)
+
+
 @pytest.mark.parametrize("hidden,ffn,n,max_tree", [
     (128, 4112, 700, 256),    # down's 132 stages in four parts of 33, one row group
     (128, 6640, 700, 64),     # two parts, then a step whose kernels need the partial area clear again
