@@ -540,12 +540,12 @@ int fv_prefill(fv_ctx* c, const int32_t* tokens, int32_t n, int32_t* next_token)
     int from_prompt = -1;                             // the last chunk's first row in the prompt buffers, if it came along
     const int tail = (n - 1) % c->cfg.max_tree + 1;   // rows of the last chunk, whose logits and activations can be read back
     if (c->lay.Pm > 0 && !c->gemm_shared) {
-        // Rows before the last chunk go through the layers up to Pm at a time.  Worth it from 128 rows on, the fewest
-        // measured.  Prompt and a one-token step, chunks against rows at once, us: 7B, 3 layers, 130 rows (chunks of 64) 991 -> 713, 140 (of 128)
-        // 850 -> 715, 250 (of 128) 949 -> 758, 300 (of 256) 973 -> 888, 450 (of 256) 1151 -> 906; 2 layers of 13B, 140 rows 776 -> 655, of 70B 200
-        // rows 1680 -> 1320; small-gqa 200 rows 256 -> 222.
+        // Rows before the last chunk go through the layers up to Pm at a time.  Worth it above 256 rows and two chunks: a layer of
+        // the 7B shape takes 226 us for a chunk of 256 rows, 111 for one of 64, and 430 for 512 rows at once, 830 for 1792.  From 128 rows on
+        // it was faster too (7B, 3 layers, 130 rows 991 -> 713 us), but the rows at once add over K in another order than the chunks, so
+        // such prompts' K and V moved by 2e-3 to 4e-3, and with them draws of a non-greedy step, which fall among tokens of 1e-5 each.
         memcpy(c->h_prompt, tokens, (size_t)n * 4);
-        while (n - tail - done >= 128) {
+        while (n - tail - done > 256 && n - tail - done >= 2 * c->cfg.max_tree) {
             int m = std::min(n - tail - done, c->lay.Pm);
             // The last chunk's rows come along through all layers but the last where they fit: into the padding of the 256-row tiles, or
             // as a tile more where they are many (above 64 rows a chunk of its own costs 150 to 230 us a layer, a tile 110).

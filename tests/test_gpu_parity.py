@@ -705,15 +705,37 @@ def test_long_prompt_of_several_tiles_a_workgroup(fvmod, hidden, n):
 
 
 @pytest.mark.parametrize("n,max_tree", [
-    (129, 64),       # 128 rows at once, the fewest, and the last chunk's one row in their padding
-    (161, 32),       # one piece, ragged
-    (192, 64),       # 128 rows and a last chunk of 64
-    (300, 256),      # a piece of 256 and a chunk of its own
-    (400, 256),      # 256 and the 144 of the last chunk with them
+    (129, 64),       # two chunks and a row
+    (161, 32),       # five and a row
+    (192, 64),       # three whole chunks
+    (300, 256),      # a whole chunk and one of 44
+    (400, 256),      # and one of 144
 ])
 def test_short_prompt_rows_at_once(fvmod, n, max_tree):
-    """The same for prompts of few rows, one piece of 256 among them."""
+    """The same for prompts of few rows."""
     test_long_prompt_rows_at_once(fvmod, n, max_tree)
+
+
+@pytest.mark.parametrize("n,max_tree,front", [
+    (333, 256, 256),     # one chunk of 256 and one of 77
+    (400, 256, 256),
+    (129, 64, 128),      # two chunks and a row
+    (192, 64, 128),
+    (250, 32, 224),      # seven chunks
+])
+def test_few_rows_before_the_last_chunk_go_chunk_by_chunk(fvmod, n, max_tree, front):
+    """K and V of up to 256 rows are bitwise those of a prompt that ends with them: the kernels and the order of their sums do not
+    depend on what follows.  (Draws of a non-greedy step read the last bits of what the prompt left.)"""
+    s, w = SHAPES["small-gqa"], weights_of("small-gqa")
+    prefix = fi.gen_prefix(n, n, s.vocab)
+    g = make_gpu(fvmod, s, w, max_seq=420, max_tree=max_tree)
+    g.prefill(prefix[:front])
+    want = [g.read_kv(l, 0, front) for l in range(s.n_layers)]
+    g.prefill(prefix)
+    for l in range(s.n_layers):
+        for a, b in zip(g.read_kv(l, 0, front), want[l]):
+            assert np.array_equal(a, b), l
+    g.close()
 
 
 @pytest.mark.parametrize("hidden,ffn,n,max_tree", [
