@@ -23,8 +23,7 @@
 // partial tiles are stored and k_gemm_fix, launched behind, reduces them.
 // WIDE = true: more rows (a prompt): tiles over the whole K range, column tiles of 256.  One workgroup per compute unit takes several,
 // the ring running on from one into the next: the next tile's first stages come while this one's sums go through the epilogue
-// (gate/up, five to six tiles each, 350 -> 340 us).  O and down of a shorter prompt have fewer tiles than half the compute units: then their
-// K range is cut into wide_ks parts, one a workgroup, and k_gemm_wide_fix, launched behind, adds the parts.
+// (gate/up, five to six tiles each, 350 -> 340 us).
 #pragma once
 // (included from fv_kernels.hpp after k_gemm_fix)
 
@@ -59,8 +58,6 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
     // from that XCD's L2.  A workgroup takes every t_step-th tile.
     const int tiles = WIDE ? ld / TT : 1, xcd = blockIdx.x & 7, t_step = gridDim.x >> 3;
     int ti = blockIdx.x >> 3;
-    const int ks = WIDE && EPI == EPI_RESID ? a.wide_ks : 1;   // parts of the K range; a workgroup that has a part has no other tile
-    if constexpr (WIDE && EPI == EPI_RESID) ti /= ks;
     auto group_of = [&](int i) { return (i / tiles) * 8 + xcd; };
     auto column_of = [&](int i) { return (i % tiles) * TT; };
     if constexpr (WIDE) {
@@ -68,10 +65,6 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
         if (g0 >= a.NG) return;
         const int mine = (a.NG - 1 - xcd) / 8 * tiles + tiles;   // tiles of this XCD
         k0 = 0; n = ((mine - 1 - ti) / t_step + 1) * NST;
-        if (ks > 1) {
-            const int part = (int)(blockIdx.x >> 3) - ti * ks;
-            k0 = NST * part / ks; n = NST * (part + 1) / ks - k0;
-        }
     } else {
         const long long U = (long long)a.NG * a.NB;     // computed, not looked up, as in k_gemm
         const int u0 = (int)(U * blockIdx.x / a.G), u1 = (int)(U * (blockIdx.x + 1) / a.G);
@@ -272,7 +265,7 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
         if (++k == NST || s + 1 == n) {
             if constexpr (WIDE) {
                 const int t0 = column_of(ti);
-                flush(gi, t0, rinv_lds + par * TT - t0, ks == 1, 0);
+                flush(gi, t0, rinv_lds + par * TT - t0, true, 0);
                 ti += t_step; gi = group_of(ti); par = par == 2 ? 0 : par + 1;
             } else {
                 flush(gi, 0, rinv_lds, seg_k0 == 0 && k == NST, seg);

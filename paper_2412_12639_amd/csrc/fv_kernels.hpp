@@ -214,7 +214,6 @@ struct GemmArgs {
     // the whole K range only stores its partial tiles, and k_gemm_fix, launched right behind, reduces
     // the n_fix row groups that have several contributors with one wavefront per tile.
     int defer, n_fix;
-    int wide_ks;             // k_gemm_ring, WIDE, EPI_RESID: parts of the K range (1: none)
     const int4* fix_groups;  // [n_fix] row groups with more than one contributor: (group, first and last contributor, the first one's segment index)
     float* rinv_out;         // [Tp] RMSNorm factors handed from k_gemm to k_gemm_fix
     int T, n_strips;     // real tokens; strips that carry real rows
@@ -811,43 +810,6 @@ __global__ __launch_bounds__(256) void k_gemm_fix(GemmArgs a) {
 }
 
 #include "fv_gemm_direct.hpp"
-// The same for a prompt's tiles whose K range was cut into a.wide_ks parts (k_gemm_ring, WIDE).
-template <int D>
-__global__ __launch_bounds__(256) void k_gemm_wide_fix(GemmArgs a) {
-    constexpr int R = FV_R, TB = 8, SC1 = 16;
-    const int lane = threadIdx.x & 63, nb = a.ld / 32, tile = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (tile >= a.n_strips * nb) return;
-    const int strip = tile / nb, tb = tile % nb, gi = strip / R;
-    const int wg0 = ((gi >> 3) * (nb / TB) + tb / TB) * a.wide_ks * 8 + (gi & 7);   // the first part's workgroup; the next ones' every eighth
-    EpiPre pre;
-    resid_preload(a, a.ld, strip, tb, lane, pre);
-    const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc((void*)a.part, 0, (int)a.part_bytes, 0x00020000);
-    u32x4 v[FV_WIDE_KS][4];
-#pragma unroll
-    for (int k = 0; k < FV_WIDE_KS; ++k) {
-        const int part = k < a.wide_ks ? k : a.wide_ks - 1;
-        const unsigned o = ((unsigned)(((wg0 + 8 * part) * R + strip % R) * TB + tb % TB) * 1024u + (unsigned)lane * 4u) * 4u;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[k][q] = __builtin_amdgcn_raw_buffer_load_b128(prs, o + q * 1024u, 0, SC1);
-    }
-    float acc[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll
-    for (int k = 0; k < FV_WIDE_KS; ++k) {
-        if (k < a.wide_ks) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                acc[4 * q] += __uint_as_float(v[k][q].x);
-                acc[4 * q + 1] += __uint_as_float(v[k][q].y);
-                acc[4 * q + 2] += __uint_as_float(v[k][q].z);
-                acc[4 * q + 3] += __uint_as_float(v[k][q].w);
-            }
-        }
-    }
-    gemm_epilogue<BF16, D, EPI_RESID>(a, a.ld, strip, tb, lane, acc, nullptr, pre, true);
-}
-
 #include "fv_gemm_ring.hpp"
 
 // ============================================================================ tree attention

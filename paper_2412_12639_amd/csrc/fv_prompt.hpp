@@ -48,23 +48,6 @@ int run_prompt(fv_ctx* c, const int32_t* h_tok, int m) {
             return FV_OK;
         };
         auto grid = [&](const GemmArgs& ga) { return dim3(8u * (unsigned)std::min((ga.NG + 7) / 8 * (ld / 256), 32)); };   // one workgroup per compute unit at most
-        // O and down: with fewer tiles than half the compute units (32 per XCD), in as many parts of the K range as these hold, of 32 stages and
-        // more (12 us; the launch behind costs about as much).  Prompt and a one-token step, one part against this, us: 7B, 3 layers, 600 rows 1825 -> 1715,
-        // 1000 rows 2030 -> 1950; 2 layers of 13B, 600 rows 1570 -> 1500; equal where there are more tiles.
-        auto resid = [&](GemmArgs& ga) -> int {
-            const int tiles = (ga.NG + 7) / 8 * (ld / 256);   // per XCD
-            const size_t tile_bytes = (size_t)8 * tiles * FV_R * 8 * 4096;
-            ga.wide_ks = std::max(1, std::min(std::min(FV_WIDE_KS, 32 / tiles), std::min(4 * ga.NB / 32, (int)(c->scr->part_bytes / tile_bytes))));
-            if (ga.wide_ks == 1) {
-                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_RESID, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
-                return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
-            }
-            ga.part = c->scr->part; ga.part_bytes = c->scr->part_bytes; ga.segmax = 1;
-            if (c->scr->dirty) *c->scr->dirty = true;
-            hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_RESID, true>), dim3(8u * (unsigned)(tiles * ga.wide_ks)), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
-            hipLaunchKernelGGL((k_gemm_wide_fix<D>), dim3((unsigned)((ga.n_strips * (ld / 32) + 3) / 4)), dim3(256), 0, st, ga);
-            return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
-        };
         for (int l = 0; l < cf.n_layers; ++l) {
             int rc = rinv();
             if (rc) return rc;
@@ -92,8 +75,8 @@ int run_prompt(fv_ctx* c, const int32_t* h_tok, int m) {
                 PhaseTimer pt(c, FV_PH_GEMM);
                 GemmArgs ga = args(GM_O, c->layer_w(l, 1), ly.off_pattn);
                 ga.x_in = ga.x = c->at<float>(ly.off_px); ga.xb = c->at<void>(ly.off_pxb); ga.gain_next = c->gain(2 * l + 1); ga.ssq_out = c->at<float>(ly.off_pssq);
-                rc = resid(ga);
-                if (rc) return rc;
+                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_RESID, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
+                HIPCHK(hipGetLastError());
             }
             rc = rinv();
             if (rc) return rc;
@@ -108,8 +91,8 @@ int run_prompt(fv_ctx* c, const int32_t* h_tok, int m) {
                 PhaseTimer pt(c, FV_PH_GEMM);
                 GemmArgs ga = args(GM_DN, c->layer_w(l, 3), ly.off_pact);
                 ga.x_in = ga.x = c->at<float>(ly.off_px); ga.xb = c->at<void>(ly.off_pxb); ga.gain_next = c->gain(2 * (l + 1)); ga.ssq_out = c->at<float>(ly.off_pssq);
-                rc = resid(ga);
-                if (rc) return rc;
+                hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_RESID, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
+                HIPCHK(hipGetLastError());
             }
         }
         return FV_OK;

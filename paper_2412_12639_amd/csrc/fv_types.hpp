@@ -9,7 +9,6 @@
 #define FV_FRAGS 8        // weight frags per K batch
 
 #define FV_PROMPT_ROWS 2048   // prompt rows that go through the layers at once
-#define FV_WIDE_KS 4          // most parts of the K range of a prompt's tile
 
 #define FV_DRAFT_KMAX 8   // largest k of the semi-autoregressive drafter
 #define FV_DRAFT_MMAX 32  // longest top list per drafter row

@@ -739,15 +739,32 @@ def test_few_rows_before_the_last_chunk_go_chunk_by_chunk(fvmod, n, max_tree, fr
 
 
 @pytest.mark.parametrize("hidden,ffn,n,max_tree", [
-    (128, 4112, 700, 256),    # down's 132 stages in four parts of 33, one row group
-    (128, 6640, 700, 64),     # two parts, then a step whose kernels need the partial area clear again
-    (1152, 2064, 520, 64),    # two parts of 34, nine row groups: one XCD has two; the last column tile has 8 rows
+    (128, 4112, 700, 256),    # 132 stages in down's K range, one row group
+    (128, 6640, 700, 64),     # 208
+    (1152, 2064, 520, 64),    # nine row groups: one XCD has two; the last column tile has 8 rows
 ])
 def test_long_prompt_in_parts_of_the_k_range(fvmod, hidden, ffn, n, max_tree):
-    """Products with fewer tiles than half the compute units and a long K range are cut along it."""
+    """Products with fewer tiles than half the compute units and a long K range."""
     s = ModelShape(f"parts-{hidden}-{ffn}", 2, hidden, hidden // 64, hidden // 64, 64, ffn, 600, "bf16")
     SHAPES[s.name], _W[s.name] = s, fi.gen_weights(s, seed=hidden, gain_jitter=0.1)
     test_long_prompt_rows_at_once(fvmod, n, max_tree, s.name)
+
+
+def test_prompt_rows_do_not_depend_on_the_rest_of_the_prompt(fvmod):
+    """K and V of the rows that go through the layers at once, bitwise the same whatever the prompt's length and the largest tree: their
+    products' sums run over the whole K range in one order, so a draw of a non-greedy step behind them does not hang on either."""
+    s = ModelShape("parts-128-6640", 2, 128, 2, 2, 64, 6640, 600, "bf16")
+    w = fi.gen_weights(s, seed=128, gain_jitter=0.1)
+    prefix = fi.gen_prefix(5, 1500, s.vocab)
+    want = None
+    for n, max_tree in ((1500, 256), (700, 64), (700, 256), (513, 256), (1500, 64)):
+        g = make_gpu(fvmod, s, w, max_seq=1600, max_tree=max_tree)
+        g.prefill(prefix[:n])
+        got = [x for l in range(s.n_layers) for x in g.read_kv(l, 0, 512)]
+        if want is None:
+            want = got
+        assert all(np.array_equal(a, b) for a, b in zip(got, want)), (n, max_tree)
+        g.close()
 
 
 @pytest.mark.parametrize("n,max_tree", [
