@@ -845,9 +845,8 @@ struct AttnArgs {
 
 // One (query head, block of 32 nodes) item, key part `part` of a.ks.  SHARE: two workgroups of this form fit a compute unit, so that
 // one wavefront of a SIMD is at its softmax or waits for K and V while the other multiplies.  For that q, the same in all four
-// wavefronts, lies in LDS (64 registers less), scores are kept in units of log2 (one multiply-add and the exponential a score), and a
-// block every node sees goes without the tests.  Over ranges of a few blocks a wavefront it loses what the way through LDS costs;
-// launch_attn has the rule and the figures.
+// wavefronts, lies in LDS (64 registers less), and a block every node sees goes without the tests.  Both forms compute the same bits.
+// Over ranges of a few blocks a wavefront it loses what the way through LDS costs; attn_shares has the rule and the figures.
 template <typename EL, int D, bool SHARE>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part, float* smem) {
     constexpr int E = Tr<EL>::E;
@@ -880,8 +879,6 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
             for (int fr = 0; fr < NQF; ++fr) qfl[fr] = q_at(a.q_lo, fr);
         }
     }
-    const float scale2 = a.scale * 1.44269504f;   // SHARE
-    auto ex = [](float x) { return SHARE ? __builtin_amdgcn_exp2f(x) : __expf(x); };   // of differences of maxima
     uint64_t mk[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) mk[w] = (t < a.T) ? a.mask[t * 4 + w] : 0ull;
@@ -975,16 +972,16 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         float mx = -1e30f;
         auto seen = [&](int i) { return ((vbits >> (8 * (i >> 2) + (i & 3))) & 1u) != 0u; };   // key 8*(i/4) + 4*g + i%4 of the block
         if (SHARE && n0 <= -32) {   // keys every node sees
+#pragma clang fp contract(off)      // the product is rounded before the maximum is taken off, as where it is tested
 #pragma unroll
-            for (int i = 0; i < 16; ++i) { p[i] = s[i]; mx = fmaxf(mx, p[i]); }
+            for (int i = 0; i < 16; ++i) { p[i] = s[i] * a.scale; mx = fmaxf(mx, p[i]); }
         } else {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                p[i] = seen(i) ? (SHARE ? s[i] : s[i] * a.scale) : -1e30f;
+                p[i] = seen(i) ? s[i] * a.scale : -1e30f;
                 mx = fmaxf(mx, p[i]);
             }
         }
-        if constexpr (SHARE) mx *= scale2;
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         // Lazy rescale: the running reference m_run only has to be near the running maximum, not equal
         // to it -- exp(score - m_run) stays below e^8 as long as no row's maximum has grown by more than
@@ -992,8 +989,8 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         // accumulators (64 registers, a read-multiply-write each) are rescaled only when some row of the
         // wavefront crosses that bound; after the first blocks of a long key range that is rare.
         const float m_cand = fmaxf(m_run, mx);
-        if (__any(m_cand - m_run > (SHARE ? 11.5f : 8.f))) {
-            const float alpha = ex(m_run - m_cand);
+        if (__any(m_cand - m_run > 8.f)) {
+            const float alpha = __expf(m_run - m_cand);
             l_run *= alpha;
             m_run = m_cand;
 #pragma unroll
@@ -1004,11 +1001,11 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         float psum = 0.f;
         if (SHARE && n0 <= -32) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) { p[i] = fmaxf(__builtin_amdgcn_exp2f(fmaf(p[i], scale2, -m_run)), 0.f); psum += p[i]; }   // a score that is no number counts for nothing, as below
+            for (int i = 0; i < 16; ++i) { p[i] = fmaxf(__expf(p[i] - m_run), 0.f); psum += p[i]; }   // a score that is no number counts for nothing, as below
         } else {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                p[i] = (p[i] > -1e29f) ? (SHARE ? __builtin_amdgcn_exp2f(fmaf(p[i], scale2, -m_run)) : __expf(p[i] - m_run)) : 0.f;
+                p[i] = (p[i] > -1e29f) ? __expf(p[i] - m_run) : 0.f;
                 psum += p[i];
             }
         }
@@ -1060,7 +1057,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         for (int w = 0; w < 4; ++w) M = fmaxf(M, sm[w * 32 + tl]);
         float wgt[4];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) { wgt[w] = ex(sm[w * 32 + tl] - M); lsum += wgt[w] * sl[w * 32 + tl]; }
+        for (int w = 0; w < 4; ++w) { wgt[w] = __expf(sm[w * 32 + tl] - M); lsum += wgt[w] * sl[w * 32 + tl]; }
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
 #pragma unroll
@@ -1129,7 +1126,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         for (int i = 0; i < 16; ++i) accv[i] = 0.f;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {   // part order
-            const float wc = (c < a.ks) ? ex(mc[c] - Mx) : 0.f;
+            const float wc = (c < a.ks) ? __expf(mc[c] - Mx) : 0.f;
             ltot += wc * lc[c];
 #pragma unroll
             for (int i = 0; i < 16; ++i) accv[i] += wc * v[c][i];

@@ -864,3 +864,21 @@ def test_attention_with_two_workgroups_a_compute_unit(fvmod, heads, kv, d, nodes
     case = dict(res=res, parent=parent, depth=depth, tokens=tokens, hidden=o.last_hidden.copy())
     say("shared compute units", heads, d, nodes, L, "logits err", H.check_step(g, case, got, tol, L=L, oracle_decisions=False))
     g.close()
+
+
+@pytest.mark.parametrize("d,L", [(64, 5), (64, 32), (128, 20), (128, 32)])
+def test_both_forms_of_the_attention_compute_the_same_bits(fvmod, d, L):
+    """64 heads: 32 nodes take the form with a compute unit to itself, 64 the one that shares it, both without a key split over these two
+    and three blocks.  The first 32 of 64 nodes have the logits, bit for bit, that they have as a tree of their own."""
+    s = ModelShape(f"forms-{d}", 2, 256, 64, 8, d, 272, 600, "bf16")
+    w = fi.gen_weights(s, seed=d, gain_jitter=0.1)
+    parent, depth, _ = fi.gen_tree(L, 64, [8, 4, 2, 2, 1, 1])
+    g = make_gpu(fvmod, s, w, max_seq=128, max_tree=64)
+    root = g.prefill(fi.gen_prefix(L, L, s.vocab))
+    tokens = fi.trees.fill_tokens(L, parent, s.vocab, root)
+    g.verify_tree(tokens, parent, depth)
+    want = g.logits(64)[:32].copy()
+    g.rollback(L, root)
+    g.verify_tree(tokens[:32], parent[:32], depth[:32])
+    assert np.array_equal(g.logits(32), want)
+    g.close()
