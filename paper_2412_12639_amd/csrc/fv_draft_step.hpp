@@ -154,7 +154,7 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         aa.out = c->at<void>(ly.off_attn); aa.mask = c->at<uint64_t>(ly.off_mask);
         aa.Tp = Tp; aa.ld = Tp; aa.pieces = 1; aa.T = n; aa.TK = ps.r0 + n; aa.L = d->L0; aa.Hq = cf.n_q_heads; aa.Hkv = cf.n_kv_heads; aa.S_pad = ly.S_pad;
         aa.scale = 1.f / std::sqrt((float)D);
-        aa.ks = attn_key_split(cf.n_q_heads, Tp / 32, d->L0 + ps.r0 + n, 256, attn_shares<EL>(cf.n_q_heads * (Tp / 32)));
+        aa.ks = attn_key_split(cf.n_q_heads, Tp / 32, d->L0 + ps.r0 + n, 256);
         aa.part = c->scr->apart; aa.tickets = c->scr->atick;
         int rc = launch_attn<EL, D>(aa, cf.n_q_heads * (Tp / 32), 1, st);
         if (rc) return rc;

@@ -131,25 +131,18 @@ static bool attn_shares(int items) { return Tr<EL>::E == 8 && items >= 128; }
 
 // Key split of the attention: enough workgroups per (head, node block) item to cover the CUs,
 // but at least two 32-key blocks each.
-static int attn_key_split(int n_heads, int n_blocks, int n_keys, int n_wg, bool share) {
+static int attn_key_split(int n_heads, int n_blocks, int n_keys, int n_wg) {
     const int items = n_heads * n_blocks;
     int ks = n_wg / (items > 0 ? items : 1);
     const int nkb = (n_keys + 31) / 32;
     if (ks > nkb / 2) ks = nkb / 2;
     if (ks > 8) ks = 8;
     if (ks < 1) ks = 1;
-    if (n_heads % 8) return ks;   // more parts lose where the parts of a head do not run on one XCD (144 items of 36 heads, see k_attn)
-    if (share) {
-        // Two workgroups for every compute unit, from 12 blocks a part on.  us a layer, merge included, 2 -> 4 parts of 128 items: 21.0 -> 20.3 at
-        // 50 blocks, 34.7 -> 31.7 at 125, but 16.8 -> 17.2 at 29; 1 -> 3 of 160: 26.0 -> 22.3 and 51 -> 36 (13 blocks 13.8 -> 14.8); 1 -> 2 of
-        // 256: 30.2 -> 27.6 and 58 -> 49 (32 blocks 21.6 -> 21.9, 16 blocks 15.1 -> 18.1).
-        const int two = 2 * n_wg / items < 8 ? 2 * n_wg / items : 8;
-        if (two > ks && nkb >= 12 * two) ks = two;
-    } else if (ks == 1 && items > n_wg / 2 && 3 * items <= 2 * n_wg && nkb >= 96) {
-        // Up to two thirds of the chip and a long key range: three parts each are two rounds of a third (160 items, us a layer: 132 blocks 4.4 to
-        // 5.9 less, 100 blocks 0.1 to 1.1 less, 84 blocks 1.0 less to 0.6 more).
-        ks = 3;
-    }
+    // Up to two thirds of the chip and a long key range: three parts each are two rounds of a third, if the parts of a head run on
+    // one XCD (heads a multiple of eight, see k_attn).  160 items, us a layer against one part, merge included: 132 blocks 4.4 to 5.9
+    // less, 100 blocks 0.1 to 1.1 less, 84 blocks 1.0 less to 0.6 more, 69 blocks 0.6 to 1.6 more, 31 blocks 5 to 6 more; 36 heads (144
+    // items) 2 to 7 more at 9 to 132 blocks.
+    if (ks == 1 && n_heads % 8 == 0 && items > n_wg / 2 && 3 * items <= 2 * n_wg && nkb >= 96) ks = 3;
     return ks;
 }
 
@@ -297,7 +290,7 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
             aa.out = c->at<void>(ly.off_attn); aa.mask = c->at<uint64_t>(ly.off_mask);
             aa.Tp = Tp; aa.ld = Tp; aa.pieces = 1; aa.T = T; aa.TK = T; aa.L = L; aa.Hq = cf.n_q_heads; aa.Hkv = cf.n_kv_heads; aa.S_pad = ly.S_pad;
             aa.scale = 1.f / std::sqrt((float)D);
-            aa.ks = attn_key_split(cf.n_q_heads, Tp / 32, L + T, 256, attn_shares<EL>(cf.n_q_heads * (Tp / 32)));
+            aa.ks = attn_key_split(cf.n_q_heads, Tp / 32, L + T, 256);
             aa.part = c->scr->apart; aa.tickets = c->scr->atick;
             int rc_a = launch_attn<EL, D>(aa, cf.n_q_heads * (Tp / 32), 1, st);
             if (rc_a) return rc_a;
