@@ -128,12 +128,13 @@ int build_split_tables(const GemmPlan& p, std::vector<int>& tab) {
 void plan_gemm_forms(GemmPlan& gm, GemmPlan& gd, GemmPlan& gp, bool& paired_ok, int n_strips, int K, int E, int n_wg) {
     plan_gemm(gm, n_strips, K, E, n_wg);
     // Above 64 rows a partial tile is 64 or 128 KiB, so bf16 row groups are cut into equal parts, one a workgroup, where that
-    // occupies at least two thirds of the chip: 192 partial tiles instead of 352 for QKV at the 7B shape, none
-    // instead of 500 for its head.  (256 rows, 7B: QKV 43.0 us either way and 10 -> 6 us to reduce, head 86 + 17 -> 86, gate/up on 172 workgroups
-    // 61.2 + 11.7 -> 67.2, at 128 rows 47.7 + 7.6 -> 53.1.)  fp32, whose
+    // occupies at least three quarters of the chip: 192 partial tiles instead of 352 for QKV at the 7B shape, none
+    // instead of 500 for its head.  (256 rows, 7B: QKV 43.0 us either way and 10 -> 6 us to reduce, head 86 + 17 -> 86.  Its gate/up on 172
+    // workgroups takes 67.2 us against 61.2 + 11.7 on 256, at 128 rows 53.1 against 47.7 + 7.6; it keeps its equal ranges all the same: 1 % of a
+    // step does not pay for sums in another order, which draws of a non-greedy step feel.)  fp32, whose
     // kernel multiplies far longer per row group, needs every compute unit (two layers of the 7B width and head, 100 rows 1372 us against
     // 1405 on equal parts, 250 rows 2534 against 2600).
-    if (const int k = std::min(n_wg / gm.NG, gm.NB); E == 8 && k >= 1 && 3 * gm.NG * k >= 2 * n_wg) {
+    if (const int k = std::min(n_wg / gm.NG, gm.NB); E == 8 && k >= 1 && 4 * gm.NG * k >= 3 * n_wg) {
         gm.G = gm.NG * k;
         gm.segmax = 2;
     }

@@ -20,6 +20,7 @@ CASES = [
     (333, 33, 272, "a978081561d439b4"),      # 256 rows of the prompt in a chunk of their own
     (700, 33, 6640, "dd3d9bf94e4d3737"),     # 512 rows and the last chunk at once, long K ranges
     (2048, 250, 272, "f088aacf0cbdebf1"),    # the attention of 256 (head, node block) items over 72 key blocks
+    (40, 100, 11008, "4fa621aa28cbf483"),    # 172 row groups of gate and up in equal ranges over 256 workgroups
 ]
 
 
