@@ -333,10 +333,6 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
         HIPCHK(hipEventRecord(d->core->ev0, st));
         DraftPass ps;
         ps.r0 = 0; ps.n = m; ps.l0 = 0; ps.lvl_n.assign(m, 1); ps.ext = dev_features; ps.commit = true;
-        // Predicted features, logits and top lists live as long as their phase; the last k rows' are all that is read of this commit's
-        // beyond the piece that stays open (7B width, 256 rows: 290 of 2100 us, the block's four products, head and top lists).
-        // What is no number in such a row reaches the open piece through the LSTM states, K or V.
-        ps.kv_only = n - done - m >= d->k;
         // One row costs a chain launch as much as the separate launches (the matrix is read once either way).  A chain launch
         // whose workgroups did not get on the chip together has done nothing; the pass is then run again without, and the pieces behind it too.
         ps.chain = chains && m >= 2;

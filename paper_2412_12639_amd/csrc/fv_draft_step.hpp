@@ -147,7 +147,6 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         int rc = launch_gemm<EL, D, EPI_QKV>(c, Tp, ga, core_kind(GM_QKV), &d->scr);
         if (rc) return rc;
     }
-    if (ps.kv_only) return FV_OK;
     {
         AttnArgs aa;
         aa.q = c->at<uint4>(ly.off_q); aa.q_lo = c->at<uint4>(ly.off_qlo); aa.kc = (const uint4*)c->kc(0); aa.vc = (const uint4*)c->vc(0);

@@ -160,7 +160,6 @@ struct DraftPass {
     int l0 = 0;                      // first entry of this pass in lvl_rows
     std::vector<int> lvl_n;          // rows per LSTM level
     const float* ext = nullptr;      // external features (device), rows addressed by feat_src = -1 - e
-    bool kv_only = false;            // committed pairs whose outputs nobody reads: LSTM states, K and V are all there is to do
     bool commit = false;             // committed pairs: phase rows 0, 1, 2, ... in causal order
     bool chain = false;              // both LSTM layers take all rows (a chain) or levels (a tree) in one launch each (fv_lstm_chain.hpp)
 };

@@ -418,8 +418,8 @@ def test_long_bf16_commit_in_wide_pieces():
 
 
 @pytest.mark.parametrize("n,k", [
-    (68, 4),     # four rows stay open: the piece before them leaves only states, K and V
-    (67, 4),     # three: the first level of the tree comes from the last row of that piece, which is computed in full
+    (68, 4),     # four rows stay open: all that the first level of the tree comes from
+    (67, 4),     # three: its first row comes from the last row of the piece before
     (325, 5),    # three pieces, the open one just long enough
 ])
 def test_tree_behind_a_commit_in_pieces(n, k):
@@ -443,6 +443,60 @@ def test_tree_behind_a_commit_in_pieces(n, k):
     ref = orc.draft(parent, depth, rank, int(toks[-1]), force_tokens=got)
     first = [i for i in range(len(parent)) if depth[i] <= k]     # what the committed rows' lists give
     assert sum(got[i] != ref[i] for i in first) <= 1             # a near-tie at most
+    dr.close()
+    tgt.close()
+
+
+@pytest.mark.parametrize("name", ["tiny-bf16", "tiny"])
+def test_overflow_of_an_early_rows_logits_is_reported(name):
+    """200 pairs of which the fourth alone has infinite logits, from finite states, K and V: eight units that are zero but for it, and a row
+    of the head that is 3e38 there.  Nothing behind that row shows it, so it is found only if every row of every piece goes
+    through block and head."""
+    import torch
+    s, lw, dw, tgt, dr = _make(name, 2, max_seq=300)
+    h, units = s.hidden, np.arange(8)
+
+    def put(w, key, rows, row_of):
+        a = w[key].copy() if w[key].dtype != np.uint16 else (w[key].astype(np.uint32) << 16).view(np.float32)
+        for r, u in zip(rows, units):
+            a[r] = row_of(u, a.shape[1])
+        w[key] = a if w[key].dtype != np.uint16 else (a.view(np.uint32) >> 16).astype(np.uint16)   # (the values put are exact in bf16)
+
+    def zero(u, n):
+        return np.zeros(n, dtype=np.float32)
+
+    def only(col):
+        def row(u, n):
+            v = zero(u, n)
+            v[col(u)] = 8.0
+            return v
+        return row
+
+    for layer, col in ((0, lambda u: 0), (1, lambda u: u)):
+        b = dw[f"lstm{layer}.b"].copy()
+        for gate, bias in ((0, 10.0), (1, -100.0), (2, 0.0), (3, 10.0)):   # in and out open, nothing kept, candidate from one input
+            b[gate * h + units] = bias
+            put(dw, f"lstm{layer}.w_ih", gate * h + units, only(col) if gate == 2 else zero)
+            put(dw, f"lstm{layer}.w_hh", gate * h + units, zero)
+        dw[f"lstm{layer}.b"] = b
+    put(dw, "d.wo", units, zero)
+    put(dw, "d.wd", units, zero)
+    head = lw["lm_head"].copy()
+    head[17] = 0
+    head[17, units] = 0x7F60 if head.dtype == np.uint16 else 2.9774e38
+    lw["lm_head"] = head
+    tgt.init_weights(lw)
+    dr.init_weights(dw)
+    feats = gen_features(4, 200, s.hidden)
+    feats[:, 0] = 0.0
+    toks = np.random.default_rng(4).integers(0, s.vocab, 200)
+    dr.commit(toks, torch.from_numpy(feats).cuda())
+    assert dr.state() == (200, 8, 8) and np.all(dr.rows("logits", 0, 8)[:, 17] == 0.0)
+    dr.reset()
+    feats[3, 0] = 1.0
+    with pytest.raises(Exception) as e:
+        dr.commit(toks, torch.from_numpy(feats).cuda())
+    assert e.value.status == -10
     dr.close()
     tgt.close()
 
