@@ -863,20 +863,22 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
     constexpr bool SPLIT = (E == 8);   // bf16: q and the probabilities enter the matrix cores as hi + lo pairs
     constexpr int NQF = SHARE ? 1 : NF;
     uint4 qf[NQF], qfl[SPLIT ? NQF : 1];
-    uint4* const q_lds = (uint4*)(smem + FV_ATTN_SMEM_FLOATS(D)) + lane;   // SHARE: [fragment][hi, lo][64 lanes]
-    auto q_at = [&](const uint4* q, int fr) { return q[((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t]; };
     if constexpr (SHARE) {
+        // [fragment][hi, lo][64 lanes].  (Declared here and where it is read: outside of them it changed the other form too, whose q loads then waited for
+        // one more integer division.)
+        uint4* const q_lds = (uint4*)(smem + FV_ATTN_SMEM_FLOATS(D)) + lane;
         for (int fr = wave; fr < NF; fr += 4) {
-            q_lds[(2 * fr) * 64] = q_at(a.q, fr);
-            if constexpr (SPLIT) q_lds[(2 * fr + 1) * 64] = q_at(a.q_lo, fr);
+            const size_t at = ((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t;
+            q_lds[(2 * fr) * 64] = a.q[at];
+            if constexpr (SPLIT) q_lds[(2 * fr + 1) * 64] = a.q_lo[at];
         }
         __syncthreads();
     } else {
 #pragma unroll
-        for (int fr = 0; fr < NQF; ++fr) qf[fr] = q_at(a.q, fr);
+        for (int fr = 0; fr < NF; ++fr) qf[fr] = a.q[((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t];
         if constexpr (SPLIT) {
 #pragma unroll
-            for (int fr = 0; fr < NQF; ++fr) qfl[fr] = q_at(a.q_lo, fr);
+            for (int fr = 0; fr < NF; ++fr) qfl[fr] = a.q_lo[((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t];
         }
     }
     uint64_t mk[4];
@@ -915,6 +917,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
 #pragma unroll
         for (int i = 0; i < 16; ++i) { s[i] = 0.f; s1[i] = 0.f; }
         if constexpr (SHARE) {
+            const uint4* const q_lds = (const uint4*)(smem + FV_ATTN_SMEM_FLOATS(D)) + lane;
             uint4 qb[2][4];   // a pair of fragments, hi and lo, read while the pair before multiplies
             auto read_q = [&](int fr, uint4 (&d)[4]) {
 #pragma unroll
@@ -938,11 +941,11 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         } else {
 #pragma unroll
             for (int fr = 0; fr < NF; fr += 2) {
-                s = Tr<EL>::mma(kt[fr], qf[fr % NQF], s);
-                s1 = Tr<EL>::mma(kt[fr + 1], qf[(fr + 1) % NQF], s1);
+                s = Tr<EL>::mma(kt[fr], qf[fr], s);
+                s1 = Tr<EL>::mma(kt[fr + 1], qf[fr + 1], s1);
                 if constexpr (SPLIT) {
-                    s = Tr<EL>::mma(kt[fr], qfl[fr % NQF], s);
-                    s1 = Tr<EL>::mma(kt[fr + 1], qfl[(fr + 1) % NQF], s1);
+                    s = Tr<EL>::mma(kt[fr], qfl[fr], s);
+                    s1 = Tr<EL>::mma(kt[fr + 1], qfl[fr + 1], s1);
                 }
             }
         }
@@ -970,7 +973,6 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         }
         float p[16];
         float mx = -1e30f;
-        auto seen = [&](int i) { return ((vbits >> (8 * (i >> 2) + (i & 3))) & 1u) != 0u; };   // key 8*(i/4) + 4*g + i%4 of the block
         if (SHARE && n0 <= -32) {   // keys every node sees
 #pragma clang fp contract(off)      // the product is rounded before the maximum is taken off, as where it is tested
 #pragma unroll
@@ -978,7 +980,8 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         } else {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                p[i] = seen(i) ? s[i] * a.scale : -1e30f;
+                const bool vis = (vbits >> (8 * (i >> 2) + (i & 3))) & 1u;   // key 8*(i/4) + 4*g + i%4 of the block
+                p[i] = vis ? s[i] * a.scale : -1e30f;
                 mx = fmaxf(mx, p[i]);
             }
         }
@@ -1027,7 +1030,8 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
                 if constexpr (SPLIT) o[db] = Tr<EL>::mma(vt[db * NQ + q], pbl[q], o[db]);
             }
     };
-    for (int kb = kb_lo + wave; kb < kb_hi; kb += 4) {
+    int kb = kb_lo + wave;
+    for (; kb < kb_hi; kb += 4) {
         uint4 kt[NF], vt[DB * NQ];
         load_block(kt, vt, kb);
         __builtin_amdgcn_sched_barrier(0);   // the 16 requests stay together, ahead of everything that uses them
