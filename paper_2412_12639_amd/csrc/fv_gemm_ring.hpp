@@ -194,9 +194,7 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
     // ---- what happens to the sums of a segment: the epilogue if it covered the whole K range, else partial tiles for k_gemm_fix
     auto flush = [&](int gi, int t0, const float* rinv, bool whole, int seg) {
         if (whole) {
-            // one tile after the other (all of what they read would be spilled), what the next one reads requested before this one's stores
-            EpiPre pa, pb;
-            bool have_a = false, have_b = false;
+            // one tile after the other (all of what they read would be spilled)
             auto preload = [&](int i, EpiPre& d) -> bool {
                 const int strip = gi * FV_R + wr * RS + i / CB, tb = t0 / 32 + wc * CB + i % CB;
                 if (strip >= a.n_strips) return false;
@@ -204,29 +202,35 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
                 if constexpr (EPI == EPI_QKV) return rope_preload<D>(a, strip, tb, lane, d);
                 return false;
             };
-            auto tile = [&](int i, EpiPre& cur, bool have, EpiPre& next, bool& have_next) {
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (!WIDE) { if (EPI == EPI_RESID) have = preload(i, cur); }   // rarely here: its own is enough
-                else if (i + 1 < RS * CB) have_next = preload(i + 1, next);
-                __builtin_amdgcn_sched_barrier(0);
+            auto tile = [&](int i, const EpiPre& pre, bool have) {
                 const int strip = gi * FV_R + wr * RS + i / CB, tb = t0 / 32 + wc * CB + i % CB;
                 float v[16];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) v[e] = acc[i / CB][i % CB][e];
-                if (strip < a.n_strips) gemm_epilogue<BF16, D, EPI>(a, ld, strip, tb, lane, v, rinv, cur, have);
+                int ln = lane;
+                if constexpr (!WIDE && EPI == EPI_QKV && D == 64) asm volatile("" : "+v"(ln));   // else all tiles' addresses are computed ahead of the first, and spilled: with 512 threads a wavefront has 256 registers
+                if (strip < a.n_strips) gemm_epilogue<BF16, D, EPI>(a, ld, strip, tb, ln, v, rinv, pre, have);
             };
-            if constexpr (WIDE) have_a = preload(0, pa);
-            tile(0, pa, have_a, pb, have_b);
-            tile(1, pb, have_b, pa, have_a);
-            tile(2, pa, have_a, pb, have_b);
-            tile(3, pb, have_b, pa, have_a);
-            if constexpr (RS * CB == 8) {
-                tile(4, pa, have_a, pb, have_b);
-                tile(5, pb, have_b, pa, have_a);
-                tile(6, pa, have_a, pb, have_b);
-                tile(7, pb, have_b, pa, have_a);
+            if constexpr (WIDE) {   // what the next one reads is requested before this one's stores
+                EpiPre pre[2];
+                bool have[2] = {preload(0, pre[0]), false};
+#pragma unroll
+                for (int i = 0; i < RS * CB; ++i) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (i + 1 < RS * CB) have[(i + 1) & 1] = preload(i + 1, pre[(i + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    tile(i, pre[i & 1], have[i & 1]);
+                }
+            } else {                // rarely here: its own is enough
+#pragma unroll
+                for (int i = 0; i < RS * CB; ++i) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    EpiPre pre;
+                    const bool have = EPI == EPI_RESID && preload(i, pre);
+                    __builtin_amdgcn_sched_barrier(0);
+                    tile(i, pre, have);
+                }
             }
-            static_assert(RS * CB == 4 || RS * CB == 8, "tiles of a wavefront");
         } else {
             const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc((void*)a.part, 0, (int)a.part_bytes, 0x00020000);
 #pragma unroll
