@@ -94,14 +94,16 @@ __device__ __forceinline__ float lstm_gate(float x, bool th) {
 
 // acc += a (two of every four columns) * w, the weights in accumulation registers or in vector registers.  Written out, because the compiler's
 // form copies weights that live in accumulation registers to others before each use (eight moves an instruction, as long as two of
-// them).  It does not see that this is a matrix instruction: chain_mma_done() goes between the last of a row of them and the first use of acc.
+// them).  It does not see that this is a matrix instruction, so the wait states are written here: two in front, for an operand that a vector
+// instruction has just written (500 pairs and a tree at the 7B width 4958 us without, 4961 with), and chain_mma_done() between the last
+// of a row of them and the first use of acc.  That the compiler leaves acc alone in between is checked on the built code (tests/test_kernel_code.py).
 typedef float chain_f4 __attribute__((ext_vector_type(4)));
 typedef unsigned int chain_u4 __attribute__((ext_vector_type(4)));
 typedef unsigned int chain_u8 __attribute__((ext_vector_type(8)));
 template <bool ACC_REGS>
 __device__ __forceinline__ void chain_mma(chain_f4& acc, const chain_u4& a, const chain_u8& w, int pick) {
-    if constexpr (ACC_REGS) asm volatile("v_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "a"(w), "v"(pick));
-    else asm volatile("v_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "v"(w), "v"(pick));
+    if constexpr (ACC_REGS) asm volatile("s_nop 1\n\tv_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "a"(w), "v"(pick));
+    else asm volatile("s_nop 1\n\tv_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "v"(w), "v"(pick));
 }
 __device__ __forceinline__ void chain_mma_done(chain_f4 (&acc)[4]) {
     asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));

@@ -39,6 +39,54 @@ def test_kernels_that_are_meant_to_fit_the_registers_use_no_scratch(code_objects
         notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", str(co)], capture_output=True, text=True, check=True).stdout
         for name, size in re.findall(r"\.name:\s+(_Z\S+).*?\.private_segment_fixed_size:\s+(\d+)", notes, re.S):
             scratch[name] = int(size)
-    meant = {n: b for n, b in scratch.items() if re.match(r"_Z(11k_gemm_ring|6k_attnI|13k_gemm_paired|13k_gemm_direct|10k_gemm_fix|12k_lstm_chain)", n)}
+    meant = {n: b for n, b in scratch.items() if re.match(r"_ZL?(11k_gemm_ring|6k_attnI|13k_gemm_paired|13k_gemm_direct|10k_gemm_fix|12k_lstm_chain)", n)}
     assert len(meant) > 60
     assert not {n: b for n, b in meant.items() if b}
+
+
+def _registers(text):
+    """Vector registers an operand list names."""
+    out = set()
+    for lo, hi in re.findall(r"\bv\[(\d+):(\d+)\]", text):
+        out |= set(range(int(lo), int(hi) + 1))
+    return out | {int(r) for r in re.findall(r"\bv(\d+)\b", text)}
+
+
+def smfmac_faults(lines):
+    """What in a list of instructions the chain kernel's hand-written matrix instructions do not allow: one without wait states in front of
+    it, their sums touched before the wait behind the last, a lane mask written by a vector instruction."""
+    faults, sums, count = [], set(), 0
+    for before, line in zip([""] + lines, lines):
+        op, _, args = line.partition(" ")
+        if op.startswith("v_smfmac"):
+            count += 1
+            if not re.match(r"s_nop [1-9]", before):
+                faults.append(line)
+            sums |= _registers(args.split(",")[0])
+        elif line.startswith("s_nop 15"):
+            sums = set()
+        elif op.startswith("v_cmpx") or sums & _registers(args):
+            faults.append(line)
+    return count, faults
+
+
+def test_the_chain_kernels_matrix_instructions_are_apart_from_what_they_depend_on(code_objects):
+    """They are inline assembly, which the compiler schedules without knowing their hazards."""
+    counts = []
+    for co in code_objects:
+        asm = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", str(co)], capture_output=True, text=True, check=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(_ZL?12k_lstm_chain\S+)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", asm, re.S | re.M):
+            lines = [" ".join(l.split("//")[0].split()) for l in body.splitlines() if l.strip()]
+            count, faults = smfmac_faults(lines)
+            assert not faults, (name, faults[:5])
+            counts.append(count)
+    assert sorted(counts) == [4, 8, 16, 32, 64]      # four gates, one instruction for every 64 columns of a wavefront's quarter
+
+
+def test_the_look_finds_what_it_is_for():
+    ok = ["ds_read_b128 v[20:23], v9", "s_nop 1", "v_smfmac_f32_16x16x64_bf16 v[0:3], v[20:23], a[0:7], v8", "v_mov_b32_e32 v30, v31", "s_nop 1",
+          "v_smfmac_f32_16x16x64_bf16 v[0:3], v[20:23], v[40:47], v8", "s_nop 15", "s_nop 3", "v_add_f32_e32 v0, v0, v1"]
+    assert smfmac_faults(ok) == (2, [])
+    assert len(smfmac_faults([l for l in ok if l != "s_nop 1"])[1]) == 2
+    assert len(smfmac_faults(ok[:3] + ["v_mov_b32_e32 v30, v2"] + ok[3:])[1]) == 1
+    assert len(smfmac_faults(ok[:6] + ok[8:])[1]) == 1
