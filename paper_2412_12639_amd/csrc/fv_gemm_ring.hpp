@@ -7,7 +7,7 @@
 // wavefront whose load is not taken yet stands still with it, matrix instructions included; so four wavefronts (one a SIMD) do nothing
 // but fill the ring, five (256 rows) or eight (128 rows) stages ahead, and the four that multiply issue no load at all.  With the
 // loads in the multiplying wavefronts, one at a time between matrix instructions, the two took as long as their sum: a stage of a
-// prompt's products 0.52 us, now 0.36 to 0.41, where the matrix instructions alone take 0.34 (the chip's power limit, 1.6 PFLOP/s).
+// prompt's products 0.52 us, now 0.36 to 0.41, where the matrix instructions alone take 0.34 (1.6 PFLOP/s over the chip).
 // (Eight multiplying wavefronts that load for themselves: 1 %.)  A step's products read HBM besides, at its latency: 256 rows 0.55.
 //
 // Measured (7B width), loads among the matrix instructions -> this: a prompt of 2000 rows, gate/up 445 -> 340 us, QKV 240 -> 192, O and
@@ -175,8 +175,8 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[r][c][i] = 0.f;
     };
-    // Multiplies a half stage; between(i) runs behind matrix instruction i.  Reads and loads are issued there, one at a time: a
-    // wavefront issues in order, and a burst of them ahead of the matrix instructions leaves the matrix cores idle meanwhile.
+    // Multiplies a half stage; between(i) runs behind matrix instruction i.  The next half's fragments are read there, one at a time: a
+    // wavefront issues in order, and a burst of reads ahead of the matrix instructions leaves the matrix cores idle meanwhile.
     auto mul = [&](const Frags& d, auto&& between) {
 #pragma unroll
         for (int r = 0; r < RS; ++r)
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
             }
     };
     constexpr int NM = RS * CB, NR = RS + CB;   // matrix instructions and fragment reads of a half stage
-    static_assert(NR <= NM && LPS <= NM, "one of each behind a matrix instruction");
+    static_assert(NR <= NM, "one behind a matrix instruction");
 
     // ---- what happens to the sums of a segment: the epilogue if it covered the whole K range, else partial tiles for k_gemm_fix
     auto flush = [&](int gi, int t0, const float* rinv, bool whole, int seg) {

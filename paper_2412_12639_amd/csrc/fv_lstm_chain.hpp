@@ -12,7 +12,7 @@
 //
 // Split: workgroup w owns hidden units 16w .. 16w+15 with their four gates (four 16-row blocks); its four wavefronts
 // take a quarter of the K range each, so a wavefront needs only a quarter of the previous hidden state.  The sums of the
-// four wavefronts meet in LDS (the one barrier of a step), wavefront 0 applies the cell and publishes 16 new values.
+// four wavefronts meet in LDS (one of a step's two barriers; the other is in front of the looks), wavefront 0 applies the cell and publishes 16 new values.
 //
 // Exchange: the hidden state is published as bf16 (what the weight multiplication takes) in two buffers used in turn, by
 // write-through stores, and read past the caches.  No flag or barrier across workgroups: |h| <= 1, so bit 14 of its bf16
@@ -60,8 +60,9 @@ constexpr size_t lstm_chain_smem(int nkf) {
 // Sigmoid, or tanh, of a gate: both from e^-|a| (a = x or 2x) and one quotient, without a branch between the lanes of different gates
 // (the library's functions, of which every lane ran both, took two thirds of the cell's 0.63 us).  The exponential is the Taylor polynomial
 // behind a reduction by multiples of ln 2: the hardware's own, a unit in the last place off, gave tanh a larger error than the library's.
-// Small tanh by its series, where 1 - e cancels.  Largest error against 64 bits over 1e-6 .. 100, absolute and relative (the library's):
-// sigmoid 0.44e-7 and 1.18e-7 (0.89e-7 and 1.47e-7), tanh 0.66e-7 and 1.31e-7 (0.82e-7 and 1.46e-7).
+// Small tanh by its series, where 1 - e cancels.  Largest error against 64 bits, absolute and relative, of every 61st value of 1e-6 .. 128 and all
+// around the ends of series and saturation, reciprocal exact or a unit off (tests/test_lstm_gate.py; in brackets the library's, 1e-6 .. 100):
+// sigmoid 0.44e-7 and 1.18e-7 (0.89e-7 and 1.47e-7), tanh 0.67e-7 and 1.33e-7 (0.82e-7 and 1.46e-7).  |result| <= 1, which the exchange relies on.
 __device__ __forceinline__ float lstm_gate(float x, bool th) {
     const float ax = fabsf(x), a = fminf(th ? 2.f * ax : ax, 104.f);   // e^-104 is zero in 32 bits
     const float n = rintf(a * -1.44269504f), y = fmaf(n, 1.90465421e-9f, fmaf(n, -0.693147182f, -a));   // -a = n ln 2 + y
@@ -114,7 +115,6 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
     typedef float floatx4 __attribute__((ext_vector_type(4)));
     typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
     typedef unsigned int u32x8_t __attribute__((ext_vector_type(8)));
-    typedef __bf16 bf16x16_t __attribute__((ext_vector_type(16)));
     constexpr int NM = NKF / 2, RM = lstm_chain_reg_frags(NKF) / 2, LM = NM - RM;   // 64-column instructions per gate; with their weights in registers, in LDS
     constexpr int GM = NM < 4 ? NM : 4;
     constexpr int PIN = RM * 4 < 30 ? 0 : 30;   // weights in accumulation registers

@@ -122,10 +122,13 @@ int set_gemm_attrs_d() {
     if (!rc) rc = set_gemm_attrs_e<EL, D, EPI_LOGITS>();
     return rc;
 }
-// Which form of the attention: SHARE (two workgroups a compute unit) where there are at least half as many items as compute units.  us a
-// layer against the other form at the same split: 128 items 0 to 1 less at 11 to 50 blocks of keys, 2.3 less at 125; 256 items 0.3 to 4 less;
-// 320 items of 13B at 18 blocks 27.4 -> 19.6, at 130 blocks 113 -> 73.6; head size 64, 512 items, 14.9 -> 13.7 and 68 -> 57; a prompt of
-// 2000 rows 122 -> 84.  Fewer items: equal to 0.7 more.  bf16 only (fp32 tiles do not fit half a register file).
+// Which form of the attention: SHARE (two workgroups a compute unit; the same bits) where there are at least half as many items as compute
+// units.  us a layer, the other form -> this one, the same key split.  More workgroups than compute units: 320 items of 13B at 10 blocks 20.4 ->
+// 15.0, at 127 104 -> 69; its 160 items in three parts at 132 blocks 50.7 -> 36.8; 512 items of 70B at 30 blocks 38.0 -> 28.7; a prompt of 2000 rows,
+// 7B, 66 -> 49.  One each, where only the blocks without tests gain: 128 items in two parts equal at 5 to 25 blocks, 1.0 less at 129; 160 in one part
+// equal at 10 and 25, 1.6 less at 94; 256 items 0.3 to 0.8 more at 10 to 30, 0.6 less at 43, 1.9 less at 127.  Fewer items: equal to 0.7 more.
+// (Requesting a key block ahead in registers instead: slower than the other form below 60 blocks, up to 2 less above.)  bf16 only: fp32 tiles do
+// not fit half a register file.
 template <typename EL>
 static bool attn_shares(int items) { return Tr<EL>::E == 8 && items >= 128; }
 
