@@ -1003,8 +1003,11 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         }
         float psum = 0.f;
         if (SHARE && n0 <= -32) {
+            // What the test below leaves out counts for nothing here either: a score that is no number, and one of -1e29 or less while the
+            // reference, which starts at -1e30, is that low too; against the next number above -1e29 its exponential is zero.
+            const float m_ref = fmaxf(m_run, -0x1.431e0ep+96f);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) { p[i] = fmaxf(__expf(p[i] - m_run), 0.f); psum += p[i]; }   // a score that is no number counts for nothing, as below
+            for (int i = 0; i < 16; ++i) { p[i] = fmaxf(__expf(p[i] - m_ref), 0.f); psum += p[i]; }
         } else {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {

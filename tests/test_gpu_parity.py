@@ -882,3 +882,26 @@ def test_both_forms_of_the_attention_compute_the_same_bits(fvmod, d, L):
     g.verify_tree(tokens[:32], parent[:32], depth[:32])
     assert np.array_equal(g.logits(32), want)
     g.close()
+
+
+def test_both_forms_of_the_attention_count_the_same_scores(fvmod):
+    """Scores of -4e29, below what counts as masked but above where the running maximum starts: the block of 32 keys that every node sees has
+    to count for nothing in the form without tests as well."""
+    s = ModelShape("low-scores", 1, 256, 64, 8, 64, 272, 600, "bf16")
+    w = dict(fi.gen_weights(s, seed=3))
+    bits = lambda x: np.uint16(np.float32(x).view(np.uint32) >> 16)
+    w["embed"] = w["embed"].copy()
+    w["embed"][:, 0] = bits(8.0)                  # 16 after the norm, in every row
+    for name, value in (("l0.wq", 1.118e14), ("l0.wk", -1.118e14)):
+        w[name] = np.zeros_like(w[name])
+        w[name][31::64, 0] = bits(value)          # the slowest rotation: the same sign at all positions
+    parent, depth, _ = fi.gen_tree(1, 64, [8, 4, 2, 2, 1, 1])
+    g = make_gpu(fvmod, s, w, max_seq=128, max_tree=64)
+    root = g.prefill(fi.gen_prefix(1, 32, s.vocab))
+    tokens = fi.trees.fill_tokens(1, parent, s.vocab, root)
+    g.verify_tree(tokens, parent, depth)
+    want = g.logits(64)[:32].copy()
+    g.rollback(32, root)
+    g.verify_tree(tokens[:32], parent[:32], depth[:32])
+    assert np.array_equal(g.logits(32), want)
+    g.close()
