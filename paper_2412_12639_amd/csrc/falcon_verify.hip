@@ -130,7 +130,7 @@ void plan_gemm_forms(GemmPlan& gm, GemmPlan& gd, GemmPlan& gp, bool& paired_ok, 
     // Above 64 rows a partial tile is 64 or 128 KiB, so bf16 row groups are cut into equal parts, one a workgroup, where that
     // occupies at least three quarters of the chip: 192 partial tiles instead of 352 for QKV at the 7B shape, none
     // instead of 500 for its head.  (256 rows, 7B: QKV 43.0 us either way and 10 -> 6 us to reduce, head 86 + 17 -> 86.  Its gate/up on 172
-    // workgroups takes 67.2 us against 61.2 + 11.7 on 256, at 128 rows 53.1 against 47.7 + 7.6; it keeps its equal ranges all the same: 1 % of a
+    // workgroups takes 67.2 us against 61.2 + 11.7 on 256, at 128 rows 53.1 against 47.7 + 7.6; it keeps its equal ranges all the same: 2 % of a
     // step does not pay for sums in another order, which draws of a non-greedy step feel.)  fp32, whose
     // kernel multiplies far longer per row group, needs every compute unit (two layers of the 7B width and head, 100 rows 1372 us against
     // 1405 on equal parts, 250 rows 2534 against 2600).
