@@ -87,8 +87,8 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
         char* const w = ring + fslot * SB + wave * 2048;
         char* const x = ring + fslot * SB + AB + wave * (TT * 16);
         switch (i) {
-            case 0: __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 0, 0); break;
-            case 1: __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 1024, 0); break;
+            case 0: __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 0, WIDE ? 0 : FV_READ_ONCE); break;
+            case 1: __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 1024, WIDE ? 0 : FV_READ_ONCE); break;
             case 2: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 0, 0); break;
             case 3: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 1024, 0); break;
             case 4: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 2048, 0); break;

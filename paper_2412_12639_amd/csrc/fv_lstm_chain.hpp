@@ -110,6 +110,9 @@ __device__ __forceinline__ void chain_mma_done(chain_f4 (&acc)[4]) {
     asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
 }
 
+// The recurrent matrix, read once a launch: past the caches where it is as large as the L2s and more (33 and 134 MB).
+template <int NKF> __device__ __forceinline__ uint4 ld_matrix(const uint4* p) { return NKF >= 16 ? ld_once(p) : *p; }
+
 template <int NKF>
 static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
     typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -150,7 +153,7 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             const int m = LM > 0 ? i / 3 * 4 + i % 3 : i;
-            const uint4 lo = *w_addr(g, 2 * m), hi = *w_addr(g, 2 * m + 1);
+            const uint4 lo = ld_matrix<NKF>(w_addr(g, 2 * m)), hi = ld_matrix<NKF>(w_addr(g, 2 * m + 1));
             w[i][g] = u32x8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
         }
     // The matrix instructions take their operand from the accumulation registers as well, but the compiler, left alone, parks
@@ -165,7 +168,7 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) v[g][e] = *w_addr(g, 2 * (4 * i + 3) + e);
+            for (int e = 0; e < 2; ++e) v[g][e] = ld_matrix<NKF>(w_addr(g, 2 * (4 * i + 3) + e));
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
@@ -383,7 +386,7 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_levels(LstmLevelArgs la)
 #pragma unroll
     for (int i = 0; i < RKF; ++i)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) w[i][g] = *(const u32x4_t*)w_addr(g, LKF > 0 ? i / 3 * 4 + i % 3 : i);
+        for (int g = 0; g < 4; ++g) w[i][g] = __builtin_bit_cast(u32x4_t, ld_matrix<NKF>(w_addr(g, LKF > 0 ? i / 3 * 4 + i % 3 : i)));
 #pragma unroll
     for (int i = 0; i < RKF; ++i)
 #pragma unroll
@@ -392,7 +395,7 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_levels(LstmLevelArgs la)
     for (int i = 0; i < LKF; ++i) {
         uint4 v[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) v[g] = *w_addr(g, 4 * i + 3);
+        for (int g = 0; g < 4; ++g) v[g] = ld_matrix<NKF>(w_addr(g, 4 * i + 3));
 #pragma unroll
         for (int g = 0; g < 4; ++g) wl[(i * 4 + g) * 64] = v[g];
     }
