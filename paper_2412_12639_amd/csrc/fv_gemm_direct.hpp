@@ -18,14 +18,18 @@
 //
 // A stage is 8 weight tiles of 1 KiB: RS = 1: 8 fragments of one strip (a K batch) with 8*TB
 // activation tiles; RS = 2: 4 fragments of each of two strips (half a K batch) with 4*TB
-// activation tiles.  Tiles are requested three stages ahead into three rotating register sets in a
-// fixed issue order, so the hardware's in-order load counter lets each wait be exact.
+// activation tiles.  Tiles are requested two (RS = 2) or three (RS = 1) stages ahead into as many rotating
+// register sets in a fixed issue order, so the hardware's in-order load counter lets each wait be exact.
+// Two of the paired form's stages under way in each of three wavefronts, 48 KiB of weights a compute unit, take in
+// all that HBM gives (a launch that only reads: 6.6 TB/s from 48 KiB on); a third only queues up in front of
+// the exchange's looks, and 64 rows of 7B take 3719 us a step with it, 3667 without, one row in four layers 498 and 493.
+// The direct form's matrices are so short that a slice is three stages or a few more.
 //
 // The streaming loop is kept to the instructions that matter.  With one wavefront per SIMD nothing
 // hides instruction issue, and an earlier form of this loop (a general cursor advanced three times
 // per stage, accumulators shuttled between the two register files around a conditional) spent
 // more cycles on bookkeeping than on waiting for HBM.  Now: every slice is padded to whole rounds
-// of three stages; a padded stage loads 16 bytes of zeros per instruction instead of tiles, so
+// of that many stages; a padded stage loads 16 bytes of zeros per instruction instead of tiles, so
 // its MFMAs add nothing and the loop body has no conditional at all; addresses advance by
 // constants inside a slice and are recomputed only when the request stream enters the next slice.
 #pragma once
@@ -83,11 +87,11 @@ struct DPlan {
 };
 
 // Request stream of one wavefront: the stages of its slices in order, every slice padded to a
-// multiple of three stages.  (wp, xp) are this lane's addresses for the current stage; past the
+// multiple of the register sets.  (wp, xp) are this lane's addresses for the current stage; past the
 // real stages of a slice, and past the last slice, `live` is false and the loads read zeros.
 struct DReq {
     int s;          // slice (= segment) being requested; nseg when the stream has ended
-    int j, n, n3;   // padded stage index inside the slice, real stages, padded stages
+    int j, n, np;   // padded stage index inside the slice, real stages, padded stages
     const uint4* wp;
     const uint4* xp;
 };
@@ -99,6 +103,7 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
     constexpr int SF = FV_FRAGS / RS;            // fragments per stage
     constexpr int NX = SF * TB;                  // activation tiles per stage
     constexpr int NT = RS * TB;                  // accumulator tiles per wavefront
+    constexpr int SETS = RS == 2 ? 2 : 3;        // register sets, that is stages under way
     static_assert(RS == 1 || RS == 2, "one or two strips per wavefront");
     float* red = smem;                           // [2][streaming wavefront][tile][16][64]
     float* rinv_lds = red + 2 * FV_STREAMERS * NT * 1024;
@@ -149,12 +154,12 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
     // ---- request stream
     DReq rq;
     auto enter_slice = [&](int s) {     // position the stream at the first non-empty slice >= s
-        rq.s = s; rq.j = 0; rq.n = 0; rq.n3 = 0; rq.wp = zeros; rq.xp = zeros;
+        rq.s = s; rq.j = 0; rq.n = 0; rq.np = 0; rq.wp = zeros; rq.xp = zeros;
         while (rq.s < nseg) {
             int gi, ws, we;
             pl.slice(rq.s, gi, ws, we);
             if (we > ws) {
-                rq.n = we - ws; rq.n3 = (rq.n + 2) / 3 * 3;
+                rq.n = we - ws; rq.np = (rq.n + SETS - 1) / SETS * SETS;
                 // weights are tiled [strip pair][half K batch][2 strips][4 frags]: a paired stage (half a batch of both
                 // strips) is 8 KiB contiguous, a one-strip stage (a whole batch of one strip) two 4 KiB pieces 8 KiB apart
                 rq.wp = (RS == 2) ? a.Wt + ((size_t)gi * a.NB + ws) * (FV_FRAGS * 64) + lane
@@ -197,24 +202,24 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
         ++rq.j;
         rq.wp += (RS == 2 ? FV_FRAGS : 2 * FV_FRAGS) * 64;
         rq.xp += 2 * SF * Tp;
-        if (rq.j >= rq.n3) enter_slice(rq.s + 1);   // also taken, harmlessly, once the stream has ended
+        if (rq.j >= rq.np) enter_slice(rq.s + 1);   // also taken, harmlessly, once the stream has ended
     };
 
-    uint4 x[3][NX], w[3][FV_FRAGS];
+    uint4 x[SETS][NX], w[SETS][FV_FRAGS];
     // Timing aid (stand-alone probe builds only): with FV_PROBE_NO_W / FV_PROBE_NO_X the weight / activation
     // requests are left out and the matrix instructions run on constants, which shows what a launch costs
     // apart from its operand traffic.  The results are meaningless; nothing in the library defines these.
 #ifdef FV_PROBE_NO_W
-    for (int i_ = 0; i_ < 3; ++i_) for (int j_ = 0; j_ < FV_FRAGS; ++j_) w[i_][j_] = make_uint4(tid, 1, 0, 0);
+    for (int i_ = 0; i_ < SETS; ++i_) for (int j_ = 0; j_ < FV_FRAGS; ++j_) w[i_][j_] = make_uint4(tid, 1, 0, 0);
 #endif
 #ifdef FV_PROBE_NO_X
-    for (int i_ = 0; i_ < 3; ++i_) for (int j_ = 0; j_ < NX; ++j_) x[i_][j_] = make_uint4(tid, 0, 0, 0);
+    for (int i_ = 0; i_ < SETS; ++i_) for (int j_ = 0; j_ < NX; ++j_) x[i_][j_] = make_uint4(tid, 0, 0, 0);
 #endif
     enter_slice(0);
     FV_TS(2)
     // prologue in the loop's own issue order: X(0) W(0) X(1) W(1) X(2) W(2)
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < SETS; ++i) {
         load_x(x[i]);
         __builtin_amdgcn_sched_barrier(0);
         load_w(w[i]);
@@ -240,7 +245,7 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
         __syncthreads();
     }
 
-    // One stage: multiply what register set S holds, then request into it the stage three ahead.
+    // One stage: multiply what register set S holds, then request into it the stage SETS ahead.
 #define FV_DSTAGE(S)                                                                        \
     {                                                                                       \
         _Pragma("unroll") for (int r_ = 0; r_ < RS; ++r_)                                   \
@@ -412,13 +417,13 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
         if (wave < FV_STREAMERS) {
             int gi, ws, we;
             pl.slice(s, gi, ws, we);
-            const int rounds = (we - ws + 2) / 3;
+            const int rounds = (we - ws + SETS - 1) / SETS;
             floatx16 acc[NT];
             zero_acc<NT>(acc);
             for (int r = 0; r < rounds; ++r) {
                 FV_DSTAGE(0)
                 FV_DSTAGE(1)
-                FV_DSTAGE(2)
+                if constexpr (SETS > 2) FV_DSTAGE(2)
             }
             // this wavefront's sums of segment s (zeros if none of its stages were ours) into LDS
             // (16 bytes per lane and access: [area][wavefront][tile][register quad][lane])
