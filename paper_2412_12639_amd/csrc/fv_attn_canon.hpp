@@ -59,8 +59,9 @@ struct CanonArgs {
 #define FV_CANON_VSTRIDE 24
 #define FV_CANON_WIN_BYTES(D, ESZ) \
     (32 * FV_CANON_SROW * 4 + FV_CANON_WIN_BLOCKS * ((D) / 32) * (ESZ) * 64 * FV_CANON_VSTRIDE)   /* NQ = 32 / (2E) = ESZ */
+#define FV_CANON_MERGE_FLOATS(D) (3 * ((D) / 32) * 64 * 16 + 8 * 32 + 4)   // accumulators of three wavefronts, maxima and sums of four
 #define FV_CANON_SMEM_BYTES(D, ESZ) \
-    (FV_CANON_WIN_BYTES(D, ESZ) > FV_ATTN_SMEM_FLOATS(D) * 4 ? FV_CANON_WIN_BYTES(D, ESZ) : FV_ATTN_SMEM_FLOATS(D) * 4)
+    (FV_CANON_WIN_BYTES(D, ESZ) > FV_CANON_MERGE_FLOATS(D) * 4 ? FV_CANON_WIN_BYTES(D, ESZ) : FV_CANON_MERGE_FLOATS(D) * 4)
 
 // Wavefront-wide maximum and sum through the cross-lane data path (no LDS round trips): four steps
 // inside each row of 16 lanes, then row 0 into 1 and 2 into 3, then the lower half into the upper;

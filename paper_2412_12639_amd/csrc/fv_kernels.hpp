@@ -840,7 +840,7 @@ struct AttnArgs {
     int* tickets;
 };
 
-#define FV_ATTN_SMEM_FLOATS(D) (3 * ((D) / 32) * 64 * 16 + 8 * 32 + 4)
+#define FV_ATTN_SMEM_FLOATS(D) (4 * ((D) / 32) * 64 * 16 + 8 * 32 + 4)   // [feature block][wavefront][4 quads][64 lanes][4], then maxima and sums
 #define FV_ATTN_PART_FLOATS(D) (((D) / 32) * 1024 + 64)
 
 // One (query head, block of 32 nodes) item, key part `part` of a.ks.  SHARE: two workgroups of this form fit a compute unit, so that
@@ -866,7 +866,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
     if constexpr (SHARE) {
         // [fragment][hi, lo][64 lanes].  (Declared here and where it is read: outside of them it changed the other form too, whose q loads then waited for
         // one more integer division.)
-        uint4* const q_lds = (uint4*)(smem + FV_ATTN_SMEM_FLOATS(D)) + lane;
+        uint4* const q_lds = (uint4*)smem + lane;
         for (int fr = wave; fr < NF; fr += 4) {
             const size_t at = ((size_t)(qh * (D / E) + 2 * fr + g)) * a.ld + t;
             q_lds[(2 * fr) * 64] = a.q[at];
@@ -917,7 +917,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
 #pragma unroll
         for (int i = 0; i < 16; ++i) { s[i] = 0.f; s1[i] = 0.f; }
         if constexpr (SHARE) {
-            const uint4* const q_lds = (const uint4*)(smem + FV_ATTN_SMEM_FLOATS(D)) + lane;
+            const uint4* const q_lds = (const uint4*)smem + lane;
             uint4 qb[2][4];   // a pair of fragments, hi and lo, read while the pair before multiplies
             auto read_q = [&](int fr, uint4 (&d)[4]) {
 #pragma unroll
@@ -1042,71 +1042,62 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
     }
     l_run += __shfl_xor(l_run, 32);
 
-    // ---- merge the four wavefronts: 1..3 park their accumulators in LDS, wavefront 0 combines
-    float* so = smem;                              // [3][DB][64][16]
-    float* sm = smem + 3 * DB * 64 * 16;           // [4][32] running max
+    // ---- merge the four wavefronts: all park their accumulators in LDS, wavefront w combines 32-feature block w (blocks beyond D/32
+    // have no wavefront).  With all blocks combined by wavefront 0 this, and the stores behind it, took four times as long.
+    float* so = smem;                              // [DB][4 wavefronts][4 quads][64 lanes][4]
+    float* sm = smem + 4 * DB * 64 * 16;           // [4][32] running max
     float* sl = sm + 4 * 32;                       // [4][32] running sum
-    if (wave > 0) {
+    if constexpr (SHARE) __syncthreads();          // q lies there
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                ((float4*)so)[(((wave - 1) * DB + db) * 64 + lane) * 4 + q] =
-                    make_float4(o[db][4 * q], o[db][4 * q + 1], o[db][4 * q + 2], o[db][4 * q + 3]);
-    }
+        for (int q = 0; q < 4; ++q)
+            ((float4*)so)[((db * 4 + wave) * 4 + q) * 64 + lane] = make_float4(o[db][4 * q], o[db][4 * q + 1], o[db][4 * q + 2], o[db][4 * q + 3]);
     if (g == 0) { sm[wave * 32 + tl] = m_run; sl[wave * 32 + tl] = l_run; }
     __syncthreads();
     int* ticket_lds = (int*)(sl + 4 * 32);
     float M = -1e30f, lsum = 0.f;
-    float r[DB][16];
-    if (wave == 0) {
+    float r[16];
+    if (wave < DB) {
 #pragma unroll
         for (int w = 0; w < 4; ++w) M = fmaxf(M, sm[w * 32 + tl]);
         float wgt[4];
 #pragma unroll
         for (int w = 0; w < 4; ++w) { wgt[w] = __expf(sm[w * 32 + tl] - M); lsum += wgt[w] * sl[w * 32 + tl]; }
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
+        for (int w = 0; w < 4; ++w)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) r[db][i] = wgt[0] * o[db][i];
-#pragma unroll
-            for (int w = 1; w < 4; ++w)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 v = ((const float4*)so)[(((w - 1) * DB + db) * 64 + lane) * 4 + q];
-                    r[db][4 * q] += wgt[w] * v.x; r[db][4 * q + 1] += wgt[w] * v.y;
-                    r[db][4 * q + 2] += wgt[w] * v.z; r[db][4 * q + 3] += wgt[w] * v.w;
-                }
-        }
+            for (int q = 0; q < 4; ++q) {
+                const float4 v = ((const float4*)so)[((wave * 4 + w) * 4 + q) * 64 + lane];
+                if (w == 0) { r[4 * q] = wgt[0] * v.x; r[4 * q + 1] = wgt[0] * v.y; r[4 * q + 2] = wgt[0] * v.z; r[4 * q + 3] = wgt[0] * v.w; }
+                else { r[4 * q] += wgt[w] * v.x; r[4 * q + 1] += wgt[w] * v.y; r[4 * q + 2] += wgt[w] * v.z; r[4 * q + 3] += wgt[w] * v.w; }
+            }
     }
     if (a.ks == 1) {
-        if (wave == 0) {
+        if (wave < DB) {
             const float inv = (lsum > 0.f) ? 1.f / lsum : 0.f;
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int blk = 0; blk < 4; ++blk)
-                    store4_act<EL>(a.out, a.ld, qh * D + db * 32 + 8 * blk + 4 * g, t, r[db][4 * blk] * inv,
-                                        r[db][4 * blk + 1] * inv, r[db][4 * blk + 2] * inv, r[db][4 * blk + 3] * inv);
+            for (int blk = 0; blk < 4; ++blk)
+                store4_act<EL>(a.out, a.ld, qh * D + wave * 32 + 8 * blk + 4 * g, t, r[4 * blk] * inv, r[4 * blk + 1] * inv, r[4 * blk + 2] * inv,
+                               r[4 * blk + 3] * inv);
         }
         return;
     }
     // ---- several workgroups share this item: partial triple out (agent-scope atomic stores,
     // acknowledged), ticket, and the last arriver combines all parts in part order
     constexpr int PF = FV_ATTN_PART_FLOATS(D);
-    if (wave == 0) {
+    if (wave < DB) {
         float* pp = a.part + (size_t)(item * a.ks + part) * PF + lane;
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) __hip_atomic_store(pp + (db * 16 + i) * 64, r[db][i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (g == 0) {
+        for (int i = 0; i < 16; ++i) __hip_atomic_store(pp + (wave * 16 + i) * 64, r[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (wave == 0 && g == 0) {
             __hip_atomic_store(pp + DB * 1024, M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);         // lanes 0..31
             __hip_atomic_store(pp + DB * 1024 + 32, lsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         handoff_release();
-        if (lane == 0) *ticket_lds = __hip_atomic_fetch_add(&a.tickets[item], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    __syncthreads();   // every wavefront's stores are acknowledged
+    if (tid == 0) *ticket_lds = __hip_atomic_fetch_add(&a.tickets[item], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     handoff_acquire();
     if (*ticket_lds != a.ks - 1) return;
@@ -1149,7 +1140,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
 // grid = items * ks
 template <typename EL, int D, bool SHARE>
 __global__ __launch_bounds__(256, SHARE ? 2 : 1) void k_attn(AttnArgs a) {
-    __shared__ __attribute__((aligned(16))) float smem[FV_ATTN_SMEM_FLOATS(D) + (SHARE ? D * 32 : 0)];
+    __shared__ __attribute__((aligned(16))) float smem[FV_ATTN_SMEM_FLOATS(D)];   // (SHARE: q lies where the accumulators are parked at the end)
     // Workgroups go to the 8 XCDs round-robin (workgroup b runs on XCD b % 8) and every XCD has its
     // own L2, so all node blocks and key parts of a query head -- and the query heads that share a
     // KV head -- are given to workgroups of one XCD: a head's K/V then comes from HBM once and is
