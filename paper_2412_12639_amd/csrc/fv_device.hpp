@@ -83,6 +83,15 @@ template <> struct Tr<F32> {
     }
 };
 
+// Division by a number that the host knows: two multiplications and a correction in scalar registers.  The compiler's own way, a reciprocal through the
+// vector unit, is some twenty dependent instructions; a kernel that splits its work by several of them asked for its first tile half a microsecond later.
+struct Div { unsigned d, m; };                       // divisor, floor(2^32 / d)
+inline Div make_div(unsigned d) { return Div{d, d > 1 ? (unsigned)((1ull << 32) / d) : 0xffffffffu}; }
+__host__ __device__ __forceinline__ unsigned operator/(unsigned v, const Div& k) {
+    const unsigned q = (unsigned)(((unsigned long long)v * k.m) >> 32);   // the quotient, or one less: v / d - v * (2^32 / d - m) / 2^32, the last term below 1
+    return v - q * k.d >= k.d ? q + 1 : q;
+}
+
 // A 16-byte load of what a launch reads once (weights): not kept in the caches behind it.  A launch of 256 workgroups that does nothing but
 // read reaches 5.8 to 6.0 TB/s with plain loads and 6.3 to 6.6 with these (100 and 183 MB at a time out of 3 GB); where the bytes lie in the
 // memory-side cache already it is no slower (100 MB read again and again 6.7 -> 7.5, 25 MB 10.1 -> 11.0).

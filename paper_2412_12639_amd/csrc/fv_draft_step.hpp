@@ -31,7 +31,7 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         memset(&ga, 0, sizeof(ga));
         ga.Wt = (const uint4*)Wt; ga.X = (const uint4*)X; ga.part = d->scr.part; ga.part_bytes = d->scr.part_bytes;
         ga.tickets = d->scr.tickets; ga.zeros = c->at<uint4>(ly.off_zeros);
-        ga.NG = p.NG; ga.NB = p.NB; ga.G = p.G; ga.segmax = p.segmax; ga.aligned = p.aligned;
+        set_split(ga, p);
         ga.tab_u0 = (const int*)(d->arena + p.off_tab); ga.tab_g0 = ga.tab_u0 + p.G + 1; ga.tab_cf = ga.tab_g0 + p.G; ga.tab_cl = ga.tab_cf + p.NG;
         ga.fix_groups = (const int4*)(ga.tab_u0 + (((size_t)2 * p.G + 1 + 2 * p.NG + 3) & ~(size_t)3)); ga.n_fix = p.n_fix;
         ga.rinv_out = c->at<float>(ly.off_rinv);

@@ -48,24 +48,11 @@
 struct DPlan {
     int u0, u1, g0, nseg, NB, wave;
     __device__ __forceinline__ void init(const GemmArgs& a, int wg, int wave_) {
-        // computed, not looked up: a table read would put one more memory round trip in front of
-        // the first weight load
-        // (32-bit arithmetic: the host only selects these kernels when NG * NB * G < 2^31; G is a
-        // power of two whenever there is at least one unit per compute unit, and then a shift)
-        const unsigned G = (unsigned)a.G;
-        const bool pow2 = (G & (G - 1)) == 0;
-        const int sh = 31 - __builtin_clz(G);
-        auto divG = [&](unsigned v) { return pow2 ? (v >> sh) : v / G; };
-        if (a.aligned) {   // whole row groups per workgroup: counts differ by at most one
-            u0 = (int)divG((unsigned)(a.NG * wg)) * a.NB;
-            u1 = (int)divG((unsigned)(a.NG * (wg + 1))) * a.NB;
-        } else {
-            const unsigned U = (unsigned)(a.NG * a.NB);
-            u0 = (int)divG(U * (unsigned)wg);
-            u1 = (int)divG(U * (unsigned)(wg + 1));
-        }
+        // computed, not looked up: a table read would put one more memory round trip in front of the first weight load
+        u0 = split_unit(a, wg);
+        u1 = split_unit(a, wg + 1);
         NB = a.NB; wave = wave_;
-        g0 = u0 / NB;
+        g0 = (int)((unsigned)u0 / a.div_NB);
         nseg = 1;
         for (int e_ = (g0 + 1) * NB; e_ < u1; e_ += NB) ++nseg;
     }
@@ -123,23 +110,21 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
     // The partial sums of a token are added in an order that does not depend on the number of tokens
     // (SL slices whatever Tp is: with 32 tokens half of the threads sit this out), so a row's factor,
     // and with it everything computed from it, is bitwise the same in a step of 1 and of 64 rows.
+    // Rows that are not there read as zeros, behind the end of the buffer: with branches around the loads the compiler put a wait for the
+    // first ones between them, a round trip before the first weight was asked for.
     static_assert(TB <= 2, "the statistics reduction is laid out for up to 64 tokens");
     if (with_norm) {
         constexpr int C4 = Tp / 4, SL = 16;
         const int col = tid % C4, sl = tid / C4;
-        const float4* sp = (const float4*)a.ssq_in + col;
+        const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc((void*)a.ssq_in, 0, a.n_ssq * (Tp * 4), 0x00020000);
+        const unsigned at = sl < SL ? (unsigned)(sl * C4 + col) * 16u : 0x80000000u;
+        auto row = [&](int i) { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(srs, at + (unsigned)(i * (Tp * 4)), 0, 0)); };
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int i = sl + k * SL;
-            sv[k] = (sl < SL && i < a.n_ssq) ? sp[(size_t)i * C4] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        for (int i0 = sl + 8 * SL; sl < SL && i0 < a.n_ssq; i0 += 8 * SL) {   // more than 8 rows per thread (hidden size above 256 * SL)
+        for (int k = 0; k < 8; ++k) sv[k] = row(k * SL);
+        for (int i0 = 8 * SL; i0 < a.n_ssq; i0 += 8 * SL) {   // more than 8 rows per thread (hidden size above 256 * SL)
             float4 v[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int i = i0 + k * SL;
-                v[k] = (i < a.n_ssq) ? sp[(size_t)i * C4] : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+            for (int k = 0; k < 8; ++k) v[k] = row(i0 + k * SL);
 #pragma unroll
             for (int k = 0; k < 8; ++k) { s4.x += v[k].x; s4.y += v[k].y; s4.z += v[k].z; s4.w += v[k].w; }
         }
@@ -467,6 +452,7 @@ __device__ __forceinline__ int split_index(const GemmArgs& a) {
 template <typename EL, int TB, int D, int EPI>
 __global__ __launch_bounds__(256, 1) void k_gemm_direct(GemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) float smem_dyn[];   // FV_DIRECT_SMEM_FLOATS(TB) floats
+    request_args(a);
     gemm_direct_body<EL, TB, D, EPI>(a, split_index(a), smem_dyn);
 }
 
@@ -474,5 +460,6 @@ __global__ __launch_bounds__(256, 1) void k_gemm_direct(GemmArgs a) {
 template <typename EL, int TB, int D, int EPI>
 __global__ __launch_bounds__(256, 1) void k_gemm_paired(GemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) float smem_dyn[];   // FV_PAIRED_SMEM_FLOATS(TB) floats
+    request_args(a);
     gemm_direct_body<EL, TB, D, EPI, 2>(a, split_index(a), smem_dyn);
 }

@@ -50,6 +50,7 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
     const bool filler = __builtin_amdgcn_readfirstlane(tid >> 8) != 0;
     const int wr = wave >> 1, wc = wave & 1;
+    request_args(a);
     const int NST = 4 * a.NB;                           // stages of a row group
     const int ld = WIDE ? a.ld : TT;                    // rows of the activation buffers
     int g0, k0, n;                                      // first group, its first stage, stages
@@ -66,9 +67,8 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
         const int mine = (a.NG - 1 - xcd) / 8 * tiles + tiles;   // tiles of this XCD
         k0 = 0; n = ((mine - 1 - ti) / t_step + 1) * NST;
     } else {
-        const long long U = (long long)a.NG * a.NB;     // computed, not looked up, as in k_gemm
-        const int u0 = (int)(U * blockIdx.x / a.G), u1 = (int)(U * (blockIdx.x + 1) / a.G);
-        g0 = u0 / a.NB; k0 = 4 * (u0 - g0 * a.NB); n = 4 * (u1 - u0);
+        const int u0 = split_unit(a, blockIdx.x), u1 = split_unit(a, blockIdx.x + 1);   // computed, not looked up, as in k_gemm
+        g0 = (int)((unsigned)u0 / a.div_NB); k0 = 4 * (u0 - g0 * a.NB); n = 4 * (u1 - u0);
     }
 
     // ---- fill: wavefront w brings strip w's weights and vector w of the activations, through buffer descriptors (bounds-checked;

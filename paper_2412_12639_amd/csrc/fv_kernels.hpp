@@ -207,6 +207,9 @@ struct GemmArgs {
     unsigned* fault;
     int NG, NB, G, segmax;
     int aligned;         // direct kernels: workgroup ranges end on row-group boundaries (no partial tiles)
+    // the split: workgroup w starts at unit per * w + rem * w / G of the (row group, K stage) space (aligned: at that row group)
+    unsigned per, rem;
+    Div div_G, div_NB;
     // stream-K split, precomputed on the host: range start of every workgroup (G+1 entries), its
     // first row group, and the first / last contributing workgroup of every row group
     const int* tab_u0; const int* tab_g0; const int* tab_cf; const int* tab_cl;
@@ -245,6 +248,17 @@ struct GemmArgs {
     int Vpad;
     int ld;              // ring kernel over a prompt: rows of the activation buffers (a multiple of 256)
 };
+
+// First unit of workgroup w's range (w = G: the end)
+__device__ __forceinline__ int split_unit(const GemmArgs& a, int w) {
+    const unsigned x = a.per * (unsigned)w + a.rem * (unsigned)w / a.div_G;
+    return (int)(a.aligned ? x * (unsigned)a.NB : x);
+}
+// Asks for all of a product's arguments at once.  Read where they are used they come a cache line at a time, each a trip to memory that the next waits for.
+__device__ __forceinline__ void request_args(const GemmArgs& a) {
+    asm volatile("" ::"s"(a.Wt), "s"(a.zeros), "s"(a.mark), "s"(a.NG), "s"(a.aligned), "s"(a.div_NB.m), "s"(a.tab_cl), "s"(a.n_ssq), "s"(a.q_out), "s"(a.Hq), "s"(a.x),
+                 "s"(a.Vpad));
+}
 
 // Epilogue of one 32-row strip x 32-token block, in accumulator layout: lane (tl, g), acc[i] is
 // row 8*(i/4) + 4*g + i%4 of the strip for token tb*32 + tl.
@@ -607,10 +621,8 @@ __global__ __launch_bounds__(64 * FV_R, 1) void k_gemm(GemmArgs a) {
     // stage loads zeros as its activation chunk (and one weight line, finite), so the loop body has
     // no conditional, the accumulators stay in the accumulation registers, and the number of loads
     // per stage -- which the wait counts are computed from -- is fixed.
-    const long long U = (long long)a.NG * a.NB;   // computed, not looked up: no extra round trip before the first load
-    const int u0 = (int)(U * blockIdx.x / a.G);
-    const int u1 = (int)(U * (blockIdx.x + 1) / a.G);
-    const int g0 = u0 / a.NB;
+    const int u0 = split_unit(a, blockIdx.x), u1 = split_unit(a, blockIdx.x + 1);   // computed, not looked up: no extra round trip before the first load
+    const int g0 = (int)((unsigned)u0 / a.div_NB);
     int nseg = 1;
     for (int e_ = (g0 + 1) * a.NB; e_ < u1; e_ += a.NB) ++nseg;
     auto segment = [&](int sgm, int& gi, int& b0, int& nb) {
@@ -1110,11 +1122,17 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         float mc[8], lc[8], v[8][16];
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const float* cp = base + (size_t)(c < a.ks ? c : 0) * PF;
-            mc[c] = __hip_atomic_load(cp + DB * 1024 + tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            lc[c] = __hip_atomic_load(cp + DB * 1024 + 32 + tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (c < a.ks) {   // the same in all lanes
+                const float* cp = base + (size_t)c * PF;
+                mc[c] = __hip_atomic_load(cp + DB * 1024 + tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                lc[c] = __hip_atomic_load(cp + DB * 1024 + 32 + tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[c][i] = __hip_atomic_load(cp + (db * 16 + i) * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int i = 0; i < 16; ++i) v[c][i] = __hip_atomic_load(cp + (db * 16 + i) * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                mc[c] = lc[c] = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[c][i] = 0.f;
+            }
         }
         float Mx = -1e30f;
 #pragma unroll

@@ -23,6 +23,13 @@ struct PhaseTimer {   // brackets launches with events when profiling is on
     ~PhaseTimer() { if (on) (void)hipEventRecord(c->pev[idx + 1], c->stream); }
 };
 
+static void set_split(GemmArgs& ga, const GemmPlan& p) {
+    ga.NG = p.NG; ga.NB = p.NB; ga.G = p.G; ga.segmax = p.segmax; ga.aligned = p.aligned;
+    const unsigned units = p.aligned ? (unsigned)p.NG : (unsigned)p.NG * (unsigned)p.NB;
+    ga.per = units / (unsigned)p.G; ga.rem = units % (unsigned)p.G;
+    ga.div_G = make_div((unsigned)p.G); ga.div_NB = make_div((unsigned)p.NB);
+}
+
 template <typename EL, int TB, int D, int EPI>
 int launch_gemm_t(fv_ctx* c, const GemmArgs& ga0) {
     const size_t lds = (size_t)2 * TB * 32 * 256;
@@ -255,7 +262,7 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
         memset(&ga, 0, sizeof(ga));
         ga.Wt = (const uint4*)Wt; ga.X = c->at<uint4>(x_off); ga.part = c->scr->part; ga.part_bytes = c->scr->part_bytes;
         ga.tickets = c->scr->tickets; ga.zeros = c->at<uint4>(ly.off_zeros);
-        ga.NG = p.NG; ga.NB = p.NB; ga.G = p.G; ga.segmax = p.segmax; ga.aligned = p.aligned;
+        set_split(ga, p);
         ga.tab_u0 = c->at<int>(p.off_tab); ga.tab_g0 = ga.tab_u0 + p.G + 1; ga.tab_cf = ga.tab_g0 + p.G; ga.tab_cl = ga.tab_cf + p.NG;
         ga.fix_groups = (const int4*)(ga.tab_u0 + (((size_t)2 * p.G + 1 + 2 * p.NG + 3) & ~(size_t)3)); ga.n_fix = p.n_fix; ga.rinv_out = c->at<float>(ly.off_rinv);
         ga.T = T; ga.n_strips = p.n_strips;

@@ -145,7 +145,9 @@ int main(int argc, char** argv) {
     auto args_of = [&](Case& c) {
         GemmArgs ga; std::memset(&ga, 0, sizeof(ga));
         ga.X = (const uint4*)X; ga.part = part; ga.part_bytes = 64u << 20; ga.tickets = tickets; ga.zeros = (const uint4*)zb; ga.aligned = c.p.aligned;
-        ga.NG = c.p.NG; ga.NB = c.p.NB; ga.G = c.p.G; ga.segmax = c.p.segmax; ga.T = T; ga.n_strips = c.p.n_strips;
+        ga.NG = c.p.NG; ga.NB = c.p.NB; ga.G = c.p.G; ga.segmax = c.p.segmax; ga.T = T;
+        const unsigned units = c.p.aligned ? c.p.NG : c.p.NG * c.p.NB;
+        ga.per = units / c.p.G; ga.rem = units % c.p.G; ga.div_G = make_div(c.p.G); ga.div_NB = make_div(c.p.NB); ga.n_strips = c.p.n_strips;
         ga.tab_u0 = c.p.dtab; ga.tab_g0 = c.p.dtab + c.p.G + 1; ga.tab_cf = ga.tab_g0 + c.p.G; ga.tab_cl = ga.tab_cf + c.p.NG;
         ga.ssq_in = ssq; ga.n_ssq = h / 32; ga.inv_h = 1.f / h; ga.eps = 1e-5f;
         ga.q_out = out; ga.q_lo_out = out + (32 << 20); ga.kcache = kv; ga.vcache = kv + (size_t)Hkv * S_pad * D * 2; ga.rope_cs = rope;
