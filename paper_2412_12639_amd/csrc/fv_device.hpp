@@ -51,6 +51,10 @@ template <> struct Tr<BF16> {
     static __device__ __forceinline__ float load(const void* p, size_t i) {
         return bf16_bits_to_f32(((const uint16_t*)p)[i]);
     }
+    static __device__ __forceinline__ float at(const uint4& v, int i) {   // element i (a constant) of a vector
+        const uint32_t w = i < 2 ? v.x : i < 4 ? v.y : i < 6 ? v.z : v.w;
+        return __builtin_bit_cast(float, (i & 1) ? w & 0xffff0000u : w << 16);
+    }
     static __device__ __forceinline__ void store(void* p, size_t i, float v) {
         __bf16 h = (__bf16)v;
         ((uint16_t*)p)[i] = __builtin_bit_cast(uint16_t, h);
@@ -77,6 +81,7 @@ template <> struct Tr<F32> {
         return c;
     }
     static __device__ __forceinline__ float load(const void* p, size_t i) { return ((const float*)p)[i]; }
+    static __device__ __forceinline__ float at(const uint4& v, int i) { return __builtin_bit_cast(float, i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w); }
     static __device__ __forceinline__ void store(void* p, size_t i, float v) { ((float*)p)[i] = v; }
     static __device__ __forceinline__ uint4 pack(const float* p) {
         return __builtin_bit_cast(uint4, make_float4(p[0], p[1], p[2], p[3]));

@@ -109,8 +109,16 @@ static __global__ __launch_bounds__(256) void k_draft_begin(DraftInArgs a, Draft
             int tok = (nd >= 0) ? a.top_tok[(size_t)a.tab.node_gen[nd] * FV_DRAFT_MMAX + a.tab.node_rank[nd]] : a.tab.tok_val[r];
             if (tok < 0 || tok >= a.vocab) tok = 0;   // only after a non-finite row, which fails the phase anyway
             const size_t base = (size_t)tok * a.h + (f0 - a.h);
+            if constexpr (Tr<EL>::E == 8) {
+                const uint2 u = *(const uint2*)((const uint16_t*)a.table + base);
+                const uint4 w = make_uint4(u.x, u.y, 0u, 0u);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = Tr<EL>::load(a.table, base + c);
+                for (int c = 0; c < 4; ++c) v[c] = Tr<EL>::at(w, c);
+            } else {
+                const uint4 w = *(const uint4*)((const float*)a.table + base);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = Tr<EL>::at(w, c);
+            }
         }
     }
     store4_act<EL>(a.xz, a.Tp, f0, t, v[0], v[1], v[2], v[3]);

@@ -133,21 +133,27 @@ struct EmbedArgs {
     int h, T, Tp;
 };
 
-// 32 features (strip s) of row t
+// 32 features (strip s) of row t.  All that is read is asked for before anything is stored: the buffers could overlap for all the compiler knows, and
+// with a load behind every store a strip took eight trips to memory (2000 rows of a prompt 44 us, the start of a step 6.7).
 template <typename EL>
 __device__ __forceinline__ void embed_strip(const EmbedArgs& a, int s, int t) {
+    constexpr int E = Tr<EL>::E, NV = 32 / E;   // 16-byte vectors of a strip (rows are whole ones: h is a multiple of 64)
+    uint4 raw[NV];
+    float4 gn[8];
+    const uint4* const row = (const uint4*)a.table + ((size_t)(t < a.T ? a.tok[t] : 0) * a.h + s * 32) / E;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) raw[k] = t < a.T ? row[k] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) gn[q] = *(const float4*)(a.gain + s * 32 + q * 4);
     float ssq = 0.f;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int f0 = s * 32 + q * 4;
-        float v[4] = {0.f, 0.f, 0.f, 0.f};
-        if (t < a.T) {
-            const size_t base = (size_t)a.tok[t] * a.h + f0;
-            for (int c = 0; c < 4; ++c) v[c] = Tr<EL>::load(a.table, base + c);
-        }
+        float v[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = Tr<EL>::at(raw[q * 4 / E], (q * 4 + c) % E);
         ((float4*)a.x)[(size_t)(f0 >> 2) * a.Tp + t] = make_float4(v[0], v[1], v[2], v[3]);
-        store4_act<EL>(a.xb, a.Tp, f0, t, v[0] * a.gain[f0], v[1] * a.gain[f0 + 1], v[2] * a.gain[f0 + 2],
-                       v[3] * a.gain[f0 + 3]);
+        store4_act<EL>(a.xb, a.Tp, f0, t, v[0] * gn[q].x, v[1] * gn[q].y, v[2] * gn[q].z, v[3] * gn[q].w);
         ssq += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
     }
     a.ssq_part[(size_t)s * a.Tp + t] = ssq;
@@ -1471,8 +1477,8 @@ static __global__ __launch_bounds__(FV_SAMPLED_THREADS) void k_sampled_nodes(Sam
 //   T workgroups, one per possible path position, write a feature row: the LM head's input (final RMSNorm of the last layer's
 //     output) of path node j, j = 0..accepted_len, fp32 [max_tree][h];
 //   the others compact the cache, 256 / D slabs (layer, KV head) each: slot L + j <- slot L + path[j], j = 0..accepted_len.
-//     Tree K/V were written at slots L + node index; path[j] >= j, and a thread moves its feature for j = 0, 1, ... in
-//     order, so a slot is always read before it can be overwritten.
+//     Tree K/V were written at slots L + node index; path[j] >= j and ascends, so a slot that a row is read from is written for
+//     that row at the earliest: rows may be read ahead of the writes of earlier ones.
 // Greedy: match[i] = (i is the root) or tok[i] == argmax[parent[i]]; node i is accepted iff every node of its ancestor set
 // matches; best = deepest accepted node, lowest index among equals; path = members of best's ancestor set in increasing index
 // (= depth) order.  SAMPLED: from the root along the children the nodes took, to the token drawn at the end.
@@ -1578,8 +1584,18 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a) {
             __syncthreads();
         }
         const float rinv = rsqrtf(red[0] * a.inv_h + a.eps);
-        for (int f = i; f < a.h; f += 256)
-            a.feat[(size_t)b * a.h + f] = a.x[((size_t)(f >> 2) * a.Tp + t) * 4 + (f & 3)] * rinv * a.gain[f];
+        for (int f0 = i; f0 < a.h; f0 += 8 * 256) {   // eight values read before the first is stored: one trip to memory for them, not one each
+            float x[8], gn[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int f = f0 + k * 256 < a.h ? f0 + k * 256 : f0;
+                x[k] = a.x[((size_t)(f >> 2) * a.Tp + t) * 4 + (f & 3)];
+                gn[k] = a.gain[f];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (f0 + k * 256 < a.h) a.feat[(size_t)b * a.h + f0 + k * 256] = x[k] * rinv * gn[k];
+        }
         return;
     }
     const int slab = (b - a.T) * (256 / D) + i / D, e = i % D;
@@ -1587,11 +1603,21 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a) {
     char* ks = (char*)a.kcache + (size_t)slab * a.S_pad * D * Tr<EL>::ESZ;
     char* vs = (char*)a.vcache + (size_t)slab * a.S_pad * D * Tr<EL>::ESZ;
     typedef typename Tr<EL>::elem_t el_t;
-    for (int j = 0; j <= len; ++j) {
-        const int src = s_path[j];
-        if (src == j) continue;
-        ((el_t*)ks)[kcache_index<EL, D>(a.L + j, e)] = ((el_t*)ks)[kcache_index<EL, D>(a.L + src, e)];
-        ((el_t*)vs)[vcache_index<EL, D>(a.L + j, e)] = ((el_t*)vs)[vcache_index<EL, D>(a.L + src, e)];
+    for (int j0 = 0; j0 <= len; j0 += 4) {   // four rows read before the first is written
+        el_t k[4], v[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int src = s_path[j0 + c <= len ? j0 + c : len];
+            k[c] = ((const el_t*)ks)[kcache_index<EL, D>(a.L + src, e)];
+            v[c] = ((const el_t*)vs)[vcache_index<EL, D>(a.L + src, e)];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int j = j0 + c;
+            if (j > len || s_path[j] == j) continue;
+            ((el_t*)ks)[kcache_index<EL, D>(a.L + j, e)] = k[c];
+            ((el_t*)vs)[vcache_index<EL, D>(a.L + j, e)] = v[c];
+        }
     }
 }
 
