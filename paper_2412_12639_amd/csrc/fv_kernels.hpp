@@ -32,10 +32,16 @@ struct IngestArgs {
 
 // one workgroup (`blk`) per four rows: their ancestor masks (a chain of dependent reads each, from LDS: out of memory 256 rows of a
 // prompt took 25 us) and their rows of the rotary table (double-precision sincos, one or two entries per thread)
-__device__ __forceinline__ void ingest_rows(const IngestArgs& a, int blk, int32_t* s_parent, int32_t* s_depth) {
+// (The first nodes that follow each other -- all rows of a prompt, the root tokens of a tree -- need no walk: the set of node j among them is 0..j.  The
+// last of 256 prompt rows took 255 reads of LDS one after the other, 37 us a launch.)
+__device__ __forceinline__ void ingest_rows(const IngestArgs& a, int blk, int32_t* s_parent, int32_t* s_depth, int* s_chain) {
     const int tid = threadIdx.x;
     if (tid < a.T) { s_parent[tid] = a.tok_in[a.cap + tid]; s_depth[tid] = a.tok_in[2 * a.cap + tid]; }
+    if (tid == 0) *s_chain = a.T;
     __syncthreads();
+    if (tid < a.T && s_parent[tid] != tid - 1) atomicMin(s_chain, tid);
+    __syncthreads();
+    const int chain = *s_chain;   // nodes 0 .. chain - 1 each follow the one before
     const int t0 = blk * 4, t1 = (t0 + 4 < a.Tp) ? t0 + 4 : a.Tp;
     for (int i = t0 + tid; i < t1; i += 256) {
         uint64_t m[4] = {0, 0, 0, 0};
@@ -47,6 +53,11 @@ __device__ __forceinline__ void ingest_rows(const IngestArgs& a, int blk, int32_
 #pragma unroll
                 for (int w = 0; w < 4; ++w) m[w] |= (j >> 6) == w ? 1ull << (j & 63) : 0ull;
                 if (by_depth && s_depth[j] >= 0 && s_depth[j] <= FV_CANON_DEPTH) a.anc[i * (FV_CANON_DEPTH + 1) + s_depth[j]] = (uint8_t)j;
+                if (!by_depth && j < chain) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) m[w] |= j + 1 >= 64 * (w + 1) ? ~0ull : j + 1 > 64 * w ? (1ull << (j + 1 - 64 * w)) - 1ull : 0ull;
+                    break;
+                }
                 j = s_parent[j];
             }
             p = a.L + s_depth[i];
@@ -168,11 +179,12 @@ __global__ __launch_bounds__(256) void k_embed(EmbedArgs a) { embed_strip<EL>(a,
 template <typename EL>
 __global__ __launch_bounds__(256) void k_begin(IngestArgs ia, EmbedArgs ea, int n_embed, PadArgs pa) {
     __shared__ int32_t s_parent[FV_MAX_TREE], s_depth[FV_MAX_TREE];
+    __shared__ int s_chain;
     if ((int)blockIdx.x < n_embed) {
         const int s = blockIdx.x * (256 / ea.Tp) + threadIdx.x / ea.Tp;
         if (s < ea.h / 32) embed_strip<EL>(ea, s, threadIdx.x % ea.Tp);
     } else if ((int)blockIdx.x < n_embed + ia.Tp / 4) {
-        ingest_rows(ia, blockIdx.x - n_embed, s_parent, s_depth);
+        ingest_rows(ia, blockIdx.x - n_embed, s_parent, s_depth, &s_chain);
     } else {
         clear_pads(pa, (blockIdx.x - n_embed - ia.Tp / 4) * 256 + threadIdx.x);
     }
