@@ -50,7 +50,6 @@ void make_draft_layout(const fv_cfg& t, int n_wg, DraftLayout& L) {
     L.off_top_tok = take((size_t)FV_DRAFT_OUT_ROWS * FV_DRAFT_MMAX * 4);
     L.off_top_val = take((size_t)FV_DRAFT_OUT_ROWS * FV_DRAFT_MMAX * 4);
     L.off_logits = take((size_t)2 * FV_MAX_TREE * core.Vpad * 4);   // a pass writes its padded row count from its first row on
-    L.off_node_tok = take(FV_MAX_TREE * 4);
     L.off_tables = take((size_t)FV_DRAFT_TABLES * FV_MAX_TREE * 4);
     L.off_bad = take(256);
     for (GemmPlan* p : {&L.ih0.gm, &L.ih0.gd, &L.ih0.gp, &L.hh.gm, &L.hh.gd, &L.hh.gp}) p->off_tab = take(plan_table_bytes(*p));
@@ -341,10 +340,10 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
             if (rc) return rc;
             StateKeepArgs ka;
             ka.state0 = d->state(0); ka.state1 = d->state(1); ka.aborted = d->at<uint32_t>(d->lay.off_bad) + 2; ka.row = m - 1; ka.h = cf.hidden;
+            ka.bad = d->at<int32_t>(d->lay.off_bad); ka.bad_out = d->h_out + FV_MAX_TREE;
             hipLaunchKernelGGL(k_state_keep, dim3((2 * cf.hidden + 255) / 256), dim3(256), 0, st, ka);
             HIPCHK(hipGetLastError());
             HIPCHK(hipEventRecord(d->core->ev1, st));
-            HIPCHK(hipMemcpyAsync(d->h_out + FV_MAX_TREE, d->at<int32_t>(d->lay.off_bad), 12, hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
             if (ps.chain) d->chain_outcome(d->h_out[FV_MAX_TREE + 2]);
             if (!ps.chain || !d->h_out[FV_MAX_TREE + 2] || d->h_out[FV_MAX_TREE + 1]) break;
@@ -468,22 +467,20 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
         for (DraftPass& ps : passes) ps.chain = false;
     }
     for (;;) {
-        HIPCHK(hipMemcpyAsync(d->at<int32_t>(d->lay.off_node_tok), &root_token, 4, hipMemcpyHostToDevice, st));
         HIPCHK(hipEventRecord(d->core->ev0, st));
         for (const DraftPass& ps : passes) {
             rc = pass_any(d, ps);
             if (rc) return rc;
         }
-        if (exp_at > 0) {   // every node's token (the passes read theirs from the top lists)
+        {   // every node's token (the passes read theirs from the top lists)
             ExpandArgs ea;
-            ea.tab = dev_tables(d); ea.top_tok = d->at<int32_t>(d->lay.off_top_tok); ea.node_tok = d->at<int32_t>(d->lay.off_node_tok);
+            ea.tab = dev_tables(d); ea.top_tok = d->at<int32_t>(d->lay.off_top_tok); ea.node_tok = d->h_out;
+            ea.bad = d->at<int32_t>(d->lay.off_bad); ea.bad_out = d->h_out + FV_MAX_TREE;
             ea.n = exp_at;
-            hipLaunchKernelGGL(k_draft_expand, dim3((ea.n + 255) / 256), dim3(256), 0, st, ea);
+            hipLaunchKernelGGL(k_draft_expand, dim3(1), dim3(256), 0, st, ea);
             HIPCHK(hipGetLastError());
         }
         HIPCHK(hipEventRecord(d->core->ev1, st));
-        HIPCHK(hipMemcpyAsync(d->h_out, d->at<int32_t>(d->lay.off_node_tok), (size_t)n * 4, hipMemcpyDeviceToHost, st));
-        HIPCHK(hipMemcpyAsync(d->h_out + FV_MAX_TREE, d->at<int32_t>(d->lay.off_bad), 12, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         if (any_chain) d->chain_outcome(d->h_out[FV_MAX_TREE + 2]);
         if (!any_chain || !d->h_out[FV_MAX_TREE + 2] || d->h_out[FV_MAX_TREE + 1]) break;
@@ -501,6 +498,7 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
         HIPCHK(hipMemset(d->at<int32_t>(d->lay.off_bad), 0, 4));
         return FV_E_NONFINITE;
     }
+    d->h_out[0] = root_token;
     for (int i = 0; i < n; ++i)
         if (d->h_out[i] < 0 || d->h_out[i] >= cf.vocab) return FV_E_HIP;   // cannot happen with finite logits
     memcpy(tokens_out, d->h_out, (size_t)n * 4);

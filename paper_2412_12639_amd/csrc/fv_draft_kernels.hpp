@@ -218,9 +218,11 @@ static __global__ __launch_bounds__(256) void k_lstm_cell(LstmCellArgs a) {
 
 // state after the last committed pair <- state of phase row `row` (both layers are laid out back to back); not if *aborted
 // (a chain launch gave up: the rows' states are not there)
-struct StateKeepArgs { float* state0; float* state1; const uint32_t* aborted; int row, h; };
+// The call's error words go to the host's memory with it.
+struct StateKeepArgs { float* state0; float* state1; const uint32_t* aborted; const int32_t* bad; int32_t* bad_out; int row, h; };
 static __global__ __launch_bounds__(256) void k_state_keep(StateKeepArgs a) {
     const int idx = blockIdx.x * 256 + threadIdx.x;
+    if (idx < 3) { a.bad_out[idx] = a.bad[idx]; __threadfence_system(); }
     if (idx >= 2 * a.h || *a.aborted) return;
     a.state0[(size_t)FV_MAX_TREE * 2 * a.h + idx] = a.state0[(size_t)a.row * 2 * a.h + idx];
     a.state1[(size_t)FV_MAX_TREE * 2 * a.h + idx] = a.state1[(size_t)a.row * 2 * a.h + idx];
@@ -230,8 +232,8 @@ static __global__ __launch_bounds__(256) void k_state_keep(StateKeepArgs a) {
 // predicted feature rows: the block's residual stream after its MLP, fp32 [256 + KMAX][h] by output row id
 struct DraftOutArgs { const float* x; float* fout; int r0, n, Tp, h; };
 __device__ __forceinline__ void draft_out_row(const DraftOutArgs& a, int t) {
-    for (int f = threadIdx.x; f < a.h; f += blockDim.x)
-        a.fout[(size_t)(a.r0 + t) * a.h + f] = a.x[((size_t)(f >> 2) * a.Tp + t) * 4 + (f & 3)];
+    for (int q = threadIdx.x; q < a.h / 4; q += blockDim.x)   // four features a thread, a whole row of 4096 at once
+        ((float4*)(a.fout + (size_t)(a.r0 + t) * a.h))[q] = ((const float4*)a.x)[(size_t)q * a.Tp + t];
 }
 
 // Top-m of one row of logits: descending value, lower token id first among equals (a total order, so
@@ -373,12 +375,16 @@ static __global__ __launch_bounds__(FV_TOPM_THREADS) void k_topm(TopmArgs a, Dra
 }
 
 // tokens of the tree nodes a pass generates: node_tok[i] = top list of its generating row at its rank
-struct ExpandArgs { DraftTables tab; const int32_t* top_tok; int32_t* node_tok; int n; };
+// (and the call's error words), into the host's memory
+struct ExpandArgs { DraftTables tab; const int32_t* top_tok; const int32_t* bad; int32_t* node_tok; int32_t* bad_out; int n; };
 static __global__ __launch_bounds__(256) void k_draft_expand(ExpandArgs a) {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= a.n) return;
-    const int i = a.tab.exp_list[j];
-    a.node_tok[i] = a.top_tok[(size_t)a.tab.node_gen[i] * FV_DRAFT_MMAX + a.tab.node_rank[i]];
+    const int j = threadIdx.x;   // one workgroup: at most 256 nodes
+    if (j < 3) a.bad_out[j] = a.bad[j];
+    if (j < a.n) {
+        const int i = a.tab.exp_list[j];
+        a.node_tok[i] = a.top_tok[(size_t)a.tab.node_gen[i] * FV_DRAFT_MMAX + a.tab.node_rank[i]];
+    }
+    __threadfence_system();
 }
 
 // History of the last k-1 committed rows' outputs (predicted feature, top list), kept across phases in
@@ -391,7 +397,13 @@ static __global__ __launch_bounds__(256) void k_draft_hist(HistArgs a) {
         const int c = a.n_prev + j;
         const int src = (c < a.k - 1) ? FV_MAX_TREE + c : c - (a.k - 1);
         const int dst = FV_MAX_TREE + j;
-        for (int f = threadIdx.x; f < a.h; f += 256) a.fout[(size_t)dst * a.h + f] = a.fout[(size_t)src * a.h + f];
+        for (int q0 = threadIdx.x; q0 < a.h / 4; q0 += 4 * 256) {   // four vectors read before the first is stored
+            float4 v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = ((const float4*)(a.fout + (size_t)src * a.h))[q0 + k * 256 < a.h / 4 ? q0 + k * 256 : q0];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) if (q0 + k * 256 < a.h / 4) ((float4*)(a.fout + (size_t)dst * a.h))[q0 + k * 256] = v[k];
+        }
         if (threadIdx.x < FV_DRAFT_MMAX) {
             a.top_tok[dst * FV_DRAFT_MMAX + threadIdx.x] = a.top_tok[src * FV_DRAFT_MMAX + threadIdx.x];
             a.top_val[dst * FV_DRAFT_MMAX + threadIdx.x] = a.top_val[src * FV_DRAFT_MMAX + threadIdx.x];

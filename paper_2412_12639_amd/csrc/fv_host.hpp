@@ -103,9 +103,9 @@ struct fv_ctx {
     int last_T = 0, last_Tp = 0, last_L = 0;
     int input_Tp = 0;             // row padding the products' inputs are laid out for (PadArgs)
     bool last_was_verify = false;
-    int32_t* h_in = nullptr;      // pinned [3][256]
+    int32_t* h_in = nullptr;      // pinned [3][256]; steps of up to 64 rows read it from the device
     int32_t* h_prompt = nullptr;  // pinned [max_seq]: the prompt while its pieces are on their way (lay.Pm > 0 only)
-    FvResult* h_res = nullptr;    // pinned
+    FvResult* h_res = nullptr;    // pinned; a verification step's last kernel writes it
     double* h_unif = nullptr;     // pinned [2][256]: u_accept, u_sample of a non-greedy step
     double sample_inv_temperature = 1.0;      // of the non-greedy step being run
     const float* sample_draft = nullptr;      // device [n][vocab] or null
@@ -148,7 +148,7 @@ struct DraftLayout {
     size_t off_bias = 0, off_ones = 0;
     size_t off_xz = 0, off_xh = 0, off_xprev = 0, off_gin = 0, off_grec = 0;
     size_t off_state = 0, state_layer_bytes = 0;
-    size_t off_fout = 0, off_top_tok = 0, off_top_val = 0, off_logits = 0, off_node_tok = 0, off_tables = 0, off_bad = 0;
+    size_t off_fout = 0, off_top_tok = 0, off_top_val = 0, off_logits = 0, off_tables = 0, off_bad = 0;
     size_t off_part = 0, part_bytes = 0, off_tickets = 0, ticket_bytes = 0;
     size_t off_chain = 0, chain_bytes = 0;   // exchange area of the chain kernel: arrival counters, hidden states of both layers
     size_t total = 0;

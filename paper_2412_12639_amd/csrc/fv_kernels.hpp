@@ -13,6 +13,9 @@
 // prefix ++ root path, so it sits depth[i] places after the root at position L).
 struct IngestArgs {
     const int32_t* tok_in;   // [3][cap]: tokens, parent, depth
+    int32_t* tok_out;        // tok_in is host memory: the copy that later kernels read, or null
+    const double* unif_in;   // non-greedy step, host memory: [2][cap] uniforms, to unif_out; or null
+    double* unif_out;
     int cap, T, Tp, L, half_d;
     double log2_base;
     uint64_t* mask;          // [Tp][4]
@@ -36,7 +39,21 @@ struct IngestArgs {
 // last of 256 prompt rows took 255 reads of LDS one after the other, 37 us a launch.)
 __device__ __forceinline__ void ingest_rows(const IngestArgs& a, int blk, int32_t* s_parent, int32_t* s_depth, int* s_chain) {
     const int tid = threadIdx.x;
-    if (tid < a.T) { s_parent[tid] = a.tok_in[a.cap + tid]; s_depth[tid] = a.tok_in[2 * a.cap + tid]; }
+    if (tid < a.T) {
+        const int32_t p = a.tok_in[a.cap + tid], d = a.tok_in[2 * a.cap + tid];
+        s_parent[tid] = p;
+        s_depth[tid] = d;
+        if (a.tok_out && blk == 0) {
+            a.tok_out[tid] = a.tok_in[tid];
+            a.tok_out[a.cap + tid] = p;
+            a.tok_out[2 * a.cap + tid] = d;
+        }
+        if (a.unif_in && blk == 0) {
+            const double ua = a.unif_in[tid], us = a.unif_in[a.cap + tid];
+            a.unif_out[tid] = ua;
+            a.unif_out[a.cap + tid] = us;
+        }
+    }
     if (tid == 0) *s_chain = a.T;
     __syncthreads();
     if (tid < a.T && s_parent[tid] != tid - 1) atomicMin(s_chain, tid);
@@ -1485,7 +1502,7 @@ static __global__ __launch_bounds__(FV_SAMPLED_THREADS) void k_sampled_nodes(Sam
 // The accepted path, and what is kept of it: one launch.  Every workgroup finds the path by itself (a few KB of node data and
 // a microsecond; handing it on would be a launch, 5 us with its gap, and a step of two small layers is 100 us) and then does its
 // share:
-//   workgroup 0 writes the result record;
+//   workgroup 0 writes the result record, straight into the host's memory (a copy behind the launch is 3 us and its gap);
 //   T workgroups, one per possible path position, write a feature row: the LM head's input (final RMSNorm of the last layer's
 //     output) of path node j, j = 0..accepted_len, fp32 [max_tree][h];
 //   the others compact the cache, 256 / D slabs (layer, KV head) each: slot L + j <- slot L + path[j], j = 0..accepted_len.
@@ -1498,9 +1515,10 @@ struct FinishArgs {
     const int32_t* tok_in;     // [3][cap]
     int cap, T;
     const uint64_t* mask;      // greedy
-    const int32_t* am;         // greedy: [Tp]
+    const int32_t* am;         // [Tp]
     const int32_t* outcome;    // SAMPLED: [T], see SampledArgs
-    FvResult* res;
+    const uint32_t* fault;
+    FvResult* res;             // host memory
     // features
     const float* x;            // residual stream after the last layer, fp32 [h/4][Tp][4]
     const float* ssq;          // its per-strip sums of squares [h/32][Tp]
@@ -1577,11 +1595,13 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a) {
     const int len = s_len;
     int b = blockIdx.x;
     if (b == 0) {
-        if (i == 0) { a.res->accepted_len = len; a.res->next_token = s_next; a.res->best = s_best; a.res->pad = 0; }
+        if (i == 0) { a.res->accepted_len = len; a.res->next_token = s_next; a.res->best = s_best; a.res->fault = *a.fault; }
         if (i <= len) {
             a.res->path[i] = s_path[i];
             if (i >= 1) a.res->accepted_tokens[i - 1] = s_tok[s_path[i]];
         }
+        if (i < a.T) a.res->argmax[i] = a.am[i];
+        __threadfence_system();
         return;
     }
     if (--b < a.T) {

@@ -221,19 +221,26 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
     const int h = cf.hidden;
     hipStream_t st = c->stream;
 
-    HIPCHK(hipMemcpyAsync(c->at<int32_t>(ly.off_stepin), c->h_in, 3 * FV_MAX_TREE * 4, hipMemcpyHostToDevice, st));
-    if (mode == STEP_VERIFY_SAMPLED)
-        HIPCHK(hipMemcpyAsync(c->at<double>(ly.off_unif), c->h_unif, 2 * FV_MAX_TREE * 8, hipMemcpyHostToDevice, st));
+    // Up to 64 rows the first kernel reads the step's inputs where the host wrote them (pinned memory) and leaves a copy for the later ones: a copy
+    // of its own in front is 3 us and its gap.  Above, its workgroups would read 256 KB across the bus.
+    const bool in_place = Tp <= 64;
+    if (!in_place) {
+        HIPCHK(hipMemcpyAsync(c->at<int32_t>(ly.off_stepin), c->h_in, 3 * FV_MAX_TREE * 4, hipMemcpyHostToDevice, st));
+        if (mode == STEP_VERIFY_SAMPLED)
+            HIPCHK(hipMemcpyAsync(c->at<double>(ly.off_unif), c->h_unif, 2 * FV_MAX_TREE * 8, hipMemcpyHostToDevice, st));
+    }
     if (from_prompt < 0) HIPCHK(hipEventRecord(c->ev0, st));   // else the rows' work began in run_prompt
     {
         PhaseTimer pt(c, FV_PH_OTHER);
         IngestArgs ia;
-        ia.tok_in = c->at<int32_t>(ly.off_stepin); ia.cap = FV_MAX_TREE; ia.T = T; ia.Tp = Tp; ia.L = L; ia.half_d = D / 2;
+        ia.tok_in = in_place ? c->h_in : c->at<int32_t>(ly.off_stepin); ia.tok_out = in_place ? c->at<int32_t>(ly.off_stepin) : nullptr;
+        ia.unif_in = in_place && mode == STEP_VERIFY_SAMPLED ? c->h_unif : nullptr; ia.unif_out = c->at<double>(ly.off_unif);
+        ia.cap = FV_MAX_TREE; ia.T = T; ia.Tp = Tp; ia.L = L; ia.half_d = D / 2;
         ia.log2_base = std::log2((double)cf.rope_base);
         ia.mask = c->at<uint64_t>(ly.off_mask); ia.pos = c->at<int32_t>(ly.off_pos); ia.rope_cs = c->at<float2>(ly.off_rope);
         ia.anc = c->at<uint8_t>(ly.off_anc);
         EmbedArgs ea;
-        ea.table = c->at<void>(ly.off_embed); ea.tok = c->at<int32_t>(ly.off_stepin); ea.gain = c->gain(0);
+        ea.table = c->at<void>(ly.off_embed); ea.tok = ia.tok_in; ea.gain = c->gain(0);
         ea.x = c->at<float>(ly.off_x);
         ea.xb = c->at<void>(ly.off_xb);
         ea.ssq_part = c->at<float>(ly.off_ssq);
@@ -359,7 +366,7 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
             FinishArgs fa;
             fa.tok_in = c->at<int32_t>(ly.off_stepin); fa.cap = FV_MAX_TREE; fa.T = T;
             fa.mask = c->at<uint64_t>(ly.off_mask); fa.am = c->at<FvResult>(ly.off_res)->argmax; fa.outcome = c->at<int32_t>(ly.off_outcome);
-            fa.res = c->at<FvResult>(ly.off_res);
+            fa.fault = &c->at<FvResult>(ly.off_res)->fault; fa.res = c->h_res;
             fa.x = c->at<float>(ly.off_x); fa.ssq = c->at<float>(ly.off_ssq); fa.gain = c->gain(2 * cf.n_layers); fa.feat = c->at<float>(ly.off_feat);
             fa.h = h; fa.Tp = Tp; fa.inv_h = 1.f / (float)h; fa.eps = cf.rms_eps;
             fa.kcache = c->at<void>(ly.off_k); fa.vcache = c->at<void>(ly.off_v); fa.slabs = cf.n_layers * cf.n_kv_heads; fa.L = L; fa.S_pad = ly.S_pad;
@@ -370,10 +377,9 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
         HIPCHK(hipGetLastError());
     }
     HIPCHK(hipEventRecord(c->ev1, st));
-    // the result record comes back whole (3 KB), the rows' greedy choices with it: asking for those separately would be a second
-    // synchronous copy, 10 us of a step that takes 150
-    if (mode != STEP_PREFILL_MID) HIPCHK(hipMemcpyAsync(c->h_res, c->at<FvResult>(ly.off_res), sizeof(FvResult), hipMemcpyDeviceToHost, st));
-    else HIPCHK(hipMemcpyAsync(&c->h_res->fault, &c->at<FvResult>(ly.off_res)->fault, 4, hipMemcpyDeviceToHost, st));
+    // a verification step's record is the last kernel's to write; a prompt's last chunk has its rows' greedy choices copied back with the error word
+    if (mode == STEP_PREFILL_LAST) HIPCHK(hipMemcpyAsync(c->h_res, c->at<FvResult>(ly.off_res), sizeof(FvResult), hipMemcpyDeviceToHost, st));
+    else if (mode == STEP_PREFILL_MID) HIPCHK(hipMemcpyAsync(&c->h_res->fault, &c->at<FvResult>(ly.off_res)->fault, 4, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (mode == STEP_PREFILL_LAST) c->h_res->next_token = c->h_res->argmax[T - 1];
     if (c->h_res->fault) {
