@@ -363,12 +363,9 @@ __device__ __forceinline__ void attn_canon_body(const CanonArgs& a, int item, in
                 l_run += psum;
                 uint4 pb[NQ], pbl[SPLIT ? NQ : 1];
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) pb[q] = Tr<EL>::pack(p + q * E);
-                if constexpr (SPLIT) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) p[i] = bf16_residual(p[i]);
-#pragma unroll
-                    for (int q = 0; q < NQ; ++q) pbl[q] = Tr<EL>::pack(p + q * E);
+                for (int q = 0; q < NQ; ++q) {
+                    if constexpr (SPLIT) pb[q] = Tr<EL>::pack_split(p + q * E, pbl[q]);
+                    else pb[q] = Tr<EL>::pack(p + q * E);
                 }
 #pragma unroll
                 for (int db = 0; db < DB; ++db)

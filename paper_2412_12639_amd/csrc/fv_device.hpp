@@ -23,9 +23,10 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 struct BF16 {};
 struct F32 {};
 
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-    __bf16 a = (__bf16)lo, b = (__bf16)hi;   // round to nearest even
-    return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {   // round to nearest even, both in one instruction (one by one and joined: four)
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), b2));
 }
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) {
     return __builtin_bit_cast(float, (uint32_t)b << 16);
@@ -64,6 +65,13 @@ template <> struct Tr<BF16> {
         uint4 r;
         r.x = pack_bf16x2(p[0], p[1]); r.y = pack_bf16x2(p[2], p[3]);
         r.z = pack_bf16x2(p[4], p[5]); r.w = pack_bf16x2(p[6], p[7]);
+        return r;
+    }
+    // the same, and what its rounding lost of each (bf16_residual) as a second vector
+    static __device__ __forceinline__ uint4 pack_split(const float* p, uint4& rest) {
+        const uint4 r = pack(p);
+        const float d[8] = {p[0] - at(r, 0), p[1] - at(r, 1), p[2] - at(r, 2), p[3] - at(r, 3), p[4] - at(r, 4), p[5] - at(r, 5), p[6] - at(r, 6), p[7] - at(r, 7)};
+        rest = pack(d);
         return r;
     }
 };

@@ -900,7 +900,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
     constexpr int NF = D / (2 * E);      // K frags per key block
     constexpr int NQ = 32 / (2 * E);     // V frags per (key block, 32 features)
     constexpr int DB = D / 32;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int tl = lane & 31, g = lane >> 5;
     const int TB = a.Tp >> 5;
     const int qh = item / TB, tb = item % TB;
@@ -947,17 +947,17 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
     const int nkb = (n_keys + 31) >> 5;
     const int kb_lo = nkb * part / a.ks, kb_hi = nkb * (part + 1) / a.ks;   // this workgroup's key blocks
     const int lidx = tl * 2 + g;   // position of this lane's 16 bytes inside a 1 KiB tile
-    // all K and V tiles of a block are requested before the first is used: one memory round trip
-    // per block instead of two
-    auto load_block = [&](uint4 (&kt)[NF], uint4 (&vt)[DB * NQ], int kb) {
+    auto load_k = [&](uint4 (&kt)[NF], int kb) {
         const uint4* kp = kslab + (size_t)kb * NF * 64 + lidx;
-        const uint4* vp = vslab + (size_t)kb * DB * NQ * 64 + lidx;
 #pragma unroll
         for (int fr = 0; fr < NF; ++fr) kt[fr] = kp[fr * 64];
+    };
+    auto load_v = [&](uint4 (&vt)[DB * NQ], int kb) {
+        const uint4* vp = vslab + (size_t)kb * DB * NQ * 64 + lidx;
 #pragma unroll
         for (int j = 0; j < DB * NQ; ++j) vt[j] = vp[j * 64];
     };
-    auto use_block = [&](const uint4 (&kt)[NF], const uint4 (&vt)[DB * NQ], int kb) {
+    auto use_block = [&](uint4 (&kt)[NF], const uint4 (&vt)[DB * NQ], int kb, int kb_next) {
         // two accumulation chains (a dependent MFMA waits ~50 cycles for its predecessor, two
         // interleaved chains issue back to back), added at the end
         floatx16 s, s1;
@@ -996,6 +996,9 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
                 }
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        load_k(kt, kb_next);   // into the registers that the products have just read
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[i] += s1[i];
 
@@ -1065,12 +1068,9 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
         l_run += psum;
         uint4 pb[NQ], pbl[SPLIT ? NQ : 1];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) pb[q] = Tr<EL>::pack(p + q * E);
-        if constexpr (SPLIT) {   // what the probabilities lose to bf16 rounding goes through the matrix cores too
-#pragma unroll
-            for (int i = 0; i < 16; ++i) p[i] = bf16_residual(p[i]);
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) pbl[q] = Tr<EL>::pack(p + q * E);
+        for (int q = 0; q < NQ; ++q) {
+            if constexpr (SPLIT) pb[q] = Tr<EL>::pack_split(p + q * E, pbl[q]);   // what the probabilities lose to bf16 rounding goes through the matrix cores too
+            else pb[q] = Tr<EL>::pack(p + q * E);
         }
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -1080,12 +1080,20 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
                 if constexpr (SPLIT) o[db] = Tr<EL>::mma(vt[db * NQ + q], pbl[q], o[db]);
             }
     };
+    // K of the next block is asked for when this block's has been multiplied, and arrives during the softmax and V's products; V of the next when
+    // those are done, and arrives during K's.  No register more than with all of a block asked for at its start, which for 256 items of 72 blocks (7B,
+    // 2298 keys), one workgroup a compute unit, was 33.5 us a layer, 30.7 this way.  (The last block asks for itself again: in range, not used.)
     int kb = kb_lo + wave;
+    uint4 kt[NF], vt[DB * NQ];
+    load_k(kt, kb < nkb ? kb : nkb - 1);
+    load_v(vt, kb < nkb ? kb : nkb - 1);
+    __builtin_amdgcn_sched_barrier(0);
     for (; kb < kb_hi; kb += 4) {
-        uint4 kt[NF], vt[DB * NQ];
-        load_block(kt, vt, kb);
-        __builtin_amdgcn_sched_barrier(0);   // the 16 requests stay together, ahead of everything that uses them
-        use_block(kt, vt, kb);
+        const int kb_next = kb + 4 < kb_hi ? kb + 4 : kb;
+        use_block(kt, vt, kb, kb_next);
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(vt, kb_next);
+        __builtin_amdgcn_sched_barrier(0);
     }
     l_run += __shfl_xor(l_run, 32);
 
@@ -1150,8 +1158,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, int item, int part,
     if (*ticket_lds != a.ks - 1) return;
     if (tid == 0) __hip_atomic_store(&a.tickets[item], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next use
     // wavefront w combines 32-feature block w (blocks beyond D/32 have no wavefront).  Everything it
-    // needs from the up to eight parts is requested in one go (parts beyond ks re-read part 0 and
-    // get weight zero), so the merge costs one memory round trip.
+    // needs from the up to eight parts is requested in one go, so the merge costs one memory round trip.
     const float* base = a.part + (size_t)item * a.ks * PF;
     for (int db = wave; db < DB; db += 4) {
         float mc[8], lc[8], v[8][16];

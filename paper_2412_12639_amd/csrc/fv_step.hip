@@ -134,7 +134,7 @@ int set_gemm_attrs_d() {
 // 15.0, at 127 104 -> 69; its 160 items in three parts at 132 blocks 50.7 -> 36.8; 512 items of 70B at 30 blocks 38.0 -> 28.7; a prompt of 2000 rows,
 // 7B, 66 -> 49.  One each, where only the blocks without tests gain: 128 items in two parts equal at 5 to 25 blocks, 1.0 less at 129; 160 in one part
 // equal at 10 and 25, 1.6 less at 94; 256 items 0.3 to 0.8 more at 10 to 30, 0.6 less at 43, 1.9 less at 127.  Fewer items: equal to 0.7 more.
-// (Requesting a key block ahead in registers instead: slower than the other form below 60 blocks, up to 2 less above.)  bf16 only: fp32 tiles do
+// (A whole key block ahead in more registers instead: slower than the other form below 60 blocks, up to 2 less above.)  bf16 only: fp32 tiles do
 // not fit half a register file.
 template <typename EL>
 static bool attn_shares(int items) { return Tr<EL>::E == 8 && items >= 128; }
