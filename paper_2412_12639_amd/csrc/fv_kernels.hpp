@@ -1308,7 +1308,7 @@ static __global__ __launch_bounds__(NT) void k_argmax(ArgmaxArgs a) {
 // one workgroup each (k_sampled_nodes), and the path is read off afterwards (k_finish).  One
 // workgroup that walked the path node by node took 390 us at 33 nodes of vocabulary 32000, as much as
 // three layers: a dozen passes over the vocabulary one after the other, through one compute unit; this way
-// it takes 58 us.  A node's
+// it takes 52 us.  A node's
 // own passes are still serial: one over its logits (32 fp64 exponentials per thread) and one per
 // rejected child over w and q (384 KB through one compute unit's caches).  w is kept in memory: in registers it would
 // take half the register file of a compute unit, and the compiler spilled it.
@@ -1323,10 +1323,53 @@ struct SampledArgs {
     const double* u_sample;    // [T]
     double* work;              // [T][Vpad] w of every node
     int32_t* outcome;          // [T] child taken (> node), or -1 - token drawn, or FV_SAMPLED_BAD
+    int32_t* am;               // [T] greedy choices (written by k_sampled_resident)
 };
 
 #define FV_SAMPLED_THREADS 1024
+// 16-byte loads of the caller's array only where they are aligned
+__host__ __device__ __forceinline__ bool sampled_vectors(const float* draft_probs, int V) { return draft_probs && (V & 3) == 0 && ((uintptr_t)draft_probs & 15) == 0; }
 #define FV_SAMPLED_BAD ((int32_t)0x80000000)   // the node's logits hold a NaN or an infinity
+
+// One group of the draw: this thread's four tokens from v on, whose wavefront's share begins at `at`; incl: the wavefront's mass up to and with this
+// thread's.  The token drawn, if it is here, goes into s_pick.
+__device__ __forceinline__ void sampled_draw(int v, const double (&w)[4], double at, double incl, double target, int lane, int& last, int& s_pick) {
+    const double end = at + incl, prev = __shfl_up(incl, 1);
+    double cum = lane > 0 ? at + prev : at;
+    int pick = 0x7fffffff, mass = -1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        cum += w[e];
+        if (w[e] > 0.0) { mass = v + e; if (pick == 0x7fffffff && cum > target) pick = v + e; }
+    }
+    if (mass >= 0) last = mass;
+    if (!(end > target)) pick = 0x7fffffff;
+    else if (pick == 0x7fffffff && mass >= 0) pick = mass;   // rounding inside the four
+    const unsigned long long m = __ballot(pick != 0x7fffffff);   // tokens ascend with the lane
+    if (m && lane == __builtin_ctzll(m)) atomicMin(&s_pick, pick);
+}
+__device__ __forceinline__ double sampled_scan(const double (&w)[4], int lane) {   // prefix sum over the wavefront
+    double incl = (w[0] + w[1]) + (w[2] + w[3]);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double o = __shfl_up(incl, off);
+        if (lane >= off) incl += o;
+    }
+    return incl;
+}
+
+template <typename LAST>   // the thread's last token with any mass: asked for only where nothing was picked
+__device__ __forceinline__ void sampled_finish(const SampledArgs& a, int node, LAST last_with_mass, int& s_pick, int& s_flag) {
+    __syncthreads();
+    if (s_pick == 0x7fffffff) {   // target at or beyond the total (u_sample ~ 1 and rounding): the last token that has any mass
+        const int last = last_with_mass();
+        if (last >= 0) atomicMax(&s_flag, last + 1);
+        __syncthreads();
+        if (threadIdx.x == 0) a.outcome[node] = s_flag > 0 ? -s_flag : FV_SAMPLED_BAD;
+    } else if (threadIdx.x == 0) {
+        a.outcome[node] = -1 - s_pick;
+    }
+}
 
 static __global__ __launch_bounds__(FV_SAMPLED_THREADS) void k_sampled_nodes(SampledArgs a) {
     constexpr int NW = FV_SAMPLED_THREADS / 64, STRIDE = 4 * FV_SAMPLED_THREADS;   // a thread's tokens: four neighbours of every group of 4096
@@ -1341,7 +1384,7 @@ static __global__ __launch_bounds__(FV_SAMPLED_THREADS) void k_sampled_nodes(Sam
     const float* row = a.logits + (size_t)node * a.Vpad;      // rows of logits and of work are padded to 32 values
     double* work = a.work + (size_t)node * a.Vpad;
     const float* q = a.draft_probs ? a.draft_probs + (size_t)node * V : nullptr;
-    const bool q16 = q && (V & 3) == 0 && ((uintptr_t)a.draft_probs & 15) == 0;   // the caller's array: 16-byte loads only where they are aligned
+    const bool q16 = sampled_vectors(a.draft_probs, V);
 
     if (tid == 0) { s_flag = 0; s_pick = 0x7fffffff; }
     if (tid < FV_MAX_TREE) {   // the node's children as a bit mask
@@ -1469,40 +1512,258 @@ static __global__ __launch_bounds__(FV_SAMPLED_THREADS) void k_sampled_nodes(Sam
         const int v = v0 + tid * 4;
         double w[4] = {0.0, 0.0, 0.0, 0.0};
         if (v < V) load_w(v, w);
-        double incl = (w[0] + w[1]) + (w[2] + w[3]);   // prefix sum over the wavefront
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const double o = __shfl_up(incl, off);
-            if (lane >= off) incl += o;
-        }
+        const double incl = sampled_scan(w, lane);
         if (lane == 63) s_sum[turn][wave] = incl;
         __syncthreads();
         double at = base;
         for (int k = 0; k < NW; ++k) { if (k == wave) at = base; base += s_sum[turn][k]; }
         turn ^= 1;
-        const double end = at + incl, prev = __shfl_up(incl, 1);
-        double cum = lane > 0 ? at + prev : at;
-        int pick = 0x7fffffff, mass = -1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            cum += w[e];
-            if (w[e] > 0.0) { mass = v + e; if (pick == 0x7fffffff && cum > target) pick = v + e; }
-        }
-        if (mass >= 0) last = mass;
-        if (!(end > target)) pick = 0x7fffffff;
-        else if (pick == 0x7fffffff && mass >= 0) pick = mass;   // rounding inside the four
-        const unsigned long long m = __ballot(pick != 0x7fffffff);   // tokens ascend with the lane
-        if (m && lane == __builtin_ctzll(m)) atomicMin(&s_pick, pick);
+        sampled_draw(v, w, at, incl, target, lane, last, s_pick);
         if (base > target) break;   // the same in every thread
     }
-    __syncthreads();
-    if (s_pick == 0x7fffffff) {   // target at or beyond the total (u_sample ~ 1 and rounding): the last token that has any mass
-        if (last >= 0) atomicMax(&s_flag, last + 1);
-        __syncthreads();
-        if (tid == 0) a.outcome[node] = s_flag > 0 ? -s_flag : FV_SAMPLED_BAD;
-    } else if (tid == 0) {
-        a.outcome[node] = -1 - s_pick;
+    sampled_finish(a, node, [&]() { return last; }, s_pick, s_flag);
+}
+
+// Sums over a wavefront in every lane, by moves between registers instead of through LDS: the partners of the exchanges are those of shfl_xor with
+// 32, 16 .. 1, or with 1, 2 .. 32 (where a pattern has other partners, these hold the same sums by then), so the sums are too, bit for bit.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xf, 0xf, true), hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+template <int OFF>   // 16 or 32
+__device__ __forceinline__ double swap_add(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t l = (uint32_t)b, h = (uint32_t)(b >> 32);
+    const auto lo = OFF == 16 ? __builtin_amdgcn_permlane16_swap(l, l, false, false) : __builtin_amdgcn_permlane32_swap(l, l, false, false);
+    const auto hi = OFF == 16 ? __builtin_amdgcn_permlane16_swap(h, h, false, false) : __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) + __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+__device__ __forceinline__ double wave_sum_from32(double v) {
+    v = swap_add<16>(swap_add<32>(v));
+    return dpp_add<0xB1>(dpp_add<0x4E>(dpp_add<0x124>(dpp_add<0x128>(v))));   // row_ror 8, 4; quad_perm 2,3,0,1 and 1,0,3,2
+}
+__device__ __forceinline__ double wave_sum_from1(double v) {
+    v = dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(v))));      // ...; row_half_mirror, row_mirror
+    return swap_add<32>(swap_add<16>(v));
+}
+
+// The same decisions from the same sums for up to FV_SAMPLED_RESIDENT tokens, with w in registers and the greedy choice (k_argmax) found on the way:
+// the logits are read once, w never leaves the compute unit, the node's row of the draft distribution comes to LDS while w is formed, and
+// the draw adds up all groups before it looks into the one that the target lies in.  Half as many threads, each with the tokens and sums
+// of two of the other kernel's (number tid and tid + 512): with one's share, 64 registers of 128, the compiler spilled it.  33 nodes of 32000
+// tokens, argmax included: 61 -> 31 us (a node's two starts are most of it: the first look at its 128 KB, 5 us, and 64 fp64 exponentials a thread,
+// 5 us; then 3 us a rejected child, and the draw).  With the row read again by every rejected child and the draw group by group: 61 -> 34.
+#define FV_SAMPLED_GROUPS 8
+#define FV_SAMPLED_RESIDENT (FV_SAMPLED_GROUPS * 4 * FV_SAMPLED_THREADS)
+// Q: there is a draft distribution, which sampled_vectors allows 16-byte loads of.
+template <bool Q>
+static __global__ __launch_bounds__(FV_SAMPLED_THREADS / 2) void k_sampled_resident(SampledArgs a) {
+    constexpr int NT = FV_SAMPLED_THREADS / 2, NWH = NT / 64, NW = 2 * NWH;
+    constexpr int STRIDE = 4 * NT, G = 2 * FV_SAMPLED_GROUPS;   // groups of half the size: even ones are the first thread's, odd ones the second's
+    __shared__ double s_sum[2][NW], s_w[2], s_tot[G][NWH];
+    __shared__ float s_max[NWH];
+    __shared__ int s_arg, s_bad[NWH];
+    __shared__ unsigned long long s_kids[FV_MAX_TREE / 64];
+    __shared__ int32_t s_tok[FV_MAX_TREE];
+    __shared__ double s_u[FV_MAX_TREE];
+    extern __shared__ uint4 sampled_q[];   // Q: FV_SAMPLED_RESIDENT floats, the node's row of the draft distribution
+    __shared__ int s_flag, s_pick;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int node = blockIdx.x, V = a.V;
+    const int32_t* parent = a.tok_in + a.cap;
+    const float* q = Q ? a.draft_probs + (size_t)node * V : nullptr;
+    // loads past a row's end give zeros: no branch in the loops over groups (the last vector of logits that has a token is inside Vpad)
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.logits + (size_t)node * a.Vpad), 0, ((V + 3) & ~3) * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t qrs = __builtin_amdgcn_make_buffer_rsrc((void*)q, 0, Q ? V * 4 : 0, 0x00020000);
+
+    if (tid == 0) { s_flag = 0; s_pick = s_arg = 0x7fffffff; }
+    if (tid < FV_MAX_TREE) {   // the node's children as a bit mask
+        const unsigned long long m = __ballot(tid > node && tid < a.T && parent[tid < a.T ? tid : 0] == node);
+        if (lane == 0) s_kids[wave] = m;
+        s_tok[tid] = tid < a.T ? a.tok_in[tid] : 0;
+        s_u[tid] = tid < a.T ? a.u_accept[tid] : 0.0;
     }
+    auto here = [&]() {   // the thread's place in a group, in bytes (said to be new: sums with it are not kept in registers all the way through)
+        unsigned o = tid * 16u;
+        asm volatile("" : "+v"(o));
+        return o;
+    };
+    int wd = -1, c = -1, t = 0, taken = -1;
+    unsigned long long kids = 0;
+    auto next_child = [&]() {   // in index order; c < 0: none left
+        while (!kids && ++wd < FV_MAX_TREE / 64) kids = s_kids[wd];
+        c = -1;
+        if (!kids) return;
+        c = wd * 64 + __builtin_ctzll(kids);
+        kids &= kids - 1;
+        t = s_tok[c];
+    };
+    double w[G][4];
+    double S = 0.0;
+    int turn = 0;
+    for (bool first_time = true;; first_time = false) {   // again when nothing is left besides what was rejected (probability zero): the last p is kept
+        float x[G][4];
+        const unsigned o = here();
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const u32x4 r = __builtin_amdgcn_raw_buffer_load_b128(xrs, o + g * STRIDE * 4u, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[g][e] = __uint_as_float(r[e]);
+        }
+        // ---- largest logit
+        int left = V - tid * 4;   // tokens from this thread's first on (said to be new, as above)
+        asm volatile("" : "+v"(left));
+        float own = -INFINITY, nf = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) nf = fmaf(x[g][e], 0.f, nf);   // no longer zero behind a NaN or an infinity
+            if ((g + 1) * STRIDE > V) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[g][e] = g * STRIDE + e < left ? x[g][e] : -INFINITY;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) own = x[g][e] > own ? x[g][e] : own;
+            __builtin_amdgcn_sched_barrier(0);   // group by group, as they arrive
+        }
+        float mx = own;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        const bool wave_nf = __any(nf != 0.f);
+        if (lane == 0) { s_max[wave] = mx; s_bad[wave] = wave_nf; }
+        __syncthreads();
+        bool bad = false;
+#pragma unroll
+        for (int k = 0; k < NWH; ++k) { mx = fmaxf(mx, s_max[k]); bad |= s_bad[k] != 0; }
+        if (bad) {
+            if (tid == 0) { a.am[node] = -1; a.outcome[node] = FV_SAMPLED_BAD; }
+            return;
+        }
+        if (own == mx) {   // lowest token first, here and among the threads that have it
+            int at = 0;
+#pragma unroll
+            for (int k = 4 * G - 1; k >= 0; --k) at = x[k >> 2][k & 3] == mx ? (k >> 2) * STRIDE + (k & 3) : at;
+            atomicMin(&s_arg, at + tid * 4);
+        }
+        if (first_time) {
+            next_child();
+            if (Q && c >= 0) {   // the row is on its way while w is formed
+                typedef __attribute__((address_space(3))) void* lptr;
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(qrs, (lptr)(sampled_q + g * NT + wave * 64), 16, tid * 16 + g * STRIDE * 4, 0, 0, 0);
+            }
+        }
+
+        // ---- w before any rejection (zero beyond the vocabulary).  ls[k]: the sum of what is thread tid + 512 k's in the other kernel
+        const double zmax = (double)mx * a.inv_temperature;
+        double ls[2] = {0.0, 0.0};
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                w[g][e] = exp((double)x[g][e] * a.inv_temperature - zmax);
+                ls[g & 1] += w[g][e];
+            }
+            if (g & 1) __builtin_amdgcn_sched_barrier(0);   // eight at a time
+        }
+        // ---- the children, in index order
+        bool again = false;
+        for (bool filled = true;; filled = false) {
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(w[g][e]));   // w stays where it is
+            // the sum, in the other kernel's order, and the next child's w; every thread gets them.  Two areas in turn: one barrier.
+#pragma unroll
+            for (int k = 0; k < 2; ++k) ls[k] = wave_sum_from32(ls[k]);
+            if (lane == 0) { s_sum[turn][wave] = ls[0]; s_sum[turn][NWH + wave] = ls[1]; }
+            if (c >= 0 && ((t >> 2) & (NT - 1)) == tid) {
+                const int at = t - tid * 4;
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) if (at == g * STRIDE + e) s_w[turn] = w[g][e];
+            }
+            if (Q && filled) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wavefront's share of the row is in LDS
+            __syncthreads();
+            S = 0.0;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) S += s_sum[turn][k];
+            const double w_t = s_w[turn];
+            turn ^= 1;
+            again = !(S > 0.0) && !filled;
+            if (again || c < 0) break;
+            if (s_u[c] * (Q ? (double)((const float*)sampled_q)[t] : 1.0) * S <= w_t) { taken = c; break; }
+            const int struck = t - tid * 4;
+            next_child();
+            ls[0] = ls[1] = 0.0;
+            if constexpr (Q) {
+                int left = V - tid * 4;
+                asm volatile("" : "+v"(left));
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const float4 f = ((const float4*)sampled_q)[g * NT + tid];
+                    const bool in = g * STRIDE < left;   // all four or none (sampled_vectors); past the row's end LDS holds anything
+                    const float qv[4] = {in ? f.x : 0.f, in ? f.y : 0.f, in ? f.z : 0.f, in ? f.w : 0.f};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        w[g][e] = fmax(w[g][e] - S * (double)qv[e], 0.0);
+                        ls[g & 1] += w[g][e];
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        w[g][e] = g * STRIDE + e == struck ? 0.0 : w[g][e];
+                        ls[g & 1] += w[g][e];
+                    }
+            }
+        }
+        if (!again) break;
+    }
+    if (tid == 0) a.am[node] = s_arg;
+    if (taken >= 0) {
+        if (tid == 0) a.outcome[node] = taken;
+        return;
+    }
+
+    // ---- draw, as in k_sampled_nodes, but all groups' sums first: only the group that the target lies in is looked into
+    const double target = a.u_sample[node] * S;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const double total = wave_sum_from1((w[g][0] + w[g][1]) + (w[g][2] + w[g][3]));   // the last lane's of sampled_scan
+        if (lane == 0) s_tot[g][wave] = total;
+    }
+    __syncthreads();
+    double base = 0.0, at[2] = {0.0, 0.0};
+    int g2 = 0;
+    for (; g2 < G && g2 * STRIDE < V; g2 += 2) {
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            if (k % NWH == wave) at[k / NWH] = base;
+            base += s_tot[g2 + k / NWH][k % NWH];
+        }
+        if (base > target) break;   // the same in every thread
+    }
+    int last = -1;
+#pragma unroll
+    for (int g = 0; g < G; g += 2)
+        if (g == g2) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) sampled_draw((g + k) * STRIDE + tid * 4, w[g + k], at[k], sampled_scan(w[g + k], lane), target, lane, last, s_pick);
+        }
+    sampled_finish(a, node, [&]() {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) if (g < g2 + 2 && w[g][e] > 0.0) last = g * STRIDE + tid * 4 + e;
+        return last;
+    }, s_pick, s_flag);
 }
 
 // ============================================================================ end of a step

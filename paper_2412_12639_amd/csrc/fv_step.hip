@@ -123,6 +123,7 @@ template <typename EL, int D>
 int set_gemm_attrs_d() {
     HIPCHK(hipFuncSetAttribute((const void*)k_attn_canon<EL, D>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                FV_CANON_SMEM_BYTES(D, Tr<EL>::ESZ)));
+    HIPCHK(hipFuncSetAttribute((const void*)k_sampled_resident<true>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_SAMPLED_RESIDENT * 4));
     int rc = set_gemm_attrs_e<EL, D, EPI_QKV>();
     if (!rc) rc = set_gemm_attrs_e<EL, D, EPI_RESID>();
     if (!rc) rc = set_gemm_attrs_e<EL, D, EPI_SWIGLU>();
@@ -349,17 +350,21 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
         PhaseTimer pt(c, FV_PH_OTHER);
         ArgmaxArgs am;
         am.logits = c->at<float>(ly.off_logits); am.am = c->at<FvResult>(ly.off_res)->argmax; am.V = cf.vocab; am.Vpad = ly.Vpad;
+        const bool resident = mode == STEP_VERIFY_SAMPLED && cf.vocab <= FV_SAMPLED_RESIDENT &&   // the acceptance finds them as well
+                              (!c->sample_draft || sampled_vectors(c->sample_draft, cf.vocab));
         // one round of requests per row where it has more than a round's worth for 256 threads (8192 values)
-        if (cf.vocab > 8192) hipLaunchKernelGGL(k_argmax<1024>, dim3(T), dim3(1024), 0, st, am);
-        else hipLaunchKernelGGL(k_argmax<256>, dim3(T), dim3(256), 0, st, am);
+        if (!resident && cf.vocab > 8192) hipLaunchKernelGGL(k_argmax<1024>, dim3(T), dim3(1024), 0, st, am);
+        else if (!resident) hipLaunchKernelGGL(k_argmax<256>, dim3(T), dim3(256), 0, st, am);
         if (mode == STEP_VERIFY_SAMPLED) {
             SampledArgs sa;
             sa.tok_in = c->at<int32_t>(ly.off_stepin); sa.cap = FV_MAX_TREE; sa.T = T;
             sa.logits = c->at<float>(ly.off_logits); sa.V = cf.vocab; sa.Vpad = ly.Vpad;
             sa.inv_temperature = c->sample_inv_temperature; sa.draft_probs = c->sample_draft;
             sa.u_accept = c->at<double>(ly.off_unif); sa.u_sample = sa.u_accept + FV_MAX_TREE;
-            sa.work = c->at<double>(ly.off_pwork); sa.outcome = c->at<int32_t>(ly.off_outcome);
-            hipLaunchKernelGGL(k_sampled_nodes, dim3(T), dim3(FV_SAMPLED_THREADS), 0, st, sa);
+            sa.work = c->at<double>(ly.off_pwork); sa.outcome = c->at<int32_t>(ly.off_outcome); sa.am = am.am;
+            if (resident && sa.draft_probs) hipLaunchKernelGGL(k_sampled_resident<true>, dim3(T), dim3(FV_SAMPLED_THREADS / 2), FV_SAMPLED_RESIDENT * 4, st, sa);
+            else if (resident) hipLaunchKernelGGL(k_sampled_resident<false>, dim3(T), dim3(FV_SAMPLED_THREADS / 2), 0, st, sa);
+            else hipLaunchKernelGGL(k_sampled_nodes, dim3(T), dim3(FV_SAMPLED_THREADS), 0, st, sa);
         }
         if (mode == STEP_VERIFY || mode == STEP_VERIFY_SAMPLED) {
             // accepted path, its features (what the drafter is given next to the tokens), cache compaction

@@ -201,3 +201,37 @@ def test_sampled_decisions_at_any_vocabulary_size(fvmod, vocab):
             assert 0 <= got[2] < vocab
     assert checked >= 3
     g.close()
+
+
+@pytest.mark.parametrize("vocab", [2048, 4100, 30724, 32764, 32768, 32772])
+def test_sampled_decisions_do_not_depend_on_where_the_proposals_lie(fvmod, vocab):
+    """Proposals at an address that 16-byte loads take, and up to 32768 tokens, are kept on the chip; the same numbers four bytes
+    further on are read from memory for every rejected child.  Both add up in the same order, so every decision, the token drawn
+    and the greedy choices are equal, not close; also where a rejection leaves nothing behind, and at the end of the sum."""
+    import torch
+    from dataclasses import replace
+    s = replace(fi.SHAPES["tiny"], name=f"tiny-v{vocab}", vocab=vocab)
+    L, n = 20, 24
+    g = fvmod.FalconVerifier(s, max_seq=64, max_tree=32)
+    g.init_weights(fi.gen_weights(s, seed=6))
+    root = g.prefill(fi.gen_prefix(4, L, s.vocab))
+    parent, depth, _ = fi.gen_tree(9, n, [12, 2, 2])
+    rng = np.random.default_rng(vocab)
+    for over in (0.0, 0.0, 3.0):
+        tokens = rng.integers(0, vocab, n).astype(np.int32)
+        tokens[0] = root
+        tokens[-1] = vocab - 1
+        ua, us = rng.uniform(0.2, 1.0, n), rng.random(n)
+        us[0] = 1.0 if over else us[0]
+        q = rng.random((n, vocab)).astype(np.float32) ** 3
+        q = (q / q.sum(axis=1, keepdims=True)).astype(np.float32) + np.float32(over)
+        out = []
+        for at in (0, 1):
+            qdev = torch.empty(n * vocab + 1, device="cuda")[at:][:n * vocab].view(n, vocab)
+            qdev.copy_(torch.from_numpy(q))
+            a, acc, nxt = g.verify_tree_sampled(tokens, parent, depth, 1.0, ua, us, qdev)
+            out.append((a, list(acc), nxt, list(g.argmax())))
+            assert out[-1][3] == [int(i) for i in np.argmax(g.logits(n), axis=1)]
+            g.rollback(L, root)
+        assert out[0] == out[1]
+    g.close()
