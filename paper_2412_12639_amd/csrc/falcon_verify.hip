@@ -147,7 +147,7 @@ void plan_gemm_forms(GemmPlan& gm, GemmPlan& gd, GemmPlan& gp, bool& paired_ok, 
     // measured 3 to 5 us slower than split ones, and the paired form 8 to 15 us slower than the direct one.)
     const bool small = gd.n_strips < n_wg && gd.NB <= 24;
     // a full K range must give each streaming wavefront at least three stages, so that no
-    // wavefront meets more than two segment ends within one round of three stages
+    // wavefront meets more than two segment ends within one round of its stages (two, in the paired form)
     paired_ok = gp.NB >= 12 && !small;
     // Whole row groups per workgroup need no partial-tile exchange at all, but the group counts
     // differ by one between workgroups: worth it only when that idles little of the chip (the

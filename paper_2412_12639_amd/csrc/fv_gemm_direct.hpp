@@ -23,7 +23,7 @@
 // Two of the paired form's stages under way in each of three wavefronts, 48 KiB of weights a compute unit, take in
 // all that HBM gives (a launch that only reads: 6.6 TB/s from 48 KiB on); a third only queues up in front of
 // the exchange's looks, and 64 rows of 7B take 3719 us a step with it, 3667 without, one row in four layers 498 and 493.
-// The direct form's matrices are so short that a slice is three stages or a few more.
+// The direct form's matrices are so short that a slice is three stages or a few more: it keeps three.
 //
 // The streaming loop is kept to the instructions that matter.  With one wavefront per SIMD nothing
 // hides instruction issue, and an earlier form of this loop (a general cursor advanced three times
@@ -202,7 +202,7 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
 #endif
     enter_slice(0);
     FV_TS(2)
-    // prologue in the loop's own issue order: X(0) W(0) X(1) W(1) X(2) W(2)
+    // prologue in the loop's own issue order: X(0) W(0) X(1) W(1), RS = 1 also X(2) W(2)
 #pragma unroll
     for (int i = 0; i < SETS; ++i) {
         load_x(x[i]);
