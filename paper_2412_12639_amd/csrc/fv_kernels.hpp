@@ -1553,7 +1553,7 @@ __device__ __forceinline__ double wave_sum_from1(double v) {
 // the logits are read once, w never leaves the compute unit, the node's row of the draft distribution comes to LDS while w is formed, and
 // the draw adds up all groups before it looks into the one that the target lies in.  Half as many threads, each with the tokens and sums
 // of two of the other kernel's (number tid and tid + 512): with one's share, 64 registers of 128, the compiler spilled it.  33 nodes of 32000
-// tokens, argmax included: 61 -> 31 us (a node's two starts are most of it: the first look at its 128 KB, 5 us, and 64 fp64 exponentials a thread,
+// tokens, argmax included: 61 -> 27 us (a node's two starts are most of it: the first look at its 128 KB, 5 us, and 64 fp64 exponentials a thread,
 // 5 us; then 3 us a rejected child, and the draw).  With the row read again by every rejected child and the draw group by group: 61 -> 34.
 #define FV_SAMPLED_GROUPS 8
 #define FV_SAMPLED_RESIDENT (FV_SAMPLED_GROUPS * 4 * FV_SAMPLED_THREADS)
@@ -1620,12 +1620,11 @@ static __global__ __launch_bounds__(FV_SAMPLED_THREADS / 2) void k_sampled_resid
         for (int g = 0; g < G; ++g) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) nf = fmaf(x[g][e], 0.f, nf);   // no longer zero behind a NaN or an infinity
-            if ((g + 1) * STRIDE > V) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) x[g][e] = g * STRIDE + e < left ? x[g][e] : -INFINITY;
+            for (int e = 0; e < 4; ++e) {
+                x[g][e] = g * STRIDE + e < left ? x[g][e] : -INFINITY;
+                own = x[g][e] > own ? x[g][e] : own;
             }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) own = x[g][e] > own ? x[g][e] : own;
             __builtin_amdgcn_sched_barrier(0);   // group by group, as they arrive
         }
         float mx = own;
