@@ -1555,20 +1555,24 @@ __device__ __forceinline__ double wave_sum_from1(double v) {
 // of two of the other kernel's (number tid and tid + 512): with one's share, 64 registers of 128, the compiler spilled it.  33 nodes of 32000
 // tokens, argmax included: 61 -> 27 us (a node's two starts are most of it: the first look at its 128 KB, 5 us, and 64 fp64 exponentials a thread,
 // 5 us; then 3 us a rejected child, and the draw).  With the row read again by every rejected child and the draw group by group: 61 -> 34.
-#define FV_SAMPLED_GROUPS 8
-#define FV_SAMPLED_RESIDENT (FV_SAMPLED_GROUPS * 4 * FV_SAMPLED_THREADS)
-// Q: there is a draft distribution, which sampled_vectors allows 16-byte loads of.
-template <bool Q>
+// Q: there is a draft distribution, which sampled_vectors allows 16-byte loads of.  G: groups of 2048 tokens.  Those past the vocabulary cost as much as
+// the others, so the host takes the fewest of 2, 4, 8 and 16 that hold it.  A call with 24 nodes (two layers of hidden 512; us without / with a draft
+// distribution): 2000 tokens 143 / 131 in 16 groups, 124 / 122 in 2, 132 / 126 by k_argmax and k_sampled_nodes; 8000 tokens 145 / 141 in 16, 130 / 127 in 4,
+// 141 / 139 by the two; 16000 tokens 147 / 139 in 16, 139 / 135 in 8, 155 / 147 by the two.
+#define FV_SAMPLED_GROUP (2 * FV_SAMPLED_THREADS)
+#define FV_SAMPLED_RESIDENT (16 * FV_SAMPLED_GROUP)
+template <bool Q, int G>
 static __global__ __launch_bounds__(FV_SAMPLED_THREADS / 2) void k_sampled_resident(SampledArgs a) {
     constexpr int NT = FV_SAMPLED_THREADS / 2, NWH = NT / 64, NW = 2 * NWH;
-    constexpr int STRIDE = 4 * NT, G = 2 * FV_SAMPLED_GROUPS;   // groups of half the size: even ones are the first thread's, odd ones the second's
+    constexpr int STRIDE = FV_SAMPLED_GROUP;   // half of the other kernel's: even groups are the first thread's, odd ones the second's
+    static_assert(STRIDE == 4 * NT && G % 2 == 0);
     __shared__ double s_sum[2][NW], s_w[2], s_tot[G][NWH];
     __shared__ float s_max[NWH];
     __shared__ int s_arg, s_bad[NWH];
     __shared__ unsigned long long s_kids[FV_MAX_TREE / 64];
     __shared__ int32_t s_tok[FV_MAX_TREE];
     __shared__ double s_u[FV_MAX_TREE];
-    extern __shared__ uint4 sampled_q[];   // Q: FV_SAMPLED_RESIDENT floats, the node's row of the draft distribution
+    extern __shared__ uint4 sampled_q[];   // Q: G * FV_SAMPLED_GROUP floats, the node's row of the draft distribution
     __shared__ int s_flag, s_pick;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int node = blockIdx.x, V = a.V;

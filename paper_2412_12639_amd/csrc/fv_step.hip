@@ -30,6 +30,13 @@ static void set_split(GemmArgs& ga, const GemmPlan& p) {
     ga.div_G = make_div((unsigned)p.G); ga.div_NB = make_div((unsigned)p.NB);
 }
 
+template <int G>
+static void launch_sampled_resident(const SampledArgs& sa, hipStream_t st) {
+    const dim3 nt(FV_SAMPLED_THREADS / 2);
+    if (sa.draft_probs) hipLaunchKernelGGL((k_sampled_resident<true, G>), dim3(sa.T), nt, G * FV_SAMPLED_GROUP * 4, st, sa);
+    else hipLaunchKernelGGL((k_sampled_resident<false, G>), dim3(sa.T), nt, 0, st, sa);
+}
+
 template <typename EL, int TB, int D, int EPI>
 int launch_gemm_t(fv_ctx* c, const GemmArgs& ga0) {
     const size_t lds = (size_t)2 * TB * 32 * 256;
@@ -123,7 +130,8 @@ template <typename EL, int D>
 int set_gemm_attrs_d() {
     HIPCHK(hipFuncSetAttribute((const void*)k_attn_canon<EL, D>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                FV_CANON_SMEM_BYTES(D, Tr<EL>::ESZ)));
-    HIPCHK(hipFuncSetAttribute((const void*)k_sampled_resident<true>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_SAMPLED_RESIDENT * 4));
+    HIPCHK(hipFuncSetAttribute((const void*)k_sampled_resident<true, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * FV_SAMPLED_GROUP * 4));
+    HIPCHK(hipFuncSetAttribute((const void*)k_sampled_resident<true, 16>, hipFuncAttributeMaxDynamicSharedMemorySize, 16 * FV_SAMPLED_GROUP * 4));
     int rc = set_gemm_attrs_e<EL, D, EPI_QKV>();
     if (!rc) rc = set_gemm_attrs_e<EL, D, EPI_RESID>();
     if (!rc) rc = set_gemm_attrs_e<EL, D, EPI_SWIGLU>();
@@ -362,8 +370,11 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
             sa.inv_temperature = c->sample_inv_temperature; sa.draft_probs = c->sample_draft;
             sa.u_accept = c->at<double>(ly.off_unif); sa.u_sample = sa.u_accept + FV_MAX_TREE;
             sa.work = c->at<double>(ly.off_pwork); sa.outcome = c->at<int32_t>(ly.off_outcome); sa.am = am.am;
-            if (resident && sa.draft_probs) hipLaunchKernelGGL(k_sampled_resident<true>, dim3(T), dim3(FV_SAMPLED_THREADS / 2), FV_SAMPLED_RESIDENT * 4, st, sa);
-            else if (resident) hipLaunchKernelGGL(k_sampled_resident<false>, dim3(T), dim3(FV_SAMPLED_THREADS / 2), 0, st, sa);
+            const int groups = (cf.vocab + FV_SAMPLED_GROUP - 1) / FV_SAMPLED_GROUP;
+            if (resident && groups <= 2) launch_sampled_resident<2>(sa, st);
+            else if (resident && groups <= 4) launch_sampled_resident<4>(sa, st);
+            else if (resident && groups <= 8) launch_sampled_resident<8>(sa, st);
+            else if (resident) launch_sampled_resident<16>(sa, st);
             else hipLaunchKernelGGL(k_sampled_nodes, dim3(T), dim3(FV_SAMPLED_THREADS), 0, st, sa);
         }
         if (mode == STEP_VERIFY || mode == STEP_VERIFY_SAMPLED) {

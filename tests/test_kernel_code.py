@@ -44,6 +44,22 @@ def test_kernels_that_are_meant_to_fit_the_registers_use_no_scratch(code_objects
     assert not {n: b for n, b in meant.items() if b}
 
 
+def test_the_resident_acceptance_does_no_more_exponentials_than_its_groups_hold_tokens(code_objects):
+    """A group is 2048 tokens for 512 threads: four exponentials a thread, one scaling by a power of two each.  A vocabulary takes the fewest groups
+    that hold it, so that a small one does not pay for 32768 tokens; and the working distribution is in registers, which the largest instances fill (one
+    value of theirs, eight bytes, is kept in scratch)."""
+    found = {}
+    for co in code_objects:
+        asm = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", str(co)], capture_output=True, text=True, check=True).stdout
+        notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", str(co)], capture_output=True, text=True, check=True).stdout
+        scratch = dict(re.findall(r"\.name:\s+(_Z\S+).*?\.private_segment_fixed_size:\s+(\d+)", notes, re.S))
+        for name, q, groups, body in re.findall(r"^[0-9a-f]+ <(_ZL18k_sampled_residentILb([01])ELi(\d+)E\S+)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", asm, re.S | re.M):
+            assert body.count("v_ldexp_f64") == 4 * int(groups), name
+            assert int(scratch[name]) <= (8 if groups == "16" else 0), name
+            found[q, int(groups)] = name
+    assert sorted(found) == [(q, g) for q in "01" for g in (2, 4, 8, 16)]
+
+
 def _registers(text):
     """Vector registers an operand list names."""
     out = set()
