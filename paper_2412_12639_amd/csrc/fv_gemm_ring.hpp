@@ -77,6 +77,11 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
     const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, (int)((unsigned)a.NB * 256u * (unsigned)ld), 0x00020000);
     int fg = g0, fk = k0, fn = 0, fslot = 0, fi = ti, ft0 = WIDE ? column_of(ti) : 0, fpar = 0;   // group, stage inside it, stages issued, slot; tile, its first column, its factors' place
     unsigned wo = 0, xo = 0;
+    // A matrix of 32 MiB and more, all that the L2s hold, goes past the caches in a step (a row group's K batch is 32 KiB).  Smaller ones are better read plainly,
+    // also where the layers together are more than the memory-side cache holds.  us a step of 100 / 250 rows, all plainly, all past the caches, by this rule:
+    // hidden 1024, 8 layers 569 / 698, 599 / 730, 563 / 693; hidden 2048, 2 layers 231 / 298, 251 / 318, 236 / 294, 6 layers 600 / 787, 618 / 803, 588 / 777;
+    // 7B width, 2 layers 434 / 568, 411 / 538, 406 / 534; 13B 518 / 684, 477 / 660, 474 / 659.  (From 64 MiB on instead: equal to 1 % either way; from 128 on 0 to 3 % more.)
+    const bool once = !WIDE && (unsigned)a.NG * (unsigned)a.NB >= 1024u;
     auto place = [&]() {                                // of the stage to fill next
         const int strip = fg * FV_R + wave;             // tiled [strip pair][half K batch][2 strips][4 frags]: a stage of a strip is 2 KiB
         wo = ((((unsigned)(strip >> 1) * (2 * a.NB) + (fk >> 1)) * 2 + (strip & 1)) * 4 + (fk & 1) * 2) * 1024u;
@@ -87,8 +92,16 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
         char* const w = ring + fslot * SB + wave * 2048;
         char* const x = ring + fslot * SB + AB + wave * (TT * 16);
         switch (i) {
-            case 0: __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 0, WIDE ? 0 : FV_READ_ONCE); break;
-            case 1: __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 1024, WIDE ? 0 : FV_READ_ONCE); break;
+            case 0:                                     // both of the strip's fragments
+                if (once) {
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 0, FV_READ_ONCE);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 1024, FV_READ_ONCE);
+                } else {
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lptr)w, 16, lane * 16, (int)wo, 1024, 0);
+                }
+                break;
+            case 1: break;
             case 2: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 0, 0); break;
             case 3: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 1024, 0); break;
             case 4: __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (lptr)x, 16, lane * 16, (int)xo, 2048, 0); break;

@@ -60,6 +60,23 @@ def test_the_resident_acceptance_does_no_more_exponentials_than_its_groups_hold_
     assert sorted(found) == [(q, g) for q in "01" for g in (2, 4, 8, 16)]
 
 
+def test_the_ring_reads_a_steps_weights_past_the_caches_or_plainly(code_objects):
+    """By the matrix's size, which the kernel sees at run time: of every stage's weights (two loads a wavefront) both forms are there, of its activations (one load for
+    64 rows) and of a prompt's tiles only the plain one."""
+    found = 0
+    for co in code_objects:
+        asm = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", str(co)], capture_output=True, text=True, check=True).stdout
+        for name, tb, wide, body in re.findall(r"^[0-9a-f]+ <(_Z11k_gemm_ringILi(\d)ELi\d+ELi\dELb([01])E\S+)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", asm, re.S | re.M):
+            loads = [l for l in body.splitlines() if "buffer_load_dwordx4" in l and " lds" in l]
+            past = sum(" nt" in l for l in loads)
+            if wide == "1":
+                assert loads and not past, name
+            else:
+                assert past and 2 * (len(loads) - past) == past * (2 + int(tb) // 2), (name, len(loads), past)
+            found += 1
+    assert found == 2 * (4 * 2 + 3)     # four epilogues at 128 and at 256 rows, three for prompts, two head sizes
+
+
 def _registers(text):
     """Vector registers an operand list names."""
     out = set()
