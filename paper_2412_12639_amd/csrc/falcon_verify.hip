@@ -224,7 +224,7 @@ void make_layout(const fv_cfg& c, int n_wg, Layout& L, bool own_head, size_t min
     L.off_pos = take(FV_MAX_TREE * 4);
     L.off_anc = take(FV_MAX_TREE * (FV_CANON_DEPTH + 1));
     L.off_rope = take((size_t)FV_MAX_TREE * (d / 2) * 8);
-    L.off_res = take(sizeof(FvResult));
+    L.off_rows = take(sizeof(FvRows));
     L.off_feat = take((size_t)FV_MAX_TREE * c.hidden * 4);
     L.off_unif = take((size_t)2 * FV_MAX_TREE * 8);
     L.off_outcome = take(FV_MAX_TREE * 4);
@@ -688,7 +688,7 @@ int fv_get_logits(fv_ctx* c, float* out, int32_t n) {
 
 int fv_get_argmax(fv_ctx* c, int32_t* out, int32_t n) {
     if (!c || !out || n < 1 || n > c->last_T) return FV_E_BAD_ARG;
-    memcpy(out, c->h_res->argmax, (size_t)n * 4);   // came back with the step's result
+    memcpy(out, c->h_res->rows.argmax, (size_t)n * 4);   // came back with the step's result
     return FV_OK;
 }
 

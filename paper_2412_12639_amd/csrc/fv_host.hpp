@@ -52,7 +52,7 @@ struct Layout {
     size_t off_k = 0, off_v = 0, kv_layer_bytes = 0;
     size_t off_x = 0, off_xb = 0, off_q = 0, off_qlo = 0, off_attn = 0, off_act = 0, off_logits = 0;
     size_t off_ssq = 0, off_rinv = 0, off_part = 0, part_bytes = 0, off_tickets = 0;
-    size_t off_stepin = 0, off_mask = 0, off_pos = 0, off_anc = 0, off_rope = 0, off_res = 0;
+    size_t off_stepin = 0, off_mask = 0, off_pos = 0, off_anc = 0, off_rope = 0, off_rows = 0;
     size_t off_kvread = 0, off_stage = 0, stage_bytes = 0;
     size_t off_apart = 0, off_atick = 0, off_zeros = 0, off_feat = 0;
     size_t off_unif = 0, off_pwork = 0, off_outcome = 0;   // non-greedy acceptance: uniforms [2][256] fp64, working distributions [max_tree][Vpad] fp64 (over the staging area), what each node decided [256]
@@ -105,7 +105,7 @@ struct fv_ctx {
     bool last_was_verify = false;
     int32_t* h_in = nullptr;      // pinned [3][256]; steps of up to 64 rows read it from the device
     int32_t* h_prompt = nullptr;  // pinned [max_seq]: the prompt while its pieces are on their way (lay.Pm > 0 only)
-    FvResult* h_res = nullptr;    // pinned; a verification step's last kernel writes it
+    FvResult* h_res = nullptr;    // pinned
     double* h_unif = nullptr;     // pinned [2][256]: u_accept, u_sample of a non-greedy step
     double sample_inv_temperature = 1.0;      // of the non-greedy step being run
     const float* sample_draft = nullptr;      // device [n][vocab] or null

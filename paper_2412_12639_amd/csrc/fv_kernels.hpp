@@ -1866,12 +1866,12 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a) {
     const int len = s_len;
     int b = blockIdx.x;
     if (b == 0) {
-        if (i == 0) { a.res->accepted_len = len; a.res->next_token = s_next; a.res->best = s_best; a.res->fault = *a.fault; }
+        if (i == 0) { a.res->accepted_len = len; a.res->next_token = s_next; a.res->best = s_best; a.res->rows.fault = *a.fault; }
         if (i <= len) {
             a.res->path[i] = s_path[i];
             if (i >= 1) a.res->accepted_tokens[i - 1] = s_tok[s_path[i]];
         }
-        if (i < a.T) a.res->argmax[i] = a.am[i];
+        if (i < a.T) a.res->rows.argmax[i] = a.am[i];
         __threadfence_system();
         return;
     }

@@ -285,7 +285,7 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
         ga.ssq_in = c->at<float>(ly.off_ssq); ga.n_ssq = h / 32; ga.inv_h = 1.f / (float)h; ga.eps = cf.rms_eps;
         ga.mark = c->exchange_test ? 0u : 1u;   // the test of the time-out leaves the partial tiles unmarked
         ga.spin_limit = c->exchange_test ? 2u : FV_EXCHANGE_SPINS;
-        ga.fault = &c->at<FvResult>(ly.off_res)->fault;
+        ga.fault = &c->at<FvRows>(ly.off_rows)->fault;
         return ga;
     };
 
@@ -357,7 +357,7 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
         }
         PhaseTimer pt(c, FV_PH_OTHER);
         ArgmaxArgs am;
-        am.logits = c->at<float>(ly.off_logits); am.am = c->at<FvResult>(ly.off_res)->argmax; am.V = cf.vocab; am.Vpad = ly.Vpad;
+        am.logits = c->at<float>(ly.off_logits); am.am = c->at<FvRows>(ly.off_rows)->argmax; am.V = cf.vocab; am.Vpad = ly.Vpad;
         const bool resident = mode == STEP_VERIFY_SAMPLED && cf.vocab <= FV_SAMPLED_RESIDENT &&   // the acceptance finds them as well
                               (!c->sample_draft || sampled_vectors(c->sample_draft, cf.vocab));
         // one round of requests per row where it has more than a round's worth for 256 threads (8192 values)
@@ -381,8 +381,8 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
             // accepted path, its features (what the drafter is given next to the tokens), cache compaction
             FinishArgs fa;
             fa.tok_in = c->at<int32_t>(ly.off_stepin); fa.cap = FV_MAX_TREE; fa.T = T;
-            fa.mask = c->at<uint64_t>(ly.off_mask); fa.am = c->at<FvResult>(ly.off_res)->argmax; fa.outcome = c->at<int32_t>(ly.off_outcome);
-            fa.fault = &c->at<FvResult>(ly.off_res)->fault; fa.res = c->h_res;
+            fa.mask = c->at<uint64_t>(ly.off_mask); fa.am = c->at<FvRows>(ly.off_rows)->argmax; fa.outcome = c->at<int32_t>(ly.off_outcome);
+            fa.fault = &c->at<FvRows>(ly.off_rows)->fault; fa.res = c->h_res;
             fa.x = c->at<float>(ly.off_x); fa.ssq = c->at<float>(ly.off_ssq); fa.gain = c->gain(2 * cf.n_layers); fa.feat = c->at<float>(ly.off_feat);
             fa.h = h; fa.Tp = Tp; fa.inv_h = 1.f / (float)h; fa.eps = cf.rms_eps;
             fa.kcache = c->at<void>(ly.off_k); fa.vcache = c->at<void>(ly.off_v); fa.slabs = cf.n_layers * cf.n_kv_heads; fa.L = L; fa.S_pad = ly.S_pad;
@@ -394,11 +394,11 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
     }
     HIPCHK(hipEventRecord(c->ev1, st));
     // a verification step's record is the last kernel's to write; a prompt's last chunk has its rows' greedy choices copied back with the error word
-    if (mode == STEP_PREFILL_LAST) HIPCHK(hipMemcpyAsync(c->h_res, c->at<FvResult>(ly.off_res), sizeof(FvResult), hipMemcpyDeviceToHost, st));
-    else if (mode == STEP_PREFILL_MID) HIPCHK(hipMemcpyAsync(&c->h_res->fault, &c->at<FvResult>(ly.off_res)->fault, 4, hipMemcpyDeviceToHost, st));
+    if (mode == STEP_PREFILL_LAST) HIPCHK(hipMemcpyAsync(&c->h_res->rows, c->at<FvRows>(ly.off_rows), sizeof(FvRows), hipMemcpyDeviceToHost, st));
+    else if (mode == STEP_PREFILL_MID) HIPCHK(hipMemcpyAsync(&c->h_res->rows.fault, &c->at<FvRows>(ly.off_rows)->fault, 4, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (mode == STEP_PREFILL_LAST) c->h_res->next_token = c->h_res->argmax[T - 1];
-    if (c->h_res->fault) {
+    if (mode == STEP_PREFILL_LAST) c->h_res->next_token = c->h_res->rows.argmax[T - 1];
+    if (c->h_res->rows.fault) {
         if (c->scr->dirty) *c->scr->dirty = true;   // unconsumed partial tiles may be left behind
         return FV_E_EXCHANGE_TIMEOUT;
     }

@@ -15,13 +15,18 @@
 
 #define FV_SCAN_NONFINITE (-2)   // FvResult.accepted_len when some node's logits hold a NaN or an infinity
 
-// Result of the longest-accepted-path scan, written by the device and copied to the host.
+// What a step leaves in device memory for its last kernel and for a prompt's end.
+struct FvRows {
+    uint32_t fault, pad[3];        // set by a GEMM whose partial-tile wait ran out (never cleared: the context is unusable then)
+    int32_t argmax[FV_MAX_TREE];   // greedy choice at every row of the step (-1: none)
+};
+
+// A step's result, in pinned host memory: written whole by a verification step's last kernel; a prompt's steps have `rows` copied there (of all but the last, the error word).
 struct FvResult {
+    FvRows rows;
     int32_t accepted_len, next_token, best, pad;
-    uint32_t fault, pad2[3];   // fault: set by a GEMM whose partial-tile wait ran out (never cleared: the context is unusable then)
     int32_t path[FV_MAX_TREE];
     int32_t accepted_tokens[FV_MAX_TREE];
-    int32_t argmax[FV_MAX_TREE];   // greedy choice at every row of the step (-1: none), read back with the rest
 };
 
 enum { TILE_NAT = 0, TILE_QKV = 1, TILE_GU = 2 };   // weight re-tiling: natural row order, q|k|v with rotary pairing, gate/up interleaved
