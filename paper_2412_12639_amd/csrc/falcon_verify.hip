@@ -459,7 +459,8 @@ int fv_create_ex(const fv_cfg* cfg, void* dev_arena, size_t arena_bytes, void* h
         p.n_fix = build_split_tables(p, tab);
         if (hipMemcpy(c->arena + p.off_tab, tab.data(), tab.size() * 4, hipMemcpyHostToDevice) != hipSuccess) return fail(FV_E_HIP);
     }
-    for (int i = 0; i < GM_COUNT; ++i)   // the direct kernels split their work with 32-bit arithmetic
+    // split_unit numbers a matrix's units with 32 bits.  (Stricter than that needs, by the factor of workgroups: the product that an earlier form of it took.)
+    for (int i = 0; i < GM_COUNT; ++i)
         for (const GemmPlan* q : {&c->lay.gd[i], &c->lay.gp[i]})
             if ((long long)q->NG * q->NB * (q->G + 1) >= (1LL << 31)) return fail(FV_E_BAD_ARG);
     // the shared-activation kernel addresses the partial tiles with 32-bit byte offsets

@@ -165,7 +165,10 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
 #endif
         const bool live = rq.j < rq.n;
         const uint4* p = live ? rq.wp : zeros;
-        // The paired form's matrices (12 MB and more) go past the caches: the four products of a 7B layer 115 -> 106.5 us at 64 rows, 97.5 -> 90 at 32.
+        // The paired form's matrices go past the caches: the four products of a 7B layer 115 -> 106.5 us at 64 rows, 97.5 -> 90 at 32.  Its smallest ones (3.4 MB
+        // and more) are read equally fast either way: hidden 256 with FFN 6640, 512 with 8192, 1024 with 2752 and 4096, at 1, 32 and 64 rows, within 1 %.  Where all
+        // layers lie in the memory-side cache together, plain loads are 1 to 2.5 % faster (hidden 2048, two layers, 145 against 148 us at one row, 167 against 171 at 64); with
+        // more layers of the same matrices they are slower (six layers 351 against 339, 415 against 403), and a matrix does not know how many there are.
         // The direct form's are small, and those of a small model stay in the L2s from step to step (hidden 512, one token: 126 us a step, 134 past them).
         // tile order inside a stage: paired: (strip r, frag f) at r*4 + f; one strip: frags 0-3, then frags 4-7 one
         // pair-row (8 tiles) further on

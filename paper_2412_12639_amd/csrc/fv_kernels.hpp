@@ -1558,7 +1558,7 @@ __device__ __forceinline__ double wave_sum_from1(double v) {
 // Q: there is a draft distribution, which sampled_vectors allows 16-byte loads of.  G: groups of 2048 tokens.  Those past the vocabulary cost as much as
 // the others, so the host takes the fewest of 2, 4, 8 and 16 that hold it.  A call with 24 nodes (two layers of hidden 512; us without / with a draft
 // distribution): 2000 tokens 143 / 131 in 16 groups, 124 / 122 in 2, 132 / 126 by k_argmax and k_sampled_nodes; 8000 tokens 145 / 141 in 16, 130 / 127 in 4,
-// 141 / 139 by the two; 16000 tokens 147 / 139 in 16, 139 / 135 in 8, 155 / 147 by the two.
+// 141 / 139 by the two; 16000 tokens 147 / 139 in 16, 139 / 135 in 8, 155 / 147 by the two.  16 groups fill the registers: one value of eight bytes is in scratch.
 #define FV_SAMPLED_GROUP (2 * FV_SAMPLED_THREADS)
 #define FV_SAMPLED_RESIDENT (16 * FV_SAMPLED_GROUP)
 template <bool Q, int G>
