@@ -206,7 +206,7 @@ int main(int argc, char** argv) {
         long long t0 = 1LL << 62;
         for (int w = 0; w < c.p.G * 4; ++w) if (ts[w * 16] && ts[w * 16] < t0) t0 = ts[w * 16];
         const char* nm[8] = {"kernel entry", "statistics loads issued", "split computed, request stream positioned", "first stage requested",
-                             "three stages requested", "RMSNorm factors reduced, streaming loop entered", "first segment streamed, sums in LDS",
+                             "first stages requested", "RMSNorm factors reduced, streaming loop entered", "first segment streamed, sums in LDS",
                              "last segment finished (exchange, epilogue)"};
         // wall_clock64 counts at 100 MHz
         for (int k = 0; k < 8; ++k) {
