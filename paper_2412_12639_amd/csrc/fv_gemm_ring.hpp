@@ -80,7 +80,8 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
     // A matrix of 32 MiB and more, all that the L2s hold, goes past the caches in a step (a row group's K batch is 32 KiB).  Smaller ones are better read plainly,
     // also where the layers together are more than the memory-side cache holds.  us a step of 100 / 250 rows, all plainly, all past the caches, by this rule:
     // hidden 1024, 8 layers 569 / 698, 599 / 730, 563 / 693; hidden 2048, 2 layers 231 / 298, 251 / 318, 236 / 294, 6 layers 600 / 787, 618 / 803, 588 / 777;
-    // 7B width, 2 layers 434 / 568, 411 / 538, 406 / 534; 13B 518 / 684, 477 / 660, 474 / 659.  (From 64 MiB on instead: equal to 1 % either way; from 128 on 0 to 3 % more.)
+    // 7B width, 2 layers 434 / 568, 411 / 538, 406 / 534; 13B 518 / 684, 477 / 660, 474 / 659.  From 64 MiB on instead: two
+    // layers of hidden 3072, or of 4096 with eight key heads, 3 to 6 % faster at 100 rows, the 7B width equal with two layers and 1 to 2 % slower with six; from 128 MiB on that 1 to 2 % slower with either.
     const bool once = !WIDE && (unsigned)a.NG * (unsigned)a.NB >= 1024u;
     auto place = [&]() {                                // of the stage to fill next
         const int strip = fg * FV_R + wave;             // tiled [strip pair][half K batch][2 strips][4 frags]: a stage of a strip is 2 KiB
