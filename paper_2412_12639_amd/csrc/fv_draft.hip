@@ -22,15 +22,60 @@ fv_cfg core_cfg(const fv_cfg& t) {
     return c;
 }
 
-size_t lstm_stage_elems(const fv_cfg& t) { return (size_t)4 * t.hidden * 2 * t.hidden; }   // lstm0.w_ih, the largest tensor
+int lstm_chain_size(int h);
+
+// Buffers of a long commit: byte offsets inside the core context's staging area.  bf16 drafters whose recurrence runs in chain launches and whose
+// matrices the ring kernel can address.
+DraftWide plan_wide(const fv_cfg& t, const Layout& core, const GemmPlan& ih0, const GemmPlan& hh) {
+    DraftWide w;
+    bool ok = t.dtype == FV_BF16 && t.max_seq > 256 && lstm_chain_size(t.hidden) != 0 && gemm_ring_takes(ih0.NG, ih0.NB) && gemm_ring_takes(hh.NG, hh.NB);
+    for (int i = 0; i < GM_COUNT; ++i) ok = ok && gemm_ring_takes(core.gm[i].NG, core.gm[i].NB);
+    if (!ok) return w;
+    const size_t P = w.P = (int)std::min(rup(t.max_seq, 256), (size_t)FV_DRAFT_WIDE_ROWS);
+    const size_t h = t.hidden, qd = (size_t)t.n_q_heads * t.head_dim;
+    size_t o = 0;
+    auto take = [&](size_t bytes) { size_t r = o; o = rup(o + bytes, 256); return r; };
+    w.tok = take(P * 4);
+    w.xz = take((size_t)ih0.Kpad * P * 2);
+    w.xh = take((size_t)hh.Kpad * P * 2);
+    w.gin = take(P * 4 * h * 4);
+    for (size_t& s : w.state) s = take(P * 2 * h * 4);
+    w.x = take(h * P * 4);
+    w.xb = take((size_t)core.gm[GM_QKV].Kpad * P * 2);
+    w.q = take(qd * P * 2);
+    w.qlo = take(qd * P * 2);
+    w.attn = take((size_t)core.gm[GM_O].Kpad * P * 2);
+    w.act = take((size_t)core.gm[GM_DN].Kpad * P * 2);
+    w.ssq = take(h / 32 * P * 4);
+    w.rinv = take(P * 4);
+    w.ones = take(P * 4);
+    w.rope = take(P * (t.head_dim / 2) * 8);
+    w.mask = take(256 * 4 * 8);
+    w.bytes = o;
+    return w;
+}
+
+// What the staging area has to hold: the largest tensor (lstm0.w_ih) and a long commit's buffers
+size_t draft_stage_elems(const fv_cfg& t, int n_wg) {
+    const size_t lstm = (size_t)4 * t.hidden * 2 * t.hidden;
+    if (t.dtype != FV_BF16) return lstm;
+    Layout core;
+    make_layout(core_cfg(t), n_wg, core, false, lstm);
+    GemmPlan ih0, hh, gd, gp;
+    bool ok;
+    plan_gemm_forms(ih0, gd, gp, ok, (int)(4 * t.hidden / 32), (int)(2 * t.hidden), core.E, n_wg);
+    plan_gemm_forms(hh, gd, gp, ok, (int)(4 * t.hidden / 32), (int)t.hidden, core.E, n_wg);
+    return std::max(lstm, (plan_wide(t, core, ih0, hh).bytes + 1) / 2);
+}
 
 void make_draft_layout(const fv_cfg& t, int n_wg, DraftLayout& L) {
     const fv_cfg cc = core_cfg(t);
     Layout core;
-    make_layout(cc, n_wg, core, false, lstm_stage_elems(t));
+    make_layout(cc, n_wg, core, false, draft_stage_elems(t, n_wg));
     const size_t h = t.hidden, ESZ = core.ESZ, Tpm = FV_MAX_TREE;
     plan_gemm_forms(L.ih0.gm, L.ih0.gd, L.ih0.gp, L.ih0.paired_ok, (int)(4 * h / 32), (int)(2 * h), core.E, n_wg);
     plan_gemm_forms(L.hh.gm, L.hh.gd, L.hh.gp, L.hh.paired_ok, (int)(4 * h / 32), (int)h, core.E, n_wg);
+    L.wide = plan_wide(t, core, L.ih0.gm, L.hh.gm);
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t r = o; o = rup(o + bytes, 256); return r; };
     L.off_core = take(core.total);
@@ -80,6 +125,12 @@ DraftTables dev_tables(const fv_drafter* d) {
     t.lpred = d->tab(T_LPRED); t.block = d->tab(T_BLOCK); t.pos = d->tab(T_POS); t.lvl_rows = d->tab(T_LVL);
     t.node_gen = d->tab(T_NODEGEN); t.node_rank = d->tab(T_NODERANK); t.exp_list = d->tab(T_EXP);
     return t;
+}
+
+int wide_any(fv_drafter* d, const float* ext, int m, int keep) {
+    const int rc = d->core->cfg.head_dim == 128 ? run_draft_wide<BF16, 128>(d, ext, m, keep) : run_draft_wide<BF16, 64>(d, ext, m, keep);
+    if (rc != FV_OK) d->part_dirty = true;
+    return rc;
 }
 
 int32_t* htab(fv_drafter* d, int which) { return d->h_tab + (size_t)which * FV_MAX_TREE; }
@@ -138,23 +189,24 @@ int lstm_chain_fits(const fv_cfg& c, bool& fits) {
 
 }  // namespace
 
-int launch_lstm_chain(fv_drafter* d, const DraftPass& ps, int layer, int Tp) {
+int launch_lstm_chain(fv_drafter* d, const ChainRows& cr, int layer) {
     ++d->chain_launches;
     fv_ctx* c = d->core;
     const DraftLayout& dl = d->lay;
     const int h = c->cfg.hidden;
     LstmChainArgs a;
     a.Wt = (const uint4*)(d->arena + dl.off_w[2 * layer + 1]); a.zeros = c->at<uint4>(c->lay.off_zeros);
-    a.g_in = d->at<float>(dl.off_gin); a.bias = d->at<float>(dl.off_bias) + (size_t)layer * 4 * h; a.state = d->state(layer);
-    a.xnext = layer == 0 ? d->at<void>(dl.off_xh) : nullptr;
+    a.g_in = cr.g_in; a.bias = d->at<float>(dl.off_bias) + (size_t)layer * 4 * h; a.state = cr.state;
+    a.xnext = cr.xnext;
     a.sync = d->at<uint32_t>(dl.off_chain) + 32 * layer;
     a.xchg = d->at<uint16_t>(dl.off_chain + 256) + (size_t)layer * 2 * h;
     a.fault = d->at<uint32_t>(dl.off_bad) + 1; a.aborted = d->at<uint32_t>(dl.off_bad) + 2;
-    a.t0 = 0; a.r0 = ps.r0; a.n = ps.n; a.lpred = FV_DRAFT_STATE_COMMITTED; a.Tp = Tp; a.h = h;
+    a.t0 = 0; a.r0 = cr.r0; a.n = cr.n; a.from = d->state(layer) + (size_t)FV_DRAFT_STATE_COMMITTED * 2 * h; a.Tp = cr.Tp; a.h = h;
     a.expect = (unsigned)(h / 16) + (d->chain_test ? 1u : 0u);
     a.arrive_looks = d->chain_test ? 2u : 4000u;   // some milliseconds
     a.spin_limit = FV_EXCHANGE_SPINS;
-    if (!ps.commit) {
+    if (cr.levels) {
+        const DraftPass& ps = *cr.levels;
         LstmLevelArgs la;
         la.c = a;
         la.c.xchg = d->at<uint16_t>(dl.off_chain + 256) + (size_t)layer * 32 * h;
@@ -206,7 +258,7 @@ int fv_drafter_create(fv_ctx* target, int32_t k, void* dev_arena, size_t arena_b
     d->arena = (char*)dev_arena;
     auto fail = [&](int code) { fv_drafter_destroy(d); return code; };
     const fv_cfg cc = core_cfg(target->cfg);
-    int rc = fv_create_ex(&cc, d->arena + d->lay.off_core, d->lay.core_bytes, target->stream, false, lstm_stage_elems(target->cfg), &d->core);
+    int rc = fv_create_ex(&cc, d->arena + d->lay.off_core, d->lay.core_bytes, target->stream, false, draft_stage_elems(target->cfg, n_workgroups()), &d->core);
     if (rc) return fail(rc);
     hipStream_t st = d->core->stream;
     // everything outside the core context's part of the arena starts at zero too (states, pad columns, tickets)
@@ -240,6 +292,7 @@ int fv_drafter_create(fv_ctx* target, int32_t k, void* dev_arena, size_t arena_b
     { const char* e = getenv("FV_EXCHANGE_TEST"); d->chain_test = e && !strcmp(e, "chain"); }
     if (hipHostMalloc((void**)&d->h_tab, (size_t)FV_DRAFT_TABLES * FV_MAX_TREE * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
     if (hipHostMalloc((void**)&d->h_out, (FV_MAX_TREE + 64) * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
+    if (d->lay.wide.P && hipHostMalloc((void**)&d->h_tok, (size_t)d->lay.wide.P * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
     memset(d->h_tab, 0, (size_t)FV_DRAFT_TABLES * FV_MAX_TREE * 4);
     *out = d;
     return FV_OK;
@@ -250,6 +303,7 @@ void fv_drafter_destroy(fv_drafter* d) {
     if (d->core) fv_destroy(d->core);
     if (d->h_tab) (void)hipHostFree(d->h_tab);
     if (d->h_out) (void)hipHostFree(d->h_out);
+    if (d->h_tok) (void)hipHostFree(d->h_tok);
     delete d;
 }
 
@@ -303,60 +357,109 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
         if (tokens[i] < 0 || tokens[i] >= cf.vocab) return FV_E_TOKEN_RANGE;
     hipStream_t st = d->core->stream;
     bool chains = n >= 2 && d->chain_call();
+    bool merge = cf.dtype == FV_BF16;   // pieces whose last rows stay open; off once one of them came to nothing
+    bool hist_done = false;
     float total_ms = 0.f;
     for (int done = 0; done < n;) {
-        // Pieces of 64 rows, of which the last stays open as the phase's chain.  bf16: the rows before it go in pieces of up to 256,
-        // which read every matrix a quarter as often (7B width: 520 us of products per piece against 4 times 300).
-        const int tail = (n - 1) % 64 + 1, front = n - tail - done;
-        const int m = front > 0 ? std::min(front, cf.dtype == FV_BF16 ? 256 : 64) : n - done;
-        if (d->n_chain > 0 && d->k > 1) {       // outputs of the last k-1 committed rows survive the phase that ends
+        // What stays open as the phase's chain are the last 1 to 64 rows (so that a tree has room for its own).  fp32: pieces of 64 rows, of which those
+        // are the last.  bf16: up to 256 rows go in one pass, open ones included (65 to 256 rows at the 7B width: a pass of up to 256
+        // rows 430 us and another of up to 64 rows 390 before), more than 256 in wide passes of up to 1024 (fv_draft_wide.hpp).  Where that came to
+        // nothing -- a chain launch that left, a value that is no number, which is reported with the piece it lies in -- the call goes on with
+        // pieces of 256 rows and the open ones by themselves.
+        const int left = n - done, tail = (n - 1) % 64 + 1, front = left - tail;
+        const bool wide = merge && left > 256 && d->lay.wide.P > 0 && chains;
+        int m, keep;                             // rows of this pass, those of them that stay open
+        if (wide) {
+            m = std::min(left, d->lay.wide.P);
+            keep = m == left ? tail : 64;
+        } else if (merge && left > 64) {
+            m = std::min(left, 256);
+            keep = m == left ? tail : m;
+        } else {
+            m = front > 0 ? std::min(front, cf.dtype == FV_BF16 ? 256 : 64) : left;
+            keep = m;
+        }
+        if (d->n_chain > 0 && d->k > 1 && !hist_done) {       // outputs of the last k-1 committed rows survive the phase that ends
             HistArgs ha;
             ha.fout = d->at<float>(d->lay.off_fout); ha.top_tok = d->at<int32_t>(d->lay.off_top_tok); ha.top_val = d->at<float>(d->lay.off_top_val);
             ha.n_prev = d->n_chain; ha.k = d->k; ha.h = cf.hidden;
             hipLaunchKernelGGL(k_draft_hist, dim3(1), dim3(256), 0, st, ha);
             HIPCHK(hipGetLastError());
         }
+        hist_done = false;
         d->L0 = d->L;
-        for (int i = 0; i < m; ++i) {
-            htab(d, T_FEAT)[i] = -1 - (done + i);
-            htab(d, T_TOKNODE)[i] = -1;
-            htab(d, T_TOKVAL)[i] = tokens[done + i];
-            htab(d, T_PRED)[i] = i - 1;
-            htab(d, T_LPRED)[i] = i == 0 ? FV_DRAFT_STATE_COMMITTED : i - 1;
-            htab(d, T_BLOCK)[i] = i;           // committed pairs: plain causal order
-            htab(d, T_POS)[i] = d->L0 + i;
-            htab(d, T_LVL)[i] = i;
+        const bool cut = keep < m;
+        auto tables = [&](int rows, int skip) {   // committed pairs: plain causal order
+            for (int i = 0; i < rows; ++i) {
+                htab(d, T_FEAT)[i] = -1 - (done + skip + i);
+                htab(d, T_TOKNODE)[i] = -1;
+                htab(d, T_TOKVAL)[i] = tokens[done + skip + i];
+                htab(d, T_PRED)[i] = i - 1;
+                htab(d, T_LPRED)[i] = i == 0 ? FV_DRAFT_STATE_COMMITTED : i - 1;
+                htab(d, T_BLOCK)[i] = i;
+                htab(d, T_POS)[i] = d->L0 + i;
+                htab(d, T_LVL)[i] = i;
+            }
+        };
+        int rc;
+        bool took_chain = false;   // the rows' recurrence ran in chain launches
+        if (wide) memcpy(d->h_tok, tokens + done, (size_t)m * 4);
+        else {
+            tables(m, 0);
+            rc = upload_tables(d);
+            if (rc) return rc;
         }
-        int rc = upload_tables(d);
-        if (rc) return rc;
         HIPCHK(hipEventRecord(d->core->ev0, st));
         DraftPass ps;
-        ps.r0 = 0; ps.n = m; ps.l0 = 0; ps.lvl_n.assign(m, 1); ps.ext = dev_features; ps.commit = true;
+        ps.r0 = 0; ps.n = m; ps.l0 = 0; ps.ext = dev_features; ps.commit = true;
+        if (!wide) ps.lvl_n.assign(m, 1);
         // One row costs a chain launch as much as the separate launches (the matrix is read once either way).  A chain launch
         // whose workgroups did not get on the chip together has done nothing; the pass is then run again without, and the pieces behind it too.
         ps.chain = chains && m >= 2;
         for (;;) {
-            rc = pass_any(d, ps);
+            took_chain = wide || ps.chain;
+            rc = wide ? wide_any(d, dev_features + (size_t)done * cf.hidden, m, keep) : pass_any(d, ps);
             if (rc) return rc;
-            StateKeepArgs ka;
-            ka.state0 = d->state(0); ka.state1 = d->state(1); ka.aborted = d->at<uint32_t>(d->lay.off_bad) + 2; ka.row = m - 1; ka.h = cf.hidden;
-            ka.bad = d->at<int32_t>(d->lay.off_bad); ka.bad_out = d->h_out + FV_MAX_TREE;
-            hipLaunchKernelGGL(k_state_keep, dim3((2 * cf.hidden + 255) / 256), dim3(256), 0, st, ka);
-            HIPCHK(hipGetLastError());
+            if (!wide) {
+                if (cut) {
+                    DraftSliceArgs sa;
+                    sa.fout = d->at<float>(d->lay.off_fout); sa.top_tok = d->at<int32_t>(d->lay.off_top_tok); sa.top_val = d->at<float>(d->lay.off_top_val);
+                    sa.logits = d->at<float>(d->lay.off_logits); sa.state[0] = d->state(0); sa.state[1] = d->state(1);
+                    sa.bad = d->at<int32_t>(d->lay.off_bad); sa.s = m - keep; sa.keep = keep; sa.k = d->k; sa.h = cf.hidden; sa.Vpad = d->core->lay.Vpad;
+                    hipLaunchKernelGGL(k_draft_slice, dim3(keep + d->k - 1), dim3(256), 0, st, sa);
+                    HIPCHK(hipGetLastError());
+                }
+                StateKeepArgs ka;
+                ka.state0 = d->state(0); ka.state1 = d->state(1); ka.aborted = d->at<uint32_t>(d->lay.off_bad) + 2; ka.row = keep - 1; ka.h = cf.hidden;
+                ka.bad = d->at<int32_t>(d->lay.off_bad); ka.bad_out = d->h_out + FV_MAX_TREE; ka.finite_only = cut ? 1 : 0;
+                hipLaunchKernelGGL(k_state_keep, dim3((2 * cf.hidden + 255) / 256), dim3(256), 0, st, ka);
+                HIPCHK(hipGetLastError());
+            }
             HIPCHK(hipEventRecord(d->core->ev1, st));
             HIPCHK(hipStreamSynchronize(st));
-            if (ps.chain) d->chain_outcome(d->h_out[FV_MAX_TREE + 2]);
-            if (!ps.chain || !d->h_out[FV_MAX_TREE + 2] || d->h_out[FV_MAX_TREE + 1]) break;
+            if (took_chain) d->chain_outcome(d->h_out[FV_MAX_TREE + 2]);
+            if (!took_chain || !d->h_out[FV_MAX_TREE + 2] || d->h_out[FV_MAX_TREE + 1]) break;
             hipLaunchKernelGGL(k_draft_fill, dim3(1), dim3(256), 0, st, d->at<uint32_t>(d->lay.off_bad), 0u, (size_t)3);
             HIPCHK(hipGetLastError());
             ps.chain = chains = false;
+            if (wide) break;
         }
         if (d->h_out[FV_MAX_TREE + 1]) { d->part_dirty = true; return FV_E_EXCHANGE_TIMEOUT; }
         float ms = 0.f;
         HIPCHK(hipEventElapsedTime(&ms, d->core->ev0, d->core->ev1));
         total_ms += ms;
+        if (wide && !chains) { hist_done = true; continue; }   // the launches left: the same rows again, without them
+        if (cut && d->h_out[FV_MAX_TREE]) {                    // not finite somewhere: which piece, and what stands before it, the small pieces say
+            HIPCHK(hipMemset(d->at<int32_t>(d->lay.off_bad), 0, 4));
+            merge = false; hist_done = true;
+            continue;
+        }
         d->L += m;
-        d->n_chain = d->n_rows = m;
+        d->n_chain = d->n_rows = keep;
+        if (cut) {
+            d->L0 = d->L - keep;
+            tables(keep, m - keep);
+        }
         done += m;
         if (d->h_out[FV_MAX_TREE]) {
             d->cache_bad = true;

@@ -219,11 +219,12 @@ static __global__ __launch_bounds__(256) void k_lstm_cell(LstmCellArgs a) {
 // state after the last committed pair <- state of phase row `row` (both layers are laid out back to back); not if *aborted
 // (a chain launch gave up: the rows' states are not there)
 // The call's error words go to the host's memory with it.
-struct StateKeepArgs { float* state0; float* state1; const uint32_t* aborted; const int32_t* bad; int32_t* bad_out; int row, h; };
+// (finite_only: not if the pass had values that are no numbers either: the call then runs again in smaller pieces)
+struct StateKeepArgs { float* state0; float* state1; const uint32_t* aborted; const int32_t* bad; int32_t* bad_out; int row, h, finite_only; };
 static __global__ __launch_bounds__(256) void k_state_keep(StateKeepArgs a) {
     const int idx = blockIdx.x * 256 + threadIdx.x;
     if (idx < 3) { a.bad_out[idx] = a.bad[idx]; __threadfence_system(); }
-    if (idx >= 2 * a.h || *a.aborted) return;
+    if (idx >= 2 * a.h || *a.aborted || (a.finite_only && a.bad[0])) return;
     a.state0[(size_t)FV_MAX_TREE * 2 * a.h + idx] = a.state0[(size_t)a.row * 2 * a.h + idx];
     a.state1[(size_t)FV_MAX_TREE * 2 * a.h + idx] = a.state1[(size_t)a.row * 2 * a.h + idx];
 }
@@ -248,6 +249,7 @@ struct TopmArgs {
     int32_t* top_tok;      // [256 + KMAX][FV_DRAFT_MMAX] by output row id
     float* top_val;
     int32_t* bad;          // set to 1 if some row is non-finite
+    const int32_t* gate;   // not null: nothing is written if gate[0] or gate[2] is set (a long commit that came to nothing)
     int r0, n, V, Vpad, m;
 };
 
@@ -277,6 +279,7 @@ __device__ __forceinline__ unsigned long long topm_wave_max(unsigned long long k
 
 // (workgroups n .. 2n-1 write the predicted feature rows, which wait for nothing the top lists do)
 static __global__ __launch_bounds__(FV_TOPM_THREADS) void k_topm(TopmArgs a, DraftOutArgs oa) {
+    if (a.gate && (a.gate[0] || a.gate[2])) return;
     if ((int)blockIdx.x >= a.n) { draft_out_row(oa, blockIdx.x - a.n); return; }
     __shared__ unsigned long long wave_key[16];
     __shared__ unsigned long long cand[FV_TOPM_FAST];
@@ -410,6 +413,41 @@ static __global__ __launch_bounds__(256) void k_draft_hist(HistArgs a) {
         }
         __syncthreads();
     }
+}
+
+// The last `keep` rows of a commit's pass become the phase's rows 0 .. keep-1, the k-1 rows in front of them the history: predicted feature, top
+// list and logits, and the last row's states.  Rows move by s, which is no less than keep, so only history rows are read where others are written,
+// and a workgroup that writes one of those has moved it first.  Grid: keep + k - 1.
+struct DraftSliceArgs { float* fout; int32_t* top_tok; float* top_val; float* logits; float* state[2]; const int32_t* bad; int s, keep, k, h, Vpad; };
+static __global__ __launch_bounds__(256) void k_draft_slice(DraftSliceArgs a) {
+    if (a.bad[0] || a.bad[2]) return;
+    const int b = blockIdx.x, tid = threadIdx.x, hist0 = a.s - (a.k - 1);
+    const int r = b < a.keep ? b : hist0 + (b - a.keep);   // the row this workgroup writes, or only takes into the history
+    if (b >= a.keep && r < a.keep) return;
+    const bool hist = r >= hist0 && r < a.s;
+    float4* const f = (float4*)a.fout;
+    const size_t hq = a.h / 4;
+    for (size_t q = tid; q < hq; q += 256) {
+        if (hist) f[(size_t)(FV_MAX_TREE + r - hist0) * hq + q] = f[(size_t)r * hq + q];
+        if (b < a.keep) f[(size_t)r * hq + q] = f[(size_t)(a.s + r) * hq + q];
+    }
+    if (tid < FV_DRAFT_MMAX) {
+        if (hist) {
+            a.top_tok[(FV_MAX_TREE + r - hist0) * FV_DRAFT_MMAX + tid] = a.top_tok[r * FV_DRAFT_MMAX + tid];
+            a.top_val[(FV_MAX_TREE + r - hist0) * FV_DRAFT_MMAX + tid] = a.top_val[r * FV_DRAFT_MMAX + tid];
+        }
+        if (b < a.keep) {
+            a.top_tok[r * FV_DRAFT_MMAX + tid] = a.top_tok[(a.s + r) * FV_DRAFT_MMAX + tid];
+            a.top_val[r * FV_DRAFT_MMAX + tid] = a.top_val[(a.s + r) * FV_DRAFT_MMAX + tid];
+        }
+    }
+    if (b >= a.keep) return;
+    const float4* const from = (const float4*)(a.logits + (size_t)(a.s + r) * a.Vpad);   // Vpad is a multiple of 32
+    float4* const to = (float4*)(a.logits + (size_t)r * a.Vpad);
+    for (int q = tid; q < a.Vpad / 4; q += 256) to[q] = from[q];
+    if (r == a.keep - 1)
+        for (int l = 0; l < 2; ++l)
+            for (int i = tid; i < 2 * a.h; i += 256) a.state[l][(size_t)r * 2 * a.h + i] = a.state[l][(size_t)(a.s + r) * 2 * a.h + i];
 }
 
 // plain fill (pad columns of activation buffers after a change of the row padding)

@@ -99,12 +99,15 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
                 la.r0 = ps.r0; la.l0 = ps.l0; la.n_lvl = ps.lvl_n[0]; la.Tpl = 32; la.h = h;
                 hipLaunchKernelGGL((k_lstm_gather<EL>), dim3((unsigned)(((size_t)(h / 4) * 32 + 255) / 256)), dim3(256), 0, st, la);
             }
-            int rc = launch_lstm_chain(d, ps, layer, Tp);
+            ChainRows cr;
+            cr.n = n; cr.Tp = Tp; cr.r0 = ps.r0; cr.g_in = d->at<float>(dl.off_gin); cr.state = d->state(layer); cr.xnext = layer == 0 ? d->at<void>(dl.off_xh) : nullptr;
+            cr.levels = ps.commit ? nullptr : &ps;
+            int rc = launch_lstm_chain(d, cr, layer);
             if (rc) return rc;
             if (layer == 1) {
                 LstmOutArgs oa;
                 oa.state = d->state(1); oa.x = c->at<float>(ly.off_x); oa.xb = c->at<void>(ly.off_xb); oa.gain = c->gain(0); oa.ssq = c->at<float>(ly.off_ssq);
-                oa.r0 = ps.r0; oa.n = n; oa.Tp = Tp; oa.h = h;
+                oa.r0 = ps.r0; oa.n = oa.rows = n; oa.Tp = Tp; oa.h = h;
                 const size_t items = (size_t)(h / 4) * n;
                 hipLaunchKernelGGL((k_lstm_out<EL>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, oa);
                 HIPCHK(hipGetLastError());
@@ -187,7 +190,7 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
     {
         TopmArgs ta;
         ta.logits = d->at<float>(dl.off_logits) + (size_t)ps.r0 * ly.Vpad; ta.top_tok = d->at<int32_t>(dl.off_top_tok);
-        ta.top_val = d->at<float>(dl.off_top_val); ta.bad = d->at<int32_t>(dl.off_bad);
+        ta.top_val = d->at<float>(dl.off_top_val); ta.bad = d->at<int32_t>(dl.off_bad); ta.gate = nullptr;
         ta.r0 = ps.r0; ta.n = n; ta.V = cf.vocab; ta.Vpad = ly.Vpad; ta.m = FV_DRAFT_MMAX;
         DraftOutArgs oa;
         oa.x = c->at<float>(ly.off_x); oa.fout = d->at<float>(dl.off_fout); oa.r0 = ps.r0; oa.n = n; oa.Tp = Tp; oa.h = h;

@@ -38,7 +38,7 @@ template <int N> __device__ __forceinline__ void wait_vm() {   // all but the N 
 #define FV_RING_THREADS 512   // wavefronts 0..3 multiply, 4..7 fill the ring
 
 template <int TB, int D, int EPI, bool WIDE>
-__global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
+__device__ __forceinline__ void gemm_ring_body(const GemmArgs& a) {
     constexpr int NS = ring_slots(TB), SB = ring_stage_bytes(TB), AB = FV_R * 2048;
     constexpr int RS = 2, CB = TB / 2, TT = TB * 32;    // strips and column blocks of a wavefront, columns of the tile
     constexpr int LX = TT / 64, LPS = 2 + LX;           // loads per wavefront and stage: one strip's weights, one of four vectors of every column
@@ -295,3 +295,11 @@ __global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) {
         }
     }
 }
+
+template <int TB, int D, int EPI, bool WIDE>
+__global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_ring(GemmArgs a) { gemm_ring_body<TB, D, EPI, WIDE>(a); }
+
+// What only a drafter's long commit has over so many rows: products without a norm and an epilogue of their own (the LSTM's input multiplications), and the
+// head that looks at all rows and keeps few.
+template <int D, int EPI>
+__global__ __launch_bounds__(FV_RING_THREADS, 1) void k_gemm_commit(GemmArgs a) { gemm_ring_body<8, D, EPI, true>(a); }

@@ -141,7 +141,15 @@ struct GemmForms {
     const GemmPlan& pick(int kind) const { return kind == GEMM_DIRECT ? gd : kind == GEMM_PAIRED ? gp : gm; }
 };
 
+// Buffers of a long commit (fv_draft_wide.hpp), over the core context's staging area, which is idle once the weights are in: byte offsets there
+struct DraftWide {
+    int P = 0;       // rows at once, 0: no such pass
+    size_t tok = 0, xz = 0, xh = 0, gin = 0, state[2] = {0, 0}, x = 0, xb = 0, q = 0, qlo = 0, attn = 0, act = 0, ssq = 0, rinv = 0, ones = 0, rope = 0, mask = 0;
+    size_t bytes = 0;
+};
+
 struct DraftLayout {
+    DraftWide wide;
     GemmForms ih0, hh;                    // [4h x 2h] and [4h x h] (the latter serves lstm0.w_hh, lstm1.w_ih, lstm1.w_hh)
     size_t off_core = 0, core_bytes = 0;  // the decoder block: a one-layer context without head and embedding
     size_t off_w[4] = {0, 0, 0, 0};       // tiled lstm0.w_ih, lstm0.w_hh, lstm1.w_ih, lstm1.w_hh
@@ -164,6 +172,15 @@ struct DraftPass {
     bool chain = false;              // both LSTM layers take all rows (a chain) or levels (a tree) in one launch each (fv_lstm_chain.hpp)
 };
 
+// the rows of one layer's recurrence that go in one launch
+struct ChainRows {
+    int n = 0, Tp = 0, r0 = 0;           // rows, row padding of the product's buffers, first state row
+    const float* g_in = nullptr;         // [Tp][4h] input multiplication
+    float* state = nullptr;              // this layer's state rows
+    void* xnext = nullptr;               // next layer's input, or null
+    const DraftPass* levels = nullptr;   // a tree pass: its levels; null: a chain behind the last committed pair
+};
+
 struct fv_drafter {
     fv_ctx* target = nullptr;
     fv_ctx* core = nullptr;
@@ -179,6 +196,7 @@ struct fv_drafter {
     int n_rows = 0;               // phase rows so far
     int last_Tp = 0;
     int32_t* h_tab = nullptr;     // pinned [FV_DRAFT_TABLES][256]
+    int32_t* h_tok = nullptr;     // pinned [lay.wide.P]: the tokens of a long commit while it is under way
     int32_t* h_out = nullptr;     // pinned [256] node tokens + [1] error flag
     float last_ms = 0.f;
     bool cache_bad = false;       // a call ended with FV_E_NONFINITE: its rows' K and V may be no numbers
@@ -233,8 +251,10 @@ template <typename EL, int D> int read_kv_t(fv_ctx* c, int layer, int slot0, int
 // upload one weight tensor (up to three host pieces) and re-tile it on the device (independent of D)
 // one pass of the drafter (defined in fv_draft_step.hpp, part of the fv_step.hip units)
 template <typename EL, int D> int run_draft_pass(fv_drafter* d, const DraftPass& ps);
+// m committed pairs at once, of which the last `keep` stay open (fv_draft_wide.hpp; bf16)
+template <typename EL, int D> int run_draft_wide(fv_drafter* d, const float* ext, int m, int keep);
 // ---- defined in fv_draft.hip: one layer's recurrence over the rows of a chain pass (bf16 only)
-int launch_lstm_chain(fv_drafter* d, const DraftPass& ps, int layer, int Tp);
+int launch_lstm_chain(fv_drafter* d, const ChainRows& cr, int layer);
 template <typename EL>
 int tile_upload(fv_ctx* c, int kind, const GemmPlan& p, char* out, const void* h0, size_t n0, const void* h1, size_t n1,
                 const void* h2, size_t n2, int N);

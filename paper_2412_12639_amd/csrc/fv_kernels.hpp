@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void k_begin(IngestArgs ia, EmbedArgs ea, int 
 // accumulators go to `part`, the workgroup takes a ticket on the row group's counter, and
 // the workgroup that draws the last ticket sums all segments of the group in ascending
 // workgroup order (so the result does not depend on who arrives last) and runs the epilogue.
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3, EPI_HEAD = 4 };
 
 // n 32-bit words to zero (a template so that every translation unit may hold it)
 template <int UNUSED>
@@ -279,6 +279,8 @@ struct GemmArgs {
     // EPI_SWIGLU: act = silu(gate) * up
     void* act;
     // EPI_LOGITS
+    // EPI_HEAD (a drafter's long commit): logits of which few rows are wanted.  Row L + i goes to row i, row L - Hq + j to row FV_MAX_TREE + j,
+    // the rows before those nowhere; a value of any row below T and any of the first Hkv tokens that is not finite sets *tickets to 1.
     float* logits;       // [Tp][Vpad]
     int Vpad;
     int ld;              // ring kernel over a prompt: rows of the activation buffers (a multiple of 256)
@@ -357,6 +359,18 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int Tp, int str
                 st_f4((float4*)(a.logits + (size_t)t * a.Vpad + f0),
                            make_float4(acc[4 * blk], acc[4 * blk + 1], acc[4 * blk + 2], acc[4 * blk + 3]));
             }
+        } else if constexpr (EPI == EPI_HEAD) {
+            bool bad = false;
+            const int row = t >= a.L ? t - a.L : t >= a.L - a.Hq ? FV_MAX_TREE + t - (a.L - a.Hq) : -1;
+#pragma unroll
+            for (int blk = 0; blk < 4; ++blk) {
+                const int f0 = strip * 32 + 8 * blk + 4 * g;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) bad = bad || (f0 + c < a.Hkv && !(__builtin_fabsf(acc[4 * blk + c]) < INFINITY));
+                if (t < a.T && row >= 0)
+                    st_f4((float4*)(a.logits + (size_t)row * a.Vpad + f0), make_float4(acc[4 * blk], acc[4 * blk + 1], acc[4 * blk + 2], acc[4 * blk + 3]));
+            }
+            if (bad && t < a.T) *a.tickets = 1;
         } else if constexpr (EPI == EPI_SWIGLU) {
             // strip covers activation features [16*strip, 16*strip+16): accumulator blocks 0,2 are
             // gate rows, blocks 1,3 the matching up rows

@@ -43,7 +43,7 @@ struct LstmChainArgs {
     uint32_t* aborted;     // counts the launches whose workgroups did not get on the chip together
     uint32_t* fault;       // set to 1 when a published value did not arrive
     int t0, r0, n;         // the chain: pass rows t0 .. t0+n-1, state rows r0 + t0 ..  (t0 is 0; without it the compiler's addresses cost 45 ns a row)
-    int lpred;             // state row the first one continues
+    const float* from;     // [2][h] the state the first one continues
     int Tp, h;
     unsigned expect;       // arrivals to wait for (the grid; one more in the test of the give-up path)
     unsigned arrive_looks; // looks at the counter before giving up
@@ -192,7 +192,7 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
         if (vec < 4 * NKF) {
             float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             if (vec < 4 * kf_real) {
-                const float4* sp = (const float4*)(a.state + (size_t)a.lpred * 2 * h + wave * quarter + vec * 8);
+                const float4* sp = (const float4*)(a.from + wave * quarter + vec * 8);
                 const float4 x0 = sp[0], x1 = sp[1];
                 f[0] = x0.x; f[1] = x0.y; f[2] = x0.z; f[3] = x0.w; f[4] = x1.x; f[5] = x1.y; f[6] = x1.z; f[7] = x1.w;
             }
@@ -202,7 +202,7 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
     // wavefront 0: lane (q, u) owns gate q of unit u; every lane of a unit keeps the same cell state
     const size_t unit = (size_t)16 * wg + u;
     const float bias = a.bias[(size_t)q * h + unit];
-    float c = a.state[((size_t)a.lpred * 2 + 1) * h + unit];
+    float c = a.from[h + unit];
 
     if (tid == 0) {
         // set here, *aborted is an earlier launch's, or this one's after its counter said "leave": nobody can start then
@@ -346,7 +346,7 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
 // level's predecessors are gathered by k_lstm_gather; the operand goes from the exchange area straight to registers, a few
 // fragments at a time; all four wavefronts apply the cell.
 struct LstmLevelArgs {
-    LstmChainArgs c;               // n, t0, lpred are not used; xchg: [2][h / 8][16][8]
+    LstmChainArgs c;               // n, t0, from are not used; xchg: [2][h / 8][16][8]
     DraftTables tab;
     const uint4* xprev;            // [h / 8][32][8] bf16 predecessors' states of the first level
     int l0, n_lvl;                 // first entry in lvl_rows; levels
@@ -540,15 +540,15 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_levels(LstmLevelArgs la)
 
 // What LAYER 1 leaves for the decoder block, for rows whose states are there: the residual stream x, x * gain and the
 // per-strip sums of squares (the second half of k_lstm_cell).
-struct LstmOutArgs { const float* state; float* x; void* xb; const float* gain; float* ssq; int r0, n, Tp, h; };
+struct LstmOutArgs { const float* state; float* x; void* xb; const float* gain; float* ssq; int r0, n, rows, Tp, h; };   // rows n .. rows-1: zeros
 template <typename EL>
 static __global__ __launch_bounds__(256) void k_lstm_out(LstmOutArgs a) {
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
     const int qn = a.h / 4;
     const int t = (int)(idx / qn);
     const int f0 = (int)(idx % qn) * 4;
-    if (t >= a.n) return;                  // whole strips leave together: h is a multiple of 64
-    const float4 v = *(const float4*)(a.state + (size_t)(a.r0 + t) * 2 * a.h + f0);
+    if (t >= a.rows) return;               // whole strips leave together: h is a multiple of 64
+    const float4 v = t < a.n ? *(const float4*)(a.state + (size_t)(a.r0 + t) * 2 * a.h + f0) : make_float4(0.f, 0.f, 0.f, 0.f);
     ((float4*)a.x)[(size_t)(f0 >> 2) * a.Tp + t] = v;
     const float4 gn = *(const float4*)(a.gain + f0);
     store4_act<EL>(a.xb, a.Tp, f0, t, v.x * gn.x, v.y * gn.y, v.z * gn.z, v.w * gn.w);

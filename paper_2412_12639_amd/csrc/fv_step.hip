@@ -113,6 +113,10 @@ template <typename EL, int D, int EPI>
 int set_gemm_attrs_e() {
     // the 256-token instantiation double-buffers 2 x 64 KiB of activations in LDS
     if constexpr (Tr<EL>::E == 8) {
+        if constexpr (EPI == EPI_LOGITS) {
+            HIPCHK(hipFuncSetAttribute((const void*)k_gemm_commit<D, EPI_LOGITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem(8)));
+            HIPCHK(hipFuncSetAttribute((const void*)k_gemm_commit<D, EPI_HEAD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem(8)));
+        }
         HIPCHK(hipFuncSetAttribute((const void*)k_gemm_ring<8, D, EPI, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem(8)));
         HIPCHK(hipFuncSetAttribute((const void*)k_gemm_ring<4, D, EPI, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem(4)));
         if constexpr (EPI != EPI_LOGITS)
@@ -462,10 +466,12 @@ int read_kv_t(fv_ctx* c, int layer, int slot0, int n, float* k_out, float* v_out
 
 #include "fv_draft_step.hpp"
 #include "fv_prompt.hpp"
+#include "fv_draft_wide.hpp"
 
 template int run_step<FV_INST_EL, FV_INST_D>(fv_ctx*, int, StepMode, int);
 template int run_prompt<FV_INST_EL, FV_INST_D>(fv_ctx*, const int32_t*, int);
 template int run_draft_pass<FV_INST_EL, FV_INST_D>(fv_drafter*, const DraftPass&);
+template int run_draft_wide<FV_INST_EL, FV_INST_D>(fv_drafter*, const float*, int, int);
 template int set_gemm_attrs_d<FV_INST_EL, FV_INST_D>();
 template int read_kv_t<FV_INST_EL, FV_INST_D>(fv_ctx*, int, int, int, float*, float*);
 #if FV_INST_D == 128

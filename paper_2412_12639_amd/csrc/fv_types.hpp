@@ -10,6 +10,7 @@
 
 #define FV_PROMPT_ROWS 2048   // prompt rows that go through the layers at once
 
+#define FV_DRAFT_WIDE_ROWS 1024   // committed pairs that go through the drafter at once
 #define FV_DRAFT_KMAX 8   // largest k of the semi-autoregressive drafter
 #define FV_DRAFT_MMAX 32  // longest top list per drafter row
 

@@ -447,6 +447,62 @@ def test_tree_behind_a_commit_in_pieces(n, k):
     tgt.close()
 
 
+@pytest.mark.parametrize("n,k", [
+    (65, 8),      # one pass of which a single row stays open; the rows in front of it are the history of the first levels
+    (128, 8),     # the history lies in rows that the open ones move over
+    (256, 1),     # the longest pass of its kind, no history
+    (257, 8),     # the shortest wide pass, a single open row
+    (1024, 3),    # the longest, 64 open rows
+    (1089, 2),    # a wide pass, one of 65 rows behind it
+    (1300, 4),    # two wide passes
+])
+def test_commits_of_more_rows_than_stay_open(n, k):
+    """Commits whose open rows are the last of a pass that others precede: state, outputs of the open rows, K and V of all, and a tree, whose first k levels
+    come from the last k rows.  A second phase continues the LSTM states that were kept."""
+    import torch
+    s, lw, dw, tgt, dr = _make("tiny-bf16", k, max_seq=1400)
+    orc = do.DrafterOracle(s, lw, dw, k, 1400)
+    parent, depth, _ = gen_tree(31, 30, [4, 2, 2, 1, 1, 1, 1, 1, 1, 1], 9)
+    rank = sibling_ranks(parent)
+    for rows in (n, 3):
+        feats = gen_features(rows + k, rows, s.hidden)
+        toks = np.random.default_rng(rows).integers(0, s.vocab, rows)
+        dr.commit(toks, torch.from_numpy(feats).cuda())
+        orc.commit(feats, toks)
+        tail = (rows - 1) % 64 + 1
+        assert dr.state() == (orc.L, tail, tail)
+        f_ref, l_ref = np.array(orc.phase["f"]), np.array(orc.phase["logits"])
+        assert _rel(dr.rows("features", 0, tail), f_ref[-tail:]) <= 2e-2 and _rel(dr.rows("logits", 0, tail), l_ref[-tail:]) <= 2e-2
+        kd, vd = dr.read_kv(0, orc.L)
+        assert _rel(kd, orc.K[:orc.L]) <= 2e-2 and _rel(vd, orc.V[:orc.L]) <= 2e-2
+        got = dr.draft_tree(parent, depth, rank, int(toks[-1]))
+        ref = orc.draft(parent, depth, rank, int(toks[-1]), force_tokens=got)
+        first = [i for i in range(len(parent)) if depth[i] <= k]
+        assert sum(got[i] != ref[i] for i in first) <= 1
+    dr.close()
+    tgt.close()
+
+
+@pytest.mark.parametrize("n,row,committed", [
+    (100, 5, 64),       # the piece of 64 rows in front of the open ones
+    (100, 70, 100),     # an open one
+    (400, 5, 256),      # a wide pass: the first piece of 256, ..
+    (400, 300, 384),    # .. the 128 rows between it and the open ones
+])
+def test_a_value_that_is_no_number_ends_the_piece_it_lies_in(n, row, committed):
+    """Passes with rows in front of the open ones that turn out to hold a NaN: pairs count as committed up to the end of the piece that has it, pieces
+    being 256 rows, then what is left before the open ones."""
+    import torch
+    s, lw, dw, tgt, dr = _make("tiny-bf16", 2, max_seq=500)
+    feats = gen_features(n, n, s.hidden)
+    feats[row, 5] = np.nan
+    with pytest.raises(Exception) as e:
+        dr.commit(np.arange(n), torch.from_numpy(feats).cuda())
+    assert e.value.status == -10 and dr.state()[0] == committed
+    dr.close()
+    tgt.close()
+
+
 @pytest.mark.parametrize("name", ["tiny-bf16", "tiny"])
 def test_overflow_of_an_early_rows_logits_is_reported(name):
     """200 pairs of which the fourth alone has infinite logits, from finite states, K and V: eight units that are zero but for it, and a row
