@@ -5,10 +5,15 @@
 // multiplication, cell) every row streams the whole 4h x h matrix again: 134 MB and 33 us per row and layer at hidden
 // 4096, of which 23 us are the stream.  That matrix is 512 KiB per compute unit, and a compute unit has 512 KiB of
 // vector registers and 160 KiB of LDS: each wavefront keeps three quarters of its share in registers and one in LDS, the
-// matrix is read once per launch, and a row costs what the exchange of the hidden state (0.7 us), 64 matrix instructions per
-// wavefront (0.7), the sum over the wavefronts (0.1) and the cell (0.4) cost.
-// Measured at hidden 4096: 256 rows 510 us per layer (29 us to read the matrix, 1.9 us a row; before the sparse form of the matrix
-// instruction, the barrier in front of the looks and the short cell 880, 3.34 a row) against 8400; 4 rows 33 against 130.
+// matrix is read once per launch, and a row costs what the exchange of the hidden state (0.8 us), 64 matrix instructions per
+// wavefront with their reads of LDS (0.6), and the way from the sums of the wavefronts through the cell to the next publication (0.4) cost.
+// A wavefront that has its SIMD to itself issues an instruction every 8.4 cycles, a matrix instruction every 16, and LDS delivers a wavefront's 1 KiB
+// in 8: what is on a row's path is counted in instructions.  (Taking the state's operands from lanes of the same row by moves across lanes instead
+// of from LDS, eight moves an instruction: 0.3 us a row more.)  The look at the others' values takes half a microsecond and has to come when they are there, about
+// 0.4 us behind the own publication: what a wavefront does in between (states and input rows) costs nothing, a look that comes 0.3 us earlier
+// costs another look, 0.3 us a row.
+// Measured at hidden 4096: 500 rows 954 us per layer (27 us to read the matrix, 1.85 us a row; with five instructions for every word of the
+// state, a cell with branches and exchanges through LDS 1020, 1.99 a row) against 16500 as separate launches; 4 rows 33 against 130.
 //
 // Split: workgroup w owns hidden units 16w .. 16w+15 with their four gates (four 16-row blocks); its four wavefronts
 // take a quarter of the K range each, so a wavefront needs only a quarter of the previous hidden state.  The sums of the
@@ -57,40 +62,32 @@ constexpr size_t lstm_chain_smem(int nkf) {
     return ((size_t)4 * (nkf - lstm_chain_reg_frags(nkf)) * 4 * 64 + (size_t)4 * nkf * 4) * 16 + 2 * 4 * 4 * 16 * 4 + 16;
 }
 
-// Sigmoid, or tanh, of a gate: both from e^-|a| (a = x or 2x) and one quotient, without a branch between the lanes of different gates
-// (the library's functions, of which every lane ran both, took two thirds of the cell's 0.63 us).  The exponential is the Taylor polynomial
-// behind a reduction by multiples of ln 2: the hardware's own, a unit in the last place off, gave tanh a larger error than the library's.
-// Small tanh by its series, where 1 - e cancels.  Largest error against 64 bits, absolute and relative, of every 61st value of 1e-6 .. 128 and all
-// around the ends of series and saturation, reciprocal exact or a unit off (tests/test_lstm_gate.py; in brackets the library's, 1e-6 .. 100):
-// sigmoid 0.44e-7 and 1.18e-7 (0.89e-7 and 1.47e-7), tanh 0.67e-7 and 1.33e-7 (0.82e-7 and 1.46e-7).  |result| <= 1, which the exchange relies on.
+// Sigmoid, or tanh, of a gate: both from e = e^-|a| (a = x or 2x) and one quotient, without a branch (the library's functions, of which every lane ran
+// both, took two thirds of the cell's 0.63 us).  A wavefront that has its SIMD to itself issues an instruction every eight cycles, so what counts in the cell
+// is how many there are.  The exponential is the Taylor polynomial behind a reduction by multiples of ln 2: the hardware's own, a unit in the last
+// place off, gave tanh a larger error than the library's.  tanh's numerator 1 - e comes from the same polynomial without the cancellation, with what its
+// rounding lost beside it (a series of its own below 0.5, as before: ten instructions and two branches more).  Largest error against 64 bits,
+// absolute and relative, of every 61st value of 1e-6 .. 128 and all around the ends of saturation, reciprocal exact or a unit off
+// (tests/test_lstm_gate.py; in brackets the library's, 1e-6 .. 100): sigmoid 0.44e-7 and 1.18e-7 (0.89e-7 and 1.47e-7), tanh 0.62e-7 and 1.20e-7
+// (0.82e-7 and 1.46e-7; with the series 0.67e-7 and 1.33e-7).  |result| <= 1, which the exchange relies on.
 __device__ __forceinline__ float lstm_gate(float x, bool th) {
-    const float ax = fabsf(x), a = fminf(th ? 2.f * ax : ax, 104.f);   // e^-104 is zero in 32 bits
+    const float ax = fabsf(x), ax2 = th ? ax + ax : ax, a = ax2 > 104.f ? 104.f : ax2;   // e^-104 is zero in 32 bits; no number stays none
     const float n = rintf(a * -1.44269504f), y = fmaf(n, 1.90465421e-9f, fmaf(n, -0.693147182f, -a));   // -a = n ln 2 + y
-    float p = 1.f / 5040.f;
-    p = fmaf(p, y, 1.f / 720.f);
-    p = fmaf(p, y, 1.f / 120.f);
-    p = fmaf(p, y, 1.f / 24.f);
-    p = fmaf(p, y, 1.f / 6.f);
-    p = fmaf(p, y, 0.5f);
-    p = fmaf(p, y, 1.f);
-    const float e = ldexpf(fmaf(p, y, 1.f), (int)n);
+    float t = 1.f / 5040.f;
+    t = fmaf(t, y, 1.f / 720.f);
+    t = fmaf(t, y, 1.f / 120.f);
+    t = fmaf(t, y, 1.f / 24.f);
+    t = fmaf(t, y, 1.f / 6.f);
+    t = fmaf(t, y, 0.5f);
+    const float s = ldexpf(1.f, (int)n), ys = y * s;
+    const float e = fmaf(fmaf(t, y, 1.f), ys, s);                                          // s + ys (1 + t y)
+    const float b = (1.f - s) - ys, c = t * y, m = fmaf(-c, ys, b), m_lo = fmaf(-c, ys, b - m);   // 1 - e
     const float d = 1.f + e, d_lo = e - (d - 1.f);
-    const float num = th ? 2.f * e : (x >= 0.f ? 1.f : e);
+    const float num = th ? m : (x >= 0.f ? 1.f : e), num_lo = th ? m_lo : 0.f;
     const float r0 = __builtin_amdgcn_rcpf(d);
     float r = num * r0;
-    r = fmaf(r0, fmaf(-d_lo, r, fmaf(-d, r, num)), r);
-    if (th) {
-        r = 1.f - r;
-        const float x2 = x * x;
-        float t = fmaf(x2, -929569.f / 638512875.f, 21844.f / 6081075.f);
-        t = fmaf(x2, t, -1382.f / 155925.f);
-        t = fmaf(x2, t, 62.f / 2835.f);
-        t = fmaf(x2, t, -17.f / 315.f);
-        t = fmaf(x2, t, 2.f / 15.f);
-        t = fmaf(x2, t, -1.f / 3.f);
-        r = ax < 0.5f ? fmaf(x, x2 * t, x) : copysignf(r, x);
-    }
-    return x == x ? r : x;
+    r = fmaf(r0, fmaf(-d_lo, r, fmaf(-d, r, num)) + num_lo, r);
+    return th ? copysignf(r, x) : r;
 }
 
 // acc += a (two of every four columns) * w, the weights in accumulation registers or in vector registers.  Written out, because the compiler's
@@ -118,6 +115,7 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
     typedef float floatx4 __attribute__((ext_vector_type(4)));
     typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
     typedef unsigned int u32x8_t __attribute__((ext_vector_type(8)));
+    typedef short short2_t __attribute__((ext_vector_type(2)));
     constexpr int NM = NKF / 2, RM = lstm_chain_reg_frags(NKF) / 2, LM = NM - RM;   // 64-column instructions per gate; with their weights in registers, in LDS
     constexpr int GM = NM < 4 ? NM : 4;
     constexpr int PIN = RM * 4 < 30 ? 0 : 30;   // weights in accumulation registers
@@ -232,9 +230,19 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
     const float* gin_p = a.g_in + (size_t)a.t0 * 4 * h + (size_t)q * h + unit;
     float gin = *gin_p;
     unsigned limit = a.spin_limit;
+    // What a step needs besides its operands is ready before the barrier that it starts with
+    int vec_of[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) vec_of[j] = ((lane + 64 * j < 4 * kf_real) ? lane + 64 * j : 4 * kf_real - 1) * 16 + wave * quarter * 2;
+    const bool packs = q == 0 && (u & 1) == 0;                       // lanes that publish two units
+    const unsigned pub = packs ? (unsigned)unit * 2u : 0x40000000u;  // elsewhere behind the end of the area: not stored
     for (int s = 0; s < a.n; ++s) {
-        const float gin_now = gin;
-        if (s + 1 < a.n) gin = gin_p[(size_t)(s + 1) * 4 * h];
+        const float gin_now = gin + bias;
+        if (s + 1 < a.n) gin_p += (size_t)4 * h;   // (the last step asks for its own again)
+        gin = *gin_p;
+        floatx4 acc[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
         u32x8_t wb[4];
         auto fetch_w = [&](int gr) {
             if constexpr (LM > 0) {
@@ -251,38 +259,49 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
             // Nobody looks for the others' values before this workgroup's own are out: the looks of three wavefronts that have nothing
             // else to do (8 KiB a workgroup and look, past the caches) held up everybody's stores (a row 2.57 -> 1.90 us).
             __builtin_amdgcn_s_barrier();
-            const unsigned ph = (((s - 1) >> 1) & 1) ? 0u : TAG;
+            const bool tagged = !(((s - 1) >> 1) & 1);
+            const unsigned from = (unsigned)((s - 1) & 1) * 2u * (unsigned)h;
             u32x4_t v[NV];
             for (unsigned looks = 0;; ++looks) {
                 asm volatile("" ::: "memory");   // a look is a look: the loads stay in the loop
-                unsigned off = 0u;
 #pragma unroll
-                for (int j = 0; j < NV; ++j) {
-                    const int vec = (lane + 64 * j < 4 * kf_real) ? lane + 64 * j : 4 * kf_real - 1;
-                    v[j] = __builtin_amdgcn_raw_buffer_load_b128(xrs, (unsigned)((((s - 1) & 1) * h + wave * quarter + vec * 8) * 2), 0, SC1);
+                for (int j = 0; j < NV; ++j) v[j] = __builtin_amdgcn_raw_buffer_load_b128(xrs, vec_of[j] + from, 0, SC1);
+                unsigned all = ~0u, any = 0u;
+                if (tagged) {
+#pragma unroll
+                    for (int j = 0; j < NV; ++j) all = all & v[j].x & v[j].y & v[j].z & v[j].w;
+                    any = ~all;
+                } else {
+#pragma unroll
+                    for (int j = 0; j < NV; ++j) any = any | v[j].x | v[j].y | v[j].z | v[j].w;
                 }
-#pragma unroll
-                for (int j = 0; j < NV; ++j) off |= (v[j].x ^ ph) | (v[j].y ^ ph) | (v[j].z ^ ph) | (v[j].w ^ ph);
-                if (__all((off & TAG) == 0u)) break;
+                if (__all((any & TAG) == 0u)) break;
                 if (looks >= limit) {
                     limit = 0;   // the results are lost: the rest is not waited for either
                     if (lane == 0) __hip_atomic_store(a.fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;
                 }
             }
-            auto plain = [&](unsigned x) {
-                x ^= ph;
-                const unsigned over = ((x & 0x7fff7fffu) + 0x407f407fu) & 0x80008000u;   // halves above 1.0: a NaN without its top exponent bit
-                return x | (over >> 1);
-            };
+            // What lies above 1.0 without its top exponent bit was a NaN (published as a positive one, so a maximum of signed halves finds it).
+            short2_t top = short2_t{0, 0};
 #pragma unroll
             for (int j = 0; j < NV; ++j)
-                if (lane + 64 * j < 4 * kf_real) put_state(lane + 64 * j, make_uint4(plain(v[j].x), plain(v[j].y), plain(v[j].z), plain(v[j].w)));
+#pragma unroll
+                for (int c_ = 0; c_ < 4; ++c_) {
+                    v[j][c_] &= ~TAG;
+                    top = __builtin_elementwise_max(top, __builtin_bit_cast(short2_t, (unsigned)v[j][c_]));
+                }
+            if (__any(top.x > 0x3F80 || top.y > 0x3F80)) {
+#pragma unroll
+                for (int j = 0; j < NV; ++j)
+#pragma unroll
+                    for (int c_ = 0; c_ < 4; ++c_) v[j][c_] |= (((v[j][c_] & 0x3fff3fffu) + 0x007f007fu) & TAG);
+            }
+#pragma unroll
+            for (int j = 0; j < NV; ++j)   // (pieces past h repeat one in front of it: their weights are zero)
+                if (64 * (j + 1) <= 4 * NKF || lane + 64 * j < 4 * NKF) put_state(lane + 64 * j, make_uint4(v[j].x, v[j].y, v[j].z, v[j].w));
         }
         __builtin_amdgcn_wave_barrier();   // hs belongs to this wavefront: LDS accesses of one wavefront stay in order
-        floatx4 acc[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
         asm volatile("s_nop 1" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
         // groups of GM instructions a gate; the state of a group is read from LDS while the group before it multiplies, the weights of its
         // last instructions while its first ones do
@@ -311,27 +330,28 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
         __builtin_amdgcn_wave_barrier();
         chain_mma_done(acc);
         // every lane has an even and an odd row of each gate, for unit u: lane (q, u) hands on gate q
-        float* const ps = part + (s & 1) * (4 * 4 * 16);
+        float* const ps = part + (s & 1) * (4 * 4 * 16);   // [64 lanes][4 wavefronts]
         {
-            const float s0 = acc[0][0] + acc[0][1], s1 = acc[1][0] + acc[1][1], s2 = acc[2][0] + acc[2][1], s3 = acc[3][0] + acc[3][1];
-            ps[wave * 64 + lane] = q == 0 ? s0 : q == 1 ? s1 : q == 2 ? s2 : s3;
+            const float even = q < 2 ? (q == 0 ? acc[0][0] : acc[1][0]) : (q == 2 ? acc[2][0] : acc[3][0]);
+            const float odd = q < 2 ? (q == 0 ? acc[0][1] : acc[1][1]) : (q == 2 ? acc[2][1] : acc[3][1]);
+            ps[lane * 4 + wave] = even + odd;
         }
         __syncthreads();   // part[s & 1] is next written after the barrier of step s + 1, which wavefront 0 reaches when it has read it
         if (wave == 0) {
-            float g_rec = ps[(0 * 4 + q) * 16 + u];
-#pragma unroll
-            for (int w_ = 1; w_ < 4; ++w_) g_rec += ps[(w_ * 4 + q) * 16 + u];
-            const float pre = gin_now + g_rec + bias;
+            const float4 sums = ((const float4*)ps)[lane];
+            const float pre = (((sums.x + sums.y) + sums.z) + sums.w) + gin_now;
             const float act = lstm_gate(pre, q == 2);
-            const float gi = __shfl(act, u), gf = __shfl(act, 16 + u), gg = __shfl(act, 32 + u), go_ = __shfl(act, 48 + u);
+            // rows of lanes 0 .. 3 hold the four gates: every lane gets all of them by exchanging halves, then rows (through LDS it was four trips)
+            const auto half = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, act), __builtin_bit_cast(unsigned, act), false, false);
+            const auto in_f = __builtin_amdgcn_permlane16_swap(half[0], half[0], false, false), cell_o = __builtin_amdgcn_permlane16_swap(half[1], half[1], false, false);
+            const float gi = __builtin_bit_cast(float, (unsigned)in_f[0]), gf = __builtin_bit_cast(float, (unsigned)in_f[1]);
+            const float gg = __builtin_bit_cast(float, (unsigned)cell_o[0]), go_ = __builtin_bit_cast(float, (unsigned)cell_o[1]);
             c = gf * c + gi * gg;
-            const float hn = go_ * lstm_gate(c, true);
-            const __bf16 hb = (__bf16)hn;
-            const unsigned mine = __builtin_bit_cast(uint16_t, hb), other = (unsigned)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xF, 0xF, false);   // the neighbour's
-            const unsigned pair = mine | (other << 16);   // even lanes: units u, u + 1
-            const bool packs = q == 0 && (u & 1) == 0;
-            if (packs && s + 1 < a.n)
-                __builtin_amdgcn_raw_buffer_store_b32((pair & ~TAG) | (((s >> 1) & 1) ? 0u : TAG), xrs, (unsigned)(((s & 1) * h + (int)unit) * 2), 0, SC1);
+            float hn = go_ * lstm_gate(c, true);
+            hn = hn == hn ? hn : __builtin_nanf("");   // a positive one
+            const float other = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, hn), 0xB1, 0xF, 0xF, false));   // the neighbour's
+            const unsigned pair = pack_bf16x2(hn, other);   // even lanes: units u, u + 1
+            __builtin_amdgcn_raw_buffer_store_b32((pair & ~TAG) | (((s >> 1) & 1) ? 0u : TAG), xrs, pub + (unsigned)(s & 1) * 2u * (unsigned)h, 0, SC1);
             const int t = a.t0 + s;
             if (q < 2) a.state[((size_t)(a.r0 + t) * 2 + q) * h + unit] = q == 0 ? hn : c;
             if (a.xnext && packs) *(unsigned*)((char*)a.xnext + ((unit >> 3) * a.Tp + t) * 16 + (unit & 7) * 2) = pair;
