@@ -210,7 +210,7 @@ int launch_lstm_chain(fv_drafter* d, const ChainRows& cr, int layer) {
         LstmLevelArgs la;
         la.c = a;
         la.c.xchg = d->at<uint16_t>(dl.off_chain + 256) + (size_t)layer * 32 * h;
-        la.tab = dev_tables(d); la.xprev = d->at<uint4>(dl.off_xprev); la.l0 = ps.l0; la.n_lvl = (int)ps.lvl_n.size();
+        la.tab = dev_tables(d); la.xprev = (const uint4*)cr.xprev; la.x = cr.x; la.xb = cr.xb; la.gain = cr.gain; la.ssq = cr.ssq; la.l0 = ps.l0; la.n_lvl = (int)ps.lvl_n.size();
         for (int i = 0; i < FV_DRAFT_KMAX; ++i) la.rows[i] = i < la.n_lvl ? ps.lvl_n[i] : 0;
         switch (lstm_chain_size(h)) {
             case 2: return launch_levels_t<2>(la, c->stream);
@@ -542,9 +542,9 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
             ps.lvl_n.push_back((int)by_level[j].size());
             for (int t : by_level[j]) t_lvl[lvl_at++] = t;
         }
-        // Two levels and more of up to 16 rows each in one launch per layer (a level's rows are a subset of the blocks of the level
-        // before, so the counts never grow, which the kernel's exchange relies on); one level gains nothing.
-        ps.chain = d->chain_ok && ps.lvl_n.size() >= 2 && ps.lvl_n.size() <= FV_DRAFT_KMAX;
+        // Levels of up to 16 rows each in one launch per layer (a level's rows are a subset of the blocks of the level
+        // before, so the counts never grow, which the kernel's exchange relies on).
+        ps.chain = d->chain_ok && ps.lvl_n.size() >= 1 && ps.lvl_n.size() <= FV_DRAFT_KMAX;
         for (size_t j = 0; j < ps.lvl_n.size(); ++j) ps.chain = ps.chain && ps.lvl_n[j] <= 16 && (j == 0 || ps.lvl_n[j] <= ps.lvl_n[j - 1]);
         any_chain = any_chain || ps.chain;
         passes.push_back(ps);

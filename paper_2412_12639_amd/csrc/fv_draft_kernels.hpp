@@ -85,11 +85,43 @@ struct DraftInArgs {
     int r0, n, Tp, h, vocab;
 };
 
-// The start of a pass, input rows and ingest side by side in one launch (they do not depend on each other; a small launch is 5 us
-// with its gap): the first n_in workgroups take 256 four-feature groups each, the next Tp / 4 four rows' masks and rotary entries, the others clear padding.
+// previous hidden state of every row of a level -> vector-major input of the recurrent multiplication
+struct LstmGatherArgs {
+    DraftTables tab;
+    const float* state;   // this layer's state rows
+    void* xprev;          // [h/E][Tpl][E]
+    int r0, l0, n_lvl, Tpl, h;
+};
 template <typename EL>
-static __global__ __launch_bounds__(256) void k_draft_begin(DraftInArgs a, DraftIngestArgs ia, int n_in, PadArgs pa) {
-    if ((int)blockIdx.x >= n_in + ia.Tp / 4) { clear_pads(pa, (blockIdx.x - n_in - ia.Tp / 4) * 256 + threadIdx.x); return; }
+__device__ __forceinline__ void lstm_gather(const LstmGatherArgs& a, size_t idx) {
+    const int i = (int)(idx % a.Tpl);
+    const int f0 = (int)(idx / a.Tpl) * 4;
+    if (f0 >= a.h) return;
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < a.n_lvl) {
+        const int r = a.r0 + a.tab.lvl_rows[a.l0 + i];
+        x = *(const float4*)(a.state + ((size_t)a.tab.lpred[r] * 2) * a.h + f0);
+    }
+    store4_act<EL>(a.xprev, a.Tpl, f0, i, x.x, x.y, x.z, x.w);
+}
+
+// What a tree pass whose levels go in one launch a layer needs besides, of both layers (the first level's predecessors are rows of earlier passes): their
+// states, and the statistics that the launch of layer 1 adds to, cleared.
+struct DraftLevelArgs { LstmGatherArgs layer[2]; float* ssq; int n_ssq, n_gather; };   // n_gather workgroups a layer; 0: none
+
+// The start of a pass, input rows, ingest and first predecessors side by side in one launch (they do not depend on each other; a small launch is 5 us
+// with its gap): the first n_in workgroups take 256 four-feature groups each, the next Tp / 4 four rows' masks and rotary entries, then come the
+// predecessors' states, the others clear padding.
+template <typename EL>
+static __global__ __launch_bounds__(256) void k_draft_begin(DraftInArgs a, DraftIngestArgs ia, int n_in, DraftLevelArgs lv, PadArgs pa) {
+    if ((int)blockIdx.x >= n_in + ia.Tp / 4) {
+        int b = blockIdx.x - n_in - ia.Tp / 4;
+        if (b >= 2 * lv.n_gather) { clear_pads(pa, (b - 2 * lv.n_gather) * 256 + threadIdx.x); return; }
+        for (int i = b * 256 + threadIdx.x; i < lv.n_ssq; i += 2 * lv.n_gather * 256) lv.ssq[i] = 0.f;
+        const int l = b >= lv.n_gather;
+        lstm_gather<EL>(lv.layer[l], (size_t)(b - l * lv.n_gather) * 256 + threadIdx.x);
+        return;
+    }
     if ((int)blockIdx.x >= n_in) { draft_ingest_rows(ia, blockIdx.x - n_in); return; }
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
     for (size_t i = idx; i < (size_t)a.chain_words; i += (size_t)n_in * 256) a.chain[i] = 0u;
@@ -129,27 +161,8 @@ static __global__ __launch_bounds__(256) void k_draft_begin(DraftInArgs a, Draft
 // One level = the rows of a pass whose predecessors' states are all known; level rows are listed in
 // lvl_rows[l0 .. l0 + n_lvl).
 
-// previous hidden state of every row of a level -> vector-major input of the recurrent multiplication
-struct LstmGatherArgs {
-    DraftTables tab;
-    const float* state;   // this layer's state rows
-    void* xprev;          // [h/E][Tpl][E]
-    int r0, l0, n_lvl, Tpl, h;
-};
-
 template <typename EL>
-static __global__ __launch_bounds__(256) void k_lstm_gather(LstmGatherArgs a) {
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const int i = (int)(idx % a.Tpl);
-    const int f0 = (int)(idx / a.Tpl) * 4;
-    if (f0 >= a.h) return;
-    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i < a.n_lvl) {
-        const int r = a.r0 + a.tab.lvl_rows[a.l0 + i];
-        x = *(const float4*)(a.state + ((size_t)a.tab.lpred[r] * 2) * a.h + f0);
-    }
-    store4_act<EL>(a.xprev, a.Tpl, f0, i, x.x, x.y, x.z, x.w);
-}
+static __global__ __launch_bounds__(256) void k_lstm_gather(LstmGatherArgs a) { lstm_gather<EL>(a, (size_t)blockIdx.x * 256 + threadIdx.x); }
 
 // gates = G_in[row] + G_rec[level row] + bias (rows ordered input, forget, cell, output);
 // c' = sigmoid(f) c + sigmoid(i) tanh(g);  h' = sigmoid(o) tanh(c').

@@ -23,6 +23,8 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
     hipStream_t st = c->stream;
     const DraftTables tab = draft_tables(d);
     constexpr int E = Tr<EL>::E;
+    const bool levels = ps.chain && !ps.commit;   // a tree pass whose levels go in one launch a layer
+    auto xprev = [&](int layer) { return (void*)(d->at<char>(dl.off_xprev) + (size_t)layer * 64 * h); };   // [h / 8][32][8] each
 
     auto kind_for = [&](int tp, int small_kind) { return tp <= 64 ? small_kind : (int)GEMM_SHARED; };
     // a weight multiplication with no norm in front (n_ssq = 0, eps = 1: the per-row factor is rsqrt(1) = 1)
@@ -75,7 +77,17 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
         const int n_in = (int)((items + 255) / 256);
         PadArgs pa = k_padding<EL>(c, ly.off_xb, ly.off_attn, ly.off_act, Tp);
         if (Tp == d->last_Tp) pa.n[0] = pa.n[1] = pa.n[2] = 0;
-        hipLaunchKernelGGL((k_draft_begin<EL>), dim3(n_in + Tp / 4 + pad_blocks(pa)), dim3(256), 0, st, da, ia, n_in, pa);
+        DraftLevelArgs lv;
+        memset(&lv, 0, sizeof(lv));
+        if (levels) {
+            for (int l = 0; l < 2; ++l) {
+                LstmGatherArgs& la = lv.layer[l];
+                la.tab = tab; la.state = d->state(l); la.xprev = xprev(l);
+                la.r0 = ps.r0; la.l0 = ps.l0; la.n_lvl = ps.lvl_n[0]; la.Tpl = 32; la.h = h;
+            }
+            lv.ssq = c->at<float>(ly.off_ssq); lv.n_ssq = h / 32 * Tp; lv.n_gather = (h / 4 * 32 + 255) / 256;
+        }
+        hipLaunchKernelGGL((k_draft_begin<EL>), dim3(n_in + Tp / 4 + 2 * lv.n_gather + pad_blocks(pa)), dim3(256), 0, st, da, ia, n_in, lv, pa);
         d->last_Tp = Tp;
         HIPCHK(hipGetLastError());
     }
@@ -93,18 +105,16 @@ int run_draft_pass(fv_drafter* d, const DraftPass& ps) {
             if (rc) return rc;
         }
         if (ps.chain) {   // all rows in one launch
-            if (!ps.commit) {   // the first level's predecessors are rows of earlier passes
-                LstmGatherArgs la;
-                la.tab = tab; la.state = d->state(layer); la.xprev = d->at<void>(dl.off_xprev);
-                la.r0 = ps.r0; la.l0 = ps.l0; la.n_lvl = ps.lvl_n[0]; la.Tpl = 32; la.h = h;
-                hipLaunchKernelGGL((k_lstm_gather<EL>), dim3((unsigned)(((size_t)(h / 4) * 32 + 255) / 256)), dim3(256), 0, st, la);
-            }
             ChainRows cr;
             cr.n = n; cr.Tp = Tp; cr.r0 = ps.r0; cr.g_in = d->at<float>(dl.off_gin); cr.state = d->state(layer); cr.xnext = layer == 0 ? d->at<void>(dl.off_xh) : nullptr;
-            cr.levels = ps.commit ? nullptr : &ps;
+            if (levels) {
+                cr.levels = &ps;
+                cr.xprev = xprev(layer);
+                if (layer == 1) { cr.x = c->at<float>(ly.off_x); cr.xb = c->at<void>(ly.off_xb); cr.gain = c->gain(0); cr.ssq = c->at<float>(ly.off_ssq); }
+            }
             int rc = launch_lstm_chain(d, cr, layer);
             if (rc) return rc;
-            if (layer == 1) {
+            if (layer == 1 && !levels) {
                 LstmOutArgs oa;
                 oa.state = d->state(1); oa.x = c->at<float>(ly.off_x); oa.xb = c->at<void>(ly.off_xb); oa.gain = c->gain(0); oa.ssq = c->at<float>(ly.off_ssq);
                 oa.r0 = ps.r0; oa.n = oa.rows = n; oa.Tp = Tp; oa.h = h;

@@ -179,6 +179,8 @@ struct ChainRows {
     float* state = nullptr;              // this layer's state rows
     void* xnext = nullptr;               // next layer's input, or null
     const DraftPass* levels = nullptr;   // a tree pass: its levels; null: a chain behind the last committed pair
+    const void* xprev = nullptr;         // levels: the first one's predecessors' states
+    float* x = nullptr; void* xb = nullptr; const float* gain = nullptr; float* ssq = nullptr;   // levels of layer 1: what the decoder block takes in
 };
 
 struct fv_drafter {

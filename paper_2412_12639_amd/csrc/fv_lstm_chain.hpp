@@ -360,15 +360,17 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_chain(LstmChainArgs a) {
 }
 
 // The same for the levels of a tree pass: up to 16 rows a level, which are the 16 columns of the matrix instruction (a chain uses
-// one of them).  Two levels of 7 to 11 rows at hidden 4096: 48 us per layer (and 5 to gather) against 2 x (gather 5, product
-// 23 to 31, cell 5 us and gaps); 4 pairs and a 64-node tree 1632 -> 1585 us.  Differences to
+// one of them).  At hidden 4096 a launch takes 31 us for one level, of which 25 read the matrix, and 5.5 for another (separate launches: gather 5, product
+// 23 to 31, cell 5 us and gaps a level).  Differences to
 // the chain: a level's rows continue rows anywhere in the level before, so a lane reads its column's predecessor; the first
-// level's predecessors are gathered by k_lstm_gather; the operand goes from the exchange area straight to registers, a few
+// level's predecessors of both layers are gathered at the start of the pass, and layer 1 leaves what the decoder block takes in itself (a launch
+// each of 5 us before; 2 us of layer 1's launch now); the operand goes from the exchange area straight to registers, a few
 // fragments at a time; all four wavefronts apply the cell.
 struct LstmLevelArgs {
     LstmChainArgs c;               // n, t0, from are not used; xchg: [2][h / 8][16][8]
     DraftTables tab;
     const uint4* xprev;            // [h / 8][32][8] bf16 predecessors' states of the first level
+    float* x; void* xb; const float* gain; float* ssq;   // layer 1 (else null): residual stream, x * gain, and its sums of squares, zero when the launch starts, as k_lstm_out leaves them
     int l0, n_lvl;                 // first entry in lvl_rows; levels
     int rows[FV_DRAFT_KMAX];       // rows of each level, 1..16
 };
@@ -552,6 +554,19 @@ static __global__ __launch_bounds__(256, 1) void k_lstm_levels(LstmLevelArgs la)
             }
             a.state[((size_t)cr * 2) * H + unit] = hn;
             a.state[((size_t)cr * 2 + 1) * H + unit] = cn;
+        }
+        if (la.x) {   // a strip's statistics are the sum of two workgroups', in either order the same
+            const float xg = hn * la.gain[unit], xg_next = __shfl_xor(xg, 1);
+            float ssq = hn * hn;
+            ssq += __shfl_xor(ssq, 1);
+            ssq += __shfl_xor(ssq, 2);
+            ssq += __shfl_xor(ssq, 4);
+            ssq += __shfl_xor(ssq, 8);
+            if (cell) {
+                la.x[((unit >> 2) * a.Tp + ct) * 4 + (unit & 3)] = hn;
+                if ((cu & 1) == 0) *(unsigned*)((char*)la.xb + ((unit >> 3) * a.Tp + ct) * 16 + (unit & 7) * 2) = pack_bf16x2(xg, xg_next);
+                if (cu == 0) __hip_atomic_fetch_add(la.ssq + (unit >> 5) * a.Tp + ct, ssq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
         __syncthreads();   // part is written again, and the next level reads this one's cell states
         l_at += n;
