@@ -44,6 +44,8 @@
 #define FV_DIRECT_SMEM_FLOATS(TB) ((2 * FV_STREAMERS + FV_PARK) * (TB) * 1024 + (TB) * 32 + 1024 + 4)
 #define FV_PAIRED_SMEM_FLOATS(TB) ((2 * FV_STREAMERS + FV_PARK) * 2 * (TB) * 1024 + (TB) * 32 + 1024 + 4)
 
+template <int N> struct Tiles { static constexpr int value = N; };
+
 // This workgroup's range of the (row group, K stage) space and this wavefront's slices of it.
 struct DPlan {
     int u0, u1, g0, nseg, NB, wave;
@@ -350,19 +352,23 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
                         r[4 * q] = f.x; r[4 * q + 1] = f.y; r[4 * q + 2] = f.z; r[4 * q + 3] = f.w;
                     }
                 }
-                for (int c0 = c_first + 1; c0 <= c_last; c0 += 4) {   // ascending order, four tiles in flight
-                    u32x4 v[4][4];
+                // N tiles from workgroup c0 on, all in flight.  The paired form asks for those that there are: a wavefront alone on its SIMD issues an instruction
+                // every eight cycles, and with four tiles always asked for, looked over and added, absent ones times zero, a group of two contributors
+                // (QKV, gate and up) paid 150 instructions more than it needed (with the code below in one place instead of two, half as long: 7B, 64 rows
+                // 3579 -> 3535 us a step).  The direct form, whose long rows have a dozen contributors, always takes four (23 fp32 rows of hidden 512 128.3 us, 130 the other way).
+                auto add_tiles = [&](auto n_, int c0) {
+                    constexpr int N = decltype(n_)::value;
+                    u32x4 v[N][4];
                     for (unsigned spins = 0;; ++spins) {
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const int c = (c0 + k <= c_last) ? c0 + k : c_last;
-                            const unsigned o = tile_ofs(c);
+                        for (int k = 0; k < N; ++k) {
+                            const unsigned o = tile_ofs(RS == 2 || c0 + k <= c_last ? c0 + k : c_last);
 #pragma unroll
                             for (int q = 0; q < 4; ++q) v[k][q] = __builtin_amdgcn_raw_buffer_load_b128(prs, o + q * 1024u, 0, SC1);
                         }
                         unsigned all1 = 1u;
 #pragma unroll
-                        for (int k = 0; k < 4; ++k)
+                        for (int k = 0; k < N; ++k)
 #pragma unroll
                             for (int q = 0; q < 4; ++q) all1 &= v[k][q].x & v[k][q].y & v[k][q].z & v[k][q].w;
                         if (__all((int)(all1 & 1u))) break;
@@ -375,8 +381,8 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
                         __builtin_amdgcn_s_sleep(16);
                     }
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const float m = (c0 + k <= c_last) ? 1.f : 0.f;
+                    for (int k = 0; k < N; ++k) {
+                        const float m = RS == 2 || c0 + k <= c_last ? 1.f : 0.f;
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             r[4 * q] += m * __uint_as_float(v[k][q].x & ~1u);
@@ -388,12 +394,20 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
                     // the tiles just consumed go back to zero (nobody reads them again in this launch)
                     u32x4 zero4; zero4.x = 0u; zero4.y = 0u; zero4.z = 0u; zero4.w = 0u;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        if (c0 + k > c_last) break;
+                    for (int k = 0; k < N; ++k) {
+                        if (RS == 1 && c0 + k > c_last) break;
                         const unsigned o = tile_ofs(c0 + k);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b128(zero4, prs, o + q * 1024u, 0, SC1);
                     }
+                };
+                int c0 = c_first + 1;   // ascending order
+                if constexpr (RS == 1) {
+                    for (; c0 <= c_last; c0 += 4) add_tiles(Tiles<4>{}, c0);
+                } else {
+                    for (; c0 + 2 <= c_last; c0 += 3) add_tiles(Tiles<3>{}, c0);
+                    if (c0 + 1 == c_last) add_tiles(Tiles<2>{}, c0);
+                    else if (c0 == c_last) add_tiles(Tiles<1>{}, c0);
                 }
                 if (mine_out) gemm_epilogue<EL, D, EPI>(a, Tp, strip, tb_, lane, r, rinv_lds, pre, have_pre);
             }
@@ -428,7 +442,14 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
         // it parked is visible to everybody behind this barrier.
         __syncthreads();
         const int s0 = s - s % FV_PARK;
-        if (s == nseg - 1) {               // nothing left to stream: one tile each
+        const bool last = s == nseg - 1;   // nothing left to stream: one tile each
+        if constexpr (RS == 2) {           // (one call)
+            const int t_lo = last ? wave : 0, t_hi = last ? wave + 1 : NT;
+            if (last ? wave < NT : wave == FV_STREAMERS) {
+                for (int t = t_lo; t < t_hi; ++t) park_tile(s, t);
+                if (last || s % FV_PARK == FV_PARK - 1) flush_parked(s0, s, t_lo, t_hi);
+            }
+        } else if (last) {
             if (wave < NT) { park_tile(s, wave); flush_parked(s0, s, wave, wave + 1); }
         } else if (wave == FV_STREAMERS) {
             for (int t = 0; t < NT; ++t) park_tile(s, t);
