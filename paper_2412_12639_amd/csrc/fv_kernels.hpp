@@ -5,6 +5,7 @@
 #pragma once
 #include "fv_device.hpp"
 #include "fv_types.hpp"
+#include <float.h>
 
 // ============================================================================ ingest
 // Tree ingest: ancestor sets, positions, rotary table.  One block.
@@ -1256,26 +1257,85 @@ __device__ __forceinline__ void argmax_combine(float& v, int& i, float ov, int o
     if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
 }
 
-// NT threads: a row of 32000 values took 256 threads four rounds of requests (13 us for a single row), 1024 take one.
+// A wavefront's largest value, in every lane: within rows of 16 by moves across lanes, then rows and halves exchanged
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, dpp_move<0xB1>(v));    // quad_perm [1, 0, 3, 2]
+    v = fmaxf(v, dpp_move<0x4E>(v));    // quad_perm [2, 3, 0, 1]
+    v = fmaxf(v, dpp_move<0x141>(v));   // row_half_mirror
+    v = fmaxf(v, dpp_move<0x140>(v));   // row_mirror
+    const auto rows = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    v = fmaxf(__builtin_bit_cast(float, (unsigned)rows[0]), __builtin_bit_cast(float, (unsigned)rows[1]));
+    const auto halves = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    return fmaxf(__builtin_bit_cast(float, (unsigned)halves[0]), __builtin_bit_cast(float, (unsigned)halves[1]));
+}
+
+// The greedy choice of one row, in thread 0; -1 if it has none.  NT threads: a row of 32000 values took 256 threads four rounds of requests (13 us for a
+// single row), 1024 take one.  A row that they hold at once is asked for its largest value first and for the first place that has it then: one
+// maximum and one addition a value (of zeros, which a NaN or an infinity turns into a NaN), where value and place together took five instructions and two trips
+// through LDS for each step of the reduction (us a step, device time: 7B width, four layers, 49 rows 562.7 -> 557.9; 250 rows 1019 -> 1014).
 template <int NT>
-static __global__ __launch_bounds__(NT) void k_argmax(ArgmaxArgs a) {
+__device__ __forceinline__ int argmax_row(const float* row, int V) {
     __shared__ float sv[NT / 64];
     __shared__ int si[NT / 64];
     __shared__ int sbad[NT / 64];
-    const int t = blockIdx.x, tid = threadIdx.x;
-    const float* row = a.logits + (size_t)t * a.Vpad;
+    const int tid = threadIdx.x;
+    if (V <= 32 * NT) {
+        float4 x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int v = (tid + k * NT) * 4;
+            x[k] = (v < V) ? *(const float4*)(row + v) : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX);   // (a row is padded to a multiple of 32)
+            if (v + 1 >= V) x[k].y = -FLT_MAX;
+            if (v + 2 >= V) x[k].z = -FLT_MAX;
+            if (v + 3 >= V) x[k].w = -FLT_MAX;
+        }
+        float bv = -FLT_MAX, zero = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            bv = fmaxf(fmaxf(bv, x[k].x), x[k].y);
+            bv = fmaxf(fmaxf(bv, x[k].z), x[k].w);
+            zero = fmaf(x[k].x, 0.f, zero); zero = fmaf(x[k].y, 0.f, zero);
+            zero = fmaf(x[k].z, 0.f, zero); zero = fmaf(x[k].w, 0.f, zero);
+        }
+        const float wv = wave_max(bv);
+        const bool wbad = __any(!(zero == 0.f));
+        if ((tid & 63) == 0) { sv[tid >> 6] = wv; sbad[tid >> 6] = wbad ? 1 : 0; }
+        if (tid == 0) si[0] = 0x7fffffff;
+        __syncthreads();
+        float best = sv[0];
+        int any = sbad[0];
+#pragma unroll
+        for (int w = 1; w < NT / 64; ++w) { best = fmaxf(best, sv[w]); any |= sbad[w]; }
+        if (bv == best) {   // -0 and +0 are equal here too
+            int at = 0x7fffffff;
+#pragma unroll
+            for (int k = 7; k >= 0; --k) {
+                const int v = (tid + k * NT) * 4;
+                if (x[k].w == best && v + 3 < V) at = v + 3;
+                if (x[k].z == best && v + 2 < V) at = v + 2;
+                if (x[k].y == best && v + 1 < V) at = v + 1;
+                if (x[k].x == best && v < V) at = v;
+            }
+            atomicMin(&si[0], at);
+        }
+        __syncthreads();
+        return any ? -1 : si[0];
+    }
     float bv = -INFINITY;
     int bi = 0x7fffffff;
     bool bad = false;
     // eight 16-byte loads in flight per thread (the row is a latency chain otherwise: one load per
     // trip of a loop the compiler does not pipeline); indices past Vpad are not touched, values
     // between V and Vpad are skipped
-    for (int v0 = tid * 4; v0 < a.V; v0 += 8 * NT * 4) {
+    for (int v0 = tid * 4; v0 < V; v0 += 8 * NT * 4) {
         float4 x[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int v = v0 + k * NT * 4;
-            x[k] = (v < a.V) ? *(const float4*)(row + v) : make_float4(0.f, 0.f, 0.f, 0.f);
+            x[k] = (v < V) ? *(const float4*)(row + v) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -1283,7 +1343,7 @@ static __global__ __launch_bounds__(NT) void k_argmax(ArgmaxArgs a) {
             const float xs[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (v + c < a.V) {
+                if (v + c < V) {
                     // finite <=> |x| < inf; false for NaN too
                     bad = bad || !(__builtin_fabsf(xs[c]) < INFINITY);
                     argmax_combine(bv, bi, xs[c], v + c);
@@ -1299,11 +1359,15 @@ static __global__ __launch_bounds__(NT) void k_argmax(ArgmaxArgs a) {
     const bool wbad = __any(bad);
     if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; sbad[tid >> 6] = wbad ? 1 : 0; }
     __syncthreads();
-    if (tid == 0) {
-        int any = sbad[0];
-        for (int w = 1; w < NT / 64; ++w) { argmax_combine(bv, bi, sv[w], si[w]); any |= sbad[w]; }
-        a.am[t] = any ? -1 : bi;
-    }
+    int any = sbad[0];
+    for (int w = 1; w < NT / 64; ++w) { argmax_combine(bv, bi, sv[w], si[w]); any |= sbad[w]; }   // thread 0's value starts as its own wavefront's
+    return any ? -1 : bi;
+}
+
+template <int NT>
+static __global__ __launch_bounds__(NT) void k_argmax(ArgmaxArgs a) {
+    const int best = argmax_row<NT>(a.logits + (size_t)blockIdx.x * a.Vpad, a.V);
+    if (threadIdx.x == 0) a.am[blockIdx.x] = best;
 }
 
 // ============================================================================ non-greedy acceptance
@@ -1817,6 +1881,54 @@ struct FinishArgs {
     int slabs, L, S_pad;
 };
 
+// Features of row t, the b-th of the path, by NT threads; the first 256 add up the statistics
+template <int NT>
+__device__ __forceinline__ void finish_feature(const FinishArgs& a, int t, int b, float* red) {
+    const int i = threadIdx.x;
+    if (i < 256) {
+        float s = 0.f;
+        for (int k = i; k < a.h / 32; k += 256) s += a.ssq[(size_t)k * a.Tp + t];
+        red[i] = s;
+    }
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (i < w) red[i] += red[i + w];
+        __syncthreads();
+    }
+    const float rinv = rsqrtf(red[0] * a.inv_h + a.eps);
+    for (int f0 = i; f0 < a.h; f0 += 8 * NT) {   // eight values read before the first is stored: one trip to memory for them, not one each
+        float x[8], gn[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int f = f0 + k * NT < a.h ? f0 + k * NT : f0;
+            x[k] = a.x[((size_t)(f >> 2) * a.Tp + t) * 4 + (f & 3)];
+            gn[k] = a.gain[f];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (f0 + k * NT < a.h) a.feat[(size_t)b * a.h + f0 + k * NT] = x[k] * rinv * gn[k];
+    }
+}
+
+// The end of a greedy step of one node, whose path is known: its greedy choice and the step's result, and beside it its features.  (Nothing moves in the cache.)
+// Plain decoding pays for one launch here instead of two: one token of the 7B width, four layers 441.8 -> 432.6 us of device time, of hidden 512, two layers 84.5 -> 81.0.
+template <int NT>
+static __global__ __launch_bounds__(NT) void k_finish_one(ArgmaxArgs am, FinishArgs a) {
+    __shared__ float red[256];
+    if (blockIdx.x == 1) { finish_feature<NT>(a, 0, 0, red); return; }
+    const int best = argmax_row<NT>(am.logits, am.V);
+    if (threadIdx.x == 0) {
+        am.am[0] = best;
+        a.res->accepted_len = best < 0 ? FV_SCAN_NONFINITE : 0;
+        a.res->next_token = best;
+        a.res->best = 0;
+        a.res->rows.fault = *a.fault;
+        if (best >= 0) a.res->path[0] = 0;
+        a.res->rows.argmax[0] = best;
+        __threadfence_system();
+    }
+}
+
 template <typename EL, int D, bool SAMPLED>
 __global__ __launch_bounds__(256) void k_finish(FinishArgs a) {
     __shared__ unsigned long long mbits[4];
@@ -1890,29 +2002,7 @@ __global__ __launch_bounds__(256) void k_finish(FinishArgs a) {
         return;
     }
     if (--b < a.T) {
-        if (b > len) return;
-        const int t = s_path[b];
-        float s = 0.f;
-        for (int k = i; k < a.h / 32; k += 256) s += a.ssq[(size_t)k * a.Tp + t];
-        red[i] = s;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (i < w) red[i] += red[i + w];
-            __syncthreads();
-        }
-        const float rinv = rsqrtf(red[0] * a.inv_h + a.eps);
-        for (int f0 = i; f0 < a.h; f0 += 8 * 256) {   // eight values read before the first is stored: one trip to memory for them, not one each
-            float x[8], gn[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int f = f0 + k * 256 < a.h ? f0 + k * 256 : f0;
-                x[k] = a.x[((size_t)(f >> 2) * a.Tp + t) * 4 + (f & 3)];
-                gn[k] = a.gain[f];
-            }
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (f0 + k * 256 < a.h) a.feat[(size_t)b * a.h + f0 + k * 256] = x[k] * rinv * gn[k];
-        }
+        if (b <= len) finish_feature<256>(a, s_path[b], b, red);
         return;
     }
     const int slab = (b - a.T) * (256 / D) + i / D, e = i % D;

@@ -365,8 +365,9 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
         const bool resident = mode == STEP_VERIFY_SAMPLED && cf.vocab <= FV_SAMPLED_RESIDENT &&   // the acceptance finds them as well
                               (!c->sample_draft || sampled_vectors(c->sample_draft, cf.vocab));
         // one round of requests per row where it has more than a round's worth for 256 threads (8192 values)
-        if (!resident && cf.vocab > 8192) hipLaunchKernelGGL(k_argmax<1024>, dim3(T), dim3(1024), 0, st, am);
-        else if (!resident) hipLaunchKernelGGL(k_argmax<256>, dim3(T), dim3(256), 0, st, am);
+        const bool one = mode == STEP_VERIFY && T == 1;   // k_finish_one finds it
+        if (!one && !resident && cf.vocab > 8192) hipLaunchKernelGGL(k_argmax<1024>, dim3(T), dim3(1024), 0, st, am);
+        else if (!one && !resident) hipLaunchKernelGGL(k_argmax<256>, dim3(T), dim3(256), 0, st, am);
         if (mode == STEP_VERIFY_SAMPLED) {
             SampledArgs sa;
             sa.tok_in = c->at<int32_t>(ly.off_stepin); sa.cap = FV_MAX_TREE; sa.T = T;
@@ -391,7 +392,9 @@ int run_step(fv_ctx* c, int T, StepMode mode, int from_prompt) {
             fa.h = h; fa.Tp = Tp; fa.inv_h = 1.f / (float)h; fa.eps = cf.rms_eps;
             fa.kcache = c->at<void>(ly.off_k); fa.vcache = c->at<void>(ly.off_v); fa.slabs = cf.n_layers * cf.n_kv_heads; fa.L = L; fa.S_pad = ly.S_pad;
             const dim3 grid(1 + T + (fa.slabs * D + 255) / 256);
-            if (mode == STEP_VERIFY) hipLaunchKernelGGL((k_finish<EL, D, false>), grid, dim3(256), 0, st, fa);
+            if (one && cf.vocab > 8192) hipLaunchKernelGGL(k_finish_one<1024>, dim3(2), dim3(1024), 0, st, am, fa);
+            else if (one) hipLaunchKernelGGL(k_finish_one<256>, dim3(2), dim3(256), 0, st, am, fa);
+            else if (mode == STEP_VERIFY) hipLaunchKernelGGL((k_finish<EL, D, false>), grid, dim3(256), 0, st, fa);
             else hipLaunchKernelGGL((k_finish<EL, D, true>), grid, dim3(256), 0, st, fa);
         }
         HIPCHK(hipGetLastError());
