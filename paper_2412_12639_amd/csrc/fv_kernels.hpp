@@ -330,7 +330,8 @@ __device__ __forceinline__ bool rope_preload(const GemmArgs& a, int strip, int t
     return true;
 }
 
-template <typename EL, int D, int EPI>
+// IN_ORDER: the squares are added in the order that the direct and paired kernels compile to, written out, where the compiler picks another one.
+template <typename EL, int D, int EPI, bool IN_ORDER = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int Tp, int strip, int tb, int lane, float (&acc)[16],
                                               const float* rinv_lds, const EpiPre& pre, bool have_pre) {
     const int tl = lane & 31, g = lane >> 5;
@@ -345,7 +346,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int Tp, int str
             xv.x += acc[4 * blk]; xv.y += acc[4 * blk + 1]; xv.z += acc[4 * blk + 2]; xv.w += acc[4 * blk + 3];
             st_f4((float4*)a.x + (size_t)(f0 >> 2) * Tp + t, xv);
             store4_act<EL>(a.xb, Tp, f0, t, xv.x * gn.x, xv.y * gn.y, xv.z * gn.z, xv.w * gn.w);
-            ssq += xv.x * xv.x + xv.y * xv.y + xv.z * xv.z + xv.w * xv.w;
+            if constexpr (IN_ORDER) ssq += fmaf(xv.w, xv.w, fmaf(xv.z, xv.z, fmaf(xv.y, xv.y, xv.x * xv.x)));
+            else ssq += xv.x * xv.x + xv.y * xv.y + xv.z * xv.z + xv.w * xv.w;
         }
         ssq += __shfl_xor(ssq, 32);
         if (g == 0) st_f32(a.ssq_out + (size_t)strip * Tp + t, ssq);
@@ -872,6 +874,7 @@ __global__ __launch_bounds__(256) void k_gemm_fix(GemmArgs a) {
 }
 
 #include "fv_gemm_direct.hpp"
+#include "fv_gemm_small.hpp"
 #include "fv_gemm_ring.hpp"
 
 // ============================================================================ tree attention
