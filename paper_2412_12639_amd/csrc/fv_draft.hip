@@ -166,7 +166,7 @@ int set_chain_attr() {
 }
 
 // Whether the chain kernel takes this drafter: bf16, a hidden size whose recurrent matrix fits into the registers and LDS of
-// h / 16 compute units (h up to 4096), and a device with that many.  At hidden 4096 a row then costs 2.0 us per layer instead
+// h / 16 compute units (h up to 4096), and a device with that many.  At hidden 4096 a row then costs 1.85 us per layer instead
 // of 33; wider drafters and fp32 ones stream the matrix once per row as before.
 int lstm_chain_fits(const fv_cfg& c, bool& fits) {
     fits = false;
