@@ -133,6 +133,18 @@ int wide_any(fv_drafter* d, const float* ext, int m, int keep) {
     return rc;
 }
 
+// slots [slot0, slot0 + n) of a bf16 drafter's cache (see k_draft_clear_slots)
+int clear_slots(fv_drafter* d, int slot0, int n) {
+    const fv_cfg& cf = d->core->cfg;
+    ClearSlotsArgs ca;
+    ca.kcache = d->core->kc(0); ca.vcache = d->core->vc(0); ca.slot0 = slot0; ca.n = n; ca.Hkv = cf.n_kv_heads; ca.S_pad = d->core->lay.S_pad;
+    const dim3 grid((unsigned)(((size_t)n * cf.n_kv_heads * cf.head_dim + 255) / 256));
+    if (cf.head_dim == 128) hipLaunchKernelGGL((k_draft_clear_slots<BF16, 128>), grid, dim3(256), 0, d->core->stream, ca);
+    else hipLaunchKernelGGL((k_draft_clear_slots<BF16, 64>), grid, dim3(256), 0, d->core->stream, ca);
+    HIPCHK(hipGetLastError());
+    return FV_OK;
+}
+
 int32_t* htab(fv_drafter* d, int which) { return d->h_tab + (size_t)which * FV_MAX_TREE; }
 
 int upload_tables(fv_drafter* d) {
@@ -451,6 +463,8 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
         if (wide && !chains) { hist_done = true; continue; }   // the launches left: the same rows again, without them
         if (cut && d->h_out[FV_MAX_TREE]) {                    // not finite somewhere: which piece, and what stands before it, the small pieces say
             HIPCHK(hipMemset(d->at<int32_t>(d->lay.off_bad), 0, 4));
+            rc = clear_slots(d, d->L, m);
+            if (rc) return rc;
             merge = false; hist_done = true;
             continue;
         }

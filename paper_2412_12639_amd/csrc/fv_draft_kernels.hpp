@@ -482,6 +482,19 @@ static __global__ __launch_bounds__(256) void k_draft_slice(DraftSliceArgs a) {
             for (int i = tid; i < 2 * a.h; i += 256) a.state[l][(size_t)r * 2 * a.h + i] = a.state[l][(size_t)(a.s + r) * 2 * a.h + i];
 }
 
+// K and V of n slots <- 0: what a pass left there that is run again in pieces.  Its rows may be no numbers, and a piece reads whole blocks of 32 keys, the
+// slots behind its own rows masked, which a value that is no number survives.
+struct ClearSlotsArgs { void* kcache; void* vcache; int slot0, n, Hkv, S_pad; };
+template <typename EL, int D>
+static __global__ __launch_bounds__(256) void k_draft_clear_slots(ClearSlotsArgs a) {
+    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const int f = (int)(idx % D), kh = (int)(idx / D % a.Hkv), j = (int)(idx / D / a.Hkv);
+    if (j >= a.n) return;
+    const size_t slab = (size_t)kh * a.S_pad * D * Tr<EL>::ESZ;
+    st_elem<EL>((char*)a.kcache + slab, kcache_index<EL, D>(a.slot0 + j, f), 0.f);
+    st_elem<EL>((char*)a.vcache + slab, vcache_index<EL, D>(a.slot0 + j, f), 0.f);
+}
+
 // plain fill (pad columns of activation buffers after a change of the row padding)
 static __global__ __launch_bounds__(256) void k_draft_fill(uint32_t* p, uint32_t v, size_t n) {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;

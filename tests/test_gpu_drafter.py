@@ -503,13 +503,9 @@ def test_a_value_that_is_no_number_ends_the_piece_it_lies_in(n, row, committed):
     tgt.close()
 
 
-@pytest.mark.parametrize("name", ["tiny-bf16", "tiny"])
-def test_overflow_of_an_early_rows_logits_is_reported(name):
-    """200 pairs of which the fourth alone has infinite logits, from finite states, K and V: eight units that are zero but for it, and a row
-    of the head that is 3e38 there.  Nothing behind that row shows it, so it is found only if every row of every piece goes
-    through block and head."""
-    import torch
-    s, lw, dw, tgt, dr = _make(name, 2, max_seq=300)
+def _one_token_that_overflows(s, lw, dw):
+    """Weights whose logit of token 17 is infinite, from finite states, K and V, in rows whose feature has a one at place 0: eight units that are zero
+    but for it, and a row of the head that is 3e38 there."""
     h, units = s.hidden, np.arange(8)
 
     def put(w, key, rows, row_of):
@@ -541,6 +537,69 @@ def test_overflow_of_an_early_rows_logits_is_reported(name):
     head[17] = 0
     head[17, units] = 0x7F60 if head.dtype == np.uint16 else 2.9774e38
     lw["lm_head"] = head
+
+
+@pytest.mark.parametrize("n,row,committed", [
+    (100, 70, 100),     # the 64 rows in front of the open ones have none
+    (100, 5, 64),
+    (400, 260, 384),    # a wide pass: neither has the first piece of 256
+    (400, 390, 400),
+])
+def test_pieces_in_front_of_one_that_is_no_number_end_between_key_blocks(n, row, committed):
+    """The same behind three committed pairs: a piece ends inside a block of 32 keys, whose other slots must not hold what the big pass left there."""
+    import torch
+    s, lw, dw, tgt, dr = _make("tiny-bf16", 2, max_seq=500)
+    dr.commit([1, 2, 3], torch.from_numpy(gen_features(1, 3, s.hidden)).cuda())
+    feats = gen_features(n, n, s.hidden)
+    feats[row, 5] = np.nan
+    with pytest.raises(Exception) as e:
+        dr.commit(np.arange(n), torch.from_numpy(feats).cuda())
+    assert e.value.status == -10 and dr.state()[0] == 3 + committed
+    dr.close()
+    tgt.close()
+
+
+@pytest.mark.parametrize("n,late", [(200, 195), (400, 270)])     # one pass of up to 256 rows, a wide one
+def test_what_a_failed_commit_leaves_behind_its_pairs_is_not_read(n, late):
+    """Infinite logits in the fourth pair (its K, V and states are finite) and a NaN in a later piece: the call ends with the first piece.  A caller that
+    goes on without a reset gets bit for bit what it would have got without the NaN, which lay behind the committed pairs."""
+    import torch
+    s, lw, dw, tgt, dr = _make("tiny-bf16", 2, max_seq=500)
+    from paper_2412_12639_amd.binding import FalconDrafter
+    _one_token_that_overflows(s, lw, dw)
+    tgt.init_weights(lw)
+    other = FalconDrafter(tgt, 2)
+    toks = np.random.default_rng(4).integers(0, s.vocab, n)
+    more = gen_features(5, 4, s.hidden)
+    more[:, 0] = 0.0
+    rows = []
+    for d, value in ((dr, np.nan), (other, 0.25)):
+        d.init_weights(dw)
+        feats = gen_features(4, n, s.hidden)
+        feats[:, 0] = 0.0
+        feats[3, 0] = 1.0
+        feats[late, 5] = value
+        with pytest.raises(Exception) as e:
+            d.commit(toks, torch.from_numpy(feats).cuda())
+        first = min(256, (n - 1) // 64 * 64)
+        assert e.value.status == -10 and d.state()[0] == first
+        d.commit(toks[:4], torch.from_numpy(more).cuda())
+        assert d.state() == (first + 4, 4, 4)
+        rows.append((d.rows("logits", 0, 4), d.rows("features", 0, 4)) + d.read_kv(first, 4))
+    for a, b in zip(*rows):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+    for d in (dr, other, tgt):
+        d.close()
+
+
+@pytest.mark.parametrize("name", ["tiny-bf16", "tiny"])
+def test_overflow_of_an_early_rows_logits_is_reported(name):
+    """200 pairs of which the fourth alone has infinite logits, from finite states, K and V: eight units that are zero but for it, and a row
+    of the head that is 3e38 there.  Nothing behind that row shows it, so it is found only if every row of every piece goes
+    through block and head."""
+    import torch
+    s, lw, dw, tgt, dr = _make(name, 2, max_seq=300)
+    _one_token_that_overflows(s, lw, dw)
     tgt.init_weights(lw)
     dr.init_weights(dw)
     feats = gen_features(4, 200, s.hidden)
