@@ -214,8 +214,9 @@ int launch_lstm_chain(fv_drafter* d, const ChainRows& cr, int layer) {
     a.xchg = d->at<uint16_t>(dl.off_chain + 256) + (size_t)layer * 2 * h;
     a.fault = d->at<uint32_t>(dl.off_bad) + 1; a.aborted = d->at<uint32_t>(dl.off_bad) + 2;
     a.t0 = 0; a.r0 = cr.r0; a.n = cr.n; a.from = d->state(layer) + (size_t)FV_DRAFT_STATE_COMMITTED * 2 * h; a.Tp = cr.Tp; a.h = h;
-    a.expect = (unsigned)(h / 16) + (d->chain_test ? 1u : 0u);
-    a.arrive_looks = d->chain_test ? 2u : 4000u;   // some milliseconds
+    const bool leaves = d->chain_test >= 0 && d->chain_launches > d->chain_test;
+    a.expect = (unsigned)(h / 16) + (leaves ? 1u : 0u);
+    a.arrive_looks = leaves ? 2u : 4000u;   // some milliseconds
     a.spin_limit = FV_EXCHANGE_SPINS;
     if (cr.levels) {
         const DraftPass& ps = *cr.levels;
@@ -301,7 +302,7 @@ int fv_drafter_create(fv_ctx* target, int32_t k, void* dev_arena, size_t arena_b
     }
     rc = lstm_chain_fits(target->cfg, d->chain_ok);
     if (rc) return fail(rc);
-    { const char* e = getenv("FV_EXCHANGE_TEST"); d->chain_test = e && !strcmp(e, "chain"); }
+    { const char* e = getenv("FV_EXCHANGE_TEST"); if (e && !strncmp(e, "chain", 5)) d->chain_test = e[5] == ':' ? atoi(e + 6) : 0; }
     if (hipHostMalloc((void**)&d->h_tab, (size_t)FV_DRAFT_TABLES * FV_MAX_TREE * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
     if (hipHostMalloc((void**)&d->h_out, (FV_MAX_TREE + 64) * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
     if (d->lay.wide.P && hipHostMalloc((void**)&d->h_tok, (size_t)d->lay.wide.P * 4, hipHostMallocDefault) != hipSuccess) return fail(FV_E_HIP);
@@ -454,7 +455,11 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
             hipLaunchKernelGGL(k_draft_fill, dim3(1), dim3(256), 0, st, d->at<uint32_t>(d->lay.off_bad), 0u, (size_t)3);
             HIPCHK(hipGetLastError());
             ps.chain = chains = false;
-            if (wide) break;
+            if (wide) {   // its block ran on states that are not there, which may be no numbers
+                rc = clear_slots(d, d->L, m);
+                if (rc) return rc;
+                break;
+            }
         }
         if (d->h_out[FV_MAX_TREE + 1]) { d->part_dirty = true; return FV_E_EXCHANGE_TIMEOUT; }
         float ms = 0.f;

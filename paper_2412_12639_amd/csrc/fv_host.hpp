@@ -204,7 +204,7 @@ struct fv_drafter {
     bool cache_bad = false;       // a call ended with FV_E_NONFINITE: its rows' K and V may be no numbers
     int kind_ih0 = 0, kind_hh = 0;   // GemmKind up to 64 rows
     bool chain_ok = false;           // the recurrent matrix fits on the chip (lstm_chain_fits)
-    bool chain_test = false;         // FV_EXCHANGE_TEST=chain: chain launches wait for a workgroup that does not exist, and give up
+    int chain_test = -1;             // FV_EXCHANGE_TEST=chain[:n]: chain launches behind the first n wait for a workgroup that does not exist, and give up
     int chain_launches = 0, chain_gave_up = 0;   // since creation (fv_draft_get_launches)
     int chain_rest = 0;              // calls still to be made without chain launches
     int chain_pause = 0;             // how many the last give-up asked for

@@ -18,8 +18,8 @@
  *   FV_EXCHANGE_TEST = timeout   test of the bounded wait in the direct / paired GEMM kernels: contributors leave their
  *       partial tiles unmarked and finishers give up after two looks, so every step of more than one
  *       workgroup per row group returns FV_E_EXCHANGE_TIMEOUT (every kernel still ends normally).
- *   FV_EXCHANGE_TEST = chain  test of the chain launches of the drafter's LSTM (fv_lstm_chain.hpp): they wait for one workgroup
- *       more than they have, give up, and the pass is run again as separate launches.
+ *   FV_EXCHANGE_TEST = chain[:n]   test of the chain launches of the drafter's LSTM (fv_lstm_chain.hpp): all behind the first n of a drafter
+ *       (default 0) wait for one workgroup more than they have, give up, and the pass is run again as separate launches.
  *   FV_DEBUG = 1              print the failing HIP call of an FV_E_HIP status to stderr.
  */
 #ifndef FV_INTERNAL_H

@@ -399,6 +399,64 @@ def test_give_up_makes_the_next_calls_go_without(monkeypatch):
     tgt.close()
 
 
+@pytest.mark.parametrize("n,stay", [
+    (400, 0),       # the only wide pass leaves
+    (1300, 2),      # the second of two, whose rows continue what the first left
+])
+def test_wide_pass_that_leaves(n, stay, monkeypatch):
+    """Chain launches give up in a wide pass: its rows go in pieces, and nothing of it shows in state, outputs, K and V, a tree or a further commit."""
+    import torch
+    monkeypatch.setenv("FV_EXCHANGE_TEST", f"chain:{stay}")
+    s, lw, dw, tgt, dr = _make("tiny-bf16", 3, max_seq=1400)
+    orc = do.DrafterOracle(s, lw, dw, 3, 1400)
+    parent, depth, _ = gen_tree(31, 30, [4, 2, 2, 1, 1, 1, 1, 1, 1, 1], 9)
+    rank = sibling_ranks(parent)
+    for rows in (n, 5):
+        feats = gen_features(rows, rows, s.hidden)
+        toks = np.random.default_rng(rows).integers(0, s.vocab, rows)
+        dr.commit(toks, torch.from_numpy(feats).cuda())
+        orc.commit(feats, toks)
+        assert dr.launches() == (stay + 2, 1)
+        tail = (rows - 1) % 64 + 1
+        assert dr.state() == (orc.L, tail, tail)
+        f_ref, l_ref = np.array(orc.phase["f"]), np.array(orc.phase["logits"])
+        assert _rel(dr.rows("features", 0, tail), f_ref[-tail:]) <= 2e-2 and _rel(dr.rows("logits", 0, tail), l_ref[-tail:]) <= 2e-2
+        kd, vd = dr.read_kv(0, orc.L)
+        assert _rel(kd, orc.K[:orc.L]) <= 2e-2 and _rel(vd, orc.V[:orc.L]) <= 2e-2
+        got = dr.draft_tree(parent, depth, rank, int(toks[-1]))
+        ref = orc.draft(parent, depth, rank, int(toks[-1]), force_tokens=got)
+        assert sum(got[i] != ref[i] for i in range(len(parent)) if depth[i] <= 3) <= 1
+    dr.close()
+    tgt.close()
+
+
+def test_wide_pass_that_leaves_behind_one_that_was_no_numbers(monkeypatch):
+    """A wide pass that leaves runs its block on what the wide pass before it kept as states, here NaNs; the pieces that follow end inside a block of 32
+    keys and must not read what that made of the slots behind them."""
+    import torch
+    monkeypatch.setenv("FV_EXCHANGE_TEST", "chain:6")      # two launches each: a wide pass, its first piece, three pairs
+    s, lw, dw, tgt, dr = _make("tiny-bf16", 2, max_seq=500)
+    orc = do.DrafterOracle(s, lw, dw, 2, 500)
+    bad = gen_features(1, 400, s.hidden)
+    bad[5, 5] = np.nan
+    with pytest.raises(Exception) as e:
+        dr.commit(np.arange(400), torch.from_numpy(bad).cuda())
+    assert e.value.status == -10 and dr.launches() == (4, 0)
+    dr.reset()
+    for n in (3, 400):
+        feats = gen_features(n, n, s.hidden)
+        toks = np.random.default_rng(n).integers(0, s.vocab, n)
+        dr.commit(toks, torch.from_numpy(feats).cuda())
+        orc.commit(feats, toks)
+    assert dr.launches() == (8, 1) and dr.state() == (403, 16, 16)
+    f_ref, l_ref = np.array(orc.phase["f"]), np.array(orc.phase["logits"])
+    assert _rel(dr.rows("features", 0, 16), f_ref[-16:]) <= 2e-2 and _rel(dr.rows("logits", 0, 16), l_ref[-16:]) <= 2e-2
+    kd, vd = dr.read_kv(0, 403)
+    assert _rel(kd, orc.K[:403]) <= 2e-2 and _rel(vd, orc.V[:403]) <= 2e-2
+    dr.close()
+    tgt.close()
+
+
 def test_long_bf16_commit_in_wide_pieces():
     """300 pairs: 256 rows in one piece (the ring GEMM and the chain launch over 256 rows), then the 44 that stay open."""
     import torch
