@@ -609,6 +609,8 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
         // a launch over several levels left because its workgroups were not on the chip together: the tree once more without
         hipLaunchKernelGGL(k_draft_fill, dim3(1), dim3(256), 0, st, d->at<uint32_t>(d->lay.off_bad), 0u, (size_t)3);
         HIPCHK(hipGetLastError());
+        rc = clear_slots(d, d->L0 + d->n_chain, next_row - d->n_chain);   // (its passes ran on what the ones before had left of their inputs)
+        if (rc) return rc;
         any_chain = false;
         for (DraftPass& ps : passes) ps.chain = false;
     }

@@ -457,6 +457,39 @@ def test_wide_pass_that_leaves_behind_one_that_was_no_numbers(monkeypatch):
     tgt.close()
 
 
+def test_tree_that_leaves_behind_a_commit_that_was_no_numbers(monkeypatch):
+    """Tree passes of 20 rows whose level launches leave run their block on what is left of the residual stream, here a failed commit's NaNs in rows that
+    the commit behind it (of fewer rows) did not write.  The passes run again and must not read what that made of the later passes' slots."""
+    import torch
+    monkeypatch.setenv("FV_EXCHANGE_TEST", "chain:4")      # two launches each: the failed commit, four pairs
+    s, lw, dw, tgt, dr = _make("tiny-bf16", 4, max_seq=300)
+    orc = do.DrafterOracle(s, lw, dw, 4, 300)
+    bad = gen_features(1, 20, s.hidden)
+    bad[0, 5] = np.nan
+    with pytest.raises(Exception) as e:
+        dr.commit(np.arange(20), torch.from_numpy(bad).cuda())
+    assert e.value.status == -10
+    dr.reset()
+    feats = gen_features(2, 4, s.hidden)
+    toks = np.random.default_rng(2).integers(0, s.vocab, 4)
+    dr.commit(toks, torch.from_numpy(feats).cuda())
+    orc.commit(feats, toks)
+    assert dr.launches() == (4, 0)
+    parent, depth = [-1], [0]                               # five paths of twelve nodes
+    for _ in range(5):
+        for j in range(12):
+            parent.append(len(parent) - 1 if j else 0)
+            depth.append(j + 1)
+    parent, depth = np.array(parent), np.array(depth)
+    rank = sibling_ranks(parent)
+    got = dr.draft_tree(parent, depth, rank, int(toks[-1]))
+    assert dr.launches()[1] == 1
+    orc.draft(parent, depth, rank, int(toks[-1]), force_tokens=got)
+    _check_phase(s, dr, orc, 4, got, parent, depth, rank, 2e-2)
+    dr.close()
+    tgt.close()
+
+
 def test_long_bf16_commit_in_wide_pieces():
     """300 pairs: 256 rows in one piece (the ring GEMM and the chain launch over 256 rows), then the 44 that stay open."""
     import torch
