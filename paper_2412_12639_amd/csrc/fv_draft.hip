@@ -145,6 +145,14 @@ int clear_slots(fv_drafter* d, int slot0, int n) {
     return FV_OK;
 }
 
+// The first n error words (not finite, exchange fault, launches that left) to zero.  On the drafter's stream like all that sets them: the null stream's
+// own fill is not ordered against a stream that does not wait for it, and the host does not wait for either.
+int clear_errors(fv_drafter* d, size_t n) {
+    hipLaunchKernelGGL(k_draft_fill, dim3(1), dim3(256), 0, d->core->stream, d->at<uint32_t>(d->lay.off_bad), 0u, n);
+    HIPCHK(hipGetLastError());
+    return FV_OK;
+}
+
 int32_t* htab(fv_drafter* d, int which) { return d->h_tab + (size_t)which * FV_MAX_TREE; }
 
 int upload_tables(fv_drafter* d) {
@@ -452,8 +460,8 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
             HIPCHK(hipStreamSynchronize(st));
             if (took_chain) d->chain_outcome(d->h_out[FV_MAX_TREE + 2]);
             if (!took_chain || !d->h_out[FV_MAX_TREE + 2] || d->h_out[FV_MAX_TREE + 1]) break;
-            hipLaunchKernelGGL(k_draft_fill, dim3(1), dim3(256), 0, st, d->at<uint32_t>(d->lay.off_bad), 0u, (size_t)3);
-            HIPCHK(hipGetLastError());
+            rc = clear_errors(d, 3);
+            if (rc) return rc;
             ps.chain = chains = false;
             if (wide) {   // its block ran on states that are not there, which may be no numbers
                 rc = clear_slots(d, d->L, m);
@@ -467,7 +475,8 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
         total_ms += ms;
         if (wide && !chains) { hist_done = true; continue; }   // the launches left: the same rows again, without them
         if (cut && d->h_out[FV_MAX_TREE]) {                    // not finite somewhere: which piece, and what stands before it, the small pieces say
-            HIPCHK(hipMemset(d->at<int32_t>(d->lay.off_bad), 0, 4));
+            rc = clear_errors(d, 1);
+            if (rc) return rc;
             rc = clear_slots(d, d->L, m);
             if (rc) return rc;
             merge = false; hist_done = true;
@@ -482,7 +491,8 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
         done += m;
         if (d->h_out[FV_MAX_TREE]) {
             d->cache_bad = true;
-            HIPCHK(hipMemset(d->at<int32_t>(d->lay.off_bad), 0, 4));
+            rc = clear_errors(d, 1);
+            if (rc) return rc;
             return FV_E_NONFINITE;
         }
     }
@@ -607,8 +617,8 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
         if (any_chain) d->chain_outcome(d->h_out[FV_MAX_TREE + 2]);
         if (!any_chain || !d->h_out[FV_MAX_TREE + 2] || d->h_out[FV_MAX_TREE + 1]) break;
         // a launch over several levels left because its workgroups were not on the chip together: the tree once more without
-        hipLaunchKernelGGL(k_draft_fill, dim3(1), dim3(256), 0, st, d->at<uint32_t>(d->lay.off_bad), 0u, (size_t)3);
-        HIPCHK(hipGetLastError());
+        rc = clear_errors(d, 3);
+        if (rc) return rc;
         rc = clear_slots(d, d->L0 + d->n_chain, next_row - d->n_chain);   // (its passes ran on what the ones before had left of their inputs)
         if (rc) return rc;
         any_chain = false;
@@ -619,7 +629,8 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
     d->n_rows = next_row;
     if (d->h_out[FV_MAX_TREE]) {
         d->cache_bad = true;
-        HIPCHK(hipMemset(d->at<int32_t>(d->lay.off_bad), 0, 4));
+        rc = clear_errors(d, 1);
+        if (rc) return rc;
         return FV_E_NONFINITE;
     }
     d->h_out[0] = root_token;

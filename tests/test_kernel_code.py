@@ -123,3 +123,10 @@ def test_the_look_finds_what_it_is_for():
     assert len(smfmac_faults([l for l in ok if l != "s_nop 1"])[1]) == 2
     assert len(smfmac_faults(ok[:3] + ["v_mov_b32_e32 v30, v2"] + ok[3:])[1]) == 1
     assert len(smfmac_faults(ok[:6] + ok[8:])[1]) == 1
+
+
+def test_no_fill_runs_on_the_null_stream():
+    """The library's work is ordered by the caller's stream, which need not wait for the null stream: a hipMemset there can fall before or behind it."""
+    for name in sorted(os.listdir(build.CSRC)):
+        text = re.sub(r"//.*", "", open(os.path.join(build.CSRC, name)).read())
+        assert not re.search(r"\bhipMemset\s*\(", text), name
