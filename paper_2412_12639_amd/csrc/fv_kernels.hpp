@@ -1367,6 +1367,29 @@ __device__ __forceinline__ int argmax_row(const float* row, int V) {
     return any ? -1 : bi;
 }
 
+// Whether this thread's share of a row holds a NaN or an infinity (the sum of zeros of argmax_row)
+template <int NT>
+__device__ __forceinline__ bool row_has_non_finite(const float* row, int V) {
+    float zero = 0.f;
+    for (int v0 = threadIdx.x * 4; v0 < V; v0 += 8 * NT * 4) {
+        float4 x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int v = v0 + k * NT * 4;
+            x[k] = (v < V) ? *(const float4*)(row + v) : make_float4(0.f, 0.f, 0.f, 0.f);
+            if (v + 1 >= V) x[k].y = 0.f;
+            if (v + 2 >= V) x[k].z = 0.f;
+            if (v + 3 >= V) x[k].w = 0.f;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            zero = fmaf(x[k].x, 0.f, zero); zero = fmaf(x[k].y, 0.f, zero);
+            zero = fmaf(x[k].z, 0.f, zero); zero = fmaf(x[k].w, 0.f, zero);
+        }
+    }
+    return !(zero == 0.f);
+}
+
 template <int NT>
 static __global__ __launch_bounds__(NT) void k_argmax(ArgmaxArgs a) {
     const int best = argmax_row<NT>(a.logits + (size_t)blockIdx.x * a.Vpad, a.V);
@@ -1918,7 +1941,10 @@ __device__ __forceinline__ void finish_feature(const FinishArgs& a, int t, int b
 template <int NT>
 static __global__ __launch_bounds__(NT) void k_finish_one(ArgmaxArgs am, FinishArgs a) {
     __shared__ float red[256];
-    if (blockIdx.x == 1) { finish_feature<NT>(a, 0, 0, red); return; }
+    if (blockIdx.x == 1) {   // a step without a choice leaves the features of the step before
+        if (!__syncthreads_or(row_has_non_finite<NT>(am.logits, am.V))) finish_feature<NT>(a, 0, 0, red);
+        return;
+    }
     const int best = argmax_row<NT>(am.logits, am.V);
     if (threadIdx.x == 0) {
         am.am[0] = best;

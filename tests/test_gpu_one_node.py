@@ -20,6 +20,23 @@ def _session(vocab, dtype, edit=None):
     return s, w, g
 
 
+def _overflows_behind(root, s, w, token, nan):
+    """The same weights but for the logit of `token`, which is infinite, or the difference of two infinities, in a node of token `root` and finite in all
+    others: units that are zero but for the root's embedding, and 3e38 in the head there."""
+    units = np.r_[0:8, 128:136]      # the two halves of the head's K range
+    one, big = (0x3F80, 0x7F60) if s.dtype == "bf16" else (1.0, 2.9774e38)
+    w = dict(w, embed=w["embed"].copy(), lm_head=w["lm_head"].copy())
+    w["embed"][:, units] = 0
+    w["embed"][root, units] = one
+    for name in [n for n in w if n.split(".")[-1] in ("wo", "wd")]:
+        w[name] = w[name].copy()
+        w[name][units] = 0
+    w["lm_head"][token] = 0
+    w["lm_head"][token, units[:8]] = big
+    w["lm_head"][token, units[8:]] = (big | 0x8000 if s.dtype == "bf16" else -big) if nan else 0
+    return w
+
+
 def _f32(a):
     return a if a.dtype == np.float32 else (a.astype(np.uint32) << 16).view(np.float32)
 
@@ -92,4 +109,31 @@ def test_no_choice_in_the_step_itself(vocab, token):
     g.rollback(9, 1)
     a, _, nxt = g.verify_tree([1], [-1], [0])
     assert a == 0 and nxt == int(np.argmax(g.logits(1)[0]))
+    g.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vocab,token", [(1000, 999), (8192, 0), (8193, 8192), (32001, 32000), (32768, 5), (32771, 32770)])
+def test_features_stay_where_there_is_no_choice(vocab, token, dtype):
+    """Features that a step exported are the last choice's until the next choice, as behind steps of more nodes."""
+    import paper_2412_12639_amd as fv
+    s, w, g = _session(vocab, dtype)
+    for nan in (False, True):
+        g.init_weights(_overflows_behind(7, s, w, token, nan))
+        g.prefill(fi.gen_prefix(1, 9, s.vocab) % 4)
+        g.rollback(9, 3)
+        g.verify_tree([3], [-1], [0])
+        at = fv.features_device_ptr(g) - g.arena.data_ptr()
+        before = g.features(1)[0].copy()
+        g.rollback(9, 7)
+        with pytest.raises(Exception) as e:
+            g.verify_tree([7], [-1], [0])
+        assert e.value.status == -10
+        assert np.array_equal(g.arena[at:at + 4 * s.hidden].cpu().numpy().view(np.float32), before)
+        logits = g.logits(1)[0]
+        assert np.isnan(logits[token]) if nan else np.isinf(logits[token])
+        assert np.isfinite(np.delete(logits, token)).all()
+        g.rollback(9, 3)
+        g.verify_tree([3], [-1], [0])
+        assert np.array_equal(g.features(1)[0], before)
     g.close()
