@@ -81,16 +81,16 @@ def test_equal_largest_logits(vocab):
 
 
 @pytest.mark.parametrize("vocab,token", [(1000, 999), (8193, 8192), (32001, 0), (32771, 32770)])
-@pytest.mark.parametrize("bits", [0x7F7F, 0x7FC0])     # a product that overflows, a NaN
-def test_no_choice(vocab, token, bits):
-    def edit(head):
-        head[token] = bits
-        return head
-    s, w, g = _session(vocab, "bf16", edit)
+@pytest.mark.parametrize("nan", [False, True])     # a product that overflows, a NaN
+def test_no_choice(vocab, token, nan):
+    """One logit of the node is no number; the prompt before it has choices throughout."""
+    s, w, g = _session(vocab, "bf16")
+    g.init_weights(_overflows_behind(7, s, w, token, nan))
+    g.prefill(fi.gen_prefix(1, 9, s.vocab) % 4)
+    g.rollback(9, 7)
     with pytest.raises(Exception) as e:
-        root = g.prefill(fi.gen_prefix(1, 9, s.vocab))
-        g.verify_tree([root], [-1], [0])
-    assert e.value.status == -10
+        g.verify_tree([7], [-1], [0])
+    assert e.value.status == -10 and g.argmax(1)[0] == -1 and g.state() == (9, 7)
     g.close()
 
 
