@@ -438,6 +438,7 @@ int fv_create_ex(const fv_cfg* cfg, void* dev_arena, size_t arena_bytes, void* h
         }
     }
     { const char* e = getenv("FV_GEMM_FIX"); c->gemm_fix = e ? atoi(e) : 1; }
+    { const char* e = getenv("FV_GEMM_SMALL"); c->gemm_small = !(e && !strcmp(e, "0")); }
     { const char* e = getenv("FV_ATTN"); c->attn_canon = e && !strcmp(e, "invariant"); }
     { const char* e = getenv("FV_EXCHANGE_TEST"); c->exchange_test = e && !strcmp(e, "timeout"); }
     auto fail = [&](int code) { fv_destroy(c); return code; };

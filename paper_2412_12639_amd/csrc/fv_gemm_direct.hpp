@@ -409,7 +409,7 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
                     if (c0 + 1 == c_last) add_tiles(Tiles<2>{}, c0);
                     else if (c0 == c_last) add_tiles(Tiles<1>{}, c0);
                 }
-                if (mine_out) gemm_epilogue<EL, D, EPI>(a, Tp, strip, tb_, lane, r, rinv_lds, pre, have_pre);
+                if (mine_out) gemm_epilogue<EL, D, EPI, true>(a, Tp, strip, tb_, lane, r, rinv_lds, pre, have_pre);
             }
         }
     };

@@ -93,6 +93,7 @@ struct fv_ctx {
     Layout lay;
     StepScratch scr_arena;        // inside the caller's arena
     bool arena_part_dirty = false;
+    bool gemm_small = true;       // FV_GEMM_SMALL=0: small matrices go to the direct kernel like the others
     bool exchange_test = false;   // FV_EXCHANGE_TEST=timeout: contributors leave their partial tiles unmarked, finishers give up after two looks
     StepScratch scr_static;       // inside the library's static device array (steps of up to 64 rows); part == nullptr: does not fit
     const StepScratch* scr = nullptr;   // the one the next step uses

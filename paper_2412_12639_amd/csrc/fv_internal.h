@@ -14,6 +14,7 @@
  *   FV_GEMM_FIX = 0           steps of more than 64 rows with the LDS-shared-activation kernel: let the last workgroup to arrive reduce a row
  *       group's partial tiles inside the GEMM launch (default: a second launch reduces them, one
  *       wavefront per tile, for the QKV, O and down projections).
+ *   FV_GEMM_SMALL = 0         small matrices go to the direct kernel instead of the forms of their own (fv_gemm_small.hpp).  The same bits.
  *   FV_ATTN = invariant       contexts start with step-invariant rows switched on (fv_set_step_invariant(ctx, 1)).
  *   FV_EXCHANGE_TEST = timeout   test of the bounded wait in the direct / paired GEMM kernels: contributors leave their
  *       partial tiles unmarked and finishers give up after two looks, so every step of more than one

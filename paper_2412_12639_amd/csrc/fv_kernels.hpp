@@ -330,7 +330,8 @@ __device__ __forceinline__ bool rope_preload(const GemmArgs& a, int strip, int t
     return true;
 }
 
-// IN_ORDER: the squares are added in the order that the direct and paired kernels compile to, written out, where the compiler picks another one.
+// IN_ORDER: the squares are added in a written order, not in one that the compiler picks for each kernel.  The direct, paired and small forms have it: steps of up
+// to 64 rows take one or another by their row count, and a node's bits must not depend on that.
 template <typename EL, int D, int EPI, bool IN_ORDER = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int Tp, int strip, int tb, int lane, float (&acc)[16],
                                               const float* rinv_lds, const EpiPre& pre, bool have_pre) {

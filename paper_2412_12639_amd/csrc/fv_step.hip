@@ -57,12 +57,12 @@ int launch_gemm_t(fv_ctx* c, const GemmArgs& ga0) {
 // Small matrices, in the order of sums that the direct form's plan gives (fv_gemm_small.hpp)
 template <typename EL, int TB, int D, int EPI>
 int launch_gemm_direct_t(fv_ctx* c, const GemmArgs& ga) {
-    if (ga.aligned && ga.G == ga.NG && ga.NB <= FV_SMALL_NB && ga.n_ssq <= 32) {
+    if (c->gemm_small && ga.aligned && ga.G == ga.NG && ga.NB <= FV_SMALL_NB && ga.n_ssq <= 32) {
         hipLaunchKernelGGL((k_gemm_small<EL, TB, D, EPI>), dim3(ga.NG), dim3(256), 0, c->stream, ga);
         return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
     }
     if constexpr (TB == 1 && EPI == EPI_RESID) {
-        if (!ga.aligned && ga.NB > FV_SMALL_NB && ga.NB <= FV_SMALL_SPLIT_NB && ga.per <= 2 && !c->exchange_test) {
+        if (c->gemm_small && !ga.aligned && ga.NB > FV_SMALL_NB && ga.NB <= FV_SMALL_SPLIT_NB && ga.per <= 2 && !c->exchange_test) {
             hipLaunchKernelGGL((k_gemm_small_split<EL, D>), dim3(ga.NG), dim3(64 * ga.NB), (size_t)ga.NB * 4096, c->stream, ga);
             return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
         }
