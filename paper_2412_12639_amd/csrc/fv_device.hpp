@@ -133,6 +133,23 @@ __device__ __forceinline__ void handoff_acquire() { __builtin_amdgcn_fence(__ATO
 __device__ __forceinline__ void st_u64(void* p, uint64_t v) { *(uint64_t*)p = v; }
 __device__ __forceinline__ void st_f32(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st_f4(float4* p, float4 v) { *p = v; }
+template <int N> struct Const { static constexpr int value = N; };   // a constant as a type
+
+// A wavefront's largest value, in every lane: within rows of 16 by moves across lanes, then rows and halves exchanged
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, dpp_move<0xB1>(v));    // quad_perm [1, 0, 3, 2]
+    v = fmaxf(v, dpp_move<0x4E>(v));    // quad_perm [2, 3, 0, 1]
+    v = fmaxf(v, dpp_move<0x141>(v));   // row_half_mirror
+    v = fmaxf(v, dpp_move<0x140>(v));   // row_mirror
+    const auto rows = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    v = fmaxf(__builtin_bit_cast(float, (unsigned)rows[0]), __builtin_bit_cast(float, (unsigned)rows[1]));
+    const auto halves = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    return fmaxf(__builtin_bit_cast(float, (unsigned)halves[0]), __builtin_bit_cast(float, (unsigned)halves[1]));
+}
+
 // one cache element (bf16 or fp32)
 template <typename EL> __device__ __forceinline__ void st_elem(void* p, size_t i, float v) { Tr<EL>::store(p, i, v); }
 

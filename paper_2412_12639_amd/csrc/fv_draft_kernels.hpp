@@ -251,8 +251,6 @@ __device__ __forceinline__ void draft_out_row(const DraftOutArgs& a, int t) {
         ((float4*)(a.fout + (size_t)(a.r0 + t) * a.h))[q] = ((const float4*)a.x)[(size_t)q * a.Tp + t];
 }
 
-template <int N> struct Const { static constexpr int value = N; };   // a constant as a type
-
 // Top-m of one row of logits: descending value, lower token id first among equals (a total order, so
 // the result is unique).  One workgroup of 1024 threads per row; a thread keeps 32 values in registers
 // (vocabulary <= 32768).  The second best of every wavefront's 64 per-thread bests gives 32 values that
@@ -294,19 +292,6 @@ __device__ __forceinline__ unsigned long long topm_wave_max(unsigned long long k
     return k;
 }
 
-// the same of a float in every lane: within rows of 16 by moves across lanes, then rows and halves exchanged
-__device__ __forceinline__ float topm_wave_max(float v) {
-    auto dpp = [](float x, auto ctrl) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, x), __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, false)); };
-    v = fmaxf(v, dpp(v, Const<0xB1>{}));    // quad_perm [1, 0, 3, 2]
-    v = fmaxf(v, dpp(v, Const<0x4E>{}));    // quad_perm [2, 3, 0, 1]
-    v = fmaxf(v, dpp(v, Const<0x141>{}));   // row_half_mirror
-    v = fmaxf(v, dpp(v, Const<0x140>{}));   // row_mirror
-    const auto rows = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
-    v = fmaxf(__builtin_bit_cast(float, (unsigned)rows[0]), __builtin_bit_cast(float, (unsigned)rows[1]));
-    const auto halves = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
-    return fmaxf(__builtin_bit_cast(float, (unsigned)halves[0]), __builtin_bit_cast(float, (unsigned)halves[1]));
-}
-
 // (workgroups n .. 2n-1 write the predicted feature rows, which wait for nothing the top lists do)
 static __global__ __launch_bounds__(FV_TOPM_THREADS) void k_topm(TopmArgs a, DraftOutArgs oa) {
     if (a.gate && (a.gate[0] || a.gate[2])) return;
@@ -339,9 +324,9 @@ static __global__ __launch_bounds__(FV_TOPM_THREADS) void k_topm(TopmArgs a, Dra
     }
     const bool bad = !(zero == 0.f);
     // the wavefront's best and second best of its 64 thread bests
-    const float w1 = topm_wave_max(bv);
+    const float w1 = wave_max(bv);
     const unsigned long long at1 = __ballot(bv == w1);
-    const float w2 = topm_wave_max((at1 != 0ull && (tid & 63) == __ffsll((long long)at1) - 1) ? -FLT_MAX : bv);
+    const float w2 = wave_max((at1 != 0ull && (tid & 63) == __ffsll((long long)at1) - 1) ? -FLT_MAX : bv);
     if ((tid & 63) == 0) wave_best[wave] = w2;
     if (__any(bad) && (tid & 63) == 0) any_bad = 1;   // written before the barrier, read after it (only ever set to 1)
     __syncthreads();

@@ -85,29 +85,20 @@ int run_draft_wide(fv_drafter* d, const float* ext, int m, int keep) {
             hipLaunchKernelGGL(k_ingest_prompt, dim3(ld / 4 + pad_blocks(pa)), dim3(256), 0, st, ia, pa);
             HIPCHK(hipGetLastError());
         }
-        auto args = [&](const GemmPlan& p, const void* Wt, size_t x_off) {
-            GemmArgs ga;
-            memset(&ga, 0, sizeof(ga));
-            ga.Wt = (const uint4*)Wt; ga.X = (const uint4*)at(x_off); ga.NG = p.NG; ga.NB = p.NB; ga.T = m; ga.ld = ld; ga.n_strips = p.n_strips;
-            ga.rinv_out = (float*)at(w.ones);
-            return ga;
-        };
-        auto grid = [&](const GemmArgs& ga) { return dim3(8u * (unsigned)std::min((ga.NG + 7) / 8 * (ld / 256), 32)); };   // one workgroup per compute unit at most
-        auto rinv = [&]() -> int {
-            RinvArgs ra;
-            ra.ssq = (const float*)at(w.ssq); ra.rinv = (float*)at(w.rinv); ra.n_ssq = h / 32; ra.ld = ld; ra.inv_h = 1.f / (float)h; ra.eps = cf.rms_eps;
-            hipLaunchKernelGGL(k_rinv, dim3(ld / 64), dim3(256), 0, st, ra);
-            HIPCHK(hipGetLastError());
-            return FV_OK;
-        };
+        ManyRows rows;
+        rows.m = m; rows.ld = ld; rows.L = d->L;
+        rows.x = (float*)at(w.x); rows.ssq = (float*)at(w.ssq); rows.rinv = (float*)at(w.rinv);
+        rows.xb = at(w.xb); rows.q = at(w.q); rows.qlo = at(w.qlo); rows.attn = at(w.attn); rows.act = at(w.act);
+        rows.mask = (const uint64_t*)at(w.mask); rows.rope = (const float2*)at(w.rope);
+        float* const ones = (float*)at(w.ones);
         for (int layer = 0; layer < 2; ++layer) {
-            GemmArgs ga = args(layer == 0 ? dl.ih0.gm : dl.hh.gm, d->arena + dl.off_w[2 * layer], layer == 0 ? w.xz : w.xh);
+            GemmArgs ga = many_args(rows, layer == 0 ? dl.ih0.gm : dl.hh.gm, d->arena + dl.off_w[2 * layer], at(layer == 0 ? w.xz : w.xh), ones);
             ga.logits = (float*)at(w.gin); ga.Vpad = 4 * h;
-            hipLaunchKernelGGL((k_gemm_commit<D, EPI_LOGITS>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
+            hipLaunchKernelGGL((k_gemm_commit<D, EPI_LOGITS>), many_grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
             HIPCHK(hipGetLastError());
             ChainRows cr;
             cr.n = m; cr.Tp = ld; cr.r0 = 0; cr.g_in = (const float*)at(w.gin); cr.state = (float*)at(w.state[layer]); cr.xnext = layer == 0 ? at(w.xh) : nullptr;
-            int rc = launch_lstm_chain(d, cr, layer);
+            const int rc = launch_lstm_chain(d, cr, layer);
             if (rc) return rc;
         }
         LstmOutArgs oa;
@@ -116,52 +107,13 @@ int run_draft_wide(fv_drafter* d, const float* ext, int m, int keep) {
         hipLaunchKernelGGL((k_lstm_out<EL>), dim3((unsigned)(((size_t)(h / 4) * ld + 255) / 256)), dim3(256), 0, st, oa);
         HIPCHK(hipGetLastError());
 
-        // the decoder block
-        int rc = rinv();
+        const int rc = run_many_layer<EL, D>(c, rows, 0, false, d->at<float>(dl.off_ones));   // the decoder block
         if (rc) return rc;
         {
-            GemmArgs ga = args(ly.gm[GM_QKV], c->layer_w(0, 0), w.xb);
-            ga.rinv_out = (float*)at(w.rinv);
-            ga.q_out = at(w.q); ga.q_lo_out = at(w.qlo); ga.kcache = c->kc(0); ga.vcache = c->vc(0);
-            ga.rope_cs = (const float2*)at(w.rope); ga.Hq = cf.n_q_heads; ga.Hkv = cf.n_kv_heads; ga.L = d->L; ga.S_pad = ly.S_pad;
-            hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_QKV, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
-            HIPCHK(hipGetLastError());
-        }
-        {
-            AttnArgs aa;
-            aa.q = (const uint4*)at(w.q); aa.q_lo = (const uint4*)at(w.qlo); aa.kc = (const uint4*)c->kc(0); aa.vc = (const uint4*)c->vc(0);
-            aa.out = at(w.attn); aa.mask = (const uint64_t*)at(w.mask);
-            aa.Tp = 256; aa.ld = ld; aa.pieces = ld / 256; aa.T = m; aa.TK = m; aa.L = d->L; aa.Hq = cf.n_q_heads; aa.Hkv = cf.n_kv_heads; aa.S_pad = ly.S_pad;
-            aa.scale = 1.f / std::sqrt((float)D);
-            aa.ks = 1; aa.part = nullptr; aa.tickets = nullptr;
-            rc = launch_attn<EL, D>(aa, cf.n_q_heads * 8, ld / 256, st);
-            if (rc) return rc;
-        }
-        auto resid = [&](int which, int wi, size_t x_off, const float* gain_next) -> int {
-            GemmArgs ga = args(ly.gm[which], c->layer_w(0, wi), x_off);
-            ga.x_in = ga.x = (float*)at(w.x); ga.xb = at(w.xb); ga.gain_next = gain_next; ga.ssq_out = (float*)at(w.ssq);
-            hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_RESID, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
-            HIPCHK(hipGetLastError());
-            return FV_OK;
-        };
-        rc = resid(GM_O, 1, w.attn, c->gain(1));
-        if (rc) return rc;
-        rc = rinv();
-        if (rc) return rc;
-        {
-            GemmArgs ga = args(ly.gm[GM_GU], c->layer_w(0, 2), w.xb);
-            ga.rinv_out = (float*)at(w.rinv);
-            ga.act = at(w.act);
-            hipLaunchKernelGGL((k_gemm_ring<8, D, EPI_SWIGLU, true>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
-            HIPCHK(hipGetLastError());
-        }
-        rc = resid(GM_DN, 3, w.act, d->at<float>(dl.off_ones));
-        if (rc) return rc;
-        {
-            GemmArgs ga = args(ly.gm[GM_LM], d->target->arena + d->target->lay.off_lm, w.xb);
+            GemmArgs ga = many_args(rows, ly.gm[GM_LM], d->target->arena + d->target->lay.off_lm, rows.xb, ones);
             ga.logits = d->at<float>(dl.off_logits); ga.Vpad = ly.Vpad;
             ga.L = first; ga.Hq = n_hist; ga.Hkv = cf.vocab; ga.tickets = d->at<int>(dl.off_bad);   // see EPI_HEAD
-            hipLaunchKernelGGL((k_gemm_commit<D, EPI_HEAD>), grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
+            hipLaunchKernelGGL((k_gemm_commit<D, EPI_HEAD>), many_grid(ga), dim3(FV_RING_THREADS), ring_smem(8), st, ga);
             HIPCHK(hipGetLastError());
         }
         TopmArgs ta;

@@ -44,8 +44,6 @@
 #define FV_DIRECT_SMEM_FLOATS(TB) ((2 * FV_STREAMERS + FV_PARK) * (TB) * 1024 + (TB) * 32 + 1024 + 4)
 #define FV_PAIRED_SMEM_FLOATS(TB) ((2 * FV_STREAMERS + FV_PARK) * 2 * (TB) * 1024 + (TB) * 32 + 1024 + 4)
 
-template <int N> struct Tiles { static constexpr int value = N; };
-
 // This workgroup's range of the (row group, K stage) space and this wavefront's slices of it.
 struct DPlan {
     int u0, u1, g0, nseg, NB, wave;
@@ -403,11 +401,11 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
                 };
                 int c0 = c_first + 1;   // ascending order
                 if constexpr (RS == 1) {
-                    for (; c0 <= c_last; c0 += 4) add_tiles(Tiles<4>{}, c0);
+                    for (; c0 <= c_last; c0 += 4) add_tiles(Const<4>{}, c0);
                 } else {
-                    for (; c0 + 2 <= c_last; c0 += 3) add_tiles(Tiles<3>{}, c0);
-                    if (c0 + 1 == c_last) add_tiles(Tiles<2>{}, c0);
-                    else if (c0 == c_last) add_tiles(Tiles<1>{}, c0);
+                    for (; c0 + 2 <= c_last; c0 += 3) add_tiles(Const<3>{}, c0);
+                    if (c0 + 1 == c_last) add_tiles(Const<2>{}, c0);
+                    else if (c0 == c_last) add_tiles(Const<1>{}, c0);
                 }
                 if (mine_out) gemm_epilogue<EL, D, EPI, true>(a, Tp, strip, tb_, lane, r, rinv_lds, pre, have_pre);
             }

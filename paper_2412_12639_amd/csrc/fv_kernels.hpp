@@ -1261,21 +1261,6 @@ __device__ __forceinline__ void argmax_combine(float& v, int& i, float ov, int o
     if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
 }
 
-// A wavefront's largest value, in every lane: within rows of 16 by moves across lanes, then rows and halves exchanged
-template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float wave_max(float v) {
-    v = fmaxf(v, dpp_move<0xB1>(v));    // quad_perm [1, 0, 3, 2]
-    v = fmaxf(v, dpp_move<0x4E>(v));    // quad_perm [2, 3, 0, 1]
-    v = fmaxf(v, dpp_move<0x141>(v));   // row_half_mirror
-    v = fmaxf(v, dpp_move<0x140>(v));   // row_mirror
-    const auto rows = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
-    v = fmaxf(__builtin_bit_cast(float, (unsigned)rows[0]), __builtin_bit_cast(float, (unsigned)rows[1]));
-    const auto halves = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
-    return fmaxf(__builtin_bit_cast(float, (unsigned)halves[0]), __builtin_bit_cast(float, (unsigned)halves[1]));
-}
-
 // The greedy choice of one row, in thread 0; -1 if it has none.  NT threads: a row of 32000 values took 256 threads four rounds of requests (13 us for a
 // single row), 1024 take one.  A row that they hold at once is asked for its largest value first and for the first place that has it then: one
 // maximum and one addition a value (of zeros, which a NaN or an infinity turns into a NaN), where value and place together took five instructions and two trips
