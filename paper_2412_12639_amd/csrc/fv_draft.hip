@@ -384,7 +384,11 @@ int fv_draft_commit(fv_drafter* d, const int32_t* tokens, const float* dev_featu
     for (int done = 0; done < n;) {
         // What stays open as the phase's chain are the last 1 to 64 rows (so that a tree has room for its own).  fp32: pieces of 64 rows, of which those
         // are the last.  bf16: up to 256 rows go in one pass, open ones included (65 to 256 rows at the 7B width: a pass of up to 256
-        // rows 430 us and another of up to 64 rows 390 before), more than 256 in wide passes of up to 1024 (fv_draft_wide.hpp).  Where that came to
+        // rows 430 us and another of up to 64 rows 390 before), more than 256 in wide passes of up to 1024 (fv_draft_wide.hpp).  Both sides of that line, device us
+        // of the call at hidden 256 / 1024 / 2048 / 4096, the passes that it takes first: 100 rows 350 / 419 / 503 / 762 against 379 / 468 / 658 / 1024 in a wide
+        // one (which multiplies 256 columns in tiles that leave compute units idle), 256 rows 757 / 876 / 1039 / 1493 against 771 / 895 / 1123 / 1642; 257 rows
+        // 774 / 869 / 1111 / 1732 wide against 885 / 985 / 1209 / 1792 as 256 and one, 300 rows 883 / 981 / 1237 / 1897 against 992 / 1099 / 1334 / 1980, 512 rows
+        // 1411 / 1538 / 1841 / 2707 against 1513 / 1676 / 2012 / 2949.  Where a pass came to
         // nothing -- a chain launch that left, a value that is no number, which is reported with the piece it lies in -- the call goes on with
         // pieces of 256 rows and the open ones by themselves.
         const int left = n - done, tail = (n - 1) % 64 + 1, front = left - tail;
@@ -572,7 +576,9 @@ int fv_draft_tree(fv_drafter* d, const int32_t* parent, const int32_t* depth, co
             for (int t : by_level[j]) t_lvl[lvl_at++] = t;
         }
         // Levels of up to 16 rows each in one launch per layer (a level's rows are a subset of the blocks of the level
-        // before, so the counts never grow, which the kernel's exchange relies on).
+        // before, so the counts never grow, which the kernel's exchange relies on).  One level too: k = 1 and a tree of 30 nodes (five passes of a level
+        // each) 249 us of device time against 398 as separate launches at hidden 256, 270 / 423 at 512, 353 / 458 at 1024, 673 / 731 at 2048, 863 / 874 at 2560, 1187 / 1220 at
+        // 3584, and 1369 to 1384 / 1372 at 4096, where both are the read of the matrix.
         ps.chain = d->chain_ok && ps.lvl_n.size() >= 1 && ps.lvl_n.size() <= FV_DRAFT_KMAX;
         for (size_t j = 0; j < ps.lvl_n.size(); ++j) ps.chain = ps.chain && ps.lvl_n[j] <= 16 && (j == 0 || ps.lvl_n[j] <= ps.lvl_n[j - 1]);
         any_chain = any_chain || ps.chain;

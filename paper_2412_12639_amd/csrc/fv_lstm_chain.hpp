@@ -5,8 +5,9 @@
 // multiplication, cell) every row streams the whole 4h x h matrix again: 134 MB and 33 us per row and layer at hidden
 // 4096, of which 23 us are the stream.  That matrix is 512 KiB per compute unit, and a compute unit has 512 KiB of
 // vector registers and 160 KiB of LDS: each wavefront keeps three quarters of its share in registers and one in LDS, the
-// matrix is read once per launch, and a row costs what the exchange of the hidden state (0.8 us), 64 matrix instructions per
-// wavefront with their reads of LDS (0.6), and the way from the sums of the wavefronts through the cell to the next publication (0.4) cost.
+// matrix is read once per launch, and a row costs what the exchange of the hidden state (0.8 us from the own publication until the others' values are here),
+// the state's way through LDS and 64 matrix instructions per wavefront (0.7), and the way from their sums through the cell to the next publication (0.3) cost
+// (time stamps in wavefront 0 of all 256 workgroups, which agree to 1 %).
 // A wavefront that has its SIMD to itself issues an instruction every 8.4 cycles, a matrix instruction every 16, and LDS delivers a wavefront's 1 KiB
 // in 8: what is on a row's path is counted in instructions.  (Taking the state's operands from lanes of the same row by moves across lanes instead
 // of from LDS, eight moves an instruction: 0.3 us a row more.)  The look at the others' values takes half a microsecond and has to come when they are there, about
