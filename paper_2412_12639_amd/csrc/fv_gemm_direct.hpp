@@ -84,7 +84,7 @@ struct DReq {
 };
 
 // `wg` is this workgroup's index in the split.
-template <typename EL, int TB, int D, int EPI, int RS = 1>
+template <typename EL, int TB, int D, int EPI, int RS = 1, bool FOURS = RS == 1>
 __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, float* smem) {
     constexpr int Tp = TB * 32;
     constexpr int SF = FV_FRAGS / RS;            // fragments per stage
@@ -353,14 +353,15 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
                 // N tiles from workgroup c0 on, all in flight.  The paired form asks for those that there are: a wavefront alone on its SIMD issues an instruction
                 // every eight cycles, and with four tiles always asked for, looked over and added, absent ones times zero, a group of two contributors
                 // (QKV, gate and up) paid 150 instructions more than it needed (with the code below in one place instead of two, half as long: 7B, 64 rows
-                // 3579 -> 3535 us a step).  The direct form, whose long rows have a dozen contributors, always takes four (23 fp32 rows of hidden 512 128.3 us, 130 the other way).
+                // 3579 -> 3535 us a step).  FOURS: always four, in the direct form, whose long rows have a dozen contributors (23 fp32 rows of hidden 512 128.3 us, 130
+                // the other way), and in the paired form's residual products of more than four (k_gemm_paired_long).
                 auto add_tiles = [&](auto n_, int c0) {
                     constexpr int N = decltype(n_)::value;
                     u32x4 v[N][4];
                     for (unsigned spins = 0;; ++spins) {
 #pragma unroll
                         for (int k = 0; k < N; ++k) {
-                            const unsigned o = tile_ofs(RS == 2 || c0 + k <= c_last ? c0 + k : c_last);
+                            const unsigned o = tile_ofs(!FOURS || c0 + k <= c_last ? c0 + k : c_last);
 #pragma unroll
                             for (int q = 0; q < 4; ++q) v[k][q] = __builtin_amdgcn_raw_buffer_load_b128(prs, o + q * 1024u, 0, SC1);
                         }
@@ -380,7 +381,7 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
                     }
 #pragma unroll
                     for (int k = 0; k < N; ++k) {
-                        const float m = RS == 2 || c0 + k <= c_last ? 1.f : 0.f;
+                        const float m = !FOURS || c0 + k <= c_last ? 1.f : 0.f;
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             r[4 * q] += m * __uint_as_float(v[k][q].x & ~1u);
@@ -393,14 +394,14 @@ __device__ __forceinline__ void gemm_direct_body(const GemmArgs& a, int wg, floa
                     u32x4 zero4; zero4.x = 0u; zero4.y = 0u; zero4.z = 0u; zero4.w = 0u;
 #pragma unroll
                     for (int k = 0; k < N; ++k) {
-                        if (RS == 1 && c0 + k > c_last) break;
+                        if (FOURS && c0 + k > c_last) break;
                         const unsigned o = tile_ofs(c0 + k);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b128(zero4, prs, o + q * 1024u, 0, SC1);
                     }
                 };
                 int c0 = c_first + 1;   // ascending order
-                if constexpr (RS == 1) {
+                if constexpr (FOURS) {
                     for (; c0 <= c_last; c0 += 4) add_tiles(Const<4>{}, c0);
                 } else {
                     for (; c0 + 2 <= c_last; c0 += 3) add_tiles(Const<3>{}, c0);
@@ -484,4 +485,15 @@ __global__ __launch_bounds__(256, 1) void k_gemm_paired(GemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) float smem_dyn[];   // FV_PAIRED_SMEM_FLOATS(TB) floats
     request_args(a);
     gemm_direct_body<EL, TB, D, EPI, 2>(a, split_index(a), smem_dyn);
+}
+
+// The residual products whose row groups more than four workgroups share (eight above 32 rows): few row groups and a long K range, down of hidden 2048 and
+// below.  Every round of the finisher's looks is a trip past the caches, so it adds four tiles in each; absent ones times zero.  us of four launches under the profiler, the
+// form above -> this one: 32 workgroups a group (fp32, hidden 512, 2048 columns of K) 20 rows 67.7 -> 61.7, 64 rows 86.5 -> 82.9; 16 (hidden 1024, 4096 columns) bf16, 20 rows
+// 43.2 -> 41.1, fp32, 64 rows 81.4 -> 79.1; 8 (hidden 2048, 5504 columns) bf16, 32 rows 43.3 -> 42.1, but 64 rows 48.7 -> 50.5, fp32, 33 rows 167.3 -> 166.2; 5 (hidden 3200) equal.
+template <typename EL, int TB, int D>
+__global__ __launch_bounds__(256, 1) void k_gemm_paired_long(GemmArgs a) {
+    extern __shared__ __attribute__((aligned(16))) float smem_dyn[];   // FV_PAIRED_SMEM_FLOATS(TB) floats
+    request_args(a);
+    gemm_direct_body<EL, TB, D, EPI_RESID, 2, true>(a, split_index(a), smem_dyn);
 }

@@ -73,6 +73,12 @@ int launch_gemm_direct_t(fv_ctx* c, const GemmArgs& ga) {
 
 template <typename EL, int TB, int D, int EPI>
 int launch_gemm_paired_t(fv_ctx* c, const GemmArgs& ga) {
+    if constexpr (EPI == EPI_RESID) {
+        if (!ga.aligned && ga.G > (TB == 1 ? 4 : 8) * ga.NG) {   // its comment has both sides of the line
+            hipLaunchKernelGGL((k_gemm_paired_long<EL, TB, D>), dim3(ga.G), dim3(256), FV_PAIRED_SMEM_FLOATS(TB) * 4, c->stream, ga);
+            return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
+        }
+    }
     hipLaunchKernelGGL((k_gemm_paired<EL, TB, D, EPI>), dim3(ga.G), dim3(256), FV_PAIRED_SMEM_FLOATS(TB) * 4, c->stream, ga);
     return hipGetLastError() == hipSuccess ? FV_OK : FV_E_HIP;
 }
@@ -137,6 +143,10 @@ int set_gemm_attrs_e() {
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm<EL, 4, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 256));
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_direct<EL, 1, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_DIRECT_SMEM_FLOATS(1) * 4));
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_direct<EL, 2, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_DIRECT_SMEM_FLOATS(2) * 4));
+    if constexpr (EPI == EPI_RESID) {
+        HIPCHK(hipFuncSetAttribute((const void*)k_gemm_paired_long<EL, 1, D>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_PAIRED_SMEM_FLOATS(1) * 4));
+        HIPCHK(hipFuncSetAttribute((const void*)k_gemm_paired_long<EL, 2, D>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_PAIRED_SMEM_FLOATS(2) * 4));
+    }
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_paired<EL, 1, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_PAIRED_SMEM_FLOATS(1) * 4));
     HIPCHK(hipFuncSetAttribute((const void*)k_gemm_paired<EL, 2, D, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, FV_PAIRED_SMEM_FLOATS(2) * 4));
     return FV_OK;

@@ -39,7 +39,7 @@ def test_kernels_that_are_meant_to_fit_the_registers_use_no_scratch(code_objects
         notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", str(co)], capture_output=True, text=True, check=True).stdout
         for name, size in re.findall(r"\.name:\s+(_Z\S+).*?\.private_segment_fixed_size:\s+(\d+)", notes, re.S):
             scratch[name] = int(size)
-    meant = {n: b for n, b in scratch.items() if re.match(r"_ZL?(11k_gemm_ring|6k_attnI|13k_gemm_paired|13k_gemm_direct|13k_gemm_commit|12k_gemm_small|18k_gemm_small_split|10k_gemm_fix|12k_lstm_chain|13k_lstm_levels)", n)}
+    meant = {n: b for n, b in scratch.items() if re.match(r"_ZL?(11k_gemm_ring|6k_attnI|13k_gemm_paired|18k_gemm_paired_long|13k_gemm_direct|13k_gemm_commit|12k_gemm_small|18k_gemm_small_split|10k_gemm_fix|12k_lstm_chain|13k_lstm_levels)", n)}
     assert len(meant) > 60
     assert not {n: b for n, b in meant.items() if b}
 
