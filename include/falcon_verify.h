@@ -229,6 +229,7 @@ int fv_get_kv_moves(fv_ctx* ctx, int32_t* src_slot, int32_t* dst_slot, int32_t* 
  * one against the tokens).  Row j, j = 0..accepted_len, is the LM head's input of path node j --
  * the last layer's output after the final RMSNorm (the paper does not say before or after that
  * norm; after is what the shared LM head consumes) -- as fp32, row-major [n_rows, hidden].
+ * A step that ends with FV_E_NONFINITE exports nothing: the device rows stay those of the step before.
  * out: host buffer; n_rows in 1..accepted_len+1, else FV_E_BAD_ARG; nothing is changed. */
 int fv_get_features(fv_ctx* ctx, float* out, int32_t n_rows);
 /* K (after rotation) and V of cache slots [slot0, slot0+n) of one layer, as fp32
