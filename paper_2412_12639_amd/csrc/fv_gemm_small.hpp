@@ -13,8 +13,9 @@
 // form of two batches a wavefront for their 22 batches, which the general kernel keeps.
 // Both sides of the lines, device us of a step, four layers and a head of 2000 tokens, 1 / 32 / 64 nodes, both forms against the general kernel alone: bf16, hidden 256
 // and 688 behind it 92 / 105 / 114 against 128 / 140 / 170, 512 and 1376 102 / 115 / 145 against 141 / 154 / 189, 1024 (8 batches) and 2752 131 / 143 / 168 against
-// 151 / 163 / 199; fp32, 256 and 688 143 / 158 / 214 against 192 / 205 / 278, 512 (8 batches) and 1376 181 / 194 / 261 against 200 / 214 / 294.  Without the split form alone: bf16,
-// 512 and 1376 112 / 126, 512 and 2048 (16 batches) 109 / 122 with it and 119 / 130 without; fp32, 256 and 688 156 / 167, 1024 (16 batches) and 1024 233 / 248 with it, 241 / 252 without.
+// 151 / 163 / 199; fp32, 256 and 688 143 / 158 / 214 against 192 / 205 / 278, 512 (8 batches) and 1376 181 / 194 / 261 against 200 / 214 / 294.  The split form alone, 1 / 32 nodes, with it
+// against without: bf16, 512 and 1376 102 / 115 against 112 / 126, 512 and 2048 (16 batches) 109 / 122 against 119 / 130; fp32, 256 and 688 143 / 158 against 156 / 167, 1024
+// (16 batches) and 1024 233 / 248 against 241 / 252.
 #pragma once
 // (included from fv_kernels.hpp after fv_gemm_direct.hpp)
 

@@ -1924,7 +1924,7 @@ __device__ __forceinline__ void finish_feature(const FinishArgs& a, int t, int b
 
 // The end of a greedy step of one node, whose path is known: its greedy choice and the step's result, and beside it its features.  (Nothing moves in the cache.)
 // Plain decoding pays for one launch here instead of two: one token of the 7B width, four layers 441.8 -> 432.6 us of device time, of hidden 512, two layers 84.5 -> 81.0.
-// (Both workgroups read the logits, the second so that a step without a choice exports nothing: under the profiler 3.5 us a launch instead of 2.9 at 8000 tokens, 5.8
+// (Both workgroups read the logits, the second so that a step without a choice exports nothing: under the profiler 3.5 us a launch instead of 2.9 at 2000 tokens, 5.8
 // instead of 4.3 at 32000; a call of hidden 512 91.7 us without, 91.0 with it, of the 7B width 466 and 467.  Its loads ahead of the statistics: 0.2 and 0.4 us less, not kept.)
 template <int NT>
 static __global__ __launch_bounds__(NT) void k_finish_one(ArgmaxArgs am, FinishArgs a) {
